@@ -18,7 +18,9 @@ precision (its own MFMA work per launch over its launch time, measured with HIP
 events around its launches), and the CPU oracle on a bounded sample of the same
 workload.
 
-Own work of the tile kernel (row-extended form): the product T_row V over the
+Own work of the dominant kernels. FP64 (spectral_gram): per frequency of the axes
+2..d the Toeplitz product along axis 1 and the two products with U (gram_flops).
+FP32 and split bfloat16 (tile kernel, row-extended form): the product T_row V over the
 (n+2)^d rows k' and N columns h, 8 (n+2)^d N m flops, plus the reductions with the
 shifted U_l, 8 ells (n+2)^d m^2 flops (ells = d matrices). It is below F_S by about
 the factor d: F_S counts the d products T_l V that the row-extended form shares.
@@ -40,7 +42,8 @@ METRIC = "S_ℓ-build complex TFLOP/s + instances/s, FP32-MFMA vs FP64, at state
 # MI355X dense MFMA peaks; the split-bfloat16 S-build runs six bf16 products per
 # FP32 product, so its FP32-equivalent ceiling is the bf16 peak (2500) / 6
 PEAK_TFLOPS = {"fp32": 157.3, "fp64": 78.6, "bf16x3": 2500.0 / 6}
-DOMINANT = "pencil_tiles"
+# the dominant kernel of an S-build by precision (profiling names of the library)
+DOMINANT = {"fp32": "pencil_tiles", "bf16x3": "pencil_tiles", "fp64": "spectral_gram"}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "pencil_tiles_c1_traffic.json")
 
 
@@ -54,6 +57,19 @@ def tile_flops(d, n, m, ells=None):
     ells = d if ells is None else ells
     NR, N = (n + 2) ** d, (n + 1) ** d
     return 8.0 * NR * N * m + 8.0 * ells * NR * m * m
+
+
+def gram_flops(d, n, m):
+    """Own work of one spectral_gram launch (FP64, d >= 2): at each of the (2n+2)^(d-1)
+    frequencies the Toeplitz product of n+2 rows with n+1 lines of V, and the two
+    products of n+1 rows of U (plain and shifted) with it."""
+    F = (2 * n + 2) ** (d - 1)
+    return F * (8.0 * (n + 2) * (n + 1) * m + 16.0 * (n + 1) * m * m)
+
+
+def own_flops(prec, d, n, m):
+    """Own work of one launch of the dominant kernel of `prec`."""
+    return gram_flops(d, n, m) if prec == "fp64" else tile_flops(d, n, m)
 
 
 def source_digest():
@@ -158,7 +174,7 @@ def main():
     for _ in range(args.warmup):
         step(args.prec)
     torch.cuda.synchronize()
-    api.profile_enable(dev, DOMINANT)
+    api.profile_enable(dev, DOMINANT[args.prec])
     ev0, ev1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     torch.cuda.synchronize()
     wall0 = time.perf_counter()
@@ -189,14 +205,14 @@ def main():
     for prec in ("fp32", "fp64", "bf16x3"):
         for _ in range(args.warmup):
             api.build_S(f, d, n, Ud, sd, Vd, prec=prec, out=Sbuf)
-        api.profile_enable(dev, DOMINANT)
+        api.profile_enable(dev, DOMINANT[prec])
         times = per_call_ms(lambda: api.build_S(f, d, n, Ud, sd, Vd, prec=prec, out=Sbuf), max(20, args.steps))
         nl, tot = api.profile_read(dev)
         api.profile_enable(dev, None)
         med = float(np.median(times))
         sbuild[prec] = {"ms_median": round(med, 5), "ms_mean": round(float(np.mean(times)), 5),
                         "fs_equivalent_tflops": round(s_flops(d, N, m) / (med * 1e-3) / 1e12, 3),
-                        "own_work_tflops": round(tile_flops(d, n, m) / (med * 1e-3) / 1e12, 3),
+                        "own_work_tflops": round(own_flops(prec, d, n, m) / (med * 1e-3) / 1e12, 3),
                         "tiles_ms": round(tot / max(1, nl), 5), "tiles_launches": nl, "calls": len(times)}
         S_out[prec] = Sbuf.cpu().numpy().copy()
         # the same build with prepared factors (U, V packed once): tile and finishing launches only
@@ -242,19 +258,19 @@ def main():
             traffic_rec = json.load(fh)
 
     def roofline_of(prec, avg_ms, nlaunch):
-        """Roofline of the tile kernel of one precision: its own MFMA work per launch
+        """Roofline of the dominant kernel of one precision: its own MFMA work per launch
         over its average launch time (HIP events); HBM bytes per launch from the stored
         counters of the same code, workload, precision and split target (the partial
         rows written depend on the plan), else null."""
         p = autotune.plan(dev, d, n, m, prec)
         plan_key = f"{p['fragments']}x{p['workgroups']}"
         traffic = None
-        if traffic_rec.get("source_digest") == source_digest() and traffic_rec.get("workload") == args.workload:
+        if prec != "fp64" and traffic_rec.get("source_digest") == source_digest() and traffic_rec.get("workload") == args.workload:
             traffic = traffic_rec.get("entries", {}).get(prec, {}).get(plan_key, {}).get("hbm_bytes_per_launch")
-        achieved = tile_flops(d, n, m) / (avg_ms * 1e-3) / 1e12
+        achieved = own_flops(prec, d, n, m) / (avg_ms * 1e-3) / 1e12
         return {
             "bound": "mfma",
-            "kernel": "pencil_tiles_split" if prec == "bf16x3" else DOMINANT,
+            "kernel": "pencil_tiles_split" if prec == "bf16x3" else DOMINANT[prec],
             "precision": prec,
             "achieved": round(achieved, 3),
             "peak": PEAK_TFLOPS[prec],
@@ -263,9 +279,10 @@ def main():
             "traffic": traffic,
             "avg_launch_ms": round(avg_ms, 5),
             "launches_timed": nlaunch,
-            "flops_per_launch": tile_flops(d, n, m),
+            "flops_per_launch": own_flops(prec, d, n, m),
             "fs_equivalent_tflops": round(F / (avg_ms * 1e-3) / 1e12, 3),
-            "plan": {"fragments_per_wave": p["fragments"], "workgroups": p["workgroups"], "h_per_chunk": p["chunk"]},
+            "plan": {"frequencies": (2 * n + 2) ** (d - 1)} if prec == "fp64" else
+                    {"fragments_per_wave": p["fragments"], "workgroups": p["workgroups"], "h_per_chunk": p["chunk"]},
         }
 
     result = {
@@ -396,7 +413,7 @@ def paper_workload(dev, args, per_call_ms):
             S_p[prec] = api.build_S(f, d, n, Ud, sd, Vd, prec=prec)
             row[prec] = {"s_build_ms": round(ms, 4),
                          "fs_equivalent_tflops": round(s_flops(d, N, m) / (ms * 1e-3) / 1e12, 2),
-                         "own_work_tflops": round(tile_flops(d, n, m) / (ms * 1e-3) / 1e12, 2),
+                         "own_work_tflops": round(own_flops(prec, d, n, m) / (ms * 1e-3) / 1e12, 2),
                          "speedup_vs_paper_t_S": round(PAPER_T_S[m] / (ms * 1e-3), 1)}
         # the S of each precision against the FP64 S on the same factors: the paper's
         # inputs at m >= 10 have sigma_m / sigma_1 down to ~3e-12, and Sigma^{-1}
@@ -481,19 +498,20 @@ def noise_sweep_c2(dev, args, per_call_ms):
     for prec in ("fp64", "fp32", "bf16x3"):
         for _ in range(args.warmup):
             api.build_S(f, d, n, Ud, sd, Vd, prec=prec)
-        api.profile_enable(dev, DOMINANT)
+        api.profile_enable(dev, DOMINANT[prec])
         ms = float(np.median(per_call_ms(lambda: api.build_S(f, d, n, Ud, sd, Vd, prec=prec), reps)))
         nl, tot = api.profile_read(dev)
         api.profile_enable(dev, None)
         tiles = tot / max(1, nl)
-        own = tile_flops(d, n, m)
+        own = own_flops(prec, d, n, m)
         timing[prec] = {"s_build_ms_median": round(ms, 5), "calls": reps,
                         "fs_equivalent_tflops": round(s_flops(d, N, m) / (ms * 1e-3) / 1e12, 2),
                         "tiles_ms": round(tiles, 5), "tiles_own_work_tflops": round(own / (tiles * 1e-3) / 1e12, 2),
                         "tiles_frac_of_peak": round(own / (tiles * 1e-3) / 1e12 / PEAK_TFLOPS[prec], 4),
                         "plan": autotune.plan(dev, d, n, m, prec)}
     return {"workload": "c2: d=3, n=19, N=8000, m=30, separation 0.08, |c| log-uniform [1e-2, 1]", "levels": rows,
-            "s_build": timing, "own_work_flops_per_launch": tile_flops(d, n, m)}
+            "s_build": timing,
+            "own_work_flops_per_launch": {p: own_flops(p, d, n, m) for p in ("fp64", "fp32", "bf16x3")}}
 
 
 def _closed_form_factors(t, c, d, n):

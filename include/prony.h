@@ -115,8 +115,8 @@ prony_status_t prony_reserve(prony_handle_t handle, int d_max, int n_max, int m_
    by the handle is bracketed by a pair of HIP events recorded on the handle's
    stream; NULL stops recording. Each call discards earlier records.
    Kernel names: "samples", "toeplitz", "pencil_pack", "pencil_tiles",
-   "pencil_tiles_batched", "pencil_finish", "coeffs_tiles", "coeffs_finish",
-   "adjoint_pack", "adjoint_tiles". */
+   "pencil_tiles_batched", "pencil_finish", "spectral_forward", "spectral_gram",
+   "coeffs_tiles", "coeffs_finish", "adjoint_pack", "adjoint_tiles". */
 prony_status_t prony_profile_enable(prony_handle_t handle, const char* kernel);
 
 /* Synchronise the stream and report the recorded launches of the profiled kernel:
@@ -132,7 +132,9 @@ prony_status_t prony_profile_read(prony_handle_t handle, int* launches, double* 
    the same d, the same floor(log2 N) and the same column-block count ceil(m/8);
    an entry of the exact shape takes precedence, field by field. target_wgs = 0
    removes the target. PRONY_BF16X3 entries exist for single instances only
-   (batches run PRONY_FP32 or PRONY_FP64). Entries live in the handle. */
+   (batches run PRONY_FP32 or PRONY_FP64). Entries apply to the tile kernels: a
+   PRONY_FP64 S-build that runs in line-spectral form (prony_build_S) does not use
+   them. Entries live in the handle. */
 #define PRONY_TUNE_BATCHED 1u
 #define PRONY_TUNE_BUCKET 2u
 prony_status_t prony_tune_set(prony_handle_t handle, int d, int n, int m, prony_prec_t prec, unsigned flags,
@@ -209,7 +211,11 @@ prony_status_t prony_build_T(prony_handle_t handle, int d, int n, int which,
    flags:  0 or PRONY_WITH_S0.
    S:      output, (d or d+1) x m x m complex128, row-major per matrix: S_l(i,j)
            at S + 2*((l*m + i)*m + j), l counted from the first stored matrix.
-   Requires 1 <= m <= min(N, 32). */
+   Requires 1 <= m <= min(N, 32).
+   PRONY_FP64 runs in line-spectral form where it fits (lines of at most 240 points and
+   1 GiB of workspace): DFTs of length 2(n+1) along the axes 2..d (d = 1: along folded
+   lines), then one-dimensional Toeplitz products per frequency, all in FP64. Other
+   shapes and precisions run the MFMA tiles on the undivided product. */
 prony_status_t prony_build_S(prony_handle_t handle, int d, int n, int m, const double* f,
                              const double* U, int64_t u_rs, int64_t u_cs,
                              const double* sigma,
@@ -218,8 +224,9 @@ prony_status_t prony_build_S(prony_handle_t handle, int d, int n, int m, const d
 
 /* The launch plan prony_build_S would use for this call shape under the handle's
    tuning entries, without launching or allocating anything: 16-row fragments per
-   wave, workgroups of the tile launch, indices h per chunk and the workspace
-   bytes the call needs. Validates like prony_build_S (pointers aside). Works on
+   wave, workgroups of the tile launch, indices h per chunk (of the tile plan, also
+   where an FP64 call runs in line-spectral form) and the workspace bytes the call
+   needs. Validates like prony_build_S (pointers aside). Works on
    validation-only handles, which plan for 256 compute units and 160 KiB of LDS
    per workgroup (the MI355X figures). Any output pointer may be NULL. */
 prony_status_t prony_build_S_plan(prony_handle_t handle, int d, int n, int m, prony_prec_t prec, unsigned flags,

@@ -56,6 +56,7 @@
 #include "common.h"
 #include "mfma.h"
 #include "reduce.h"
+#include "spectral.h"
 
 namespace prony {
 namespace {
@@ -1696,6 +1697,10 @@ size_t pencil_workspace_bytes(prony_handle_t h, int d, int n, int m) {
                         best = std::max(best, P.ws_bytes);
                 }
     }
+    for (int s0 = 0; s0 < 2; ++s0) {
+        SpecPlan SP;
+        if (spectral_plan(h, d, n, m, s0 == 1, SP)) best = std::max(best, SP.ws_bytes);
+    }
     h->err = saved;
     return best;
 }
@@ -1734,12 +1739,24 @@ prony_status_t scratch_attach(prony_handle_t h) {
 
 namespace {
 
+// Plan of an S-build: the tile plan, and for FP64 the line-spectral plan (spectral.hip)
+// where that form applies; the call then runs it instead of the tiles.
+struct BuildPlan {
+    PencilPlan P;
+    bool spectral = false;
+    SpecPlan SP;
+    size_t ws_bytes() const { return spectral ? SP.ws_bytes : P.ws_bytes; }
+    // what prepared factors keep: the packed or transformed U and V
+    size_t factor_bytes() const { return spectral ? SP.off_f : P.off_p; }
+};
+
 // Host-side validation shared by prony_build_S and prony_build_S_noalloc, and the
-// plan of the call.
+// plan of the call. The tile plan is made in every case: a shape it cannot cover is
+// refused whatever the form.
 prony_status_t plan_build_S(prony_handle_t h, const char* who, int d, int n, int m, const double* f,
                             const double* U, int64_t u_rs, int64_t u_cs, const double* sigma, const double* V,
                             int64_t v_rs, int64_t v_cs, prony_prec_t prec, unsigned flags, double* S,
-                            PencilPlan& P, bool plan_only = false) {
+                            BuildPlan& B, bool plan_only = false) {
     prony_status_t st = check_dn(h, d, n);
     if (st != PRONY_OK) return st;
     const std::string w(who);
@@ -1756,15 +1773,34 @@ prony_status_t plan_build_S(prony_handle_t h, const char* who, int d, int n, int
     if (h->device < 0 && !plan_only) return fail(h, PRONY_ENODEV, "validation-only handle has no device");
     const bool s0 = (flags & PRONY_WITH_S0) != 0;
     const size_t ts = prec == PRONY_FP64 ? sizeof(double) : sizeof(float);
-    return make_plan(h, d, n, m, s0, ts, P, tuned_target(h, d, n, m, prec, 0), tuned_fragments(h, d, n, m, prec, 0),
-                     0, prec == PRONY_BF16X3, true);
+    st = make_plan(h, d, n, m, s0, ts, B.P, tuned_target(h, d, n, m, prec, 0), tuned_fragments(h, d, n, m, prec, 0),
+                   0, prec == PRONY_BF16X3, true);
+    B.spectral = st == PRONY_OK && prec == PRONY_FP64 && spectral_plan(h, d, n, m, s0, B.SP);
+    return st;
 }
 
-prony_status_t run_build_S(prony_handle_t h, const PencilPlan& P, unsigned char* ws, prony_prec_t prec,
+// Operands of a line-spectral S-build: the transformed factors at `base`, the
+// transformed samples and the partials at `rest` (the sections from off_f on).
+SpecPtrs spectral_ptrs(const SpecPlan& P, unsigned char* base, unsigned char* rest, const double* f, const double* U,
+                       int64_t u_rs, int64_t u_cs, const double* sigma, const double* V, int64_t v_rs, int64_t v_cs,
+                       double* S) {
+    return SpecPtrs{reinterpret_cast<const double2*>(U), reinterpret_cast<const double2*>(V), u_rs, u_cs, v_rs, v_cs,
+                    reinterpret_cast<const double2*>(f), sigma, reinterpret_cast<double2*>(base),
+                    reinterpret_cast<double2*>(base + P.off_v), reinterpret_cast<double2*>(rest),
+                    reinterpret_cast<double2*>(rest + (P.off_p - P.off_f)),
+                    reinterpret_cast<double2*>(rest + (P.off_r - P.off_f)), reinterpret_cast<double2*>(S)};
+}
+
+prony_status_t run_build_S(prony_handle_t h, const BuildPlan& B, unsigned char* ws, prony_prec_t prec,
                            const double* f, const double* U, int64_t u_rs, int64_t u_cs, const double* sigma,
                            const double* V, int64_t v_rs, int64_t v_cs, double* S) {
-    if (prec == PRONY_FP64) return launch_pencil<double>(h, P, ws, f, U, u_rs, u_cs, sigma, V, v_rs, v_cs, S);
-    return launch_pencil<float>(h, P, ws, f, U, u_rs, u_cs, sigma, V, v_rs, v_cs, S);
+    if (B.spectral) {
+        const SpecPtrs p = spectral_ptrs(B.SP, ws, ws + B.SP.off_f, f, U, u_rs, u_cs, sigma, V, v_rs, v_cs, S);
+        const prony_status_t st = spectral_forward(h, B.SP, p, true, true);
+        return st == PRONY_OK ? spectral_gram_finish(h, B.SP, p) : st;
+    }
+    if (prec == PRONY_FP64) return launch_pencil<double>(h, B.P, ws, f, U, u_rs, u_cs, sigma, V, v_rs, v_cs, S);
+    return launch_pencil<float>(h, B.P, ws, f, U, u_rs, u_cs, sigma, V, v_rs, v_cs, S);
 }
 
 }  // namespace
@@ -1776,14 +1812,14 @@ extern "C" prony_status_t prony_build_S(prony_handle_t h, int d, int n, int m, c
                                         int64_t u_rs, int64_t u_cs, const double* sigma, const double* V,
                                         int64_t v_rs, int64_t v_cs, prony_prec_t prec, unsigned flags, double* S) {
     if (!h) return PRONY_EINVAL;
-    PencilPlan P;
+    BuildPlan B;
     prony_status_t st =
-        plan_build_S(h, "prony_build_S", d, n, m, f, U, u_rs, u_cs, sigma, V, v_rs, v_cs, prec, flags, S, P);
+        plan_build_S(h, "prony_build_S", d, n, m, f, U, u_rs, u_cs, sigma, V, v_rs, v_cs, prec, flags, S, B);
     if (st != PRONY_OK) return st;
     DeviceGuard g(h->device);
     if (!g.ok) return fail(h, PRONY_EHIP, "hipSetDevice failed");
-    if ((st = ensure_workspace(h, P.ws_bytes)) != PRONY_OK) return st;
-    return run_build_S(h, P, static_cast<unsigned char*>(h->ws), prec, f, U, u_rs, u_cs, sigma, V, v_rs, v_cs, S);
+    if ((st = ensure_workspace(h, B.ws_bytes())) != PRONY_OK) return st;
+    return run_build_S(h, B, static_cast<unsigned char*>(h->ws), prec, f, U, u_rs, u_cs, sigma, V, v_rs, v_cs, S);
 }
 
 extern "C" prony_status_t prony_build_S_plan(prony_handle_t h, int d, int n, int m, prony_prec_t prec, unsigned flags,
@@ -1791,14 +1827,14 @@ extern "C" prony_status_t prony_build_S_plan(prony_handle_t h, int d, int n, int
     if (!h) return PRONY_EINVAL;
     // the plan does not read the arrays: stand-in pointers pass the null checks
     static const double dummy[2] = {0.0, 0.0};
-    PencilPlan P;
+    BuildPlan B;
     const prony_status_t st = plan_build_S(h, "prony_build_S_plan", d, n, m, dummy, dummy, 1, 1, dummy, dummy, 1, 1,
-                                           prec, flags, const_cast<double*>(dummy), P, true);
+                                           prec, flags, const_cast<double*>(dummy), B, true);
     if (st != PRONY_OK) return st;
-    if (fragments) *fragments = P.rf;
-    if (workgroups) *workgroups = P.nwg;
-    if (chunk) *chunk = P.kc;
-    if (workspace_bytes) *workspace_bytes = P.ws_bytes;
+    if (fragments) *fragments = B.P.rf;
+    if (workgroups) *workgroups = B.P.nwg;
+    if (chunk) *chunk = B.P.kc;
+    if (workspace_bytes) *workspace_bytes = B.ws_bytes();
     return PRONY_OK;
 }
 
@@ -1807,29 +1843,31 @@ extern "C" prony_status_t prony_build_S_noalloc(prony_handle_t h, int d, int n, 
                                                 const double* V, int64_t v_rs, int64_t v_cs, prony_prec_t prec,
                                                 unsigned flags, double* S) {
     if (!h) return PRONY_EINVAL;
-    PencilPlan P;
+    BuildPlan B;
     prony_status_t st = plan_build_S(h, "prony_build_S_noalloc", d, n, m, f, U, u_rs, u_cs, sigma, V, v_rs, v_cs,
-                                     prec, flags, S, P);
+                                     prec, flags, S, B);
     if (st != PRONY_OK) return st;
-    if (P.ws_bytes > kScratchBytes)
+    // the limit is the tile plan's; a line-spectral plan beyond the scratch runs the tiles
+    if (B.spectral && B.SP.ws_bytes > kScratchBytes) B.spectral = false;
+    if (B.P.ws_bytes > kScratchBytes)
         return fail(h, PRONY_ENOTSUP,
-                    "prony_build_S_noalloc: the call needs " + std::to_string(P.ws_bytes) +
+                    "prony_build_S_noalloc: the call needs " + std::to_string(B.P.ws_bytes) +
                         " bytes of scratch, more than the fixed " + std::to_string(kScratchBytes) +
                         " bytes per device; use prony_build_S");
     if (!h->scratch) return fail(h, PRONY_EHIP, "prony_build_S_noalloc: no scratch address for this device");
     DeviceGuard g(h->device);
     if (!g.ok) return fail(h, PRONY_EHIP, "hipSetDevice failed");
-    return run_build_S(h, P, static_cast<unsigned char*>(h->scratch), prec, f, U, u_rs, u_cs, sigma, V, v_rs,
+    return run_build_S(h, B, static_cast<unsigned char*>(h->scratch), prec, f, U, u_rs, u_cs, sigma, V, v_rs,
                        v_cs, S);
 }
 
-// Prepared factors: the packed operands of one (U, sigma, V) under the plan that
-// was current at creation, for repeated S-builds with other sample grids.
+// Prepared factors: the packed (or transformed) operands of one (U, sigma, V) under
+// the plan that was current at creation, for repeated S-builds with other sample grids.
 struct prony_factors_s {
     int device = -1;
     prony_prec_t prec = PRONY_FP64;
-    PencilPlan P{};
-    unsigned char* mem = nullptr;   // packed V | packed U | G table | sigma
+    BuildPlan B;
+    unsigned char* mem = nullptr;   // packed V | packed U | G table | sigma (or U~ | V~ | sigma)
     size_t off_sigma = 0;
 };
 
@@ -1842,9 +1880,9 @@ extern "C" prony_status_t prony_factors_create(prony_handle_t h, int d, int n, i
     *factors = nullptr;
     // the plan does not read the grid or the output: stand-ins pass the null checks
     static const double dummy[2] = {0.0, 0.0};
-    PencilPlan P;
+    BuildPlan B;
     prony_status_t st = plan_build_S(h, "prony_factors_create", d, n, m, dummy, U, u_rs, u_cs, sigma, V, v_rs, v_cs,
-                                     prec, flags, const_cast<double*>(dummy), P);
+                                     prec, flags, const_cast<double*>(dummy), B);
     if (st != PRONY_OK) return st;
     DeviceGuard g(h->device);
     if (!g.ok) return fail(h, PRONY_EHIP, "hipSetDevice failed");
@@ -1857,16 +1895,20 @@ extern "C" prony_status_t prony_factors_create(prony_handle_t h, int d, int n, i
     if (!F) return fail(h, PRONY_ENOMEM, "prony_factors_create: out of host memory");
     F->device = h->device;
     F->prec = prec;
-    F->P = P;
-    F->off_sigma = P.off_p;   // the packed sections end where the partial rows would start
+    F->B = B;
+    F->off_sigma = B.factor_bytes();
     e = hipMalloc(reinterpret_cast<void**>(&F->mem), F->off_sigma + align_up(sizeof(double) * (size_t)m, 256));
     if (e != hipSuccess) {
         (void)hipGetLastError();
         delete F;
         return fail(h, PRONY_ENOMEM, std::string("prony_factors_create: hipMalloc failed: ") + hipGetErrorString(e));
     }
-    st = prec == PRONY_FP64 ? pack_operands<double>(h, P, F->mem, U, u_rs, u_cs, V, v_rs, v_cs)
-                            : pack_operands<float>(h, P, F->mem, U, u_rs, u_cs, V, v_rs, v_cs);
+    if (B.spectral)
+        st = spectral_forward(h, B.SP, spectral_ptrs(B.SP, F->mem, nullptr, nullptr, U, u_rs, u_cs, sigma, V, v_rs,
+                                                     v_cs, nullptr), true, false);
+    else
+        st = prec == PRONY_FP64 ? pack_operands<double>(h, B.P, F->mem, U, u_rs, u_cs, V, v_rs, v_cs)
+                                : pack_operands<float>(h, B.P, F->mem, U, u_rs, u_cs, V, v_rs, v_cs);
     if (st == PRONY_OK) {
         e = hipMemcpyAsync(F->mem + F->off_sigma, sigma, sizeof(double) * (size_t)m, hipMemcpyDeviceToDevice,
                            h->stream);
@@ -1890,11 +1932,16 @@ extern "C" prony_status_t prony_build_S_factors(prony_handle_t h, prony_factors_
         return fail(h, PRONY_EINVAL, "prony_build_S_factors: the factors belong to another device");
     DeviceGuard g(h->device);
     if (!g.ok) return fail(h, PRONY_EHIP, "hipSetDevice failed");
-    const PencilPlan& P = F->P;
-    prony_status_t st = ensure_workspace(h, P.ws_bytes - P.off_p);
+    const PencilPlan& P = F->B.P;
+    prony_status_t st = ensure_workspace(h, F->B.ws_bytes() - F->B.factor_bytes());
     if (st != PRONY_OK) return st;
     const double* sigma = reinterpret_cast<const double*>(F->mem + F->off_sigma);
     unsigned char* part = static_cast<unsigned char*>(h->ws);
+    if (F->B.spectral) {
+        const SpecPtrs p = spectral_ptrs(F->B.SP, F->mem, part, f, nullptr, 0, 0, sigma, nullptr, 0, 0, S);
+        st = spectral_forward(h, F->B.SP, p, false, true);
+        return st == PRONY_OK ? spectral_gram_finish(h, F->B.SP, p) : st;
+    }
     if (F->prec == PRONY_FP64) return launch_tiles_finish<double>(h, P, F->mem, part, f, sigma, S);
     return launch_tiles_finish<float>(h, P, F->mem, part, f, sigma, S);
 }
@@ -1902,11 +1949,11 @@ extern "C" prony_status_t prony_build_S_factors(prony_handle_t h, prony_factors_
 extern "C" prony_status_t prony_factors_info(prony_factors_t F, int* d, int* n, int* m, prony_prec_t* prec,
                                              unsigned* flags) {
     if (!F) return PRONY_EINVAL;
-    if (d) *d = F->P.d;
-    if (n) *n = F->P.n;
-    if (m) *m = F->P.m;
+    if (d) *d = F->B.P.d;
+    if (n) *n = F->B.P.n;
+    if (m) *m = F->B.P.m;
     if (prec) *prec = F->prec;
-    if (flags) *flags = F->P.first_ell == 0 ? PRONY_WITH_S0 : 0u;
+    if (flags) *flags = F->B.P.first_ell == 0 ? PRONY_WITH_S0 : 0u;
     return PRONY_OK;
 }
 

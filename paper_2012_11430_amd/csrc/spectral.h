@@ -1,0 +1,62 @@
+// Line-spectral form of the FP64 S-build (spectral.hip): plan, operands, launches.
+#pragma once
+
+#include "common.h"
+
+namespace prony {
+
+// Plan of one instance in the line-spectral form. One axis of I_n stays direct
+// (K1 lines), the others are transformed on L = 2P points each:
+//   d >= 2: axis 1 is direct (K1 = n + 1 lines), axes 2..d have P = n + 1 points;
+//   d = 1:  the index k = k1 P + k2 is folded into K1 lines of P points.
+struct SpecPlan {
+    int d, n, N, m;
+    int P, L, K1;
+    int NP1;        // sample lines p1 = t - (K1 - 1), t < NP1
+    int F;          // frequencies: L^(transformed axes)
+    int ells, s0;   // stored matrices (S_0 first with s0), d or d + 1
+    int npb;        // blocks of 8 frequency pairs along one axis
+    // forward transforms
+    int nbw;        // d <= 2: 8-column blocks per workgroup (factors)
+    int nbwf;       //         the same for the sample lines
+    int nq;         // d = 3: factor columns per workgroup (at most 8)
+    int splits, wp; // d = 3: parts of the frequency pairs of axis 3, pairs per part
+    int wgs_x;      // workgroups per factor (U, V)
+    int wgs_f;      // workgroups of the sample grid
+    size_t lds_fwd;
+    // weighted Gram products
+    int nqb;        // 16-column blocks of V
+    int nmb, nm0;   // 16-row blocks of [U | shifted U], those with unshifted rows
+    int ns;         // sums kept: 1 with the last axis' phase, 2 plain and with that phase
+    int groups;     // groups of frequencies = rows of partials
+    int gparts;     // groups per frequency of axis 2 (d = 3), else all groups
+    size_t lds_gram;
+    // workspace sections (bytes): U~ | V~ | f~ | partials | roots; the first off_f bytes are
+    // what prepared factors keep
+    size_t off_v, off_f, off_p, off_r, ws_bytes;
+};
+
+// Operands of one instance.
+struct SpecPtrs {
+    const double2* U;
+    const double2* V;
+    int64_t u_rs, u_cs, v_rs, v_cs;
+    const double2* f;
+    const double* sigma;
+    double2* ut;      // U~[w][k1][i]
+    double2* vt;      // V~[w][h1][q]
+    double2* ft;      // f~[w][t], scaled by 1/F
+    double2* part;    // [group][i][l][q]
+    double2* roots;   // e^{2 pi i j / L}, j < L
+    double2* S;
+};
+
+// Plan of an FP64 S-build; false where the form does not apply (see there).
+bool spectral_plan(prony_handle_t h, int d, int n, int m, bool s0, SpecPlan& P);
+
+// Launches on the handle's stream: the transforms of U and V, and/or of the sample
+// grid; then the weighted Gram products and the finishing sums into S.
+prony_status_t spectral_forward(prony_handle_t h, const SpecPlan& P, const SpecPtrs& ptr, bool factors, bool grid);
+prony_status_t spectral_gram_finish(prony_handle_t h, const SpecPlan& P, const SpecPtrs& ptr);
+
+}  // namespace prony

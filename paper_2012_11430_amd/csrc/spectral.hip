@@ -1,0 +1,769 @@
+// FP64 S-build in line-spectral form.
+//
+// S_l = U_l^* T_row V with T_row[k', h] = f(k' - h) (the row-extended form of
+// pencil.hip). Along the axes 2..d both index sets lie in an embedding of
+// L = 2(n+1) points on which k' - h in {-n..n+1} is a circular difference, so a DFT
+// of length L along these axes (x~(w) = sum_k x(k) e^{-2 pi i <w,k>/L}) turns T_row
+// into F = L^(d-1) independent one-dimensional Toeplitz matrices along axis 1,
+//     Y_w[k1'] = sum_h1 f~_w(k1' - h1) V~_w[h1],
+// and, since a shift of U by e_l (l >= 2) is the phase e^{-2 pi i w_l / L},
+//     U_l^* T_row V = 1/F sum_w e^{2 pi i w_l / L} sum_k1 U~_w[k1]^* Y_w[k1]   (l >= 2),
+//     U_1^* T_row V = 1/F sum_w sum_k1 U~_w[k1]^* Y_w[k1 + 1].
+// Per instance this takes 8 (n+2)(n+1) m L^(d-1) operations for the products instead
+// of 8 (n+2)^d (n+1)^d m, plus the transforms of U, V and f, for results of the same
+// precision: every sum is FP64, and the lengths of the sums fall from (n+1)^d to
+// (d-1)(n+1) + (n+1). d = 1: k = k1 P + k2 is folded into K1 lines of P points, which
+// makes T a two-level Toeplitz matrix with f2(p1, p2) = f(p1 P + p2); S_1 is then the
+// phase form along the second level.
+//
+//   spectral_forward  DFTs of U, V and f as real contractions with the cosine and sine
+//                     tables on the FP64 matrix cores: frequency w and its mirror L - w
+//                     share both sums, x~(w), x~(L - w) = C -+ i S;
+//   spectral_gram     per frequency the Toeplitz product (window of f~_w in LDS) and the
+//                     two Gram products, chained in registers: the 16x16 FP64 result
+//                     layout (lane group g, element r: row g + 4 r) is the second
+//                     operand's layout of K step r, so Y_w never leaves the registers;
+//   spectral_finish   fixed-order sum of the groups' partials, Sigma^{-1}.
+#include <algorithm>
+#include <cmath>
+#include <type_traits>
+
+#include "mfma.h"
+#include "reduce.h"
+#include "spectral.h"
+
+namespace prony {
+namespace {
+
+constexpr int kWaves = 4;
+constexpr int kThreads = kWaves * 64;
+constexpr int kCols = 8;            // complex columns of one 16-column MFMA block
+using M = Mfma<double>;
+using acc_t = M::acc_t;
+
+// cos and sin of 2 pi j / L, j < L.
+__device__ __forceinline__ void fill_roots(double2* tab, int L) {
+    for (int j = threadIdx.x; j < L; j += kThreads) {
+        double s, c;
+        sincospi(2.0 * j / L, &s, &c);
+        tab[j] = make_double2(c, s);
+    }
+}
+
+// LDS rows of one staged line block (whole groups of K steps) and doubles per row of
+// the planes between the two transforms of d = 3 (rows 128 bytes apart modulo 256:
+// the rows of two lane groups fall into different banks).
+__host__ __device__ inline int line_rows(int K) { return (K + 15) & ~15; }
+__host__ __device__ inline int plane_stride(int pairs, int nq) { return ((4 * pairs * nq + 31) & ~31) + 16; }
+
+// Offset in f of the sample (line t, point j of the embedded axis), -1 where there is
+// none. Point j stands for p2 = j (j <= P) or j - L.
+__device__ __forceinline__ int sample_offset(const SpecPlan& P, int t, int j) {
+    const int p1 = t - (P.K1 - 1), p2 = j <= P.P ? j : j - P.L;
+    if (P.d == 2) return (p1 + P.n) * P.L + p2 + P.n;
+    const int p = p1 * P.P + p2;
+    return p >= -P.n && p <= P.n + 1 ? p + P.n : -1;
+}
+
+// Forward transforms run on 16-row blocks of 8 frequency pairs: row i < 8 of block pb
+// is the cosine row of w = w0 + 8 pb + i, row 8 + i its sine row, so that a lane holds
+// C = sum x cos (elements 0, 1) and S = sum x sin (elements 2, 3) of the pairs
+// g and g + 4 of the block. Frequency 0 has no sine row: its slot holds the signs
+// (-1)^j of frequency P.
+constexpr int kPairs = 8;
+
+// Table walk of a lane's row: its factor at j = 4 s + g for s = 0, 1, ...
+struct RowWalk {
+    int idx, step, L, part;
+    double alt;
+    bool zero_sine;
+    __device__ __forceinline__ RowWalk(int w, bool sine, int g, int L_) {
+        L = L_;
+        idx = (int)(((int64_t)w * g) % L);
+        step = (int)((4 * (int64_t)w) % L);
+        part = sine ? 1 : 0;
+        alt = g & 1 ? -1.0 : 1.0;
+        zero_sine = sine && w == 0;
+    }
+    __device__ __forceinline__ double next(const double2* tab) {
+        const double v = reinterpret_cast<const double*>(tab)[2 * idx + part];
+        idx += step;
+        if (idx >= L) idx -= L;
+        return zero_sine ? alt : v;
+    }
+};
+
+// x~(w) and x~(L - w) (one real column of a complex one, whose other component sits in
+// the neighbouring lane): C -+ i S; for w = 0 the frequencies 0 and P.
+__device__ __forceinline__ void pair_out(int w, bool odd, double C, double S, double scale, double& lo, double& hi) {
+    const double x = swap_lane_pair(S), y = odd ? -x : x;
+    lo = (w == 0 ? C : C + y) * scale;
+    hi = (w == 0 ? S : C - y) * scale;
+}
+
+// Forward transform with one transformed axis (d <= 2): nbc blocks of 8 complex
+// columns from block nb0. Columns of a factor: c = line * m + q; of the grid: the
+// sample lines t. out[w * NC + c].
+__device__ __forceinline__ void forward_lines(const SpecPlan& P, const double2* __restrict__ src, int64_t rs,
+                                              int64_t cs, bool grid, double2* __restrict__ out, int nb0, int nbc,
+                                              unsigned char* smem) {
+    const int mc = grid ? 1 : P.m;
+    const int NC = grid ? P.NP1 : P.K1 * P.m;
+    const int K = grid ? P.L : P.P, KS = (K + 3) >> 2, J = line_rows(K);
+    double2* tab = reinterpret_cast<double2*>(smem);
+    double2* xs = tab + P.L;                     // [block][j][8 columns]
+    const int tid = threadIdx.x;
+    // the inputs, along the axis that is contiguous in memory first, 8 loads in flight
+    const int J4 = 4 * KS, tot = nbc * J4 * kCols;
+    const bool jfast = grid || rs < cs;
+    constexpr int kStage = 8;
+    for (int base = 0; base < tot; base += kStage * kThreads) {
+        double2 v[kStage];
+        int at[kStage];
+#pragma unroll
+        for (int u = 0; u < kStage; ++u) {
+            const int e = base + u * kThreads + tid;
+            v[u] = make_double2(0.0, 0.0);
+            at[u] = -1;
+            if (e < tot) {
+                int cc, j, nb;
+                if (jfast) {
+                    const int rest = e / J4;
+                    j = e - rest * J4;
+                    cc = rest & 7;
+                    nb = rest >> 3;
+                } else {
+                    const int rest = e >> 3;
+                    cc = e & 7;
+                    nb = rest / J4;
+                    j = rest - nb * J4;
+                }
+                at[u] = (nb * J + j) * kCols + cc;
+                const int c = kCols * (nb0 + nb) + cc;
+                if (c < NC && j < K) {
+                    if (grid) {
+                        const int o = sample_offset(P, c, j);
+                        if (o >= 0) v[u] = src[o];
+                    } else {
+                        const int line = c / mc, q = c - line * mc, idx = line * P.P + j;
+                        if (idx < P.N) v[u] = src[idx * rs + q * cs];
+                    }
+                }
+            }
+        }
+        if (base == 0) fill_roots(tab, P.L);
+#pragma unroll
+        for (int u = 0; u < kStage; ++u)
+            if (at[u] >= 0) xs[at[u]] = v[u];
+    }
+    __syncthreads();
+    const int lane = tid & 63, wave = tid >> 6, g = lane >> 4, col = lane & 15;
+    const bool odd = lane & 1;
+    const double scale = grid ? 1.0 / P.F : 1.0;
+    // an item is one column block against two blocks of pairs, four K steps of
+    // operands ahead
+    constexpr int NP = 2, CH = 4;
+    const int npi = (P.npb + NP - 1) / NP;
+    for (int it = wave; it < nbc * npi; it += kWaves) {
+        const int nb = it / npi, pb = (it - nb * npi) * NP;
+        RowWalk row[NP] = {RowWalk(kPairs * pb + (col & 7), col >= 8, g, P.L),
+                           RowWalk(kPairs * (pb + 1) + (col & 7), col >= 8, g, P.L)};
+        const double* x = reinterpret_cast<const double*>(xs + (size_t)nb * J * kCols) + 16 * g + col;
+        acc_t acc[NP];
+        double a[2][CH][NP], b[2][CH];
+        auto read = [&](int buf, int s) {       // rows past J4 are staged or spare rows, unused
+#pragma unroll
+            for (int k = 0; k < CH; ++k) {
+                b[buf][k] = x[64 * (s + k)];
+#pragma unroll
+                for (int i = 0; i < NP; ++i) a[buf][k][i] = row[i].next(tab);
+            }
+        };
+        auto mma = [&](int buf, int s) {
+#pragma unroll
+            for (int k = 0; k < CH; ++k)
+                if (s + k < KS)
+#pragma unroll
+                    for (int i = 0; i < NP; ++i) acc[i] = M::fma(a[buf][k][i], b[buf][k], acc[i]);
+        };
+#pragma unroll
+        for (int i = 0; i < NP; ++i) acc[i] = acc_t{0, 0, 0, 0};
+        read(0, 0);
+        for (int s = 0; s < KS; s += 2 * CH) {
+            if (s + CH < KS) read(1, s + CH);
+            mma(0, s);
+            if (s + 2 * CH < KS) read(0, s + 2 * CH);
+            mma(1, s + CH);
+        }
+        const int c = kCols * (nb0 + nb) + (col >> 1);
+        double* o = reinterpret_cast<double*>(out) + 2 * c + (col & 1);
+#pragma unroll
+        for (int i = 0; i < NP; ++i)
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const int w = kPairs * (pb + i) + g + 4 * r;
+                double lo, hi;
+                pair_out(w, odd, acc[i][r], acc[i][r + 2], scale, lo, hi);
+                if (w < P.P && c < NC) {
+                    o[(size_t)w * NC * 2] = lo;
+                    o[(size_t)(w == 0 ? P.P : P.L - w) * NC * 2] = hi;
+                }
+            }
+    }
+}
+
+// Forward transform with two transformed axes (d = 3): the plane (axes 2, 3) of line
+// `line` and nq complex columns from column q0: axis 3 at the pairs split * wp ..
+// (and their mirrors) into LDS, then axis 2. out[(w2 L + w3) * rowlen + line * mc + q].
+__device__ __forceinline__ void forward_planes(const SpecPlan& P, const double2* __restrict__ src, int64_t rs,
+                                               int64_t cs, bool grid, double2* __restrict__ out, int line, int q0,
+                                               int nq, int split, unsigned char* smem) {
+    const int mc = grid ? 1 : P.m;
+    const size_t rowlen = grid ? P.NP1 : (size_t)P.K1 * P.m;
+    const int J = grid ? P.L : P.P, KS = (J + 3) >> 2;
+    const int w0 = split * P.wp, wn = min(P.wp, P.P - w0);
+    double2* tab = reinterpret_cast<double2*>(smem);
+    double* t1 = reinterpret_cast<double*>(tab + P.L);      // [j2][2 u + side][q] complex
+    const int ts = plane_stride(wn, nq);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, col = lane & 15;
+    const bool odd = lane & 1, sine = col >= 8;
+    const double* in = reinterpret_cast<const double*>(src);
+    // rows past J are zero (the K steps are whole)
+    for (int i = tid; i < (4 * KS - J) * ts; i += kThreads) t1[(size_t)J * ts + i] = 0.0;
+
+    // axis 3: columns c = j2 * nq + q in blocks of 8, NBI blocks per pass, so that one
+    // read of the tables serves all, and kIn K steps of their loads in flight
+    constexpr int NBI = 2, kIn = 6;
+    const int nc1 = J * nq, nb1 = (nc1 + 7) >> 3, npb1 = (wn + kPairs - 1) / kPairs;
+    const int items1 = (nb1 + NBI - 1) / NBI * npb1;
+    for (int it = wave; it < items1 || it == wave; it += kWaves) {   // every wave meets the barrier inside once
+        const int ng = it / npb1, pb = it - ng * npb1;
+        int64_t base[NBI];
+        bool ok[NBI];
+        int o1[NBI];
+        acc_t acc[NBI];
+#pragma unroll
+        for (int i = 0; i < NBI; ++i) {
+            const int c = 8 * (ng * NBI + i) + (col >> 1);
+            ok[i] = it < items1 && c < nc1;
+            const int j2 = c / nq, q = c - j2 * nq;
+            o1[i] = j2 * ts + 2 * q + (col & 1);
+            if (grid) {
+                const int p1 = line - (P.K1 - 1), p2 = j2 <= P.P ? j2 : j2 - P.L;
+                base[i] = 2 * ((int64_t)((p1 + P.n) * P.L + p2 + P.n) * P.L + P.n) + (col & 1);
+            } else {
+                base[i] = 2 * ((int64_t)(line * P.P + j2) * P.P * rs + (q0 + q) * cs) + (col & 1);
+            }
+            acc[i] = acc_t{0, 0, 0, 0};
+        }
+        RowWalk row(w0 + kPairs * pb + (col & 7), sine, g, P.L);
+        for (int s0 = 0; s0 < KS; s0 += kIn) {
+            double b[NBI][kIn];
+#pragma unroll
+            for (int k = 0; k < kIn; ++k) {
+                const int j = 4 * (s0 + k) + g;
+                const int64_t off = grid ? (int64_t)(j <= P.P ? j : j - P.L) * 2 : 2 * j * rs;
+#pragma unroll
+                for (int i = 0; i < NBI; ++i) b[i][k] = ok[i] && j < J ? in[base[i] + off] : 0.0;
+            }
+            if (it == wave && s0 == 0) {     // the first loads are in flight
+                fill_roots(tab, P.L);
+                __syncthreads();
+            }
+            double a[kIn];
+#pragma unroll
+            for (int k = 0; k < kIn; ++k) a[k] = row.next(tab);
+#pragma unroll
+            for (int k = 0; k < kIn; ++k)
+                if (s0 + k < KS)
+#pragma unroll
+                    for (int i = 0; i < NBI; ++i) acc[i] = M::fma(a[k], b[i][k], acc[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < NBI; ++i)
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const int u = kPairs * pb + g + 4 * r;
+                double lo, hi;
+                pair_out(w0 + u, odd, acc[i][r], acc[i][r + 2], 1.0, lo, hi);
+                if (ok[i] && u < wn) {
+                    t1[o1[i] + 4 * u * nq] = lo;
+                    t1[o1[i] + (4 * u + 2) * nq] = hi;
+                }
+            }
+    }
+    __syncthreads();
+
+    // axis 2: columns c = (2 u + side) * nq + q of the LDS rows j2
+    constexpr int NB2 = 4, CH = 3;
+    const int nc2 = 2 * wn * nq, nb2 = (nc2 + 7) >> 3;
+    const int ng2 = (nb2 + NB2 - 1) / NB2;
+    const double scale = grid ? 1.0 / P.F : 1.0;
+    for (int it = wave; it < ng2 * P.npb; it += kWaves) {
+        const int ng = it / P.npb, pb = it - ng * P.npb;
+        RowWalk row(kPairs * pb + (col & 7), sine, g, P.L);
+        acc_t acc[NB2];
+        const double* x[NB2];
+#pragma unroll
+        for (int i = 0; i < NB2; ++i) {
+            acc[i] = acc_t{0, 0, 0, 0};
+            // columns past the last read the last block again and are not stored
+            x[i] = t1 + g * ts + 16 * min(ng * NB2 + i, nb2 - 1) + col;
+        }
+        double a[2][CH], b[2][CH][NB2];
+        auto read = [&](int buf, int s) {
+#pragma unroll
+            for (int k = 0; k < CH; ++k) {
+                a[buf][k] = row.next(tab);
+#pragma unroll
+                for (int i = 0; i < NB2; ++i) b[buf][k][i] = x[i][4 * min(s + k, KS - 1) * ts];
+            }
+        };
+        auto mma = [&](int buf, int s) {
+#pragma unroll
+            for (int k = 0; k < CH; ++k)
+                if (s + k < KS)
+#pragma unroll
+                    for (int i = 0; i < NB2; ++i) acc[i] = M::fma(a[buf][k], b[buf][k][i], acc[i]);
+        };
+        read(0, 0);
+        for (int s = 0; s < KS; s += 2 * CH) {
+            if (s + CH < KS) read(1, s + CH);
+            mma(0, s);
+            if (s + 2 * CH < KS) read(0, s + 2 * CH);
+            mma(1, s + CH);
+        }
+#pragma unroll
+        for (int i = 0; i < NB2; ++i) {
+            const int c = 8 * (ng * NB2 + i) + (col >> 1);
+            const int wl = c / nq, q = c - wl * nq, w3p = w0 + (wl >> 1);
+            const int w3 = wl & 1 ? (w3p == 0 ? P.P : P.L - w3p) : w3p;
+            double* o = reinterpret_cast<double*>(out) + 2 * ((size_t)w3 * rowlen + (size_t)line * mc + q0 + q) + (col & 1);
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const int w2 = kPairs * pb + g + 4 * r;
+                double lo, hi;
+                pair_out(w2, odd, acc[i][r], acc[i][r + 2], scale, lo, hi);
+                if (w2 < P.P && c < nc2) {
+                    o[(size_t)w2 * P.L * rowlen * 2] = lo;
+                    o[(size_t)(w2 == 0 ? P.P : P.L - w2) * P.L * rowlen * 2] = hi;
+                }
+            }
+        }
+    }
+}
+
+// Workgroup `id` of an instance's forward transforms: the sample grid's first (they
+// are the longest), then V's and U's.
+__device__ __forceinline__ void forward_body(const SpecPlan& P, const SpecPtrs& p, int id, unsigned char* smem) {
+    const bool grid = id < P.wgs_f;
+    const bool second = id >= P.wgs_f + P.wgs_x;
+    if (id == 0)    // the phases of the Gram products
+        for (int j = threadIdx.x; j < P.L; j += kThreads) {
+            double sn, cn;
+            sincospi(2.0 * j / P.L, &sn, &cn);
+            p.roots[j] = make_double2(cn, sn);
+        }
+    const int x = grid ? id : id - P.wgs_f - (second ? P.wgs_x : 0);
+    const double2* src = grid ? p.f : second ? p.U : p.V;
+    const int64_t rs = second ? p.u_rs : p.v_rs, cs = second ? p.u_cs : p.v_cs;
+    double2* out = grid ? p.ft : second ? p.ut : p.vt;
+    if (P.d == 3) {
+        const int per = grid ? 1 : (P.m + P.nq - 1) / P.nq;   // column blocks of a line
+        const int split = x % P.splits, rest = x / P.splits;
+        const int qb = rest % per, line = rest / per;
+        forward_planes(P, src, rs, cs, grid, out, line, qb * P.nq, grid ? 1 : min(P.nq, P.m - qb * P.nq), split, smem);
+    } else {
+        const int nbw = grid ? P.nbwf : P.nbw;
+        const int nblk = ((grid ? P.NP1 : P.K1 * P.m) + kCols - 1) / kCols;
+        forward_lines(P, src, rs, cs, grid, out, x * nbw, min(nbw, nblk - x * nbw), smem);
+    }
+}
+
+__global__ __launch_bounds__(kThreads) void spectral_forward_kernel(SpecPlan P, SpecPtrs p, int first) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    forward_body(P, p, first + blockIdx.x, smem);
+}
+
+// A buffer of `bytes` bytes at `p` (wave-uniform): loads at byte offsets outside it,
+// negative ones included, return zero. The offset kOutside stays outside when a
+// buffer's length is added.
+constexpr int kOutside = (int)0x80000000u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const double2* p, int bytes) {
+    constexpr int kRaw32 = 0x00020000;   // untyped 32-bit data, no swizzle
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<double2*>(p), 0, bytes, kRaw32);
+}
+__device__ __forceinline__ double2 buffer_load(__amdgpu_buffer_rsrc_t b, int offset) {
+    typedef unsigned u4 __attribute__((ext_vector_type(4)));
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    const u4 v = __builtin_amdgcn_raw_buffer_load_b128(b, offset, 0, 0);
+    const d2 d = __builtin_bit_cast(d2, v);
+    return make_double2(d.x, d.y);
+}
+
+// Largest number of lines (a wave's window of f~_w is held in four registers per lane
+// between its load and its LDS store: 16 + 4 KS - 1 <= 256 entries).
+constexpr int kMaxLines = 240;
+__host__ __device__ inline size_t window_bytes(int K1) { return 16 * (size_t)(16 + ((K1 + 3) & ~3)); }
+
+// Frequencies wa .. wb - 1 of group grp; with d = 3 they share the frequency of axis 2.
+__device__ __forceinline__ void group_range(const SpecPlan& P, int grp, int& wa, int& wb) {
+    const int gp = P.gparts, n = P.d == 3 ? P.L : P.F;
+    const int o = grp / gp, k = grp - o * gp;
+    wa = o * n + n * k / gp;
+    wb = o * n + n * (k + 1) / gp;
+}
+
+// Weighted Gram products of the frequencies of group grp with the columns
+// 16 qb .. 16 qb + 15 of V. A unit is one frequency and one of its U full 16-row
+// blocks of rows k1', together with the U-th part (along h1) of the last, partial
+// row block; the units are shared out over the waves in order. Per row block: the
+// Toeplitz product in the three-product form, then the Gram products with the
+// stacked rows [U~_w[k1] | U~_w[k1 - 1]] (d >= 2; the second m rows give S_1): NMB
+// blocks of 16, of which the first NM0 hold rows of the first kind. NS = 1: their sum
+// with the phase e^{2 pi i w_d / L}; NS = 2: the plain sum and the one with that phase
+// (d = 3: axis 2's phase is the group's, applied to the plain sum at the end). The
+// shifted rows take the plain sum in either case. At most 256 registers, so that two
+// workgroups share a CU and one's loads overlap the other's products: requesting the
+// next row block's operands before the Gram products as well took the kernel past that
+// (d = 3, n = 20, m = 20: 30.0 instead of 24.1 us; d = 2, n = 63, m = 20: 12.2, 9.7 us).
+template <int NMB, int NM0, int NS>
+__device__ __forceinline__ void gram_body(const SpecPlan& P, const SpecPtrs& p, int grp, int qb, unsigned char* smem) {
+    const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, col = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    double2* win = reinterpret_cast<double2*>(smem + window_bytes(P.K1) * wave);
+    const bool shift1 = P.d >= 2;
+    const int m = P.m, K1 = P.K1, KS = (K1 + 3) >> 2;
+    const int R = shift1 ? K1 + 1 : K1, full = R >> 4, rem = R & 15;
+    const int U = max(full, 1);
+    int wa, wb;
+    group_range(P, grp, wa, wb);
+    const int units = (wb - wa) * U;
+    const int u0 = units * wave / kWaves, u1 = units * (wave + 1) / kWaves;
+    const int q = 16 * qb + col;
+    const bool qok = q < m;
+    constexpr int CH = NS == 1 ? 8 : 4;      // K steps of V per register set
+    constexpr int NW = 4;
+
+    double2 acc0[NMB][4], acc1[NS == 2 ? NM0 : 1][4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+#pragma unroll
+        for (int b = 0; b < NMB; ++b) acc0[b][r] = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int b = 0; b < (NS == 2 ? NM0 : 1); ++b) acc1[b][r] = make_double2(0.0, 0.0);
+    }
+
+    // row block: frequency w, first row r0, K steps s0 .. s1 - 1, 4-row steps ng
+    struct Block {
+        int w, r0, s0, s1, ng;
+    };
+    auto block_at = [&](int u, bool last) {
+        const int w = wa + u / U, v = u % U;
+        return last ? Block{w, 16 * full, KS * v / U, KS * (v + 1) / U, (rem + 3) >> 2} : Block{w, 16 * v, 0, KS, 4};
+    };
+    // Operands of frequency w are read as buffers of their own K1 m (or NP1) values:
+    // rows and samples outside them read as zero, padded columns take kOutside.
+    const int row_bytes = 16 * m;
+    const int voff = qok ? g * row_bytes + 16 * q : kOutside;
+    int uoff[NMB];
+#pragma unroll
+    for (int b = 0; b < NMB; ++b) {
+        const int i = 16 * b + col;   // i >= m: the second m rows, U~[k1 - 1][i - m]
+        uoff[b] = i < m ? g * row_bytes + 16 * i
+                        : shift1 && i < 2 * m ? (g - 1) * row_bytes + 16 * (i - m) : kOutside;
+    }
+    double2 wr[NW], va[CH], vb[CH];
+    auto load_v = [&](double2 (&v)[CH], const Block& B, int s) {
+        const auto vt = buffer_of(p.vt + (size_t)B.w * K1 * m, K1 * row_bytes);
+#pragma unroll
+        for (int k = 0; k < CH; ++k) v[k] = buffer_load(vt, voff + 4 * (s + k) * row_bytes);
+    };
+    // window entry x: row r0 + i, column h with x = i + 4 s1 - 1 - h
+    auto request = [&](const Block& B) {
+        const auto ft = buffer_of(p.ft + (size_t)B.w * P.NP1, 16 * P.NP1);
+        const int t0 = B.r0 + K1 - 4 * B.s1;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) wr[k] = buffer_load(ft, 16 * (t0 + lane + 64 * k));
+        load_v(va, B, B.s0);
+        load_v(vb, B, B.s0 + CH);
+    };
+    auto load_u = [&](double2 (&u)[4], const Block& B, int b) {
+        const auto ut = buffer_of(p.ut + (size_t)B.w * K1 * m, K1 * row_bytes);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) u[s] = buffer_load(ut, uoff[b] + (B.r0 + 4 * s) * row_bytes);
+    };
+
+    for (int x = 2 * u0; x < 2 * u1; ++x) {
+        const bool last = x & 1;
+        if (last ? rem == 0 : full == 0) continue;
+        const Block B = block_at(x >> 1, last);
+        request(B);
+        double2 ua[4], ub[4];
+        load_u(ua, B, 0);
+        const double2 ph = p.roots[P.d == 3 ? B.w % P.L : B.w];
+        const int cnt = 15 + 4 * (B.s1 - B.s0);
+#pragma unroll
+        for (int k = 0; k < NW; ++k)
+            if (64 * k < cnt && lane + 64 * k < cnt) win[lane + 64 * k] = wr[k];
+        __builtin_amdgcn_wave_barrier();
+        acc_t y1 = {0, 0, 0, 0}, y2 = {0, 0, 0, 0}, y3 = {0, 0, 0, 0};
+        const double2* wl = win + col + 4 * B.s1 - 1 - g;
+        auto mma = [&](const double2 (&v)[CH], int s) {
+#pragma unroll
+            for (int k = 0; k < CH; ++k)
+                if (s + k < B.s1) {
+                    const double2 a = wl[-4 * (s + k)];
+                    y1 = M::fma(a.x, v[k].x, y1);
+                    y2 = M::fma(a.y, v[k].y, y2);
+                    y3 = M::fma(a.x + a.y, v[k].x + v[k].y, y3);
+                }
+        };
+        for (int s = B.s0; s < B.s1; s += 2 * CH) {
+            mma(va, s);
+            if (s + 2 * CH < B.s1) load_v(va, B, s + 2 * CH);
+            mma(vb, s + CH);
+            if (s + 3 * CH < B.s1) load_v(vb, B, s + 3 * CH);
+        }
+        __builtin_amdgcn_wave_barrier();
+        double yr[4], yi[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            yr[r] = y1[r] - y2[r];
+            yi[r] = y3[r] - y1[r] - y2[r];
+        }
+        auto gram = [&](const double2 (&uu)[4], auto bc) {
+            constexpr int b = decltype(bc)::value;
+            acc_t e1 = {0, 0, 0, 0}, e2 = {0, 0, 0, 0}, e3 = {0, 0, 0, 0};
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                if (s < B.ng) {
+                    e1 = M::fma(uu[s].x, yr[s], e1);
+                    e2 = M::fma(uu[s].y, yi[s], e2);
+                    e3 = M::fma(uu[s].x - uu[s].y, yr[s] + yi[s], e3);
+                }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const double gr = e1[r] + e2[r], gi = e3[r] - e1[r] + e2[r];
+                double2& a0 = acc0[b][r];
+                if constexpr (NS == 1 && b < NM0) {
+                    const bool sh = shift1 && 16 * b + M::row(g, r) >= m;
+                    const double cr = sh ? 1.0 : ph.x, ci = sh ? 0.0 : ph.y;
+                    a0.x = fma(cr, gr, fma(-ci, gi, a0.x));
+                    a0.y = fma(cr, gi, fma(ci, gr, a0.y));
+                } else {
+                    a0.x += gr;
+                    a0.y += gi;
+                }
+                if constexpr (NS == 2 && b < NM0) {
+                    double2& a1 = acc1[b][r];
+                    a1.x = fma(ph.x, gr, fma(-ph.y, gi, a1.x));
+                    a1.y = fma(ph.x, gi, fma(ph.y, gr, a1.y));
+                }
+            }
+        };
+        // (the scheduling barriers keep the sums of one block at a time in registers)
+        if constexpr (NMB > 1) load_u(ub, B, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        gram(ua, std::integral_constant<int, 0>{});
+        if constexpr (NMB > 2) load_u(ua, B, 2);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (NMB > 1) gram(ub, std::integral_constant<int, 1>{});
+        if constexpr (NMB > 3) load_u(ub, B, 3);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (NMB > 2) gram(ua, std::integral_constant<int, 2>{});
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (NMB > 3) gram(ub, std::integral_constant<int, 3>{});
+    }
+
+    // fixed-order sum over the waves and the group's row of partials [i][l][q]
+    double2* red = reinterpret_cast<double2*>(smem);   // [wave][block][row][lane]
+    double2* out = p.part + (size_t)grp * m * P.ells * m;
+    const double2 ph2 = P.d == 3 ? p.roots[wa / P.L] : make_double2(1.0, 0.0);
+    auto put = [&](int i, int ell, int qq, double2 v) {
+        out[((size_t)i * P.ells + (P.s0 ? ell : ell - 1)) * m + qq] = v;
+    };
+    auto reduce = [&](const double2 (*acc)[4], auto nbc, bool phased) {
+        constexpr int NBK = decltype(nbc)::value, per = NBK * 4 * 64;
+        __syncthreads();
+#pragma unroll
+        for (int b = 0; b < NBK; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) red[wave * per + (b * 4 + r) * 64 + lane] = acc[b][r];
+        __syncthreads();
+        for (int e = tid; e < per; e += kThreads) {
+            const int l = e & 63, br = e >> 6;
+            const int i = 16 * (br >> 2) + M::row(l >> 4, br & 3), qq = 16 * qb + (l & 15);
+            if (qq >= m || i >= (shift1 ? 2 * m : m)) continue;
+            double2 v = red[e];
+#pragma unroll
+            for (int x = 1; x < kWaves; ++x) {
+                v.x += red[x * per + e].x;
+                v.y += red[x * per + e].y;
+            }
+            if (i >= m) {
+                if (!phased || NS == 1) put(i - m, 1, qq, v);
+            } else if (phased) {
+                put(i, P.d, qq, v);          // axis d's phase
+            } else {
+                if (P.s0) put(i, 0, qq, v);
+                if (P.d == 3)
+                    put(i, 2, qq, make_double2(fma(ph2.x, v.x, -ph2.y * v.y), fma(ph2.x, v.y, ph2.y * v.x)));
+            }
+        }
+    };
+    reduce(acc0, std::integral_constant<int, NMB>{}, NS == 1);
+    if constexpr (NS == 2) reduce(acc1, std::integral_constant<int, NM0>{}, true);
+}
+
+template <int NMB, int NM0, int NS>
+__global__ __launch_bounds__(kThreads, 2) void spectral_gram(SpecPlan P, SpecPtrs p) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int qb = blockIdx.x % P.nqb, grp = blockIdx.x / P.nqb;
+    gram_body<NMB, NM0, NS>(P, p, grp, qb, smem);
+}
+
+__device__ __forceinline__ void finish_body(const SpecPlan& P, const SpecPtrs& p, int slice) {
+    const int C = P.ells * P.m;
+    finish_rows(p.part, P.groups, P.m * C, slice * kFinishOuts, [&](int o, double re, double im) {
+        const int i = o / C, c = o - i * C, li = c / P.m, q = c - li * P.m;
+        const double s = p.sigma[q];
+        p.S[((size_t)li * P.m + i) * P.m + q] = make_double2(re / s, im / s);
+    });
+}
+
+__global__ __launch_bounds__(kFinishThreads) void spectral_finish(SpecPlan P, SpecPtrs p) {
+    finish_body(P, p, blockIdx.x);
+}
+
+template <typename K>
+prony_status_t allow_lds(prony_handle_t h, K kernel, size_t lds) {
+    if (lds <= 65536) return PRONY_OK;
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    return e == hipSuccess ? PRONY_OK : hip_fail(h, e, "hipFuncSetAttribute");
+}
+
+template <int NMB, int NM0, int NS>
+prony_status_t launch_gram(prony_handle_t h, const SpecPlan& P, const SpecPtrs& p) {
+    const prony_status_t st = allow_lds(h, &spectral_gram<NMB, NM0, NS>, P.lds_gram);
+    if (st != PRONY_OK) return st;
+    ProfileScope prof(h, "spectral_gram");
+    spectral_gram<NMB, NM0, NS><<<P.groups * P.nqb, kThreads, P.lds_gram, h->stream>>>(P, p);
+    return PRONY_OK;
+}
+
+// (row blocks, those with unshifted rows): m <= 8, 9..16, 17..24, 25..32; d = 1 with
+// m > 16 has two unshifted blocks
+#define PRONY_GRAM_CASES(X) X(1, 1, 1) X(2, 1, 1) X(2, 2, 1) X(3, 2, 1) X(4, 2, 1) X(1, 1, 2) X(2, 1, 2) X(2, 2, 2) X(3, 2, 2) X(4, 2, 2)
+
+}  // namespace
+
+bool spectral_plan(prony_handle_t h, int d, int n, int m, bool s0, SpecPlan& P) {
+    P = SpecPlan{};
+    P.d = d;
+    P.n = n;
+    P.N = (int)ipow(n + 1, d);
+    P.m = m;
+    P.s0 = s0 ? 1 : 0;
+    P.ells = d + P.s0;
+    if (d == 1) {
+        // lines of about sqrt(N) points, a multiple of the 16 pairs of a block
+        P.P = 16 * std::max(1, ((int)std::sqrt((double)P.N) + 8) / 16);
+        P.K1 = (P.N + P.P - 1) / P.P;
+        P.NP1 = 2 * P.K1 - 1;
+    } else {
+        P.P = n + 1;
+        P.K1 = n + 1;
+        P.NP1 = 2 * n + 2;
+    }
+    P.L = 2 * P.P;
+    const int64_t F = ipow(P.L, d == 3 ? 2 : 1);
+    if (F > (int64_t(1) << 20)) return false;
+    P.F = (int)F;
+    P.npb = (P.P + kPairs - 1) / kPairs;
+    const size_t budget = std::min<size_t>(h->lds_per_block, 80 * 1024);   // two workgroups per CU
+    if (d <= 2) {
+        // column blocks per workgroup so that its items (a block against two blocks of
+        // pairs) share out over the four waves
+        const int npi = (P.npb + 1) / 2;
+        P.nbw = 1;
+        while (P.nbw < 4 && (P.nbw * npi) % kWaves && npi < 4 * kWaves) ++P.nbw;
+        auto lds = [&](int nb, int K) { return 16 * (size_t)P.L + 16 * kCols * (size_t)nb * line_rows(K); };
+        while (P.nbw > 1 && lds(P.nbw, P.P) > budget) --P.nbw;
+        P.nbwf = P.nbw;
+        while (P.nbwf > 1 && lds(P.nbwf, P.L) > budget) --P.nbwf;
+        P.lds_fwd = std::max(lds(P.nbw, P.P), lds(P.nbwf, P.L));
+        auto wgs = [&](int64_t cols, int nb) { return (int)(((cols + kCols - 1) / kCols + nb - 1) / nb); };
+        P.wgs_x = wgs((int64_t)P.K1 * m, P.nbw);
+        P.wgs_f = wgs(P.NP1, P.nbwf);
+    } else {
+        P.nq = std::min(m, kCols);
+        auto lds = [&](int nq, int J, int wp) {
+            return 16 * (size_t)P.L + 8 * (size_t)((J + 3) & ~3) * plane_stride(wp, nq);
+        };
+        // one block of pairs per workgroup; fewer pairs where the planes do not fit
+        for (P.wp = kPairs; P.wp > 0; P.wp /= 2) {
+            P.lds_fwd = std::max(lds(P.nq, P.P, P.wp), lds(1, P.L, P.wp));
+            if (P.lds_fwd <= budget) break;
+        }
+        if (P.wp == 0) return false;
+        P.splits = (P.P + P.wp - 1) / P.wp;
+        P.wgs_x = P.K1 * ((m + P.nq - 1) / P.nq) * P.splits;
+        P.wgs_f = P.NP1 * P.splits;
+    }
+    if (P.lds_fwd > budget) return false;
+    P.nqb = (m + 15) / 16;
+    P.nmb = ((d >= 2 ? 2 * m : m) + 15) / 16;
+    P.nm0 = P.nqb;
+    P.ns = d == 3 || s0 ? 2 : 1;
+    const int outer = d == 3 ? P.L : 1;
+    P.gparts = std::min(P.F / outer, std::max(1, 2 * h->num_cus / (P.nqb * outer)));
+    P.groups = outer * P.gparts;
+    P.lds_gram = std::max<size_t>(kWaves * window_bytes(P.K1),
+                                  (size_t)kWaves * P.nmb * 4 * 64 * sizeof(double2));
+    if (P.K1 > kMaxLines || P.lds_gram > budget) return false;
+    const size_t x = align_up(16 * (size_t)P.F * P.K1 * m, 256);
+    P.off_v = x;
+    P.off_f = 2 * x;
+    P.off_p = P.off_f + align_up(16 * (size_t)P.F * P.NP1, 256);
+    P.off_r = P.off_p + align_up(16 * (size_t)P.groups * m * P.ells * m, 256);
+    P.ws_bytes = P.off_r + align_up(16 * (size_t)P.L, 256);
+    return P.ws_bytes <= (size_t(1) << 30);
+}
+
+prony_status_t spectral_forward(prony_handle_t h, const SpecPlan& P, const SpecPtrs& ptr, bool factors, bool grid) {
+    prony_status_t st = allow_lds(h, &spectral_forward_kernel, P.lds_fwd);
+    if (st != PRONY_OK) return st;
+    const int first = grid ? 0 : P.wgs_f;
+    const int wgs = (grid ? P.wgs_f : 0) + (factors ? 2 * P.wgs_x : 0);
+    {
+        ProfileScope prof(h, "spectral_forward");
+        spectral_forward_kernel<<<wgs, kThreads, P.lds_fwd, h->stream>>>(P, ptr, first);
+    }
+    return check_launch(h, "spectral_forward");
+}
+
+prony_status_t spectral_gram_finish(prony_handle_t h, const SpecPlan& P, const SpecPtrs& ptr) {
+    prony_status_t st = PRONY_OK;
+    switch (P.nmb * 16 + P.nm0 * 4 + P.ns) {
+#define PRONY_CASE(B, B0, S)                   \
+    case B * 16 + B0 * 4 + S:                  \
+        st = launch_gram<B, B0, S>(h, P, ptr); \
+        break;
+        PRONY_GRAM_CASES(PRONY_CASE)
+#undef PRONY_CASE
+        default:
+            return fail(h, PRONY_ENOTSUP, "prony_build_S: unexpected spectral plan");
+    }
+    if (st != PRONY_OK) return st;
+    if ((st = check_launch(h, "spectral_gram")) != PRONY_OK) return st;
+    {
+        ProfileScope prof(h, "pencil_finish");
+        const int tot = P.m * P.ells * P.m;
+        spectral_finish<<<(tot + kFinishOuts - 1) / kFinishOuts, kFinishThreads, 0, h->stream>>>(P, ptr);
+    }
+    return check_launch(h, "spectral_finish");
+}
+
+}  // namespace prony

@@ -1,0 +1,91 @@
+"""The line-spectral FP64 S-build at the sizes where its tilings end: lines of less
+than, exactly and just over a block of 8 frequency pairs and of 16 rows, one and two
+column blocks of V, one to four row blocks of [U | shifted U], partial row blocks
+split over the full ones, the fold of d = 1, the largest line count and the first
+size past it (tile kernel). Reference: the oracle's dense matrices, and for N too
+large for those the same products by zero-padded FFTs in numpy. Tolerance: the
+suite's FP64 bound 1e-12 (normwise and entrywise): every sum is FP64 with at most
+n + 1 terms per axis, so the error is a small multiple of (3 n) 2^-53 < 1e-13."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import prony_oracle as O
+from paper_2012_11430_amd import api
+from tests._close import assert_close_per_matrix
+
+pytestmark = pytest.mark.gpu
+
+DEV = torch.device("cuda:0")
+TOL = 1e-12
+
+
+def _dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).to(DEV)
+
+
+def _problem(d, n, m, seed):
+    rng = np.random.Generator(np.random.PCG64(seed))
+    N, G = (n + 1) ** d, (2 * n + 2) ** d
+    cn = lambda *s: rng.standard_normal(s) + 1j * rng.standard_normal(s)   # noqa: E731
+    return cn(G), cn(N, m), rng.uniform(0.5, 2.0, m), cn(N, m)
+
+
+def _fft_pencil(grid, d, n, U, s, V):
+    """S_l, l = 0..d, by a circular convolution on the (2n+2)^d box: k - h + e_l lies in
+    {-n..n+1} on every axis, where the residues modulo 2n + 2 are distinct."""
+    L, axes = 2 * n + 2, tuple(range(1, d + 1))
+    g = np.roll(grid.reshape((L,) * d), -n, axis=tuple(range(d)))      # point p at index p mod L
+    pad = np.zeros((V.shape[1],) + (L,) * d, dtype=complex)
+    box = (slice(None),) + (slice(0, n + 1),) * d
+    pad[box] = V.T.reshape((-1,) + (n + 1,) * d)
+    Z = np.fft.ifftn(np.fft.fftn(g)[None] * np.fft.fftn(pad, axes=axes), axes=axes)
+    out = []
+    for l in range(d + 1):
+        lo = [1 if l == a else 0 for a in range(1, d + 1)]
+        Y = Z[(slice(None),) + tuple(slice(x, x + n + 1) for x in lo)].reshape(V.shape[1], -1).T
+        out.append(U.conj().T @ Y / s[None, :])
+    return np.stack(out)
+
+
+@pytest.mark.parametrize("d,n,m", [
+    (1, 1, 1), (1, 14, 3), (1, 15, 8), (1, 16, 16), (1, 255, 17), (1, 576, 24), (1, 1023, 32),
+    (2, 1, 1), (2, 6, 4), (2, 7, 8), (2, 8, 9), (2, 14, 16), (2, 15, 17), (2, 16, 25), (2, 23, 32), (2, 32, 24),
+    (3, 1, 2), (3, 6, 7), (3, 7, 8), (3, 8, 9), (3, 9, 33 - 8), (3, 14, 16)])
+@pytest.mark.parametrize("with_s0", [False, True])
+def test_tile_edges_match_the_oracle(d, n, m, with_s0):
+    grid, U, s, V = _problem(d, n, m, seed=7000 + 100 * d + n + m)
+    print(f"spectral d={d} n={n} m={m} s0={with_s0}", flush=True)
+    ref = O.pencil_matrices(grid, d, n, U, s, V, with_s0=with_s0)
+    got = api.build_S(_dev(grid), d, n, _dev(U), _dev(s), _dev(V), with_s0=with_s0)
+    assert_close_per_matrix(got.cpu().numpy(), ref, TOL, "row-major factors")
+    again = api.build_S(_dev(grid), d, n, _dev(U.T).T, _dev(s), _dev(V.T).T, with_s0=with_s0)
+    assert torch.equal(got, again)       # the strides do not enter the arithmetic
+
+
+@pytest.mark.parametrize("d,n,m", [(1, 20000, 5), (1, 57599, 3), (1, 57600, 2), (2, 127, 20), (2, 239, 9), (2, 240, 4),
+                                   (3, 20, 20), (3, 24, 10), (3, 31, 4)])
+def test_large_shapes_match_padded_ffts(d, n, m):
+    grid, U, s, V = _problem(d, n, m, seed=9000 + 100 * d + n + m)
+    print(f"spectral d={d} n={n} m={m}", flush=True)
+    ref = _fft_pencil(grid, d, n, U, s, V)
+    got = api.build_S(_dev(grid), d, n, _dev(U), _dev(s), _dev(V), with_s0=True).cpu().numpy()
+    assert_close_per_matrix(got, ref, TOL, f"d={d} n={n} m={m}")
+
+
+def test_non_finite_columns_stay_in_their_columns():
+    # a NaN or infinity in one column of V (or U) reaches that column (row) of every S_l only
+    d, n, m = 2, 20, 20
+    grid, U, s, V = _problem(d, n, m, seed=11)
+    for bad in (np.nan, np.inf):
+        Vb, Ub = V.copy(), U.copy()
+        Vb[37, 3] = bad
+        Ub[100, 18] = bad
+        S = api.build_S(_dev(grid), d, n, _dev(Ub), _dev(s), _dev(Vb), with_s0=True).cpu().numpy()
+        finite = np.isfinite(S)
+        assert not finite[:, :, 3].any() and not finite[:, 18, :].any()
+        keep = np.ones((m, m), dtype=bool)
+        keep[:, 3] = keep[18, :] = False
+        assert finite[:, keep].all()
+        ref = O.pencil_matrices(grid, d, n, U, s, V, with_s0=True)
+        np.testing.assert_allclose(S[:, keep], ref[:, keep], rtol=0, atol=1e-12 * np.abs(ref).max())
