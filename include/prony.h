@@ -328,7 +328,9 @@ prony_status_t prony_build_S_adjoint(prony_handle_t handle, int d, int n, int m,
          overlap X.
    prec: arithmetic and tile-accumulation type (FP32 or FP64): MFMA tiles, or vector
          FMAs when r = 1 (one Lanczos step's product); the chunk partials are added
-         in FP64 in a fixed order (bitwise reproducible). Requires 1 <= r <= 64.
+         in FP64 in a fixed order (bitwise reproducible). FP64 runs in line-spectral
+         form where it fits (see prony_build_S; bitwise reproducible too); a
+         non-finite sample then reaches every entry of Y. Requires 1 <= r <= 64.
    Uses the handle's workspace (grown as needed; PRONY_ECAPTURE if it must grow
    under stream capture). */
 prony_status_t prony_toeplitz_mm(prony_handle_t handle, int d, int n, int adjoint, const double* f, int r,

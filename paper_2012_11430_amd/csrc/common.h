@@ -72,6 +72,10 @@ struct DeviceGuard {
 // needed while the handle's stream is being captured.
 prony_status_t ensure_workspace(prony_handle_t h, size_t bytes);
 
+// Whether the workspace can hold `bytes`: it does already, or it may grow (the stream
+// is not being captured), or it would have to grow for the `other` form as well.
+bool workspace_available(prony_handle_t h, size_t bytes, size_t other);
+
 // Brackets one kernel launch with profiling events when the handle profiles `name`.
 class ProfileScope {
   public:

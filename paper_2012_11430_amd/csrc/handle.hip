@@ -56,6 +56,12 @@ prony_status_t ensure_workspace(prony_handle_t h, size_t bytes) {
     return PRONY_OK;
 }
 
+bool workspace_available(prony_handle_t h, size_t bytes, size_t other) {
+    if (bytes <= h->ws_bytes || other > h->ws_bytes) return true;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(h->stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone;
+}
+
 static hipEvent_t next_event(prony_handle_t h) {
     if (h->prof_used == h->prof_events.size()) {
         hipEvent_t e = nullptr;

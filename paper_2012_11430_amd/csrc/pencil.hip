@@ -1818,6 +1818,7 @@ extern "C" prony_status_t prony_build_S(prony_handle_t h, int d, int n, int m, c
     if (st != PRONY_OK) return st;
     DeviceGuard g(h->device);
     if (!g.ok) return fail(h, PRONY_EHIP, "hipSetDevice failed");
+    if (B.spectral && !workspace_available(h, B.SP.ws_bytes, B.P.ws_bytes)) B.spectral = false;
     if ((st = ensure_workspace(h, B.ws_bytes())) != PRONY_OK) return st;
     return run_build_S(h, B, static_cast<unsigned char*>(h->ws), prec, f, U, u_rs, u_cs, sigma, V, v_rs, v_cs, S);
 }
@@ -2429,6 +2430,14 @@ extern "C" prony_status_t prony_toeplitz_mm(prony_handle_t h, int d, int n, int 
         st = make_plan(h, d, n, r, false, ts, P, target, 0, 1, false, true);
     if (st != PRONY_OK) return st;
     P.conj_grid = adjoint;
+    // FP64 in line-spectral form where it applies; a shape the tiles cannot cover is
+    // refused above, and a capture that the workspace of the tiles would do for runs them
+    SpecPlan SP;
+    if (prec == PRONY_FP64 && spectral_product_plan(h, d, n, r, SP) &&
+        workspace_available(h, SP.ws_bytes, P.ws_bytes)) {
+        if ((st = ensure_workspace(h, SP.ws_bytes)) != PRONY_OK) return st;
+        return spectral_product(h, SP, static_cast<unsigned char*>(h->ws), f, X, ldx, adjoint != 0, Y, ldy);
+    }
     return prec == PRONY_FP32 ? launch_toeplitz_mm<float>(h, P, f, X, ldx, Y, ldy)
                               : launch_toeplitz_mm<double>(h, P, f, X, ldx, Y, ldy);
 }

@@ -12,6 +12,7 @@ namespace prony {
 struct SpecPlan {
     int d, n, N, m;
     int P, L, K1;
+    int pmax;       // largest sample index used: n + 1, products with T: n
     int NP1;        // sample lines p1 = t - (K1 - 1), t < NP1
     int F;          // frequencies: L^(transformed axes)
     int ells, s0;   // stored matrices (S_0 first with s0), d or d + 1
@@ -31,6 +32,12 @@ struct SpecPlan {
     int groups;     // groups of frequencies = rows of partials
     int gparts;     // groups per frequency of axis 2 (d = 3), else all groups
     size_t lds_gram;
+    // inverse transforms of the products
+    int nbi;            // d <= 2: 8-column blocks per workgroup
+    int nqi;            // d = 3: columns per workgroup
+    int isplits, irows; // d = 3: parts of the rows of axis 2, rows per part
+    int wgs_i;
+    size_t lds_inv;
     // workspace sections (bytes): U~ | V~ | f~ | partials | roots; the first off_f bytes are
     // what prepared factors keep
     size_t off_v, off_f, off_p, off_r, ws_bytes;
@@ -58,5 +65,11 @@ bool spectral_plan(prony_handle_t h, int d, int n, int m, bool s0, SpecPlan& P);
 // grid; then the weighted Gram products and the finishing sums into S.
 prony_status_t spectral_forward(prony_handle_t h, const SpecPlan& P, const SpecPtrs& ptr, bool factors, bool grid);
 prony_status_t spectral_gram_finish(prony_handle_t h, const SpecPlan& P, const SpecPtrs& ptr);
+
+// Plan of an FP64 product with T or T^* and r columns (the workspace: Y~ | X~ | f~ | roots),
+// and the product.
+bool spectral_product_plan(prony_handle_t h, int d, int n, int r, SpecPlan& P);
+prony_status_t spectral_product(prony_handle_t h, const SpecPlan& P, unsigned char* ws, const double* f,
+                                const double* X, int64_t ldx, bool adjoint, double* Y, int64_t ldy);
 
 }  // namespace prony

@@ -41,12 +41,16 @@ constexpr int kCols = 8;            // complex columns of one 16-column MFMA blo
 using M = Mfma<double>;
 using acc_t = M::acc_t;
 
-// cos and sin of 2 pi j / L, j < L.
+// Table in LDS of cos and sin of 2 pi j / L, j < L, one entry skipped after every 16 (all
+// banks): the rows of a block read it at strides 4 s + g, which without the gaps fall
+// into few banks where L is a multiple of 16.
+__host__ __device__ inline int root_slot(int j) { return j + (j >> 4); }
+__host__ __device__ inline size_t roots_bytes(int L) { return 16 * (size_t)(root_slot(L - 1) + 1); }
 __device__ __forceinline__ void fill_roots(double2* tab, int L) {
     for (int j = threadIdx.x; j < L; j += kThreads) {
         double s, c;
         sincospi(2.0 * j / L, &s, &c);
-        tab[j] = make_double2(c, s);
+        tab[root_slot(j)] = make_double2(c, s);
     }
 }
 
@@ -55,14 +59,16 @@ __device__ __forceinline__ void fill_roots(double2* tab, int L) {
 // the rows of two lane groups fall into different banks).
 __host__ __device__ inline int line_rows(int K) { return (K + 15) & ~15; }
 __host__ __device__ inline int plane_stride(int pairs, int nq) { return ((4 * pairs * nq + 31) & ~31) + 16; }
+__host__ __device__ inline int inverse_stride(int rows, int nq) { return ((2 * rows * nq + 31) & ~31) + 16; }
 
 // Offset in f of the sample (line t, point j of the embedded axis), -1 where there is
-// none. Point j stands for p2 = j (j <= P) or j - L.
+// none (the products with T use the samples up to n only). Point j stands for
+// p2 = j (j <= P) or j - L.
 __device__ __forceinline__ int sample_offset(const SpecPlan& P, int t, int j) {
     const int p1 = t - (P.K1 - 1), p2 = j <= P.P ? j : j - P.L;
-    if (P.d == 2) return (p1 + P.n) * P.L + p2 + P.n;
+    if (P.d == 2) return p1 <= P.pmax && p2 <= P.pmax ? (p1 + P.n) * P.L + p2 + P.n : -1;
     const int p = p1 * P.P + p2;
-    return p >= -P.n && p <= P.n + 1 ? p + P.n : -1;
+    return p >= -P.n && p <= P.pmax ? p + P.n : -1;
 }
 
 // Forward transforms run on 16-row blocks of 8 frequency pairs: row i < 8 of block pb
@@ -72,6 +78,16 @@ __device__ __forceinline__ int sample_offset(const SpecPlan& P, int t, int j) {
 // (-1)^j of frequency P.
 constexpr int kPairs = 8;
 
+// First index and step of a walk x g, x (g + 4), x (g + 8), ... modulo L, g < 4, x < L / 2
+// (rows past the last are clamped to it; they are not stored).
+__device__ __forceinline__ void walk_start(int x, int g, int L, int& idx, int& step) {
+    x = min(x, L / 2 - 1);
+    idx = x * g;
+    if (idx >= L) idx -= L;
+    step = 4 * x;
+    if (step >= L) step -= L;
+}
+
 // Table walk of a lane's row: its factor at j = 4 s + g for s = 0, 1, ...
 struct RowWalk {
     int idx, step, L, part;
@@ -79,14 +95,13 @@ struct RowWalk {
     bool zero_sine;
     __device__ __forceinline__ RowWalk(int w, bool sine, int g, int L_) {
         L = L_;
-        idx = (int)(((int64_t)w * g) % L);
-        step = (int)((4 * (int64_t)w) % L);
+        walk_start(w, g, L, idx, step);
         part = sine ? 1 : 0;
         alt = g & 1 ? -1.0 : 1.0;
         zero_sine = sine && w == 0;
     }
     __device__ __forceinline__ double next(const double2* tab) {
-        const double v = reinterpret_cast<const double*>(tab)[2 * idx + part];
+        const double v = reinterpret_cast<const double*>(tab)[2 * root_slot(idx) + part];
         idx += step;
         if (idx >= L) idx -= L;
         return zero_sine ? alt : v;
@@ -111,34 +126,21 @@ __device__ __forceinline__ void forward_lines(const SpecPlan& P, const double2* 
     const int NC = grid ? P.NP1 : P.K1 * P.m;
     const int K = grid ? P.L : P.P, KS = (K + 3) >> 2, J = line_rows(K);
     double2* tab = reinterpret_cast<double2*>(smem);
-    double2* xs = tab + P.L;                     // [block][j][8 columns]
+    double2* xs = tab + roots_bytes(P.L) / 16;                     // [block][j][8 columns]
     const int tid = threadIdx.x;
-    // the inputs, along the axis that is contiguous in memory first, 8 loads in flight
-    const int J4 = 4 * KS, tot = nbc * J4 * kCols;
+    // the inputs in tiles of 16 points x 8 columns per half workgroup, lanes along the
+    // axis that is contiguous in memory, 8 loads in flight
     const bool jfast = grid || rs < cs;
+    const int e = tid & 127, jl = jfast ? e & 15 : e >> 3, cc = jfast ? e >> 4 : e & 7;
+    const int half = tid >> 7, per = (J / 16 + 1) / 2, turns = nbc * per;   // turns of both halves
     constexpr int kStage = 8;
-    for (int base = 0; base < tot; base += kStage * kThreads) {
+    for (int base = 0; base < turns; base += kStage) {
         double2 v[kStage];
-        int at[kStage];
 #pragma unroll
         for (int u = 0; u < kStage; ++u) {
-            const int e = base + u * kThreads + tid;
             v[u] = make_double2(0.0, 0.0);
-            at[u] = -1;
-            if (e < tot) {
-                int cc, j, nb;
-                if (jfast) {
-                    const int rest = e / J4;
-                    j = e - rest * J4;
-                    cc = rest & 7;
-                    nb = rest >> 3;
-                } else {
-                    const int rest = e >> 3;
-                    cc = e & 7;
-                    nb = rest / J4;
-                    j = rest - nb * J4;
-                }
-                at[u] = (nb * J + j) * kCols + cc;
+            if (base + u < turns) {
+                const int nb = (base + u) / per, j = 16 * (2 * (base + u - nb * per) + half) + jl;
                 const int c = kCols * (nb0 + nb) + cc;
                 if (c < NC && j < K) {
                     if (grid) {
@@ -154,7 +156,10 @@ __device__ __forceinline__ void forward_lines(const SpecPlan& P, const double2* 
         if (base == 0) fill_roots(tab, P.L);
 #pragma unroll
         for (int u = 0; u < kStage; ++u)
-            if (at[u] >= 0) xs[at[u]] = v[u];
+            if (base + u < turns) {
+                const int nb = (base + u) / per, j = 16 * (2 * (base + u - nb * per) + half) + jl;
+                if (j < J) xs[(nb * J + j) * kCols + cc] = v[u];
+            }
     }
     __syncthreads();
     const int lane = tid & 63, wave = tid >> 6, g = lane >> 4, col = lane & 15;
@@ -171,7 +176,7 @@ __device__ __forceinline__ void forward_lines(const SpecPlan& P, const double2* 
         const double* x = reinterpret_cast<const double*>(xs + (size_t)nb * J * kCols) + 16 * g + col;
         acc_t acc[NP];
         double a[2][CH][NP], b[2][CH];
-        auto read = [&](int buf, int s) {       // rows past J4 are staged or spare rows, unused
+        auto read = [&](int buf, int s) {       // rows past K are zero
 #pragma unroll
             for (int k = 0; k < CH; ++k) {
                 b[buf][k] = x[64 * (s + k)];
@@ -223,10 +228,11 @@ __device__ __forceinline__ void forward_planes(const SpecPlan& P, const double2*
     const int J = grid ? P.L : P.P, KS = (J + 3) >> 2;
     const int w0 = split * P.wp, wn = min(P.wp, P.P - w0);
     double2* tab = reinterpret_cast<double2*>(smem);
-    double* t1 = reinterpret_cast<double*>(tab + P.L);      // [j2][2 u + side][q] complex
+    double* t1 = reinterpret_cast<double*>(tab + roots_bytes(P.L) / 16);      // [j2][2 u + side][q] complex
     const int ts = plane_stride(wn, nq);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, col = lane & 15;
     const bool odd = lane & 1, sine = col >= 8;
+    const int jskip = P.pmax == P.n ? P.P : -1;      // the point p = n + 1 of an axis
     const double* in = reinterpret_cast<const double*>(src);
     // rows past J are zero (the K steps are whole)
     for (int i = tid; i < (4 * KS - J) * ts; i += kThreads) t1[(size_t)J * ts + i] = 0.0;
@@ -236,41 +242,62 @@ __device__ __forceinline__ void forward_planes(const SpecPlan& P, const double2*
     constexpr int NBI = 2, kIn = 6;
     const int nc1 = J * nq, nb1 = (nc1 + 7) >> 3, npb1 = (wn + kPairs - 1) / kPairs;
     const int items1 = (nb1 + NBI - 1) / NBI * npb1;
-    for (int it = wave; it < items1 || it == wave; it += kWaves) {   // every wave meets the barrier inside once
-        const int ng = it / npb1, pb = it - ng * npb1;
-        int64_t base[NBI];
-        bool ok[NBI];
-        int o1[NBI];
-        acc_t acc[NBI];
+    const float rnq = 1.0f / nq;
+    auto div_nq = [&](int c) { return (int)((c + 0.5f) * rnq); };     // c < 2^14: exact
+    struct Item {
+        bool live[NBI];          // columns of the plane
+        int o1[NBI];             // their places in an LDS row
+        const double* x[NBI];    // their first inputs, null where there are none
+    };
+    auto item_at = [&](int it, Item& I) {
+        const int ng = it / npb1;
 #pragma unroll
         for (int i = 0; i < NBI; ++i) {
             const int c = 8 * (ng * NBI + i) + (col >> 1);
-            ok[i] = it < items1 && c < nc1;
-            const int j2 = c / nq, q = c - j2 * nq;
-            o1[i] = j2 * ts + 2 * q + (col & 1);
+            I.live[i] = it < items1 && c < nc1;
+            const int j2 = div_nq(c), q = c - j2 * nq;
+            I.o1[i] = j2 * ts + 2 * q + (col & 1);
+            bool ok = I.live[i];
+            int64_t base;
             if (grid) {
                 const int p1 = line - (P.K1 - 1), p2 = j2 <= P.P ? j2 : j2 - P.L;
-                base[i] = 2 * ((int64_t)((p1 + P.n) * P.L + p2 + P.n) * P.L + P.n) + (col & 1);
+                ok = ok && p1 <= P.pmax && p2 <= P.pmax;
+                base = 2 * ((int64_t)((p1 + P.n) * P.L + p2 + P.n) * P.L + P.n) + (col & 1);
             } else {
-                base[i] = 2 * ((int64_t)(line * P.P + j2) * P.P * rs + (q0 + q) * cs) + (col & 1);
+                base = 2 * ((int64_t)(line * P.P + j2) * P.P * rs + (q0 + q) * cs) + (col & 1);
             }
-            acc[i] = acc_t{0, 0, 0, 0};
+            I.x[i] = ok ? in + base : nullptr;
         }
+    };
+    auto load = [&](double (&b)[NBI][kIn], const Item& I, int s0) {
+#pragma unroll
+        for (int k = 0; k < kIn; ++k) {
+            const int j = 4 * (s0 + k) + g;
+            const int64_t off = grid ? (int64_t)(j <= P.P ? j : j - P.L) * 2 : 2 * j * rs;
+            const bool ok = j < J && (!grid || j != jskip);
+#pragma unroll
+            for (int i = 0; i < NBI; ++i) b[i][k] = I.x[i] && ok ? I.x[i][off] : 0.0;
+        }
+    };
+    Item item;
+    double b[NBI][kIn];
+    item_at(wave, item);
+    load(b, item, 0);
+    fill_roots(tab, P.L);            // the first loads are in flight
+    __syncthreads();
+    for (int it = wave; it < items1; it += kWaves) {
+        const int pb = it % npb1;
+        acc_t acc[NBI];
+#pragma unroll
+        for (int i = 0; i < NBI; ++i) acc[i] = acc_t{0, 0, 0, 0};
+        Item next;
+        item_at(it + kWaves, next);
         RowWalk row(w0 + kPairs * pb + (col & 7), sine, g, P.L);
         for (int s0 = 0; s0 < KS; s0 += kIn) {
-            double b[NBI][kIn];
-#pragma unroll
-            for (int k = 0; k < kIn; ++k) {
-                const int j = 4 * (s0 + k) + g;
-                const int64_t off = grid ? (int64_t)(j <= P.P ? j : j - P.L) * 2 : 2 * j * rs;
-#pragma unroll
-                for (int i = 0; i < NBI; ++i) b[i][k] = ok[i] && j < J ? in[base[i] + off] : 0.0;
-            }
-            if (it == wave && s0 == 0) {     // the first loads are in flight
-                fill_roots(tab, P.L);
-                __syncthreads();
-            }
-            double a[kIn];
+            double a[kIn], bn[NBI][kIn];
+            // the next K steps or the next item's first ones
+            const bool more = s0 + kIn < KS;
+            load(bn, more ? item : next, more ? s0 + kIn : 0);
 #pragma unroll
             for (int k = 0; k < kIn; ++k) a[k] = row.next(tab);
 #pragma unroll
@@ -278,6 +305,10 @@ __device__ __forceinline__ void forward_planes(const SpecPlan& P, const double2*
                 if (s0 + k < KS)
 #pragma unroll
                     for (int i = 0; i < NBI; ++i) acc[i] = M::fma(a[k], b[i][k], acc[i]);
+#pragma unroll
+            for (int i = 0; i < NBI; ++i)
+#pragma unroll
+                for (int k = 0; k < kIn; ++k) b[i][k] = bn[i][k];
         }
 #pragma unroll
         for (int i = 0; i < NBI; ++i)
@@ -286,11 +317,12 @@ __device__ __forceinline__ void forward_planes(const SpecPlan& P, const double2*
                 const int u = kPairs * pb + g + 4 * r;
                 double lo, hi;
                 pair_out(w0 + u, odd, acc[i][r], acc[i][r + 2], 1.0, lo, hi);
-                if (ok[i] && u < wn) {
-                    t1[o1[i] + 4 * u * nq] = lo;
-                    t1[o1[i] + (4 * u + 2) * nq] = hi;
+                if (item.live[i] && u < wn) {
+                    t1[item.o1[i] + 4 * u * nq] = lo;
+                    t1[item.o1[i] + (4 * u + 2) * nq] = hi;
                 }
             }
+        item = next;
     }
     __syncthreads();
 
@@ -336,7 +368,7 @@ __device__ __forceinline__ void forward_planes(const SpecPlan& P, const double2*
 #pragma unroll
         for (int i = 0; i < NB2; ++i) {
             const int c = 8 * (ng * NB2 + i) + (col >> 1);
-            const int wl = c / nq, q = c - wl * nq, w3p = w0 + (wl >> 1);
+            const int wl = div_nq(c), q = c - wl * nq, w3p = w0 + (wl >> 1);
             const int w3 = wl & 1 ? (w3p == 0 ? P.P : P.L - w3p) : w3p;
             double* o = reinterpret_cast<double*>(out) + 2 * ((size_t)w3 * rowlen + (size_t)line * mc + q0 + q) + (col & 1);
 #pragma unroll
@@ -406,6 +438,65 @@ __device__ __forceinline__ double2 buffer_load(__amdgpu_buffer_rsrc_t b, int off
 constexpr int kMaxLines = 240;
 __host__ __device__ inline size_t window_bytes(int K1) { return 16 * (size_t)(16 + ((K1 + 3) & ~3)); }
 
+// Rows r0 .. r0 + 15 of Y_w = T_w V~_w over the K steps s0 .. s1 - 1 (h1 = 4 s .. 4 s + 3)
+// in the three-product form; lane (g, col) gets the rows r0 + g + 4 r, r < 4, of V's
+// column col (at byte voff + h1 * 16 m of V~_w). adjoint: T_w^* instead of T_w, i.e.
+// conj(f~_w(-p)) for f~_w(p). `between` runs after the first loads are requested.
+template <int CH, typename Between>
+__device__ __forceinline__ void toeplitz_rows(const SpecPlan& P, const SpecPtrs& p, int w, int r0, int s0, int s1,
+                                              int voff, bool adjoint, double2* win, double (&yr)[4], double (&yi)[4],
+                                              Between between) {
+    const int lane = threadIdx.x & 63, g = lane >> 4, col = lane & 15;
+    const int row_bytes = 16 * P.m, K1 = P.K1;
+    constexpr int NW = 4;
+    const auto ft = buffer_of(p.ft + (size_t)w * P.NP1, 16 * P.NP1);
+    const auto vt = buffer_of(p.vt + (size_t)w * K1 * P.m, K1 * row_bytes);
+    // window entry x: row r0 + i, column h with x = i + 4 s1 - 1 - h
+    const int t0 = r0 + K1 - 4 * s1, cnt = 15 + 4 * (s1 - s0);
+    double2 wr[NW], va[CH], vb[CH];
+#pragma unroll
+    for (int k = 0; k < NW; ++k) {
+        const int t = t0 + lane + 64 * k;
+        wr[k] = buffer_load(ft, 16 * (adjoint ? 2 * (K1 - 1) - t : t));
+    }
+    auto load_v = [&](double2 (&v)[CH], int s) {
+#pragma unroll
+        for (int k = 0; k < CH; ++k) v[k] = buffer_load(vt, voff + 4 * (s + k) * row_bytes);
+    };
+    load_v(va, s0);
+    load_v(vb, s0 + CH);
+    between();
+#pragma unroll
+    for (int k = 0; k < NW; ++k)
+        if (64 * k < cnt && lane + 64 * k < cnt)
+            win[lane + 64 * k] = adjoint ? make_double2(wr[k].x, -wr[k].y) : wr[k];
+    __builtin_amdgcn_wave_barrier();
+    acc_t y1 = {0, 0, 0, 0}, y2 = {0, 0, 0, 0}, y3 = {0, 0, 0, 0};
+    const double2* wl = win + col + 4 * s1 - 1 - g;
+    auto mma = [&](const double2 (&v)[CH], int s) {
+#pragma unroll
+        for (int k = 0; k < CH; ++k)
+            if (s + k < s1) {
+                const double2 a = wl[-4 * (s + k)];
+                y1 = M::fma(a.x, v[k].x, y1);
+                y2 = M::fma(a.y, v[k].y, y2);
+                y3 = M::fma(a.x + a.y, v[k].x + v[k].y, y3);
+            }
+    };
+    for (int s = s0; s < s1; s += 2 * CH) {
+        mma(va, s);
+        if (s + 2 * CH < s1) load_v(va, s + 2 * CH);
+        mma(vb, s + CH);
+        if (s + 3 * CH < s1) load_v(vb, s + 3 * CH);
+    }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        yr[r] = y1[r] - y2[r];
+        yi[r] = y3[r] - y1[r] - y2[r];
+    }
+}
+
 // Frequencies wa .. wb - 1 of group grp; with d = 3 they share the frequency of axis 2.
 __device__ __forceinline__ void group_range(const SpecPlan& P, int grp, int& wa, int& wb) {
     const int gp = P.gparts, n = P.d == 3 ? P.L : P.F;
@@ -415,18 +506,17 @@ __device__ __forceinline__ void group_range(const SpecPlan& P, int grp, int& wa,
 }
 
 // Weighted Gram products of the frequencies of group grp with the columns
-// 16 qb .. 16 qb + 15 of V. A unit is one frequency and one of its U full 16-row
-// blocks of rows k1', together with the U-th part (along h1) of the last, partial
-// row block; the units are shared out over the waves in order. Per row block: the
-// Toeplitz product in the three-product form, then the Gram products with the
-// stacked rows [U~_w[k1] | U~_w[k1 - 1]] (d >= 2; the second m rows give S_1): NMB
-// blocks of 16, of which the first NM0 hold rows of the first kind. NS = 1: their sum
-// with the phase e^{2 pi i w_d / L}; NS = 2: the plain sum and the one with that phase
-// (d = 3: axis 2's phase is the group's, applied to the plain sum at the end). The
-// shifted rows take the plain sum in either case. At most 256 registers, so that two
-// workgroups share a CU and one's loads overlap the other's products: requesting the
-// next row block's operands before the Gram products as well took the kernel past that
-// (d = 3, n = 20, m = 20: 30.0 instead of 24.1 us; d = 2, n = 63, m = 20: 12.2, 9.7 us).
+// 16 qb .. 16 qb + 15 of V. Per 16-row block of rows k1': the Toeplitz product in the
+// three-product form, then the Gram products with the stacked rows
+// [U~_w[k1] | U~_w[k1 - 1]] (d >= 2; the second m rows give S_1): NMB blocks of 16, of
+// which the first NM0 hold rows of the first kind. NS = 1: their sum with the phase
+// e^{2 pi i w_d / L}; NS = 2: the plain sum and the one with that phase (d = 3: axis 2's
+// phase is the group's, applied to the plain sum at the end). The shifted rows take the
+// plain sum in either case. At most 256 registers, so that two workgroups share a CU and
+// one's loads overlap the other's products. Requesting the next row block's operands
+// before the Gram products, or running the full and partial block of a frequency
+// together on shared V operands, took the kernel past that and lost more to spills
+// (d = 3, n = 20, m = 20: 24 us as it is, 30 and 26; d = 2, n = 63: 9.7, 12.2 and 10.9).
 template <int NMB, int NM0, int NS>
 __device__ __forceinline__ void gram_body(const SpecPlan& P, const SpecPtrs& p, int grp, int qb, unsigned char* smem) {
     const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, col = lane & 15;
@@ -435,15 +525,12 @@ __device__ __forceinline__ void gram_body(const SpecPlan& P, const SpecPtrs& p, 
     const bool shift1 = P.d >= 2;
     const int m = P.m, K1 = P.K1, KS = (K1 + 3) >> 2;
     const int R = shift1 ? K1 + 1 : K1, full = R >> 4, rem = R & 15;
-    const int U = max(full, 1);
     int wa, wb;
     group_range(P, grp, wa, wb);
-    const int units = (wb - wa) * U;
-    const int u0 = units * wave / kWaves, u1 = units * (wave + 1) / kWaves;
+    const int nw = wb - wa, ng = (rem + 3) >> 2;
     const int q = 16 * qb + col;
     const bool qok = q < m;
     constexpr int CH = NS == 1 ? 8 : 4;      // K steps of V per register set
-    constexpr int NW = 4;
 
     double2 acc0[NMB][4], acc1[NS == 2 ? NM0 : 1][4];
 #pragma unroll
@@ -454,13 +541,36 @@ __device__ __forceinline__ void gram_body(const SpecPlan& P, const SpecPtrs& p, 
         for (int b = 0; b < (NS == 2 ? NM0 : 1); ++b) acc1[b][r] = make_double2(0.0, 0.0);
     }
 
-    // row block: frequency w, first row r0, K steps s0 .. s1 - 1, 4-row steps ng
+    // The group's row blocks in order, shared out over the waves by their products. Up to
+    // one full 16-row block per frequency: all full blocks, then all partial ones.
+    // More: every full block followed by its part (along h1) of the frequency's partial
+    // block, so that a group of one frequency (K1 = 64: four full blocks and one row)
+    // splits evenly.
     struct Block {
         int w, r0, s0, s1, ng;
     };
-    auto block_at = [&](int u, bool last) {
-        const int w = wa + u / U, v = u % U;
-        return last ? Block{w, 16 * full, KS * v / U, KS * (v + 1) / U, (rem + 3) >> 2} : Block{w, 16 * v, 0, KS, 4};
+    const int ca = 3 * KS + 12 * NMB, cb = 3 * KS + 3 * ng * NMB;     // MFMAs of a full, a partial block
+    int x0, x1;
+    if (full > 1) {
+        x0 = 2 * (nw * full * wave / kWaves);
+        x1 = 2 * (nw * full * (wave + 1) / kWaves);
+    } else {
+        const int na = full ? nw : 0, nb = rem ? nw : 0;
+        auto cut = [&](int k) {
+            const int t = (na * ca + nb * cb) * k / kWaves;
+            return t < na * ca ? (t + ca / 2) / ca : na + (t - na * ca + cb / 2) / cb;
+        };
+        x0 = cut(wave);
+        x1 = wave + 1 < kWaves ? cut(wave + 1) : na + nb;
+    }
+    auto block_at = [&](int x) {
+        if (full > 1) {
+            const int u = x >> 1, w = wa + u / full, v = u % full;
+            if (!(x & 1)) return Block{w, 16 * v, 0, KS, 4};
+            return Block{w, 16 * full, rem ? KS * v / full : 0, rem ? KS * (v + 1) / full : 0, ng};
+        }
+        if (full && x < nw) return Block{wa + x, 0, 0, KS, 4};
+        return Block{wa + x - (full ? nw : 0), 16 * full, 0, KS, ng};
     };
     // Operands of frequency w are read as buffers of their own K1 m (or NP1) values:
     // rows and samples outside them read as zero, padded columns take kOutside.
@@ -473,65 +583,21 @@ __device__ __forceinline__ void gram_body(const SpecPlan& P, const SpecPtrs& p, 
         uoff[b] = i < m ? g * row_bytes + 16 * i
                         : shift1 && i < 2 * m ? (g - 1) * row_bytes + 16 * (i - m) : kOutside;
     }
-    double2 wr[NW], va[CH], vb[CH];
-    auto load_v = [&](double2 (&v)[CH], const Block& B, int s) {
-        const auto vt = buffer_of(p.vt + (size_t)B.w * K1 * m, K1 * row_bytes);
-#pragma unroll
-        for (int k = 0; k < CH; ++k) v[k] = buffer_load(vt, voff + 4 * (s + k) * row_bytes);
-    };
-    // window entry x: row r0 + i, column h with x = i + 4 s1 - 1 - h
-    auto request = [&](const Block& B) {
-        const auto ft = buffer_of(p.ft + (size_t)B.w * P.NP1, 16 * P.NP1);
-        const int t0 = B.r0 + K1 - 4 * B.s1;
-#pragma unroll
-        for (int k = 0; k < NW; ++k) wr[k] = buffer_load(ft, 16 * (t0 + lane + 64 * k));
-        load_v(va, B, B.s0);
-        load_v(vb, B, B.s0 + CH);
-    };
     auto load_u = [&](double2 (&u)[4], const Block& B, int b) {
         const auto ut = buffer_of(p.ut + (size_t)B.w * K1 * m, K1 * row_bytes);
 #pragma unroll
         for (int s = 0; s < 4; ++s) u[s] = buffer_load(ut, uoff[b] + (B.r0 + 4 * s) * row_bytes);
     };
 
-    for (int x = 2 * u0; x < 2 * u1; ++x) {
-        const bool last = x & 1;
-        if (last ? rem == 0 : full == 0) continue;
-        const Block B = block_at(x >> 1, last);
-        request(B);
-        double2 ua[4], ub[4];
-        load_u(ua, B, 0);
-        const double2 ph = p.roots[P.d == 3 ? B.w % P.L : B.w];
-        const int cnt = 15 + 4 * (B.s1 - B.s0);
-#pragma unroll
-        for (int k = 0; k < NW; ++k)
-            if (64 * k < cnt && lane + 64 * k < cnt) win[lane + 64 * k] = wr[k];
-        __builtin_amdgcn_wave_barrier();
-        acc_t y1 = {0, 0, 0, 0}, y2 = {0, 0, 0, 0}, y3 = {0, 0, 0, 0};
-        const double2* wl = win + col + 4 * B.s1 - 1 - g;
-        auto mma = [&](const double2 (&v)[CH], int s) {
-#pragma unroll
-            for (int k = 0; k < CH; ++k)
-                if (s + k < B.s1) {
-                    const double2 a = wl[-4 * (s + k)];
-                    y1 = M::fma(a.x, v[k].x, y1);
-                    y2 = M::fma(a.y, v[k].y, y2);
-                    y3 = M::fma(a.x + a.y, v[k].x + v[k].y, y3);
-                }
-        };
-        for (int s = B.s0; s < B.s1; s += 2 * CH) {
-            mma(va, s);
-            if (s + 2 * CH < B.s1) load_v(va, B, s + 2 * CH);
-            mma(vb, s + CH);
-            if (s + 3 * CH < B.s1) load_v(vb, B, s + 3 * CH);
-        }
-        __builtin_amdgcn_wave_barrier();
+    for (int x = x0; x < x1; ++x) {
+        const Block B = block_at(x);
+        if (B.s0 == B.s1) continue;
+        double2 ua[4], ub[4], ph;
         double yr[4], yi[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            yr[r] = y1[r] - y2[r];
-            yi[r] = y3[r] - y1[r] - y2[r];
-        }
+        toeplitz_rows<CH>(P, p, B.w, B.r0, B.s0, B.s1, voff, false, win, yr, yi, [&] {
+            load_u(ua, B, 0);
+            ph = p.roots[P.d == 3 ? B.w % P.L : B.w];
+        });
         auto gram = [&](const double2 (&uu)[4], auto bc) {
             constexpr int b = decltype(bc)::value;
             acc_t e1 = {0, 0, 0, 0}, e2 = {0, 0, 0, 0}, e3 = {0, 0, 0, 0};
@@ -636,6 +702,255 @@ __global__ __launch_bounds__(kFinishThreads) void spectral_finish(SpecPlan P, Sp
     finish_body(P, p, blockIdx.x);
 }
 
+// ---- products Y = T X, T^* X -------------------------------------------------
+
+// Y~_w[k1][q] = T_w X~_w (or T_w^* X~_w): one 16-row block of one frequency and one
+// 16-column block per wave and turn.
+__global__ __launch_bounds__(kThreads) void spectral_toeplitz(SpecPlan P, SpecPtrs p, int adjoint) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int lane = threadIdx.x & 63, g = lane >> 4, col = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    double2* win = reinterpret_cast<double2*>(smem + window_bytes(P.K1) * wave);
+    const int nrb = (P.K1 + 15) >> 4, KS = (P.K1 + 3) >> 2;
+    const int units = P.F * P.nqb * nrb;
+    for (int u = blockIdx.x * kWaves + wave; u < units; u += gridDim.x * kWaves) {
+        const int rb = u % nrb, rest = u / nrb, qb = rest % P.nqb, w = rest / P.nqb;
+        const int q = 16 * qb + col;
+        double yr[4], yi[4];
+        toeplitz_rows<8>(P, p, w, 16 * rb, 0, KS, q < P.m ? 16 * (g * P.m + q) : kOutside, adjoint, win, yr, yi, [] {});
+        double2* out = p.ut + (size_t)w * P.K1 * P.m + q;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int k1 = 16 * rb + M::row(g, r);
+            if (k1 < P.K1 && q < P.m) out[(size_t)k1 * P.m] = make_double2(yr[r], yi[r]);
+        }
+    }
+}
+
+// Inverse transforms: y(k) = sum_w Y~(w) e^{2 pi i w k / L} as A cos + (i B) sin over the
+// pairs w < P, A = Y~(w) + Y~(L - w), B = Y~(w) - Y~(L - w). Pair 0 takes A = Y~(0) and, in
+// the sine slot with the factors (-1)^k, Y~(P).
+
+// Factors of a lane's output row k at w = 4 s + g.
+struct InverseWalk {
+    int idx, step, L;
+    double alt;
+    bool first;       // the next factor is pair 0's
+    __device__ __forceinline__ InverseWalk(int k, int g, int L_) {
+        L = L_;
+        walk_start(k, g, L, idx, step);
+        alt = k & 1 ? -1.0 : 1.0;
+        first = g == 0;
+    }
+    __device__ __forceinline__ double2 next(const double2* tab) {
+        double2 v = tab[root_slot(idx)];
+        idx += step;
+        if (idx >= L) idx -= L;
+        if (first) v = make_double2(1.0, alt);
+        first = false;
+        return v;
+    }
+};
+
+// The two operands of pair w from Y~(w) and its mirror value (one real column, the other
+// component in the neighbouring lane).
+__device__ __forceinline__ void pair_in(bool zero, bool odd, double a, double b, double& c, double& s) {
+    const double x = swap_lane_pair(a - b), y = odd ? x : -x;     // i B
+    c = zero ? a : a + b;
+    s = zero ? b : y;
+}
+
+// Offset of (line t, column q, point j of the transformed axis) in Y (leading dimension
+// ld), -1 where there is none.
+__device__ __forceinline__ int64_t product_offset(const SpecPlan& P, int64_t ld, int t, int j, int q) {
+    const int idx = t * P.P + j;
+    return j < P.P && idx < P.N ? idx * ld + q : -1;
+}
+
+// One transformed axis (d <= 2): nbc blocks of 8 complex columns c = k1 * m + q of Y~ from
+// block nb0. The pairs' operands are staged as [block][w][16 real columns], A then i B.
+__global__ __launch_bounds__(kThreads) void spectral_inverse_lines(SpecPlan P, SpecPtrs p, double2* __restrict__ Y,
+                                                                   int64_t ld) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int NC = P.K1 * P.m, KS = (P.P + 3) >> 2, J = line_rows(P.P), J4 = 4 * KS;
+    const int nblk = (NC + kCols - 1) / kCols, nb0 = blockIdx.x * P.nbi, nbc = min(P.nbi, nblk - nb0);
+    double2* tab = reinterpret_cast<double2*>(smem);
+    double2* xc = tab + roots_bytes(P.L) / 16;
+    double2* xi = xc + (size_t)P.nbi * J * kCols;
+    const int tid = threadIdx.x;
+    const int tot = nbc * J4 * kCols;
+    constexpr int kStage = 4;
+    for (int base = 0; base < tot; base += kStage * kThreads) {
+        double2 a[kStage], b[kStage];
+#pragma unroll
+        for (int u = 0; u < kStage; ++u) {
+            const int e = base + u * kThreads + tid;
+            const int cc = e & 7, rest = e >> 3, nb = rest / J4, w = rest - nb * J4, c = kCols * (nb0 + nb) + cc;
+            a[u] = b[u] = make_double2(0.0, 0.0);
+            if (e < tot && c < NC && w < P.P) {
+                a[u] = p.ut[(size_t)w * NC + c];
+                b[u] = p.ut[(size_t)(w == 0 ? P.P : P.L - w) * NC + c];
+            }
+        }
+        if (base == 0) fill_roots(tab, P.L);
+#pragma unroll
+        for (int u = 0; u < kStage; ++u) {
+            const int e = base + u * kThreads + tid;
+            if (e >= tot) continue;
+            const int cc = e & 7, rest = e >> 3, nb = rest / J4, w = rest - nb * J4;
+            const int at = (nb * J + w) * kCols + cc;
+            const double2 x = a[u], y = b[u];
+            xc[at] = w == 0 ? x : make_double2(x.x + y.x, x.y + y.y);
+            xi[at] = w == 0 ? y : make_double2(y.y - x.y, x.x - y.x);
+        }
+    }
+    __syncthreads();
+    const int lane = tid & 63, wave = tid >> 6, g = lane >> 4, col = lane & 15;
+    const int nrb = (P.P + 15) >> 4;
+    for (int it = wave; it < nbc * nrb; it += kWaves) {
+        const int nb = it / nrb, rb = it - nb * nrb;
+        InverseWalk row(16 * rb + col, g, P.L);
+        const double* x1 = reinterpret_cast<const double*>(xc + (size_t)nb * J * kCols) + 16 * g + col;
+        const double* x2 = reinterpret_cast<const double*>(xi + (size_t)nb * J * kCols) + 16 * g + col;
+        acc_t ac = {0, 0, 0, 0}, as = {0, 0, 0, 0};
+        constexpr int CH = 4;
+        double2 a[2][CH];
+        double b[2][CH], c[2][CH];
+        auto read = [&](int buf, int s) {
+#pragma unroll
+            for (int k = 0; k < CH; ++k) {
+                b[buf][k] = x1[64 * (s + k)];
+                c[buf][k] = x2[64 * (s + k)];
+                a[buf][k] = row.next(tab);
+            }
+        };
+        auto mma = [&](int buf, int s) {
+#pragma unroll
+            for (int k = 0; k < CH; ++k)
+                if (s + k < KS) {
+                    ac = M::fma(a[buf][k].x, b[buf][k], ac);
+                    as = M::fma(a[buf][k].y, c[buf][k], as);
+                }
+        };
+        read(0, 0);
+        for (int s = 0; s < KS; s += 2 * CH) {
+            if (s + CH < KS) read(1, s + CH);
+            mma(0, s);
+            if (s + 2 * CH < KS) read(0, s + 2 * CH);
+            mma(1, s + CH);
+        }
+        const int cx = kCols * (nb0 + nb) + (col >> 1);
+        const int t = cx / P.m, q = cx - t * P.m;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int64_t o = cx < NC ? product_offset(P, ld, t, 16 * rb + M::row(g, r), q) : -1;
+            if (o >= 0) reinterpret_cast<double*>(Y)[2 * o + (col & 1)] = ac[r] + as[r];
+        }
+    }
+}
+
+// Two transformed axes (d = 3): the rows k2 of part `split` of one line k1 and nq
+// columns: axis 2 into LDS as the operands of axis 3's pairs, then axis 3.
+__global__ __launch_bounds__(kThreads) void spectral_inverse_planes(SpecPlan P, SpecPtrs p, double2* __restrict__ Y,
+                                                                    int64_t ld) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int per = (P.m + P.nqi - 1) / P.nqi;
+    const int split = blockIdx.x % P.isplits, rest0 = blockIdx.x / P.isplits;
+    const int q0 = rest0 % per * P.nqi, line = rest0 / per, nq = min(P.nqi, P.m - q0);
+    const int k20 = split * P.irows, kn = min(P.irows, P.P - k20);
+    const int KS = (P.P + 3) >> 2;
+    const size_t rowlen = (size_t)P.K1 * P.m;
+    double2* tab = reinterpret_cast<double2*>(smem);
+    const int ts = inverse_stride(P.irows, P.nqi);
+    double* tc = reinterpret_cast<double*>(tab + roots_bytes(P.L) / 16);      // [w3 pair][k2][q], A
+    double* ti = tc + (size_t)4 * KS * ts;                  // i B
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, col = lane & 15;
+    const bool odd = lane & 1;
+    for (int i = tid; i < (4 * KS - P.P) * ts; i += kThreads) {
+        tc[(size_t)P.P * ts + i] = 0.0;
+        ti[(size_t)P.P * ts + i] = 0.0;
+    }
+    // axis 2: columns c = u * nq + q of the pairs u of axis 3, w3 = u and its mirror
+    const double* in = reinterpret_cast<const double*>(p.ut);
+    const int nc1 = P.P * nq, nb1 = (nc1 + 7) >> 3;
+    for (int it = wave; it < nb1 || it == wave; it += kWaves) {      // every wave meets the barrier inside once
+        const int c = 8 * it + (col >> 1);
+        const bool ok = c < nc1;
+        const int u = c / nq, q = c - u * nq;
+        const int64_t col0 = 2 * ((int64_t)line * P.m + q0 + q) + (col & 1);
+        const int64_t side[2] = {2 * (int64_t)u * (int64_t)rowlen + col0,
+                                 2 * (int64_t)(u == 0 ? P.P : P.L - u) * (int64_t)rowlen + col0};
+        const int64_t step2 = 2 * (int64_t)P.L * (int64_t)rowlen;      // one frequency of axis 2
+        InverseWalk row(k20 + col, g, P.L);
+        acc_t ac[2], as[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) ac[i] = as[i] = acc_t{0, 0, 0, 0};
+        constexpr int kIn = 3;
+        for (int s0 = 0; s0 < KS; s0 += kIn) {
+            double a[2][kIn], b[2][kIn];
+#pragma unroll
+            for (int k = 0; k < kIn; ++k) {
+                const int w = 4 * (s0 + k) + g;
+                const bool in_range = ok && w < P.P;
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    a[i][k] = in_range ? in[side[i] + w * step2] : 0.0;
+                    b[i][k] = in_range ? in[side[i] + (w == 0 ? P.P : P.L - w) * step2] : 0.0;
+                }
+            }
+            if (it == wave && s0 == 0) {
+                fill_roots(tab, P.L);
+                __syncthreads();
+            }
+#pragma unroll
+            for (int k = 0; k < kIn; ++k)
+                if (s0 + k < KS) {
+                    const double2 t = row.next(tab);
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        double x, y;
+                        pair_in(4 * (s0 + k) + g == 0, odd, a[i][k], b[i][k], x, y);
+                        ac[i] = M::fma(t.x, x, ac[i]);
+                        as[i] = M::fma(t.y, y, as[i]);
+                    }
+                }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int k2 = M::row(g, r);
+            double x, y;
+            pair_in(u == 0, odd, ac[0][r] + as[0][r], ac[1][r] + as[1][r], x, y);
+            if (ok && k2 < kn) {
+                tc[u * ts + 2 * (k2 * nq + q) + (col & 1)] = x;
+                ti[u * ts + 2 * (k2 * nq + q) + (col & 1)] = y;
+            }
+        }
+    }
+    __syncthreads();
+    // axis 3: columns c = k2 * nq + q
+    const int nc2 = kn * nq, nb2 = (nc2 + 7) >> 3, nrb = (P.P + 15) >> 4;
+    for (int it = wave; it < nb2 * nrb; it += kWaves) {
+        const int nb = it / nrb, rb = it - nb * nrb;
+        InverseWalk row(16 * rb + col, g, P.L);
+        const double* x1 = tc + g * ts + 16 * nb + col;
+        const double* x2 = ti + g * ts + 16 * nb + col;
+        acc_t ac = {0, 0, 0, 0}, as = {0, 0, 0, 0};
+        for (int s = 0; s < KS; ++s) {
+            const double2 t = row.next(tab);
+            ac = M::fma(t.x, x1[4 * s * ts], ac);
+            as = M::fma(t.y, x2[4 * s * ts], as);
+        }
+        const int c = 8 * nb + (col >> 1), k2 = c / nq, q = c - k2 * nq;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int k3 = 16 * rb + M::row(g, r);
+            if (c < nc2 && k3 < P.P)
+                reinterpret_cast<double*>(Y)[2 * ((((int64_t)line * P.P + k20 + k2) * P.P + k3) * ld + q0 + q) +
+                                             (col & 1)] = ac[r] + as[r];
+        }
+    }
+}
+
 template <typename K>
 prony_status_t allow_lds(prony_handle_t h, K kernel, size_t lds) {
     if (lds <= 65536) return PRONY_OK;
@@ -659,16 +974,21 @@ prony_status_t launch_gram(prony_handle_t h, const SpecPlan& P, const SpecPtrs& 
 
 }  // namespace
 
-bool spectral_plan(prony_handle_t h, int d, int n, int m, bool s0, SpecPlan& P) {
+namespace {
+
+// Two workgroups share a CU's LDS.
+size_t lds_budget(prony_handle_t h) { return std::min<size_t>(h->lds_per_block, 80 * 1024); }
+
+// Geometry and forward transforms of a plan with m columns per factor.
+bool plan_forward(prony_handle_t h, int d, int n, int m, SpecPlan& P) {
     P = SpecPlan{};
     P.d = d;
     P.n = n;
     P.N = (int)ipow(n + 1, d);
     P.m = m;
-    P.s0 = s0 ? 1 : 0;
-    P.ells = d + P.s0;
+    P.pmax = n + 1;
     if (d == 1) {
-        // lines of about sqrt(N) points, a multiple of the 16 pairs of a block
+        // lines of about sqrt(N) points, a multiple of two blocks of pairs
         P.P = 16 * std::max(1, ((int)std::sqrt((double)P.N) + 8) / 16);
         P.K1 = (P.N + P.P - 1) / P.P;
         P.NP1 = 2 * P.K1 - 1;
@@ -679,17 +999,18 @@ bool spectral_plan(prony_handle_t h, int d, int n, int m, bool s0, SpecPlan& P) 
     }
     P.L = 2 * P.P;
     const int64_t F = ipow(P.L, d == 3 ? 2 : 1);
-    if (F > (int64_t(1) << 20)) return false;
+    if (F > (int64_t(1) << 20) || P.K1 > kMaxLines) return false;
     P.F = (int)F;
     P.npb = (P.P + kPairs - 1) / kPairs;
-    const size_t budget = std::min<size_t>(h->lds_per_block, 80 * 1024);   // two workgroups per CU
+    P.nqb = (m + 15) / 16;
+    const size_t budget = lds_budget(h);
     if (d <= 2) {
         // column blocks per workgroup so that its items (a block against two blocks of
         // pairs) share out over the four waves
         const int npi = (P.npb + 1) / 2;
         P.nbw = 1;
         while (P.nbw < 4 && (P.nbw * npi) % kWaves && npi < 4 * kWaves) ++P.nbw;
-        auto lds = [&](int nb, int K) { return 16 * (size_t)P.L + 16 * kCols * (size_t)nb * line_rows(K); };
+        auto lds = [&](int nb, int K) { return roots_bytes(P.L) + 16 * kCols * (size_t)nb * line_rows(K); };
         while (P.nbw > 1 && lds(P.nbw, P.P) > budget) --P.nbw;
         P.nbwf = P.nbw;
         while (P.nbwf > 1 && lds(P.nbwf, P.L) > budget) --P.nbwf;
@@ -700,7 +1021,7 @@ bool spectral_plan(prony_handle_t h, int d, int n, int m, bool s0, SpecPlan& P) 
     } else {
         P.nq = std::min(m, kCols);
         auto lds = [&](int nq, int J, int wp) {
-            return 16 * (size_t)P.L + 8 * (size_t)((J + 3) & ~3) * plane_stride(wp, nq);
+            return roots_bytes(P.L) + 8 * (size_t)((J + 3) & ~3) * plane_stride(wp, nq);
         };
         // one block of pairs per workgroup; fewer pairs where the planes do not fit
         for (P.wp = kPairs; P.wp > 0; P.wp /= 2) {
@@ -712,8 +1033,17 @@ bool spectral_plan(prony_handle_t h, int d, int n, int m, bool s0, SpecPlan& P) 
         P.wgs_x = P.K1 * ((m + P.nq - 1) / P.nq) * P.splits;
         P.wgs_f = P.NP1 * P.splits;
     }
-    if (P.lds_fwd > budget) return false;
-    P.nqb = (m + 15) / 16;
+    return P.lds_fwd <= budget;
+}
+
+constexpr size_t kMaxWorkspace = size_t(1) << 30;
+
+}  // namespace
+
+bool spectral_plan(prony_handle_t h, int d, int n, int m, bool s0, SpecPlan& P) {
+    if (!plan_forward(h, d, n, m, P)) return false;
+    P.s0 = s0 ? 1 : 0;
+    P.ells = d + P.s0;
     P.nmb = ((d >= 2 ? 2 * m : m) + 15) / 16;
     P.nm0 = P.nqb;
     P.ns = d == 3 || s0 ? 2 : 1;
@@ -722,14 +1052,87 @@ bool spectral_plan(prony_handle_t h, int d, int n, int m, bool s0, SpecPlan& P) 
     P.groups = outer * P.gparts;
     P.lds_gram = std::max<size_t>(kWaves * window_bytes(P.K1),
                                   (size_t)kWaves * P.nmb * 4 * 64 * sizeof(double2));
-    if (P.K1 > kMaxLines || P.lds_gram > budget) return false;
+    if (P.lds_gram > lds_budget(h)) return false;
     const size_t x = align_up(16 * (size_t)P.F * P.K1 * m, 256);
     P.off_v = x;
     P.off_f = 2 * x;
     P.off_p = P.off_f + align_up(16 * (size_t)P.F * P.NP1, 256);
     P.off_r = P.off_p + align_up(16 * (size_t)P.groups * m * P.ells * m, 256);
     P.ws_bytes = P.off_r + align_up(16 * (size_t)P.L, 256);
-    return P.ws_bytes <= (size_t(1) << 30);
+    return P.ws_bytes <= kMaxWorkspace;
+}
+
+bool spectral_product_plan(prony_handle_t h, int d, int n, int r, SpecPlan& P) {
+    if (!plan_forward(h, d, n, r, P)) return false;
+    P.pmax = n;
+    const size_t budget = lds_budget(h);
+    const int KS = (P.P + 3) / 4;
+    if (d <= 2) {
+        const int nrb = (P.P + 15) / 16;
+        auto lds = [&](int nb) { return roots_bytes(P.L) + 2 * 16 * kCols * (size_t)nb * line_rows(P.P); };
+        P.nbi = 1;
+        while (P.nbi < 4 && (P.nbi * nrb) % kWaves && nrb < 4 * kWaves) ++P.nbi;
+        while (P.nbi > 1 && lds(P.nbi) > budget) --P.nbi;
+        P.lds_inv = lds(P.nbi);
+        P.wgs_i = ((P.K1 * r + kCols - 1) / kCols + P.nbi - 1) / P.nbi;
+    } else {
+        P.isplits = (P.P + 15) / 16;
+        P.irows = (P.P + P.isplits - 1) / P.isplits;
+        for (P.nqi = std::min(r, kCols); P.nqi > 0; P.nqi /= 2) {
+            P.lds_inv = roots_bytes(P.L) + 2 * 8 * (size_t)(4 * KS) * inverse_stride(P.irows, P.nqi);
+            if (P.lds_inv <= budget) break;
+        }
+        if (P.nqi == 0) return false;
+        P.wgs_i = P.K1 * ((r + P.nqi - 1) / P.nqi) * P.isplits;
+    }
+    if (P.lds_inv > budget) return false;
+    const size_t x = align_up(16 * (size_t)P.F * P.K1 * r, 256);
+    P.off_v = x;
+    P.off_f = 2 * x;
+    P.off_r = P.off_f + align_up(16 * (size_t)P.F * P.NP1, 256);
+    P.ws_bytes = P.off_r + align_up(16 * (size_t)P.L, 256);
+    return P.ws_bytes <= kMaxWorkspace;
+}
+
+prony_status_t spectral_product(prony_handle_t h, const SpecPlan& P, unsigned char* ws, const double* f,
+                                const double* X, int64_t ldx, bool adjoint, double* Y, int64_t ldy) {
+    SpecPtrs p{};
+    p.V = reinterpret_cast<const double2*>(X);
+    p.v_rs = ldx;
+    p.v_cs = 1;
+    p.f = reinterpret_cast<const double2*>(f);
+    p.ut = reinterpret_cast<double2*>(ws);
+    p.vt = reinterpret_cast<double2*>(ws + P.off_v);
+    p.ft = reinterpret_cast<double2*>(ws + P.off_f);
+    p.roots = reinterpret_cast<double2*>(ws + P.off_r);
+    prony_status_t st = allow_lds(h, &spectral_forward_kernel, P.lds_fwd);
+    if (st != PRONY_OK) return st;
+    {
+        ProfileScope prof(h, "spectral_forward");
+        spectral_forward_kernel<<<P.wgs_f + P.wgs_x, kThreads, P.lds_fwd, h->stream>>>(P, p, 0);   // the grid and X
+    }
+    if ((st = check_launch(h, "spectral_forward")) != PRONY_OK) return st;
+    {
+        ProfileScope prof(h, "spectral_toeplitz");
+        const int64_t units = (int64_t)P.F * P.nqb * ((P.K1 + 15) / 16);
+        const int wgs = (int)std::min<int64_t>((units + kWaves - 1) / kWaves, 4 * (int64_t)h->num_cus);
+        spectral_toeplitz<<<wgs, kThreads, kWaves * window_bytes(P.K1), h->stream>>>(P, p, adjoint ? 1 : 0);
+    }
+    if ((st = check_launch(h, "spectral_toeplitz")) != PRONY_OK) return st;
+    if (P.d == 3)
+        st = allow_lds(h, &spectral_inverse_planes, P.lds_inv);
+    else
+        st = allow_lds(h, &spectral_inverse_lines, P.lds_inv);
+    if (st != PRONY_OK) return st;
+    {
+        ProfileScope prof(h, "spectral_inverse");
+        double2* y = reinterpret_cast<double2*>(Y);
+        if (P.d == 3)
+            spectral_inverse_planes<<<P.wgs_i, kThreads, P.lds_inv, h->stream>>>(P, p, y, ldy);
+        else
+            spectral_inverse_lines<<<P.wgs_i, kThreads, P.lds_inv, h->stream>>>(P, p, y, ldy);
+    }
+    return check_launch(h, "spectral_inverse");
 }
 
 prony_status_t spectral_forward(prony_handle_t h, const SpecPlan& P, const SpecPtrs& ptr, bool factors, bool grid) {

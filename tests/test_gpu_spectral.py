@@ -12,7 +12,7 @@ import torch
 
 from oracle import prony_oracle as O
 from paper_2012_11430_amd import api
-from tests._close import assert_close_per_matrix
+from tests._close import assert_close, assert_close_per_matrix
 
 pytestmark = pytest.mark.gpu
 
@@ -89,3 +89,48 @@ def test_non_finite_columns_stay_in_their_columns():
         assert finite[:, keep].all()
         ref = O.pencil_matrices(grid, d, n, U, s, V, with_s0=True)
         np.testing.assert_allclose(S[:, keep], ref[:, keep], rtol=0, atol=1e-12 * np.abs(ref).max())
+
+
+def _fft_product(grid, d, n, X, adjoint):
+    """T X or T^* X by a circular convolution on the (2n+2)^d box (samples p <= n only)."""
+    L, axes = 2 * n + 2, tuple(range(1, d + 1))
+    g = grid.reshape((L,) * d).copy()
+    for a in range(d):
+        g[(slice(None),) * a + (L - 1,)] = 0.0                          # p = n + 1 is not read
+    g = np.roll(g, -n, axis=tuple(range(d)))
+    if adjoint:                                                        # conj(f(-p))
+        g = np.conj(np.roll(np.flip(g, axis=tuple(range(d))), 1, axis=tuple(range(d))))
+    pad = np.zeros((X.shape[1],) + (L,) * d, dtype=complex)
+    box = (slice(None),) + (slice(0, n + 1),) * d
+    pad[box] = X.T.reshape((-1,) + (n + 1,) * d)
+    Y = np.fft.ifftn(np.fft.fftn(g)[None] * np.fft.fftn(pad, axes=axes), axes=axes)
+    return Y[box].reshape(X.shape[1], -1).T
+
+
+@pytest.mark.parametrize("d,n,r", [
+    (1, 1, 2), (1, 14, 1), (1, 255, 16), (1, 576, 17), (1, 1023, 64), (1, 57599, 3), (1, 57600, 2),
+    (2, 1, 1), (2, 7, 8), (2, 14, 9), (2, 15, 16), (2, 16, 33), (2, 31, 64), (2, 63, 40), (2, 95, 1), (2, 239, 5),
+    (2, 240, 3), (3, 1, 5), (3, 6, 1), (3, 7, 8), (3, 8, 12), (3, 15, 7), (3, 16, 40), (3, 20, 1), (3, 24, 9), (3, 31, 3)])
+def test_products_at_tile_edges(d, n, r):
+    rng = np.random.Generator(np.random.PCG64(5000 + 100 * d + n + r))
+    N, G = (n + 1) ** d, (2 * n + 2) ** d
+    grid = rng.standard_normal(G) + 1j * rng.standard_normal(G)
+    X = rng.standard_normal((N, r)) + 1j * rng.standard_normal((N, r))
+    # the samples with a coordinate n + 1 are not read
+    edge = np.zeros((2 * n + 2,) * d, dtype=bool)
+    for a in range(d):
+        edge[(slice(None),) * a + (2 * n + 1,)] = True
+    dirty = grid.copy()
+    dirty[edge.reshape(-1)] = np.nan
+    big = torch.zeros((N, r + 3), dtype=torch.complex128, device=DEV)
+    big[:, :r] = _dev(X)
+    for adjoint in (False, True):
+        print(f"spectral product d={d} n={n} r={r} adjoint={adjoint}", flush=True)
+        ref = _fft_product(grid, d, n, X, adjoint)
+        out = torch.full((N, r + 2), 7.0, dtype=torch.complex128, device=DEV)
+        api.toeplitz_mm(_dev(dirty), d, n, big[:, :r], adjoint=adjoint, out=out[:, :r])
+        got = out.cpu().numpy()
+        assert_close(got[:, :r], ref, TOL, f"adjoint={adjoint}")
+        assert np.all(got[:, r:] == 7.0)                 # nothing written past the r columns
+        again = api.toeplitz_mm(_dev(grid), d, n, _dev(X), adjoint=adjoint)
+        assert torch.equal(again, out[:, :r])
