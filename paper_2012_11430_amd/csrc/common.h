@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <map>
 #include <string>
@@ -114,6 +115,41 @@ size_t adjoint_workspace_bytes(prony_handle_t h, int d, int n, int m);
 struct AdjBatch;
 prony_status_t adj_batch_free(AdjBatch* a);
 
+// Line-spectral form of an FP64 batch (spectral.hip).
+struct SpecBatch;
+prony_status_t spectral_batch_free(SpecBatch* b);
+
+// Independent launches 0 .. work.size() - 1 on the handle's stream and, once created, its
+// auxiliary streams, each on the lane with the least work so far, largest first, so that
+// their tails overlap (forked from and joined to the handle's stream).
+template <typename Launch>
+prony_status_t launch_on_lanes(prony_handle_t h, const std::vector<double>& work, Launch launch) {
+    const int nl = h->aux_ready ? std::min<int>(1 + prony_handle_s::kAux, (int)work.size()) : 1;
+    hipError_t e = hipSuccess;
+    if (nl > 1) {
+        e = hipEventRecord(h->fork, h->stream);
+        for (int a = 0; a + 1 < nl && e == hipSuccess; ++a) e = hipStreamWaitEvent(h->aux[a], h->fork, 0);
+        if (e != hipSuccess) return hip_fail(h, e, "batch fork");
+    }
+    std::vector<int> by_work(work.size());
+    for (size_t c = 0; c < by_work.size(); ++c) by_work[c] = (int)c;
+    std::stable_sort(by_work.begin(), by_work.end(), [&](int a, int b) { return work[a] > work[b]; });
+    double load[1 + prony_handle_s::kAux] = {};
+    for (int c : by_work) {
+        int lane = 0;
+        for (int l = 1; l < nl; ++l)
+            if (load[l] < load[lane]) lane = l;
+        load[lane] += work[c];
+        const prony_status_t st = launch(c, lane == 0 ? h->stream : h->aux[lane - 1]);
+        if (st != PRONY_OK) return st;
+    }
+    for (int a = 0; a + 1 < nl && e == hipSuccess; ++a) {
+        e = hipEventRecord(h->join[a], h->aux[a]);
+        if (e == hipSuccess) e = hipStreamWaitEvent(h->stream, h->join[a], 0);
+    }
+    return e == hipSuccess ? PRONY_OK : hip_fail(h, e, "batch join");
+}
+
 // Key of a tuning entry: the exact shape, or its bucket (same d, floor(log2 N) and
 // column-block count ceil(m/8)).
 TuneKey tune_key(int d, int n, int m, int prec, bool batched, bool bucket);
@@ -185,4 +221,5 @@ struct prony_batch_s {
     int queue_grid = 0;
     size_t queue_lds = 0;
     prony::AdjBatch* adj = nullptr;
+    prony::SpecBatch* spec = nullptr;   // FP64 in line-spectral form: replaces the tile plan above
 };

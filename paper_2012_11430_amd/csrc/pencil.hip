@@ -2030,6 +2030,12 @@ prony_status_t batch_build(prony_handle_t h, int count, const prony_instance_t* 
                            0, false, true);
         if (st != PRONY_OK) return fail(h, st, who + h->err);
     }
+    // FP64 in line-spectral form where every instance fits it and its memory can be had
+    if constexpr (sizeof(T) == 8) {
+        const prony_status_t st = spectral_batch_build(h, B->inst, &B->spec);
+        if (st == PRONY_OK || st == PRONY_EHIP) return st;
+        h->err.clear();
+    }
     // classes by (product form, column-block count, row fragments); inside a class,
     // longest tiles first
     std::vector<int> order(count);
@@ -2166,40 +2172,15 @@ prony_status_t batch_launch(prony_handle_t h, prony_batch_s* B) {
             return fail(h, PRONY_ENOTSUP, "prony_build_S_batched: the queue schedule is FP32 only");
         }
     }
-    // The class launches are independent: they run on the handle's stream and up
-    // to kAux auxiliary streams (forked after the packing launch, joined before
-    // the finishing launch), each class on the lane with the least work so far
-    // (largest classes first), so that the tails of the classes overlap.
-    const int nl = h->aux_ready ? std::min<int>(1 + prony_handle_s::kAux, (int)B->launches.size()) : 1;
-    hipError_t e = hipSuccess;
-    if (nl > 1) {
-        e = hipEventRecord(h->fork, h->stream);
-        for (int a = 0; a + 1 < nl && e == hipSuccess; ++a) e = hipStreamWaitEvent(h->aux[a], h->fork, 0);
-        if (e != hipSuccess) return hip_fail(h, e, "batch fork");
-    }
-    std::vector<int> by_work(B->launches.size());
-    for (size_t c = 0; c < by_work.size(); ++c) by_work[c] = (int)c;
-    std::stable_sort(by_work.begin(), by_work.end(),
-                     [&](int a, int b) { return B->launches[a].work > B->launches[b].work; });
-    double load[1 + prony_handle_s::kAux] = {};
-    for (int c : by_work) {
+    std::vector<double> work;
+    for (const auto& cl : B->launches) work.push_back(cl.work);
+    st = launch_on_lanes(h, work, [&](int c, hipStream_t stream) {
         const auto& cl = B->launches[c];
-        int lane = 0;
-        for (int l = 1; l < nl; ++l)
-            if (load[l] < load[lane]) lane = l;
-        load[lane] += cl.work;
-        hipStream_t s = lane == 0 ? h->stream : h->aux[lane - 1];
-        st = dispatch_batched<T>(h, cl.nb, cl.rf, cl.ng, entries + cl.first, cl.count, cl.tiles, cl.lds, s);
-        if (st != PRONY_OK) return st;
-        if ((st = check_launch(h, "pencil_tiles_batched")) != PRONY_OK) return st;
-    }
-    if (nl > 1) {
-        for (int a = 0; a + 1 < nl && e == hipSuccess; ++a) {
-            e = hipEventRecord(h->join[a], h->aux[a]);
-            if (e == hipSuccess) e = hipStreamWaitEvent(h->stream, h->join[a], 0);
-        }
-        if (e != hipSuccess) return hip_fail(h, e, "batch join");
-    }
+        const prony_status_t s =
+            dispatch_batched<T>(h, cl.nb, cl.rf, cl.ng, entries + cl.first, cl.count, cl.tiles, cl.lds, stream);
+        return s == PRONY_OK ? check_launch(h, "pencil_tiles_batched") : s;
+    });
+    if (st != PRONY_OK) return st;
     {
         ProfileScope prof(h, "pencil_finish");
         pencil_finish_batched<T><<<dim3(B->finish_x, B->count), kFinishThreads, 0, h->stream>>>(entries);
@@ -2254,11 +2235,12 @@ extern "C" prony_status_t prony_batch_create(prony_handle_t h, int count, const 
 extern "C" prony_status_t prony_batch_destroy(prony_batch_t B) {
     if (!B) return PRONY_EINVAL;
     prony_status_t st = PRONY_OK;
-    if (B->ws || B->adj) {
+    if (B->ws || B->adj || B->spec) {
         DeviceGuard g(B->owner->device);
         if (hipStreamSynchronize(B->owner->stream) != hipSuccess) st = PRONY_EHIP;
         if (B->ws && hipFree(B->ws) != hipSuccess) st = PRONY_EHIP;
         if (B->adj && adj_batch_free(B->adj) != PRONY_OK) st = PRONY_EHIP;
+        if (B->spec && spectral_batch_free(B->spec) != PRONY_OK) st = PRONY_EHIP;
     }
     delete B;
     return st;
@@ -2281,6 +2263,7 @@ extern "C" prony_status_t prony_build_S_batched(prony_handle_t h, prony_batch_t 
     if (h->device < 0) return fail(h, PRONY_ENODEV, "validation-only handle has no device");
     DeviceGuard g(h->device);
     if (!g.ok) return fail(h, PRONY_EHIP, "hipSetDevice failed");
+    if (B->spec) return spectral_batch_launch(h, B->spec);
     return B->prec == PRONY_FP32 ? batch_launch<float>(h, B) : batch_launch<double>(h, B);
 }
 

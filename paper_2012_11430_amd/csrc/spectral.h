@@ -59,12 +59,17 @@ struct SpecPtrs {
 };
 
 // Plan of an FP64 S-build; false where the form does not apply (see there).
-bool spectral_plan(prony_handle_t h, int d, int n, int m, bool s0, SpecPlan& P);
+bool spectral_plan(prony_handle_t h, int d, int n, int m, bool s0, SpecPlan& P, bool batched = false);
 
 // Launches on the handle's stream: the transforms of U and V, and/or of the sample
 // grid; then the weighted Gram products and the finishing sums into S.
 prony_status_t spectral_forward(prony_handle_t h, const SpecPlan& P, const SpecPtrs& ptr, bool factors, bool grid);
 prony_status_t spectral_gram_finish(prony_handle_t h, const SpecPlan& P, const SpecPtrs& ptr);
+
+// FP64 batches: the plan of all instances with its own device memory (PRONY_ENOTSUP when
+// one of them does not fit the form, PRONY_ENOMEM), its launches, its release.
+prony_status_t spectral_batch_build(prony_handle_t h, const std::vector<prony_instance_t>& inst, SpecBatch** out);
+prony_status_t spectral_batch_launch(prony_handle_t h, const SpecBatch* S);
 
 // Plan of an FP64 product with T or T^* and r columns (the workspace: Y~ | X~ | f~ | roots),
 // and the product.

@@ -26,7 +26,9 @@
 //   spectral_finish   fixed-order sum of the groups' partials, Sigma^{-1}.
 #include <algorithm>
 #include <cmath>
+#include <new>
 #include <type_traits>
+#include <vector>
 
 #include "mfma.h"
 #include "reduce.h"
@@ -1040,7 +1042,7 @@ constexpr size_t kMaxWorkspace = size_t(1) << 30;
 
 }  // namespace
 
-bool spectral_plan(prony_handle_t h, int d, int n, int m, bool s0, SpecPlan& P) {
+bool spectral_plan(prony_handle_t h, int d, int n, int m, bool s0, SpecPlan& P, bool batched) {
     if (!plan_forward(h, d, n, m, P)) return false;
     P.s0 = s0 ? 1 : 0;
     P.ells = d + P.s0;
@@ -1048,7 +1050,14 @@ bool spectral_plan(prony_handle_t h, int d, int n, int m, bool s0, SpecPlan& P) 
     P.nm0 = P.nqb;
     P.ns = d == 3 || s0 ? 2 : 1;
     const int outer = d == 3 ? P.L : 1;
-    P.gparts = std::min(P.F / outer, std::max(1, 2 * h->num_cus / (P.nqb * outer)));
+    // a single instance fills the GPU with two workgroups per CU; a batch member takes
+    // workgroups of about 512 products of 16 x 16 x 4 (several microseconds, so that the
+    // fixed cost of a workgroup and its row of partials stays small)
+    const int R = d >= 2 ? P.K1 + 1 : P.K1, KS = (P.K1 + 3) / 4;
+    const int per_w = (R + 15) / 16 * 3 * KS + (R + 3) / 4 * 3 * P.nmb;
+    P.gparts = batched ? (int)(((int64_t)P.F / outer * per_w + 511) / 512)
+                       : std::max(1, 2 * h->num_cus / (P.nqb * outer));
+    P.gparts = std::min(P.F / outer, P.gparts);
     P.groups = outer * P.gparts;
     P.lds_gram = std::max<size_t>(kWaves * window_bytes(P.K1),
                                   (size_t)kWaves * P.nmb * 4 * 64 * sizeof(double2));
@@ -1134,6 +1143,197 @@ prony_status_t spectral_product(prony_handle_t h, const SpecPlan& P, unsigned ch
     }
     return check_launch(h, "spectral_inverse");
 }
+
+// ---- batches -----------------------------------------------------------------
+
+struct SpecBatch {
+    void* ws = nullptr;          // SpecEntry[count], then the instances' workspaces
+    int count = 0;
+    int fwd_wgs = 0;
+    size_t lds_fwd = 0;
+    int finish_x = 1;
+    struct ClassLaunch {
+        int nmb, nm0, ns, first, count, wgs;
+        size_t lds;
+        double work;             // products of the class
+    };
+    std::vector<ClassLaunch> launches;
+};
+
+namespace {
+
+// One instance of a batch: its plan and operands, its first workgroup in the forward
+// launch and in its class's Gram launch.
+struct SpecEntry {
+    SpecPlan P;
+    SpecPtrs p;
+    int fwd_begin, gram_begin;
+};
+
+// Last entry whose `begin` is at most id.
+template <typename Begin>
+__device__ __forceinline__ int entry_of(int id, int count, Begin begin) {
+    int lo = 0, hi = count - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (begin(mid) <= id)
+            lo = mid;
+        else
+            hi = mid - 1;
+    }
+    return lo;
+}
+
+__global__ __launch_bounds__(kThreads) void spectral_forward_batched(const SpecEntry* __restrict__ entries, int count) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int id = blockIdx.x;
+    const SpecEntry& e = entries[entry_of(id, count, [&](int i) { return entries[i].fwd_begin; })];
+    forward_body(e.P, e.p, id - e.fwd_begin, smem);
+}
+
+template <int NMB, int NM0, int NS>
+__global__ __launch_bounds__(kThreads, 2) void spectral_gram_batched(const SpecEntry* __restrict__ entries, int count) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int id = blockIdx.x;
+    const SpecEntry& e = entries[entry_of(id, count, [&](int i) { return entries[i].gram_begin; })];
+    const int x = id - e.gram_begin;
+    gram_body<NMB, NM0, NS>(e.P, e.p, x / e.P.nqb, x % e.P.nqb, smem);
+}
+
+__global__ __launch_bounds__(kFinishThreads) void spectral_finish_batched(const SpecEntry* __restrict__ entries) {
+    const SpecEntry& e = entries[blockIdx.y];
+    if ((int)blockIdx.x * kFinishOuts >= e.P.m * e.P.ells * e.P.m) return;
+    finish_body(e.P, e.p, blockIdx.x);
+}
+
+template <int NMB, int NM0, int NS>
+prony_status_t launch_gram_batched(prony_handle_t h, const SpecEntry* entries, const SpecBatch::ClassLaunch& cl,
+                                   hipStream_t stream) {
+    const prony_status_t st = allow_lds(h, &spectral_gram_batched<NMB, NM0, NS>, cl.lds);
+    if (st != PRONY_OK) return st;
+    ProfileScope prof(h, "spectral_gram", stream);
+    spectral_gram_batched<NMB, NM0, NS><<<cl.wgs, kThreads, cl.lds, stream>>>(entries + cl.first, cl.count);
+    return PRONY_OK;
+}
+
+}  // namespace
+
+prony_status_t spectral_batch_free(SpecBatch* b) {
+    const prony_status_t st = b->ws && hipFree(b->ws) != hipSuccess ? PRONY_EHIP : PRONY_OK;
+    delete b;
+    return st;
+}
+
+prony_status_t spectral_batch_build(prony_handle_t h, const std::vector<prony_instance_t>& inst, SpecBatch** out) {
+    const int count = (int)inst.size();
+    std::vector<SpecPlan> plans(count);
+    for (int i = 0; i < count; ++i)
+        if (!spectral_plan(h, inst[i].d, inst[i].n, inst[i].m, false, plans[i], true))
+            return fail(h, PRONY_ENOTSUP, "an instance does not fit the line-spectral form");
+    // classes by Gram instantiation; inside a class (and in the forward launch) the
+    // largest instances first
+    std::vector<int> order(count);
+    for (int i = 0; i < count; ++i) order[i] = i;
+    auto key = [&](int i) { return plans[i].nmb * 16 + plans[i].nm0 * 4 + plans[i].ns; };
+    auto work = [&](int i) { return (double)plans[i].F * plans[i].K1 * plans[i].m * (plans[i].K1 + 2 * plans[i].m); };
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+        return key(a) != key(b) ? key(a) > key(b) : work(a) > work(b);
+    });
+    size_t off = align_up(sizeof(SpecEntry) * (size_t)count, 256);
+    std::vector<size_t> base(count);
+    for (int pos = 0; pos < count; ++pos) {
+        base[pos] = off;
+        off += plans[order[pos]].ws_bytes;
+    }
+    SpecBatch* S = new (std::nothrow) SpecBatch;
+    if (!S) return fail(h, PRONY_ENOMEM, "prony_batch_create: out of host memory");
+    hipError_t e = hipMalloc(&S->ws, off);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        delete S;
+        return fail(h, PRONY_ENOMEM, std::string("batch workspace allocation failed: ") + hipGetErrorString(e));
+    }
+    S->count = count;
+    std::vector<SpecEntry> host(count);
+    int64_t fwd = 0, wgs = 0;
+    for (int pos = 0; pos < count; ++pos) {
+        const int i = order[pos];
+        const SpecPlan& P = plans[i];
+        const prony_instance_t& x = inst[i];
+        unsigned char* w = static_cast<unsigned char*>(S->ws) + base[pos];
+        SpecEntry& E = host[pos];
+        E.P = P;
+        E.p = SpecPtrs{reinterpret_cast<const double2*>(x.U), reinterpret_cast<const double2*>(x.V), x.m, 1, x.m, 1,
+                       reinterpret_cast<const double2*>(x.f), x.sigma, reinterpret_cast<double2*>(w),
+                       reinterpret_cast<double2*>(w + P.off_v), reinterpret_cast<double2*>(w + P.off_f),
+                       reinterpret_cast<double2*>(w + P.off_p), reinterpret_cast<double2*>(w + P.off_r),
+                       reinterpret_cast<double2*>(x.S)};
+        E.fwd_begin = (int)fwd;
+        fwd += P.wgs_f + 2 * (int64_t)P.wgs_x;
+        if (pos == 0 || key(order[pos - 1]) != key(i)) {
+            S->launches.push_back({P.nmb, P.nm0, P.ns, pos, 0, 0, 0, 0.0});
+            wgs = 0;
+        }
+        auto& cl = S->launches.back();
+        E.gram_begin = (int)wgs;
+        wgs += (int64_t)P.groups * P.nqb;
+        cl.count += 1;
+        cl.wgs = (int)wgs;
+        cl.lds = std::max(cl.lds, P.lds_gram);
+        cl.work += work(i);
+        S->lds_fwd = std::max(S->lds_fwd, P.lds_fwd);
+        S->finish_x = std::max(S->finish_x, (P.m * P.ells * P.m + kFinishOuts - 1) / kFinishOuts);
+        if (fwd > INT32_MAX || wgs > INT32_MAX) {
+            (void)spectral_batch_free(S);
+            return fail(h, PRONY_ENOTSUP, "prony_batch_create: too many workgroups");
+        }
+    }
+    S->fwd_wgs = (int)fwd;
+    e = hipMemcpyAsync(S->ws, host.data(), sizeof(SpecEntry) * (size_t)count, hipMemcpyHostToDevice, h->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+    if (e != hipSuccess) {
+        (void)spectral_batch_free(S);
+        return hip_fail(h, e, "batch work table upload");
+    }
+    *out = S;
+    return PRONY_OK;
+}
+
+prony_status_t spectral_batch_launch(prony_handle_t h, const SpecBatch* S) {
+    const SpecEntry* entries = static_cast<const SpecEntry*>(S->ws);
+    prony_status_t st = allow_lds(h, &spectral_forward_batched, S->lds_fwd);
+    if (st != PRONY_OK) return st;
+    {
+        ProfileScope prof(h, "spectral_forward");
+        spectral_forward_batched<<<S->fwd_wgs, kThreads, S->lds_fwd, h->stream>>>(entries, S->count);
+    }
+    if ((st = check_launch(h, "spectral_forward_batched")) != PRONY_OK) return st;
+    std::vector<double> work;
+    for (const auto& cl : S->launches) work.push_back(cl.work);
+    st = launch_on_lanes(h, work, [&](int c, hipStream_t stream) {
+        const auto& cl = S->launches[c];
+        prony_status_t s = PRONY_OK;
+        switch (cl.nmb * 16 + cl.nm0 * 4 + cl.ns) {
+#define PRONY_CASE(B, B0, K)                                          \
+    case B * 16 + B0 * 4 + K:                                         \
+        s = launch_gram_batched<B, B0, K>(h, entries, cl, stream);    \
+        break;
+            PRONY_GRAM_CASES(PRONY_CASE)
+#undef PRONY_CASE
+            default:
+                return fail(h, PRONY_ENOTSUP, "prony_build_S_batched: unexpected spectral plan");
+        }
+        return s == PRONY_OK ? check_launch(h, "spectral_gram_batched") : s;
+    });
+    if (st != PRONY_OK) return st;
+    {
+        ProfileScope prof(h, "pencil_finish");
+        spectral_finish_batched<<<dim3(S->finish_x, S->count), kFinishThreads, 0, h->stream>>>(entries);
+    }
+    return check_launch(h, "spectral_finish_batched");
+}
+
+// ---- single instances --------------------------------------------------------
 
 prony_status_t spectral_forward(prony_handle_t h, const SpecPlan& P, const SpecPtrs& ptr, bool factors, bool grid) {
     prony_status_t st = allow_lds(h, &spectral_forward_kernel, P.lds_fwd);

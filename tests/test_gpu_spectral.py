@@ -134,3 +134,28 @@ def test_products_at_tile_edges(d, n, r):
         assert np.all(got[:, r:] == 7.0)                 # nothing written past the r columns
         again = api.toeplitz_mm(_dev(grid), d, n, _dev(X), adjoint=adjoint)
         assert torch.equal(again, out[:, :r])
+
+
+@pytest.mark.parametrize("shapes", [
+    [(1, 63, 5), (1, 1023, 32), (2, 7, 3), (2, 63, 20), (3, 3, 9), (3, 15, 31), (2, 30, 16), (3, 8, 8)],
+    [(2, 12, 4)],
+    [(2, 240, 2), (2, 12, 4)]])      # an instance past the form: the whole batch on the tiles
+def test_fp64_batches_match_single_builds(shapes):
+    probs = [_problem(d, n, m, seed=300 + i) for i, (d, n, m) in enumerate(shapes)]
+    dev = [(d, n, _dev(f), _dev(U), _dev(s), _dev(V)) for (d, n, m), (f, U, s, V) in zip(shapes, probs)]
+    batch = api.Batch(dev, prec="fp64")
+    batch.run()
+    eager = [S.clone() for S in batch.S]
+    for S, (d, n, f, U, s, V) in zip(eager, dev):
+        ref = api.build_S(f, d, n, U, s, V)
+        # the sums over groups of frequencies are grouped differently: rounding only
+        assert_close_per_matrix(S.cpu().numpy(), ref.cpu().numpy(), TOL, f"d={d} n={n}")
+    batch.capture()
+    for rep in range(3):
+        for S in batch.S:
+            S.zero_()
+        batch.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(eager, batch.S)), f"replay {rep}"
+        (torch.randn(4096, device=DEV) * 3).sum().item()
+    batch.close()
