@@ -46,6 +46,9 @@ struct prony_handle_s {
     bool aux_ready = false;
     // orders the previous stream's work before the next stream's on a stream change
     hipEvent_t order = nullptr;
+    // tables of the line-spectral form by line length P (device memory, spectral.hip)
+    std::map<int, void*> spectral_tables;
+    size_t spectral_table_bytes = 0;
     // device address of the fixed scratch array of prony_build_S_noalloc on this
     // handle's device (looked up once per device when the handle is created)
     void* scratch = nullptr;

@@ -181,6 +181,9 @@ extern "C" prony_status_t prony_destroy(prony_handle_t h) {
         if (hipStreamSynchronize(h->stream) != hipSuccess) st = PRONY_EHIP;
         if (hipFree(h->ws) != hipSuccess) st = PRONY_EHIP;
     }
+    if (!h->spectral_tables.empty() && hipStreamSynchronize(h->stream) != hipSuccess) st = PRONY_EHIP;
+    for (const auto& t : h->spectral_tables)
+        if (hipFree(t.second) != hipSuccess) st = PRONY_EHIP;
     for (hipEvent_t e : h->prof_events) (void)hipEventDestroy(e);
     for (int a = 0; a < prony_handle_s::kAux; ++a) {
         if (h->aux[a]) {

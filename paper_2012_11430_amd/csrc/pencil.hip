@@ -1784,19 +1784,19 @@ prony_status_t plan_build_S(prony_handle_t h, const char* who, int d, int n, int
 SpecPtrs spectral_ptrs(const SpecPlan& P, unsigned char* base, unsigned char* rest, const double* f, const double* U,
                        int64_t u_rs, int64_t u_cs, const double* sigma, const double* V, int64_t v_rs, int64_t v_cs,
                        double* S) {
+    auto at = [&](size_t off) { return rest ? reinterpret_cast<double2*>(rest + (off - P.off_f)) : nullptr; };
     return SpecPtrs{reinterpret_cast<const double2*>(U), reinterpret_cast<const double2*>(V), u_rs, u_cs, v_rs, v_cs,
                     reinterpret_cast<const double2*>(f), sigma, reinterpret_cast<double2*>(base),
-                    reinterpret_cast<double2*>(base + P.off_v), reinterpret_cast<double2*>(rest),
-                    reinterpret_cast<double2*>(rest + (P.off_p - P.off_f)),
-                    reinterpret_cast<double2*>(rest + (P.off_r - P.off_f)), reinterpret_cast<double2*>(S)};
+                    reinterpret_cast<double2*>(base + P.off_v), at(P.off_f), at(P.off_p),
+                    reinterpret_cast<double2*>(S), at(P.off_r), nullptr};
 }
 
 prony_status_t run_build_S(prony_handle_t h, const BuildPlan& B, unsigned char* ws, prony_prec_t prec,
                            const double* f, const double* U, int64_t u_rs, int64_t u_cs, const double* sigma,
-                           const double* V, int64_t v_rs, int64_t v_cs, double* S) {
+                           const double* V, int64_t v_rs, int64_t v_cs, double* S, bool keep_tables = true) {
     if (B.spectral) {
-        const SpecPtrs p = spectral_ptrs(B.SP, ws, ws + B.SP.off_f, f, U, u_rs, u_cs, sigma, V, v_rs, v_cs, S);
-        const prony_status_t st = spectral_forward(h, B.SP, p, true, true);
+        SpecPtrs p = spectral_ptrs(B.SP, ws, ws + B.SP.off_f, f, U, u_rs, u_cs, sigma, V, v_rs, v_cs, S);
+        const prony_status_t st = spectral_forward(h, B.SP, p, true, true, keep_tables);
         return st == PRONY_OK ? spectral_gram_finish(h, B.SP, p) : st;
     }
     if (prec == PRONY_FP64) return launch_pencil<double>(h, B.P, ws, f, U, u_rs, u_cs, sigma, V, v_rs, v_cs, S);
@@ -1859,7 +1859,7 @@ extern "C" prony_status_t prony_build_S_noalloc(prony_handle_t h, int d, int n, 
     DeviceGuard g(h->device);
     if (!g.ok) return fail(h, PRONY_EHIP, "hipSetDevice failed");
     return run_build_S(h, B, static_cast<unsigned char*>(h->scratch), prec, f, U, u_rs, u_cs, sigma, V, v_rs,
-                       v_cs, S);
+                       v_cs, S, false);
 }
 
 // Prepared factors: the packed (or transformed) operands of one (U, sigma, V) under
@@ -1904,12 +1904,16 @@ extern "C" prony_status_t prony_factors_create(prony_handle_t h, int d, int n, i
         delete F;
         return fail(h, PRONY_ENOMEM, std::string("prony_factors_create: hipMalloc failed: ") + hipGetErrorString(e));
     }
-    if (B.spectral)
-        st = spectral_forward(h, B.SP, spectral_ptrs(B.SP, F->mem, nullptr, nullptr, U, u_rs, u_cs, sigma, V, v_rs,
-                                                     v_cs, nullptr), true, false);
-    else
+    if (B.spectral) {
+        // the tables in the workspace, should the handle not be able to keep them
+        st = ensure_workspace(h, spectral_table_bytes(B.SP));
+        SpecPtrs p = spectral_ptrs(B.SP, F->mem, nullptr, nullptr, U, u_rs, u_cs, sigma, V, v_rs, v_cs, nullptr);
+        p.tables = static_cast<double2*>(h->ws);
+        if (st == PRONY_OK) st = spectral_forward(h, B.SP, p, true, false, true);
+    } else {
         st = prec == PRONY_FP64 ? pack_operands<double>(h, B.P, F->mem, U, u_rs, u_cs, V, v_rs, v_cs)
                                 : pack_operands<float>(h, B.P, F->mem, U, u_rs, u_cs, V, v_rs, v_cs);
+    }
     if (st == PRONY_OK) {
         e = hipMemcpyAsync(F->mem + F->off_sigma, sigma, sizeof(double) * (size_t)m, hipMemcpyDeviceToDevice,
                            h->stream);
@@ -1939,8 +1943,8 @@ extern "C" prony_status_t prony_build_S_factors(prony_handle_t h, prony_factors_
     const double* sigma = reinterpret_cast<const double*>(F->mem + F->off_sigma);
     unsigned char* part = static_cast<unsigned char*>(h->ws);
     if (F->B.spectral) {
-        const SpecPtrs p = spectral_ptrs(F->B.SP, F->mem, part, f, nullptr, 0, 0, sigma, nullptr, 0, 0, S);
-        st = spectral_forward(h, F->B.SP, p, false, true);
+        SpecPtrs p = spectral_ptrs(F->B.SP, F->mem, part, f, nullptr, 0, 0, sigma, nullptr, 0, 0, S);
+        st = spectral_forward(h, F->B.SP, p, false, true, true);
         return st == PRONY_OK ? spectral_gram_finish(h, F->B.SP, p) : st;
     }
     if (F->prec == PRONY_FP64) return launch_tiles_finish<double>(h, P, F->mem, part, f, sigma, S);
@@ -1993,7 +1997,8 @@ extern "C" prony_status_t prony_reserve(prony_handle_t h, int d_max, int n_max, 
             }
             need = std::max(need, coeffs_workspace_bytes(d, n, m));
         }
-    return ensure_workspace(h, need);
+    if ((st = ensure_workspace(h, need)) != PRONY_OK) return st;
+    return spectral_reserve(h, d_max, n_max);
 }
 
 // ---------------------------------------------------------------------------

@@ -16,12 +16,12 @@ struct SpecPlan {
     int NP1;        // sample lines p1 = t - (K1 - 1), t < NP1
     int F;          // frequencies: L^(transformed axes)
     int ells, s0;   // stored matrices (S_0 first with s0), d or d + 1
-    int npb;        // blocks of 8 frequency pairs along one axis
+    int npb;        // blocks of 16 frequency pairs along one axis
     // forward transforms
     int nbw;        // d <= 2: 8-column blocks per workgroup (factors)
     int nbwf;       //         the same for the sample lines
     int nq;         // d = 3: factor columns per workgroup (at most 8)
-    int splits, wp; // d = 3: parts of the frequency pairs of axis 3, pairs per part
+    int splits;     // d = 3: blocks of 16 frequency pairs of axis 3
     int wgs_x;      // workgroups per factor (U, V)
     int wgs_f;      // workgroups of the sample grid
     size_t lds_fwd;
@@ -35,10 +35,10 @@ struct SpecPlan {
     // inverse transforms of the products
     int nbi;            // d <= 2: 8-column blocks per workgroup
     int nqi;            // d = 3: columns per workgroup
-    int isplits, irows; // d = 3: parts of the rows of axis 2, rows per part
+    int isplits, irows; // d = 3: parts of the folded rows of axis 2, rows per part
     int wgs_i;
     size_t lds_inv;
-    // workspace sections (bytes): U~ | V~ | f~ | partials | roots; the first off_f bytes are
+    // workspace sections (bytes): U~ | V~ | f~ | partials | tables; the first off_f bytes are
     // what prepared factors keep
     size_t off_v, off_f, off_p, off_r, ws_bytes;
 };
@@ -54,8 +54,9 @@ struct SpecPtrs {
     double2* vt;      // V~[w][h1][q]
     double2* ft;      // f~[w][t], scaled by 1/F
     double2* part;    // [group][i][l][q]
-    double2* roots;   // e^{2 pi i j / L}, j < L
     double2* S;
+    double2* tables;  // workspace section for the tables where the handle holds none
+    const double2* tab;
 };
 
 // Plan of an FP64 S-build; false where the form does not apply (see there).
@@ -63,15 +64,23 @@ bool spectral_plan(prony_handle_t h, int d, int n, int m, bool s0, SpecPlan& P, 
 
 // Launches on the handle's stream: the transforms of U and V, and/or of the sample
 // grid; then the weighted Gram products and the finishing sums into S.
-prony_status_t spectral_forward(prony_handle_t h, const SpecPlan& P, const SpecPtrs& ptr, bool factors, bool grid);
+// (sets ptr.tab: the handle's tables, made and kept there on the first use of a line length
+// when keep_tables, else made in ptr.tables).
+prony_status_t spectral_forward(prony_handle_t h, const SpecPlan& P, SpecPtrs& ptr, bool factors, bool grid,
+                                bool keep_tables);
 prony_status_t spectral_gram_finish(prony_handle_t h, const SpecPlan& P, const SpecPtrs& ptr);
+
+// Bytes of the tables of a plan; the tables of every shape up to (d_max, n_max), so that
+// later calls allocate none.
+size_t spectral_table_bytes(const SpecPlan& P);
+prony_status_t spectral_reserve(prony_handle_t h, int d_max, int n_max);
 
 // FP64 batches: the plan of all instances with its own device memory (PRONY_ENOTSUP when
 // one of them does not fit the form, PRONY_ENOMEM), its launches, its release.
 prony_status_t spectral_batch_build(prony_handle_t h, const std::vector<prony_instance_t>& inst, SpecBatch** out);
 prony_status_t spectral_batch_launch(prony_handle_t h, const SpecBatch* S);
 
-// Plan of an FP64 product with T or T^* and r columns (the workspace: Y~ | X~ | f~ | roots),
+// Plan of an FP64 product with T or T^* and r columns (the workspace: Y~ | X~ | f~ | tables),
 // and the product.
 bool spectral_product_plan(prony_handle_t h, int d, int n, int r, SpecPlan& P);
 prony_status_t spectral_product(prony_handle_t h, const SpecPlan& P, unsigned char* ws, const double* f,

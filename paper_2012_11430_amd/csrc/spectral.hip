@@ -17,8 +17,8 @@
 // phase form along the second level.
 //
 //   spectral_forward  DFTs of U, V and f as real contractions with the cosine and sine
-//                     tables on the FP64 matrix cores: frequency w and its mirror L - w
-//                     share both sums, x~(w), x~(L - w) = C -+ i S;
+//                     tables on the FP64 matrix cores, folded about the lines' centres:
+//                     frequencies w and -w share both sums, points t and -t both factors;
 //   spectral_gram     per frequency the Toeplitz product (window of f~_w in LDS) and the
 //                     two Gram products, chained in registers: the 16x16 FP64 result
 //                     layout (lane group g, element r: row g + 4 r) is the second
@@ -26,6 +26,7 @@
 //   spectral_finish   fixed-order sum of the groups' partials, Sigma^{-1}.
 #include <algorithm>
 #include <cmath>
+#include <map>
 #include <new>
 #include <type_traits>
 #include <vector>
@@ -43,25 +44,11 @@ constexpr int kCols = 8;            // complex columns of one 16-column MFMA blo
 using M = Mfma<double>;
 using acc_t = M::acc_t;
 
-// Table in LDS of cos and sin of 2 pi j / L, j < L, one entry skipped after every 16 (all
-// banks): the rows of a block read it at strides 4 s + g, which without the gaps fall
-// into few banks where L is a multiple of 16.
-__host__ __device__ inline int root_slot(int j) { return j + (j >> 4); }
-__host__ __device__ inline size_t roots_bytes(int L) { return 16 * (size_t)(root_slot(L - 1) + 1); }
-__device__ __forceinline__ void fill_roots(double2* tab, int L) {
-    for (int j = threadIdx.x; j < L; j += kThreads) {
-        double s, c;
-        sincospi(2.0 * j / L, &s, &c);
-        tab[root_slot(j)] = make_double2(c, s);
-    }
-}
-
 // LDS rows of one staged line block (whole groups of K steps) and doubles per row of
 // the planes between the two transforms of d = 3 (rows 128 bytes apart modulo 256:
 // the rows of two lane groups fall into different banks).
 __host__ __device__ inline int line_rows(int K) { return (K + 15) & ~15; }
-__host__ __device__ inline int plane_stride(int pairs, int nq) { return ((4 * pairs * nq + 31) & ~31) + 16; }
-__host__ __device__ inline int inverse_stride(int rows, int nq) { return ((2 * rows * nq + 31) & ~31) + 16; }
+__host__ __device__ inline int plane_stride(int columns) { return ((2 * columns + 31) & ~31) + 16; }
 
 // Offset in f of the sample (line t, point j of the embedded axis), -1 where there is
 // none (the products with T use the samples up to n only). Point j stands for
@@ -73,189 +60,245 @@ __device__ __forceinline__ int sample_offset(const SpecPlan& P, int t, int j) {
     return p >= -P.n && p <= P.pmax ? p + P.n : -1;
 }
 
-// Forward transforms run on 16-row blocks of 8 frequency pairs: row i < 8 of block pb
-// is the cosine row of w = w0 + 8 pb + i, row 8 + i its sine row, so that a lane holds
-// C = sum x cos (elements 0, 1) and S = sum x sin (elements 2, 3) of the pairs
-// g and g + 4 of the block. Frequency 0 has no sine row: its slot holds the signs
-// (-1)^j of frequency P.
-constexpr int kPairs = 8;
+// Folded transforms. A line of P points is transformed about its centre: with
+// H = (P + 1) / 2 and t = j + 1/2, point H + j lies at t and point H - 1 - j at -t, so
+//     x~(+-w) = C -+ i S,  C = sum_j (x(t) + x(-t)) cos(w t), S = sum_j (x(t) - x(-t)) sin(w t)
+// (angles in units of 2 pi / L), half the contraction length of the plain transform. The
+// phase of the centre is the same for U and V (and X and Y) and cancels; what is stored
+// at L - w is the value at -w. Frequency 0 has no sine row: its slot holds sin(P t) =
+// (-1)^j, so that x~(P) = -i S. The sample grid's lines are folded about p = 0: points
+// j and -j, j = 0..P, t = j; x~(P) is their sum with the signs (-1)^j. All angles are
+// multiples of pi / L.
+__host__ __device__ inline int folded_points(int P, bool grid) { return grid ? P + 1 : (P + 1) >> 1; }
 
-// First index and step of a walk x g, x (g + 4), x (g + 8), ... modulo L, g < 4, x < L / 2
-// (rows past the last are clamped to it; they are not stored).
-__device__ __forceinline__ void walk_start(int x, int g, int L, int& idx, int& step) {
-    x = min(x, L / 2 - 1);
-    idx = x * g;
-    if (idx >= L) idx -= L;
-    step = 4 * x;
-    if (step >= L) step -= L;
+// The factors (cos, sin) come from tables in the operand layout of the products, one
+// 16-byte load per lane and K step: [16-row block][K step][lane], zero past the contraction's
+// end. (Reading them from a table of roots in LDS took 12-15 integer operations per K step,
+// more than the products themselves: 300 cycles per step instead of 128.) They depend on P
+// only and are kept with the handle. Forward rows are the frequencies w = 16 b + lane % 16,
+// the contraction runs over j = 4 s + lane / 16; inverse rows are the points j, the
+// contraction runs over the pairs w. Roots: e^{2 pi i j / L}, j < L.
+struct TableSizes {
+    int ks_f, ks_g, ks_i;              // K steps of the three
+    int off_g, off_i, off_r, total;    // in 16-byte entries (factor table first)
+};
+__host__ __device__ inline TableSizes table_sizes(int P) {
+    TableSizes t;
+    const int H = folded_points(P, false), blocks = (P + 15) >> 4;
+    t.ks_f = (H + 3) >> 2;
+    t.ks_g = (P + 4) >> 2;
+    t.ks_i = (P + 3) >> 2;
+    t.off_g = blocks * t.ks_f * 64;
+    t.off_i = t.off_g + blocks * t.ks_g * 64;
+    t.off_r = t.off_i + ((H + 15) >> 4) * t.ks_i * 64;
+    t.total = t.off_r + 2 * P + 8 * 64;      // the K loops load up to 8 steps past a block's end
+    return t;
 }
 
-// Table walk of a lane's row: its factor at j = 4 s + g for s = 0, 1, ...
-struct RowWalk {
-    int idx, step, L, part;
-    double alt;
-    bool zero_sine;
-    __device__ __forceinline__ RowWalk(int w, bool sine, int g, int L_) {
-        L = L_;
-        walk_start(w, g, L, idx, step);
-        part = sine ? 1 : 0;
-        alt = g & 1 ? -1.0 : 1.0;
-        zero_sine = sine && w == 0;
+__global__ __launch_bounds__(kThreads) void spectral_fill_tables(int P, double2* __restrict__ tab) {
+    const TableSizes T = table_sizes(P);
+    const int H = folded_points(P, false), L = 2 * P;
+    for (int i = blockIdx.x * kThreads + threadIdx.x; i < T.total; i += gridDim.x * kThreads) {
+        double2 v = make_double2(0.0, 0.0);
+        double s, c;
+        if (i >= T.off_r) {
+            sincospi(2.0 * (i - T.off_r) / L, &s, &c);
+            if (i < T.off_r + L) v = make_double2(c, s);
+        } else {
+            const int kind = i < T.off_g ? 0 : i < T.off_i ? 1 : 2;
+            const int x = i - (kind == 0 ? 0 : kind == 1 ? T.off_g : T.off_i);
+            const int ks = kind == 0 ? T.ks_f : kind == 1 ? T.ks_g : T.ks_i;
+            const int lane = x & 63, step = (x >> 6) % ks, row = 16 * ((x >> 6) / ks) + (lane & 15);
+            const int k = 4 * step + (lane >> 4);
+            // angles pi a / L with a = w (2 j + 1), or 2 w j for the grid
+            const int w = kind == 2 ? k : row, j = kind == 2 ? row : k;
+            const int a = kind == 1 ? 2 * w * j : w * (2 * j + 1);
+            sincospi((double)(a % (2 * L)) / L, &s, &c);
+            const bool inside = w < P && j < (kind == 1 ? P + 1 : H);
+            if (inside) v = make_double2(c, kind != 1 && w == 0 ? (j & 1 ? -1.0 : 1.0) : s);
+        }
+        tab[i] = v;
     }
-    __device__ __forceinline__ double next(const double2* tab) {
-        const double v = reinterpret_cast<const double*>(tab)[2 * root_slot(idx) + part];
-        idx += step;
-        if (idx >= L) idx -= L;
-        return zero_sine ? alt : v;
-    }
-};
+}
 
-// x~(w) and x~(L - w) (one real column of a complex one, whose other component sits in
-// the neighbouring lane): C -+ i S; for w = 0 the frequencies 0 and P.
-__device__ __forceinline__ void pair_out(int w, bool odd, double C, double S, double scale, double& lo, double& hi) {
+// x~(w) and x~(-w) (one real column of a complex one, whose other component sits in the
+// neighbouring lane) from C and S; w = 0: the frequencies 0 and P (grid: from ny).
+__device__ __forceinline__ void pair_out(int w, bool odd, bool grid, double C, double S, double ny, double scale,
+                                         double& lo, double& hi) {
     const double x = swap_lane_pair(S), y = odd ? -x : x;
     lo = (w == 0 ? C : C + y) * scale;
-    hi = (w == 0 ? S : C - y) * scale;
+    hi = (w == 0 ? (grid ? ny : y) : C - y) * scale;
+}
+
+// Sum over the four lane groups of a column's partial sums.
+__device__ __forceinline__ double sum_groups(double x) {
+    x += __shfl_xor(x, 16);
+    return x + __shfl_xor(x, 32);
 }
 
 // Forward transform with one transformed axis (d <= 2): nbc blocks of 8 complex
 // columns from block nb0. Columns of a factor: c = line * m + q; of the grid: the
 // sample lines t. out[w * NC + c].
+template <bool grid>
 __device__ __forceinline__ void forward_lines(const SpecPlan& P, const double2* __restrict__ src, int64_t rs,
-                                              int64_t cs, bool grid, double2* __restrict__ out, int nb0, int nbc,
+                                              int64_t cs, double2* __restrict__ out,
+                                              const double2* __restrict__ tables, int nb0, int nbc,
                                               unsigned char* smem) {
     const int mc = grid ? 1 : P.m;
     const int NC = grid ? P.NP1 : P.K1 * P.m;
-    const int K = grid ? P.L : P.P, KS = (K + 3) >> 2, J = line_rows(K);
-    double2* tab = reinterpret_cast<double2*>(smem);
-    double2* xs = tab + roots_bytes(P.L) / 16;                     // [block][j][8 columns]
-    const int tid = threadIdx.x;
+    const int K = folded_points(P.P, grid), KS = (K + 3) >> 2, J = line_rows(K);
+    double2* xs = reinterpret_cast<double2*>(smem);     // sums, [block][j][8 columns]
+    double2* xd = xs + (size_t)nbc * J * kCols;         // differences
+    const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, col = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // an item is a 16-row block of frequency pairs against up to two column blocks; the
+    // first item's factors are requested before the inputs
+    constexpr int NB = 2, CH = 8;
+    const int items = P.npb * ((nbc + NB - 1) / NB);
+    const double2* tab = tables + (grid ? table_sizes(P.P).off_g : 0) + lane;
+    double2 tn[CH];
+    auto load_t = [&](int it, int s) {
+        const double2* x = tab + (size_t)(it % P.npb * KS + s) * 64;
+#pragma unroll
+        for (int k = 0; k < CH; ++k) tn[k] = x[64 * k];
+    };
+    load_t(wave, 0);
     // the inputs in tiles of 16 points x 8 columns per half workgroup, lanes along the
     // axis that is contiguous in memory, 8 loads in flight
     const bool jfast = grid || rs < cs;
     const int e = tid & 127, jl = jfast ? e & 15 : e >> 3, cc = jfast ? e >> 4 : e & 7;
     const int half = tid >> 7, per = (J / 16 + 1) / 2, turns = nbc * per;   // turns of both halves
-    constexpr int kStage = 8;
+    constexpr int kStage = 4;
     for (int base = 0; base < turns; base += kStage) {
-        double2 v[kStage];
+        double2 a[kStage], b[kStage];
 #pragma unroll
         for (int u = 0; u < kStage; ++u) {
-            v[u] = make_double2(0.0, 0.0);
+            a[u] = b[u] = make_double2(0.0, 0.0);
             if (base + u < turns) {
                 const int nb = (base + u) / per, j = 16 * (2 * (base + u - nb * per) + half) + jl;
                 const int c = kCols * (nb0 + nb) + cc;
                 if (c < NC && j < K) {
                     if (grid) {
-                        const int o = sample_offset(P, c, j);
-                        if (o >= 0) v[u] = src[o];
+                        const int oa = sample_offset(P, c, j);
+                        const int ob = j > 0 && j < P.P ? sample_offset(P, c, P.L - j) : -1;
+                        if (oa >= 0) a[u] = src[oa];
+                        if (ob >= 0) b[u] = src[ob];
                     } else {
-                        const int line = c / mc, q = c - line * mc, idx = line * P.P + j;
-                        if (idx < P.N) v[u] = src[idx * rs + q * cs];
+                        const int line = c / mc, q = c - line * mc;
+                        const int ia = line * P.P + K + j, ib = line * P.P + K - 1 - j;
+                        if (K + j < P.P && ia < P.N) a[u] = src[ia * rs + q * cs];
+                        if (ib < P.N) b[u] = src[ib * rs + q * cs];
                     }
                 }
             }
         }
-        if (base == 0) fill_roots(tab, P.L);
 #pragma unroll
         for (int u = 0; u < kStage; ++u)
             if (base + u < turns) {
                 const int nb = (base + u) / per, j = 16 * (2 * (base + u - nb * per) + half) + jl;
-                if (j < J) xs[(nb * J + j) * kCols + cc] = v[u];
+                if (j < J) {
+                    xs[(nb * J + j) * kCols + cc] = make_double2(a[u].x + b[u].x, a[u].y + b[u].y);
+                    xd[(nb * J + j) * kCols + cc] = make_double2(a[u].x - b[u].x, a[u].y - b[u].y);
+                }
             }
     }
     __syncthreads();
-    const int lane = tid & 63, wave = tid >> 6, g = lane >> 4, col = lane & 15;
     const bool odd = lane & 1;
-    const double scale = grid ? 1.0 / P.F : 1.0;
-    // an item is one column block against two blocks of pairs, four K steps of
-    // operands ahead
-    constexpr int NP = 2, CH = 4;
-    const int npi = (P.npb + NP - 1) / NP;
-    for (int it = wave; it < nbc * npi; it += kWaves) {
-        const int nb = it / npi, pb = (it - nb * npi) * NP;
-        RowWalk row[NP] = {RowWalk(kPairs * pb + (col & 7), col >= 8, g, P.L),
-                           RowWalk(kPairs * (pb + 1) + (col & 7), col >= 8, g, P.L)};
-        const double* x = reinterpret_cast<const double*>(xs + (size_t)nb * J * kCols) + 16 * g + col;
-        acc_t acc[NP];
-        double a[2][CH][NP], b[2][CH];
-        auto read = [&](int buf, int s) {       // rows past K are zero
+    const double scale = grid ? 1.0 / P.F : 1.0, alt = g & 1 ? -1.0 : 1.0;
+    for (int it = wave; it < items; it += kWaves) {
+        const int pb = it % P.npb, nbf = it / P.npb * NB, cnt = min(NB, nbc - nbf);
+        const double* x1 = reinterpret_cast<const double*>(xs + (size_t)nbf * J * kCols) + 16 * g + col;
+        const double* x2 = reinterpret_cast<const double*>(xd + (size_t)nbf * J * kCols) + 16 * g + col;
+        acc_t ac[NB], as[NB];
+        double ny[NB];
 #pragma unroll
-            for (int k = 0; k < CH; ++k) {
-                b[buf][k] = x[64 * (s + k)];
-#pragma unroll
-                for (int i = 0; i < NP; ++i) a[buf][k][i] = row[i].next(tab);
-            }
-        };
-        auto mma = [&](int buf, int s) {
-#pragma unroll
-            for (int k = 0; k < CH; ++k)
-                if (s + k < KS)
-#pragma unroll
-                    for (int i = 0; i < NP; ++i) acc[i] = M::fma(a[buf][k][i], b[buf][k], acc[i]);
-        };
-#pragma unroll
-        for (int i = 0; i < NP; ++i) acc[i] = acc_t{0, 0, 0, 0};
-        read(0, 0);
-        for (int s = 0; s < KS; s += 2 * CH) {
-            if (s + CH < KS) read(1, s + CH);
-            mma(0, s);
-            if (s + 2 * CH < KS) read(0, s + 2 * CH);
-            mma(1, s + CH);
+        for (int i = 0; i < NB; ++i) {
+            ac[i] = as[i] = acc_t{0, 0, 0, 0};
+            ny[i] = 0.0;
         }
-        const int c = kCols * (nb0 + nb) + (col >> 1);
-        double* o = reinterpret_cast<double*>(out) + 2 * c + (col & 1);
+        for (int s = 0; s < KS; s += CH) {
+            double2 t[CH];
 #pragma unroll
-        for (int i = 0; i < NP; ++i)
+            for (int k = 0; k < CH; ++k) t[k] = tn[k];
+            if (s + CH < KS)
+                load_t(it, s + CH);
+            else if (it + kWaves < items)
+                load_t(it + kWaves, 0);
 #pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                const int w = kPairs * (pb + i) + g + 4 * r;
+            for (int i = 0; i < NB; ++i) {
+                if (i >= cnt) break;
+                const double* y1 = x1 + 16 * J * i + 64 * s;
+                const double* y2 = x2 + 16 * J * i + 64 * s;
+#pragma unroll
+                for (int k = 0; k < CH; ++k) {
+                    if (s + k >= KS) break;
+                    const double b = y1[64 * k];
+                    ac[i] = M::fma(t[k].x, b, ac[i]);
+                    as[i] = M::fma(t[k].y, y2[64 * k], as[i]);
+                    if (grid) ny[i] = fma(alt, b, ny[i]);
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            if (i >= cnt) break;
+            if (grid) ny[i] = sum_groups(ny[i]);
+            const int c = kCols * (nb0 + nbf + i) + (col >> 1);
+            double* o = reinterpret_cast<double*>(out) + 2 * c + (col & 1);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int w = 16 * pb + M::row(g, r);
                 double lo, hi;
-                pair_out(w, odd, acc[i][r], acc[i][r + 2], scale, lo, hi);
+                pair_out(w, odd, grid, ac[i][r], as[i][r], ny[i], scale, lo, hi);
                 if (w < P.P && c < NC) {
                     o[(size_t)w * NC * 2] = lo;
                     o[(size_t)(w == 0 ? P.P : P.L - w) * NC * 2] = hi;
                 }
             }
+        }
     }
 }
 
 // Forward transform with two transformed axes (d = 3): the plane (axes 2, 3) of line
 // `line` and nq complex columns from column q0: axis 3 at the pairs split * wp ..
 // (and their mirrors) into LDS, then axis 2. out[(w2 L + w3) * rowlen + line * mc + q].
+template <bool grid>
 __device__ __forceinline__ void forward_planes(const SpecPlan& P, const double2* __restrict__ src, int64_t rs,
-                                               int64_t cs, bool grid, double2* __restrict__ out, int line, int q0,
-                                               int nq, int split, unsigned char* smem) {
+                                               int64_t cs, double2* __restrict__ out,
+                                               const double2* __restrict__ tables, int line, int q0, int nq,
+                                               int split, unsigned char* smem) {
     const int mc = grid ? 1 : P.m;
     const size_t rowlen = grid ? P.NP1 : (size_t)P.K1 * P.m;
-    const int J = grid ? P.L : P.P, KS = (J + 3) >> 2;
-    const int w0 = split * P.wp, wn = min(P.wp, P.P - w0);
-    double2* tab = reinterpret_cast<double2*>(smem);
-    double* t1 = reinterpret_cast<double*>(tab + roots_bytes(P.L) / 16);      // [j2][2 u + side][q] complex
-    const int ts = plane_stride(wn, nq);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, col = lane & 15;
-    const bool odd = lane & 1, sine = col >= 8;
-    const int jskip = P.pmax == P.n ? P.P : -1;      // the point p = n + 1 of an axis
+    const int J = grid ? P.L : P.P;                     // points of an axis
+    const int K = folded_points(P.P, grid), KS = (K + 3) >> 2;
+    const int w0 = split * 16, wn = min(16, P.P - w0);
+    double* t1 = reinterpret_cast<double*>(smem);       // [j2][2 u + side][q] complex
+    const int ts = plane_stride(2 * wn * nq);
+    const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, col = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool odd = lane & 1;
+    const double alt = g & 1 ? -1.0 : 1.0;
+    const double2* tab = tables + (grid ? table_sizes(P.P).off_g : 0) + lane;
     const double* in = reinterpret_cast<const double*>(src);
-    // rows past J are zero (the K steps are whole)
-    for (int i = tid; i < (4 * KS - J) * ts; i += kThreads) t1[(size_t)J * ts + i] = 0.0;
+    const int jskip = P.pmax == P.n ? P.P : -1;      // the point p = n + 1 of an axis
+    // row J is zero: the second operand of points without a mirror
+    for (int i = tid; i < ts; i += kThreads) t1[(size_t)J * ts + i] = 0.0;
 
-    // axis 3: columns c = j2 * nq + q in blocks of 8, NBI blocks per pass, so that one
-    // read of the tables serves all, and kIn K steps of their loads in flight
-    constexpr int NBI = 2, kIn = 6;
-    const int nc1 = J * nq, nb1 = (nc1 + 7) >> 3, npb1 = (wn + kPairs - 1) / kPairs;
-    const int items1 = (nb1 + NBI - 1) / NBI * npb1;
+    // axis 3: columns c = j2 * nq + q in blocks of 8, NBI blocks per pass, kIn K steps of
+    // factors and inputs at a time; the next ones are requested before the products
+    constexpr int NBI = grid ? 1 : 2, kIn = grid ? 6 : 3;
+    const int nc1 = J * nq, nb1 = (nc1 + 7) >> 3, items1 = (nb1 + NBI - 1) / NBI;
     const float rnq = 1.0f / nq;
     auto div_nq = [&](int c) { return (int)((c + 0.5f) * rnq); };     // c < 2^14: exact
     struct Item {
         bool live[NBI];          // columns of the plane
         int o1[NBI];             // their places in an LDS row
-        const double* x[NBI];    // their first inputs, null where there are none
+        const double* x[NBI];    // their inputs, null where there are none
     };
     auto item_at = [&](int it, Item& I) {
-        const int ng = it / npb1;
 #pragma unroll
         for (int i = 0; i < NBI; ++i) {
-            const int c = 8 * (ng * NBI + i) + (col >> 1);
+            const int c = 8 * (it * NBI + i) + (col >> 1);
             I.live[i] = it < items1 && c < nc1;
             const int j2 = div_nq(c), q = c - j2 * nq;
             I.o1[i] = j2 * ts + 2 * q + (col & 1);
@@ -271,116 +314,164 @@ __device__ __forceinline__ void forward_planes(const SpecPlan& P, const double2*
             I.x[i] = ok ? in + base : nullptr;
         }
     };
-    auto load = [&](double (&b)[NBI][kIn], const Item& I, int s0) {
+    // inputs of K steps s0 .. : offsets of the points t and -t from a column's first input
+    const int64_t up = grid ? 2 : 2 * rs;
+    const int64_t oa0 = (grid ? g : K + g) * up, ob0 = (grid ? -g : K - 1 - g) * up;
+    auto load = [&](double (&a)[NBI][kIn], double (&b)[NBI][kIn], const Item& I, int s0) {
 #pragma unroll
         for (int k = 0; k < kIn; ++k) {
             const int j = 4 * (s0 + k) + g;
-            const int64_t off = grid ? (int64_t)(j <= P.P ? j : j - P.L) * 2 : 2 * j * rs;
-            const bool ok = j < J && (!grid || j != jskip);
+            const bool ka = grid ? j < K && j != jskip : j < K && K + j < P.P, kb = grid ? j > 0 && j < P.P : j < K;
+            const int64_t d = 4 * (s0 + k) * up;
 #pragma unroll
-            for (int i = 0; i < NBI; ++i) b[i][k] = I.x[i] && ok ? I.x[i][off] : 0.0;
+            for (int i = 0; i < NBI; ++i) {
+                a[i][k] = I.x[i] && ka ? I.x[i][oa0 + d] : 0.0;
+                b[i][k] = I.x[i] && kb ? I.x[i][ob0 - d] : 0.0;
+            }
         }
     };
-    Item item;
-    double b[NBI][kIn];
-    item_at(wave, item);
-    load(b, item, 0);
-    fill_roots(tab, P.L);            // the first loads are in flight
-    __syncthreads();
-    for (int it = wave; it < items1; it += kWaves) {
-        const int pb = it % npb1;
-        acc_t acc[NBI];
+    double2 t[kIn];
+    auto load_t = [&](int pb, int s0) {
+        const double2* x = tab + (size_t)(pb * KS + s0) * 64;
 #pragma unroll
-        for (int i = 0; i < NBI; ++i) acc[i] = acc_t{0, 0, 0, 0};
+        for (int k = 0; k < kIn; ++k) t[k] = x[64 * k];
+    };
+    Item item;
+    double a[NBI][kIn], b[NBI][kIn];
+    load_t(split, 0);
+    item_at(wave, item);
+    load(a, b, item, 0);
+    for (int it = wave; it < items1; it += kWaves) {
+        acc_t ac[NBI], as[NBI];
+        double ny[NBI];
+#pragma unroll
+        for (int i = 0; i < NBI; ++i) {
+            ac[i] = as[i] = acc_t{0, 0, 0, 0};
+            ny[i] = 0.0;
+        }
         Item next;
         item_at(it + kWaves, next);
-        RowWalk row(w0 + kPairs * pb + (col & 7), sine, g, P.L);
         for (int s0 = 0; s0 < KS; s0 += kIn) {
-            double a[kIn], bn[NBI][kIn];
+            double an[NBI][kIn], bn[NBI][kIn];
+            if (KS > kIn) load_t(split, s0);
             // the next K steps or the next item's first ones
             const bool more = s0 + kIn < KS;
-            load(bn, more ? item : next, more ? s0 + kIn : 0);
-#pragma unroll
-            for (int k = 0; k < kIn; ++k) a[k] = row.next(tab);
+            load(an, bn, more ? item : next, more ? s0 + kIn : 0);
 #pragma unroll
             for (int k = 0; k < kIn; ++k)
                 if (s0 + k < KS)
 #pragma unroll
-                    for (int i = 0; i < NBI; ++i) acc[i] = M::fma(a[k], b[i][k], acc[i]);
+                    for (int i = 0; i < NBI; ++i) {
+                        const double s = a[i][k] + b[i][k];
+                        ac[i] = M::fma(t[k].x, s, ac[i]);
+                        as[i] = M::fma(t[k].y, a[i][k] - b[i][k], as[i]);
+                        if (grid) ny[i] = fma(alt, s, ny[i]);
+                    }
 #pragma unroll
             for (int i = 0; i < NBI; ++i)
 #pragma unroll
-                for (int k = 0; k < kIn; ++k) b[i][k] = bn[i][k];
+                for (int k = 0; k < kIn; ++k) {
+                    a[i][k] = an[i][k];
+                    b[i][k] = bn[i][k];
+                }
         }
 #pragma unroll
-        for (int i = 0; i < NBI; ++i)
+        for (int i = 0; i < NBI; ++i) {
+            if (grid) ny[i] = sum_groups(ny[i]);
 #pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                const int u = kPairs * pb + g + 4 * r;
+            for (int r = 0; r < 4; ++r) {
+                const int u = M::row(g, r);
                 double lo, hi;
-                pair_out(w0 + u, odd, acc[i][r], acc[i][r + 2], 1.0, lo, hi);
+                pair_out(w0 + u, odd, grid, ac[i][r], as[i][r], ny[i], 1.0, lo, hi);
                 if (item.live[i] && u < wn) {
                     t1[item.o1[i] + 4 * u * nq] = lo;
                     t1[item.o1[i] + (4 * u + 2) * nq] = hi;
                 }
             }
+        }
         item = next;
     }
-    __syncthreads();
 
-    // axis 2: columns c = (2 u + side) * nq + q of the LDS rows j2
-    constexpr int NB2 = 4, CH = 3;
-    const int nc2 = 2 * wn * nq, nb2 = (nc2 + 7) >> 3;
-    const int ng2 = (nb2 + NB2 - 1) / NB2;
+    // axis 2: columns c = (2 u + side) * nq + q of the LDS rows j2; an item is a 16-row
+    // block of pairs against NB2 column blocks. Per item and kIn K steps the factors and
+    // the rows of t and -t (row J, zero, where there is none)
+    constexpr int NB2 = grid ? 1 : 2;
+    const int nc2 = 2 * wn * nq, nb2 = (nc2 + 7) >> 3, ng2 = (nb2 + NB2 - 1) / NB2, items2 = ng2 * P.npb;
     const double scale = grid ? 1.0 / P.F : 1.0;
-    for (int it = wave; it < ng2 * P.npb; it += kWaves) {
-        const int ng = it / P.npb, pb = it - ng * P.npb;
-        RowWalk row(kPairs * pb + (col & 7), sine, g, P.L);
-        acc_t acc[NB2];
-        const double* x[NB2];
+    const int64_t step2 = 2 * (int64_t)P.L * rowlen;          // one frequency of axis 2
+    // the items of a block of pairs go to the waves in turn, block after block
+    if (wave < items2) load_t(wave / ng2, 0);
+    __syncthreads();
+    int ra[kIn], rb[kIn];
+    auto rows_at = [&](int s0) {
+#pragma unroll
+        for (int k = 0; k < kIn; ++k) {
+            const int j = 4 * (s0 + k) + g;
+            ra[k] = ((grid ? j < K : j < K && K + j < J) ? (grid ? j : K + j) : J) * ts + col;
+            rb[k] = ((grid ? j > 0 && j < P.P : j < K) ? (grid ? J - j : K - 1 - j) : J) * ts + col;
+        }
+    };
+    rows_at(0);
+    int pb_held = wave / ng2;        // the block whose factors t holds
+    for (int it = wave; it < items2; it += kWaves) {
+        const int pb = it / ng2, ng = it - pb * ng2;
+        acc_t ac[NB2], as[NB2];
+        double ny[NB2];
+        int at[NB2];
 #pragma unroll
         for (int i = 0; i < NB2; ++i) {
-            acc[i] = acc_t{0, 0, 0, 0};
+            ac[i] = as[i] = acc_t{0, 0, 0, 0};
+            ny[i] = 0.0;
             // columns past the last read the last block again and are not stored
-            x[i] = t1 + g * ts + 16 * min(ng * NB2 + i, nb2 - 1) + col;
+            at[i] = 16 * min(ng * NB2 + i, nb2 - 1);
         }
-        double a[2][CH], b[2][CH][NB2];
-        auto read = [&](int buf, int s) {
+        for (int s0 = 0; s0 < KS; s0 += kIn) {
+            if (KS > kIn || pb != pb_held) load_t(pb, s0);
+            if (KS > kIn) rows_at(s0);
+            double p[kIn][NB2], q[kIn][NB2];
 #pragma unroll
-            for (int k = 0; k < CH; ++k) {
-                a[buf][k] = row.next(tab);
+            for (int k = 0; k < kIn; ++k)
 #pragma unroll
-                for (int i = 0; i < NB2; ++i) b[buf][k][i] = x[i][4 * min(s + k, KS - 1) * ts];
-            }
-        };
-        auto mma = [&](int buf, int s) {
+                for (int i = 0; i < NB2; ++i) {
+                    p[k][i] = t1[ra[k] + at[i]];
+                    q[k][i] = t1[rb[k] + at[i]];
+                }
 #pragma unroll
-            for (int k = 0; k < CH; ++k)
-                if (s + k < KS)
+            for (int k = 0; k < kIn; ++k)
+                if (s0 + k < KS)
 #pragma unroll
-                    for (int i = 0; i < NB2; ++i) acc[i] = M::fma(a[buf][k], b[buf][k][i], acc[i]);
-        };
-        read(0, 0);
-        for (int s = 0; s < KS; s += 2 * CH) {
-            if (s + CH < KS) read(1, s + CH);
-            mma(0, s);
-            if (s + 2 * CH < KS) read(0, s + 2 * CH);
-            mma(1, s + CH);
+                    for (int i = 0; i < NB2; ++i) {
+                        const double c = p[k][i] + q[k][i];
+                        ac[i] = M::fma(t[k].x, c, ac[i]);
+                        as[i] = M::fma(t[k].y, p[k][i] - q[k][i], as[i]);
+                        if (grid) ny[i] = fma(alt, c, ny[i]);
+                    }
+        }
+        pb_held = pb;
+        // the next item's factors, should it start another block
+        if (KS <= kIn && it + kWaves < items2 && (it + kWaves) / ng2 != pb) {
+            pb_held = (it + kWaves) / ng2;
+            load_t(pb_held, 0);
         }
 #pragma unroll
         for (int i = 0; i < NB2; ++i) {
+            if (grid) ny[i] = sum_groups(ny[i]);
             const int c = 8 * (ng * NB2 + i) + (col >> 1);
-            const int wl = div_nq(c), q = c - wl * nq, w3p = w0 + (wl >> 1);
+            const int wl = div_nq(c), qq = c - wl * nq, w3p = w0 + (wl >> 1);
             const int w3 = wl & 1 ? (w3p == 0 ? P.P : P.L - w3p) : w3p;
-            double* o = reinterpret_cast<double*>(out) + 2 * ((size_t)w3 * rowlen + (size_t)line * mc + q0 + q) + (col & 1);
+            // rows w2 = 16 pb + g + 4 r and their mirrors
+            double* o = reinterpret_cast<double*>(out) + 2 * ((size_t)w3 * rowlen + (size_t)line * mc + q0 + qq) + (col & 1);
+            const int wg = 16 * pb + g;
+            double* olo = o + wg * step2;
+            double* ohi = o + (P.L - wg) * step2;
 #pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                const int w2 = kPairs * pb + g + 4 * r;
+            for (int r = 0; r < 4; ++r) {
+                const int w2 = wg + 4 * r;
                 double lo, hi;
-                pair_out(w2, odd, acc[i][r], acc[i][r + 2], scale, lo, hi);
+                pair_out(w2, odd, grid, ac[i][r], as[i][r], ny[i], scale, lo, hi);
                 if (w2 < P.P && c < nc2) {
-                    o[(size_t)w2 * P.L * rowlen * 2] = lo;
-                    o[(size_t)(w2 == 0 ? P.P : P.L - w2) * P.L * rowlen * 2] = hi;
+                    olo[4 * r * step2] = lo;
+                    (w2 == 0 ? o + P.P * step2 : ohi - 4 * r * step2)[0] = hi;
                 }
             }
         }
@@ -392,25 +483,25 @@ __device__ __forceinline__ void forward_planes(const SpecPlan& P, const double2*
 __device__ __forceinline__ void forward_body(const SpecPlan& P, const SpecPtrs& p, int id, unsigned char* smem) {
     const bool grid = id < P.wgs_f;
     const bool second = id >= P.wgs_f + P.wgs_x;
-    if (id == 0)    // the phases of the Gram products
-        for (int j = threadIdx.x; j < P.L; j += kThreads) {
-            double sn, cn;
-            sincospi(2.0 * j / P.L, &sn, &cn);
-            p.roots[j] = make_double2(cn, sn);
-        }
     const int x = grid ? id : id - P.wgs_f - (second ? P.wgs_x : 0);
     const double2* src = grid ? p.f : second ? p.U : p.V;
     const int64_t rs = second ? p.u_rs : p.v_rs, cs = second ? p.u_cs : p.v_cs;
     double2* out = grid ? p.ft : second ? p.ut : p.vt;
     if (P.d == 3) {
-        const int per = grid ? 1 : (P.m + P.nq - 1) / P.nq;   // column blocks of a line
         const int split = x % P.splits, rest = x / P.splits;
-        const int qb = rest % per, line = rest / per;
-        forward_planes(P, src, rs, cs, grid, out, line, qb * P.nq, grid ? 1 : min(P.nq, P.m - qb * P.nq), split, smem);
+        if (grid) {
+            forward_planes<true>(P, src, 0, 0, out, p.tab, rest, 0, 1, split, smem);
+        } else {
+            const int per = (P.m + P.nq - 1) / P.nq;   // column blocks of a line
+            const int qb = rest % per, line = rest / per;
+            forward_planes<false>(P, src, rs, cs, out, p.tab, line, qb * P.nq, min(P.nq, P.m - qb * P.nq), split, smem);
+        }
+    } else if (grid) {
+        const int nblk = (P.NP1 + kCols - 1) / kCols;
+        forward_lines<true>(P, src, 0, 0, out, p.tab, x * P.nbwf, min(P.nbwf, nblk - x * P.nbwf), smem);
     } else {
-        const int nbw = grid ? P.nbwf : P.nbw;
-        const int nblk = ((grid ? P.NP1 : P.K1 * P.m) + kCols - 1) / kCols;
-        forward_lines(P, src, rs, cs, grid, out, x * nbw, min(nbw, nblk - x * nbw), smem);
+        const int nblk = (P.K1 * P.m + kCols - 1) / kCols;
+        forward_lines<false>(P, src, rs, cs, out, p.tab, x * P.nbw, min(P.nbw, nblk - x * P.nbw), smem);
     }
 }
 
@@ -524,6 +615,7 @@ __device__ __forceinline__ void gram_body(const SpecPlan& P, const SpecPtrs& p, 
     const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, col = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     double2* win = reinterpret_cast<double2*>(smem + window_bytes(P.K1) * wave);
+    const double2* roots = p.tab + table_sizes(P.P).off_r;
     const bool shift1 = P.d >= 2;
     const int m = P.m, K1 = P.K1, KS = (K1 + 3) >> 2;
     const int R = shift1 ? K1 + 1 : K1, full = R >> 4, rem = R & 15;
@@ -598,7 +690,7 @@ __device__ __forceinline__ void gram_body(const SpecPlan& P, const SpecPtrs& p, 
         double yr[4], yi[4];
         toeplitz_rows<CH>(P, p, B.w, B.r0, B.s0, B.s1, voff, false, win, yr, yi, [&] {
             load_u(ua, B, 0);
-            ph = p.roots[P.d == 3 ? B.w % P.L : B.w];
+            ph = roots[P.d == 3 ? B.w % P.L : B.w];
         });
         auto gram = [&](const double2 (&uu)[4], auto bc) {
             constexpr int b = decltype(bc)::value;
@@ -647,7 +739,7 @@ __device__ __forceinline__ void gram_body(const SpecPlan& P, const SpecPtrs& p, 
     // fixed-order sum over the waves and the group's row of partials [i][l][q]
     double2* red = reinterpret_cast<double2*>(smem);   // [wave][block][row][lane]
     double2* out = p.part + (size_t)grp * m * P.ells * m;
-    const double2 ph2 = P.d == 3 ? p.roots[wa / P.L] : make_double2(1.0, 0.0);
+    const double2 ph2 = P.d == 3 ? roots[wa / P.L] : make_double2(1.0, 0.0);
     auto put = [&](int i, int ell, int qq, double2 v) {
         out[((size_t)i * P.ells + (P.s0 ? ell : ell - 1)) * m + qq] = v;
     };
@@ -729,44 +821,17 @@ __global__ __launch_bounds__(kThreads) void spectral_toeplitz(SpecPlan P, SpecPt
     }
 }
 
-// Inverse transforms: y(k) = sum_w Y~(w) e^{2 pi i w k / L} as A cos + (i B) sin over the
-// pairs w < P, A = Y~(w) + Y~(L - w), B = Y~(w) - Y~(L - w). Pair 0 takes A = Y~(0) and, in
-// the sine slot with the factors (-1)^k, Y~(P).
+// Inverse transforms about the line's centre (see the folded forward ones): at t = j + 1/2
+//     y(+-t) = C +- S,  C = sum_w A cos(w t), S = sum_w (i B) sin(w t)
+// over the pairs w < P, A = Y~(w) + Y~(-w), B = Y~(w) - Y~(-w). Pair 0: A = Y~(0), and in the
+// sine slot, with sin(P t) = (-1)^j, B = Y~(P).
 
-// Factors of a lane's output row k at w = 4 s + g.
-struct InverseWalk {
-    int idx, step, L;
-    double alt;
-    bool first;       // the next factor is pair 0's
-    __device__ __forceinline__ InverseWalk(int k, int g, int L_) {
-        L = L_;
-        walk_start(k, g, L, idx, step);
-        alt = k & 1 ? -1.0 : 1.0;
-        first = g == 0;
-    }
-    __device__ __forceinline__ double2 next(const double2* tab) {
-        double2 v = tab[root_slot(idx)];
-        idx += step;
-        if (idx >= L) idx -= L;
-        if (first) v = make_double2(1.0, alt);
-        first = false;
-        return v;
-    }
-};
-
-// The two operands of pair w from Y~(w) and its mirror value (one real column, the other
+// The two operands A and i B of pair w from Y~(w) and Y~(-w) (one real column, the other
 // component in the neighbouring lane).
 __device__ __forceinline__ void pair_in(bool zero, bool odd, double a, double b, double& c, double& s) {
-    const double x = swap_lane_pair(a - b), y = odd ? x : -x;     // i B
+    const double x = swap_lane_pair(zero ? b : a - b);
     c = zero ? a : a + b;
-    s = zero ? b : y;
-}
-
-// Offset of (line t, column q, point j of the transformed axis) in Y (leading dimension
-// ld), -1 where there is none.
-__device__ __forceinline__ int64_t product_offset(const SpecPlan& P, int64_t ld, int t, int j, int q) {
-    const int idx = t * P.P + j;
-    return j < P.P && idx < P.N ? idx * ld + q : -1;
+    s = odd ? x : -x;
 }
 
 // One transformed axis (d <= 2): nbc blocks of 8 complex columns c = k1 * m + q of Y~ from
@@ -774,100 +839,104 @@ __device__ __forceinline__ int64_t product_offset(const SpecPlan& P, int64_t ld,
 __global__ __launch_bounds__(kThreads) void spectral_inverse_lines(SpecPlan P, SpecPtrs p, double2* __restrict__ Y,
                                                                    int64_t ld) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int NC = P.K1 * P.m, KS = (P.P + 3) >> 2, J = line_rows(P.P), J4 = 4 * KS;
+    const int NC = P.K1 * P.m, KS = (P.P + 3) >> 2, J = line_rows(P.P), H = folded_points(P.P, false);
     const int nblk = (NC + kCols - 1) / kCols, nb0 = blockIdx.x * P.nbi, nbc = min(P.nbi, nblk - nb0);
-    double2* tab = reinterpret_cast<double2*>(smem);
-    double2* xc = tab + roots_bytes(P.L) / 16;
+    double2* xc = reinterpret_cast<double2*>(smem);
     double2* xi = xc + (size_t)P.nbi * J * kCols;
-    const int tid = threadIdx.x;
-    const int tot = nbc * J4 * kCols;
+    const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, col = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nrb = (H + 15) >> 4;
+    // the first item's factors are requested before the inputs
+    constexpr int CH = 8;
+    const double2* tab = p.tab + table_sizes(P.P).off_i + lane;
+    double2 fn[CH];
+    auto load_t = [&](int it, int s) {
+        const double2* x = tab + (size_t)(it % nrb * KS + s) * 64;
+#pragma unroll
+        for (int k = 0; k < CH; ++k) fn[k] = x[64 * k];
+    };
+    load_t(wave, 0);
+    // lane (w, column) of tiles of 32 pairs x 8 columns
+    const int cc = tid & 7, wl = tid >> 3, per = (J + 31) / 32, turns = nbc * per;
     constexpr int kStage = 4;
-    for (int base = 0; base < tot; base += kStage * kThreads) {
+    for (int base = 0; base < turns; base += kStage) {
         double2 a[kStage], b[kStage];
 #pragma unroll
         for (int u = 0; u < kStage; ++u) {
-            const int e = base + u * kThreads + tid;
-            const int cc = e & 7, rest = e >> 3, nb = rest / J4, w = rest - nb * J4, c = kCols * (nb0 + nb) + cc;
+            const int nb = (base + u) / per, w = 32 * (base + u - nb * per) + wl, c = kCols * (nb0 + nb) + cc;
             a[u] = b[u] = make_double2(0.0, 0.0);
-            if (e < tot && c < NC && w < P.P) {
+            if (base + u < turns && c < NC && w < P.P) {
                 a[u] = p.ut[(size_t)w * NC + c];
                 b[u] = p.ut[(size_t)(w == 0 ? P.P : P.L - w) * NC + c];
             }
         }
-        if (base == 0) fill_roots(tab, P.L);
 #pragma unroll
         for (int u = 0; u < kStage; ++u) {
-            const int e = base + u * kThreads + tid;
-            if (e >= tot) continue;
-            const int cc = e & 7, rest = e >> 3, nb = rest / J4, w = rest - nb * J4;
+            const int nb = (base + u) / per, w = 32 * (base + u - nb * per) + wl;
+            if (base + u >= turns || w >= J) continue;
             const int at = (nb * J + w) * kCols + cc;
             const double2 x = a[u], y = b[u];
+            const double2 d = w == 0 ? y : make_double2(x.x - y.x, x.y - y.y);
             xc[at] = w == 0 ? x : make_double2(x.x + y.x, x.y + y.y);
-            xi[at] = w == 0 ? y : make_double2(y.y - x.y, x.x - y.x);
+            xi[at] = make_double2(-d.y, d.x);
         }
     }
     __syncthreads();
-    const int lane = tid & 63, wave = tid >> 6, g = lane >> 4, col = lane & 15;
-    const int nrb = (P.P + 15) >> 4;
     for (int it = wave; it < nbc * nrb; it += kWaves) {
         const int nb = it / nrb, rb = it - nb * nrb;
-        InverseWalk row(16 * rb + col, g, P.L);
         const double* x1 = reinterpret_cast<const double*>(xc + (size_t)nb * J * kCols) + 16 * g + col;
         const double* x2 = reinterpret_cast<const double*>(xi + (size_t)nb * J * kCols) + 16 * g + col;
         acc_t ac = {0, 0, 0, 0}, as = {0, 0, 0, 0};
-        constexpr int CH = 4;
-        double2 a[2][CH];
-        double b[2][CH], c[2][CH];
-        auto read = [&](int buf, int s) {
+        for (int s = 0; s < KS; s += CH) {
+            double2 f[CH];
+#pragma unroll
+            for (int k = 0; k < CH; ++k) f[k] = fn[k];
+            if (s + CH < KS)
+                load_t(it, s + CH);
+            else if (it + kWaves < nbc * nrb)
+                load_t(it + kWaves, 0);
 #pragma unroll
             for (int k = 0; k < CH; ++k) {
-                b[buf][k] = x1[64 * (s + k)];
-                c[buf][k] = x2[64 * (s + k)];
-                a[buf][k] = row.next(tab);
+                if (s + k >= KS) break;
+                ac = M::fma(f[k].x, x1[64 * (s + k)], ac);
+                as = M::fma(f[k].y, x2[64 * (s + k)], as);
             }
-        };
-        auto mma = [&](int buf, int s) {
-#pragma unroll
-            for (int k = 0; k < CH; ++k)
-                if (s + k < KS) {
-                    ac = M::fma(a[buf][k].x, b[buf][k], ac);
-                    as = M::fma(a[buf][k].y, c[buf][k], as);
-                }
-        };
-        read(0, 0);
-        for (int s = 0; s < KS; s += 2 * CH) {
-            if (s + CH < KS) read(1, s + CH);
-            mma(0, s);
-            if (s + 2 * CH < KS) read(0, s + 2 * CH);
-            mma(1, s + CH);
         }
         const int cx = kCols * (nb0 + nb) + (col >> 1);
         const int t = cx / P.m, q = cx - t * P.m;
+        double* o = reinterpret_cast<double*>(Y) + 2 * q + (col & 1);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int64_t o = cx < NC ? product_offset(P, ld, t, 16 * rb + M::row(g, r), q) : -1;
-            if (o >= 0) reinterpret_cast<double*>(Y)[2 * o + (col & 1)] = ac[r] + as[r];
+            const int j = 16 * rb + M::row(g, r);
+            const int ia = t * P.P + H + j, ib = t * P.P + H - 1 - j;
+            if (cx < NC && j < H) {
+                if (H + j < P.P && ia < P.N) o[2 * ia * ld] = ac[r] + as[r];
+                if (ib < P.N) o[2 * ib * ld] = ac[r] - as[r];
+            }
         }
     }
 }
 
-// Two transformed axes (d = 3): the rows k2 of part `split` of one line k1 and nq
-// columns: axis 2 into LDS as the operands of axis 3's pairs, then axis 3.
+// Two transformed axes (d = 3): the rows k2 = H + j, H - 1 - j, j in part `split`, of one
+// line k1 and nq columns: axis 2 into LDS as the operands of axis 3's pairs, then axis 3.
 __global__ __launch_bounds__(kThreads) void spectral_inverse_planes(SpecPlan P, SpecPtrs p, double2* __restrict__ Y,
                                                                     int64_t ld) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int per = (P.m + P.nqi - 1) / P.nqi;
     const int split = blockIdx.x % P.isplits, rest0 = blockIdx.x / P.isplits;
     const int q0 = rest0 % per * P.nqi, line = rest0 / per, nq = min(P.nqi, P.m - q0);
-    const int k20 = split * P.irows, kn = min(P.irows, P.P - k20);
+    const int H = folded_points(P.P, false), j0 = split * P.irows, kn = min(P.irows, H - j0);
     const int KS = (P.P + 3) >> 2;
     const size_t rowlen = (size_t)P.K1 * P.m;
-    double2* tab = reinterpret_cast<double2*>(smem);
-    const int ts = inverse_stride(P.irows, P.nqi);
-    double* tc = reinterpret_cast<double*>(tab + roots_bytes(P.L) / 16);      // [w3 pair][k2][q], A
-    double* ti = tc + (size_t)4 * KS * ts;                  // i B
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, col = lane & 15;
+    const int ts = plane_stride(2 * P.irows * P.nqi);
+    double* tc = reinterpret_cast<double*>(smem);       // [w3 pair][2 j + side][q], A
+    double* ti = tc + (size_t)4 * KS * ts;              // i B
+    const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, col = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool odd = lane & 1;
+    const double2* tab = p.tab + table_sizes(P.P).off_i;
+    // factors of the part's rows j0 + col (they need not start a block of the table)
+    const int jr = min(j0 + col, H - 1);
+    const double2* tab2 = tab + (size_t)(jr >> 4) * KS * 64 + 16 * g + (jr & 15);
     for (int i = tid; i < (4 * KS - P.P) * ts; i += kThreads) {
         tc[(size_t)P.P * ts + i] = 0.0;
         ti[(size_t)P.P * ts + i] = 0.0;
@@ -875,7 +944,7 @@ __global__ __launch_bounds__(kThreads) void spectral_inverse_planes(SpecPlan P, 
     // axis 2: columns c = u * nq + q of the pairs u of axis 3, w3 = u and its mirror
     const double* in = reinterpret_cast<const double*>(p.ut);
     const int nc1 = P.P * nq, nb1 = (nc1 + 7) >> 3;
-    for (int it = wave; it < nb1 || it == wave; it += kWaves) {      // every wave meets the barrier inside once
+    for (int it = wave; it < nb1; it += kWaves) {
         const int c = 8 * it + (col >> 1);
         const bool ok = c < nc1;
         const int u = c / nq, q = c - u * nq;
@@ -883,15 +952,16 @@ __global__ __launch_bounds__(kThreads) void spectral_inverse_planes(SpecPlan P, 
         const int64_t side[2] = {2 * (int64_t)u * (int64_t)rowlen + col0,
                                  2 * (int64_t)(u == 0 ? P.P : P.L - u) * (int64_t)rowlen + col0};
         const int64_t step2 = 2 * (int64_t)P.L * (int64_t)rowlen;      // one frequency of axis 2
-        InverseWalk row(k20 + col, g, P.L);
         acc_t ac[2], as[2];
 #pragma unroll
         for (int i = 0; i < 2; ++i) ac[i] = as[i] = acc_t{0, 0, 0, 0};
         constexpr int kIn = 3;
         for (int s0 = 0; s0 < KS; s0 += kIn) {
             double a[2][kIn], b[2][kIn];
+            double2 t[kIn];
 #pragma unroll
             for (int k = 0; k < kIn; ++k) {
+                t[k] = tab2[64 * (s0 + k)];
                 const int w = 4 * (s0 + k) + g;
                 const bool in_range = ok && w < P.P;
 #pragma unroll
@@ -900,55 +970,70 @@ __global__ __launch_bounds__(kThreads) void spectral_inverse_planes(SpecPlan P, 
                     b[i][k] = in_range ? in[side[i] + (w == 0 ? P.P : P.L - w) * step2] : 0.0;
                 }
             }
-            if (it == wave && s0 == 0) {
-                fill_roots(tab, P.L);
-                __syncthreads();
-            }
 #pragma unroll
             for (int k = 0; k < kIn; ++k)
                 if (s0 + k < KS) {
-                    const double2 t = row.next(tab);
 #pragma unroll
                     for (int i = 0; i < 2; ++i) {
                         double x, y;
                         pair_in(4 * (s0 + k) + g == 0, odd, a[i][k], b[i][k], x, y);
-                        ac[i] = M::fma(t.x, x, ac[i]);
-                        as[i] = M::fma(t.y, y, as[i]);
+                        ac[i] = M::fma(t[k].x, x, ac[i]);
+                        as[i] = M::fma(t[k].y, y, as[i]);
                     }
                 }
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int k2 = M::row(g, r);
-            double x, y;
-            pair_in(u == 0, odd, ac[0][r] + as[0][r], ac[1][r] + as[1][r], x, y);
-            if (ok && k2 < kn) {
-                tc[u * ts + 2 * (k2 * nq + q) + (col & 1)] = x;
-                ti[u * ts + 2 * (k2 * nq + q) + (col & 1)] = y;
-            }
+            const int j = M::row(g, r);
+            double x[2], y[2];       // rows H + j0 + j and H - 1 - j0 - j
+            pair_in(u == 0, odd, ac[0][r] + as[0][r], ac[1][r] + as[1][r], x[0], y[0]);
+            pair_in(u == 0, odd, ac[0][r] - as[0][r], ac[1][r] - as[1][r], x[1], y[1]);
+            if (ok && j < kn)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int at = u * ts + 2 * ((2 * j + h) * nq + q) + (col & 1);
+                    tc[at] = x[h];
+                    ti[at] = y[h];
+                }
         }
     }
     __syncthreads();
-    // axis 3: columns c = k2 * nq + q
-    const int nc2 = kn * nq, nb2 = (nc2 + 7) >> 3, nrb = (P.P + 15) >> 4;
+    // axis 3: columns c = (2 j + side) * nq + q
+    const int nc2 = 2 * kn * nq, nb2 = (nc2 + 7) >> 3, nrb = (H + 15) >> 4;
     for (int it = wave; it < nb2 * nrb; it += kWaves) {
         const int nb = it / nrb, rb = it - nb * nrb;
-        InverseWalk row(16 * rb + col, g, P.L);
+        const double2* tab3 = tab + (size_t)rb * KS * 64 + lane;
         const double* x1 = tc + g * ts + 16 * nb + col;
         const double* x2 = ti + g * ts + 16 * nb + col;
         acc_t ac = {0, 0, 0, 0}, as = {0, 0, 0, 0};
-        for (int s = 0; s < KS; ++s) {
-            const double2 t = row.next(tab);
-            ac = M::fma(t.x, x1[4 * s * ts], ac);
-            as = M::fma(t.y, x2[4 * s * ts], as);
+        constexpr int CH = 3;
+        for (int s = 0; s < KS; s += CH) {
+            double2 t[CH];
+            double b[CH], c[CH];
+#pragma unroll
+            for (int k = 0; k < CH; ++k) {
+                const int row_s = 4 * min(s + k, KS - 1) * ts;
+                b[k] = x1[row_s];
+                c[k] = x2[row_s];
+                t[k] = tab3[64 * (s + k)];
+            }
+#pragma unroll
+            for (int k = 0; k < CH; ++k)
+                if (s + k < KS) {
+                    ac = M::fma(t[k].x, b[k], ac);
+                    as = M::fma(t[k].y, c[k], as);
+                }
         }
-        const int c = 8 * nb + (col >> 1), k2 = c / nq, q = c - k2 * nq;
+        const int c = 8 * nb + (col >> 1), kk = c / nq, q = c - kk * nq;
+        const int k2 = kk & 1 ? H - 1 - j0 - (kk >> 1) : H + j0 + (kk >> 1);
+        double* o = reinterpret_cast<double*>(Y) + 2 * (((int64_t)line * P.P + k2) * P.P * ld + q0 + q) + (col & 1);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int k3 = 16 * rb + M::row(g, r);
-            if (c < nc2 && k3 < P.P)
-                reinterpret_cast<double*>(Y)[2 * ((((int64_t)line * P.P + k20 + k2) * P.P + k3) * ld + q0 + q) +
-                                             (col & 1)] = ac[r] + as[r];
+            const int j = 16 * rb + M::row(g, r);
+            if (c < nc2 && k2 < P.P && j < H) {
+                if (H + j < P.P) o[2 * (H + j) * ld] = ac[r] + as[r];
+                o[2 * (H - 1 - j) * ld] = ac[r] - as[r];
+            }
         }
     }
 }
@@ -1003,35 +1088,32 @@ bool plan_forward(prony_handle_t h, int d, int n, int m, SpecPlan& P) {
     const int64_t F = ipow(P.L, d == 3 ? 2 : 1);
     if (F > (int64_t(1) << 20) || P.K1 > kMaxLines) return false;
     P.F = (int)F;
-    P.npb = (P.P + kPairs - 1) / kPairs;
+    P.npb = (P.P + 15) / 16;
     P.nqb = (m + 15) / 16;
     const size_t budget = lds_budget(h);
     if (d <= 2) {
-        // column blocks per workgroup so that its items (a block against two blocks of
-        // pairs) share out over the four waves
-        const int npi = (P.npb + 1) / 2;
-        P.nbw = 1;
-        while (P.nbw < 4 && (P.nbw * npi) % kWaves && npi < 4 * kWaves) ++P.nbw;
-        auto lds = [&](int nb, int K) { return roots_bytes(P.L) + 16 * kCols * (size_t)nb * line_rows(K); };
-        while (P.nbw > 1 && lds(P.nbw, P.P) > budget) --P.nbw;
+        // column blocks per workgroup so that its items (a block of pairs against up to two
+        // column blocks) occupy the four waves
+        P.nbw = P.npb == 1 ? 8 : P.npb <= 3 ? 8 / (P.npb + (P.npb & 1)) : P.npb == 4 ? 1 : 2;
+        auto lds = [&](int nb, bool grid) {
+            return 2 * 16 * kCols * (size_t)nb * line_rows(folded_points(P.P, grid));
+        };
+        while (P.nbw > 1 && lds(P.nbw, false) > budget) --P.nbw;
         P.nbwf = P.nbw;
-        while (P.nbwf > 1 && lds(P.nbwf, P.L) > budget) --P.nbwf;
-        P.lds_fwd = std::max(lds(P.nbw, P.P), lds(P.nbwf, P.L));
+        while (P.nbwf > 1 && lds(P.nbwf, true) > budget) --P.nbwf;
+        P.lds_fwd = std::max(lds(P.nbw, false), lds(P.nbwf, true));
         auto wgs = [&](int64_t cols, int nb) { return (int)(((cols + kCols - 1) / kCols + nb - 1) / nb); };
         P.wgs_x = wgs((int64_t)P.K1 * m, P.nbw);
         P.wgs_f = wgs(P.NP1, P.nbwf);
     } else {
-        P.nq = std::min(m, kCols);
-        auto lds = [&](int nq, int J, int wp) {
-            return roots_bytes(P.L) + 8 * (size_t)((J + 3) & ~3) * plane_stride(wp, nq);
-        };
-        // one block of pairs per workgroup; fewer pairs where the planes do not fit
-        for (P.wp = kPairs; P.wp > 0; P.wp /= 2) {
-            P.lds_fwd = std::max(lds(P.nq, P.P, P.wp), lds(1, P.L, P.wp));
+        // a workgroup takes one block of 16 pairs of axis 3 and as many columns as fit
+        auto lds = [&](int nq, int J) { return 8 * (size_t)(J + 1) * plane_stride(2 * std::min(P.P, 16) * nq); };
+        for (P.nq = std::min(m, kCols); P.nq > 0; P.nq /= 2) {
+            P.lds_fwd = std::max(lds(P.nq, P.P), lds(1, P.L));
             if (P.lds_fwd <= budget) break;
         }
-        if (P.wp == 0) return false;
-        P.splits = (P.P + P.wp - 1) / P.wp;
+        if (P.nq == 0) return false;
+        P.splits = P.npb;
         P.wgs_x = P.K1 * ((m + P.nq - 1) / P.nq) * P.splits;
         P.wgs_f = P.NP1 * P.splits;
     }
@@ -1039,8 +1121,57 @@ bool plan_forward(prony_handle_t h, int d, int n, int m, SpecPlan& P) {
 }
 
 constexpr size_t kMaxWorkspace = size_t(1) << 30;
+constexpr size_t kMaxTables = size_t(64) << 20;
+
+void fill_tables(prony_handle_t h, int P, double2* tab) {
+    const int blocks = (table_sizes(P).total + kThreads - 1) / kThreads;
+    spectral_fill_tables<<<std::min(blocks, 4 * h->num_cus), kThreads, 0, h->stream>>>(P, tab);
+}
+
+// The tables of lines of P points: kept by the handle from the first call that needs them
+// (at most kMaxTables in all), else made on each call at `ws`, the plan's workspace
+// section (without `keep`, under stream capture, where nothing can be allocated, or past
+// the limit). Calls of one handle on several streams are ordered (prony_set_stream).
+prony_status_t tables_for(prony_handle_t h, int P, double2* ws, bool keep, const double2** tab) {
+    const auto it = h->spectral_tables.find(P);
+    if (it != h->spectral_tables.end()) {
+        *tab = static_cast<const double2*>(it->second);
+        return PRONY_OK;
+    }
+    const size_t bytes = 16 * (size_t)table_sizes(P).total;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(h->stream, &cs);
+    if (e != hipSuccess) return hip_fail(h, e, "hipStreamIsCapturing");
+    void* mem = nullptr;
+    if (keep && cs == hipStreamCaptureStatusNone && h->spectral_table_bytes + bytes <= kMaxTables &&
+        hipMalloc(&mem, bytes) == hipSuccess) {
+        h->spectral_tables[P] = mem;
+        h->spectral_table_bytes += bytes;
+        ws = static_cast<double2*>(mem);
+    } else {
+        (void)hipGetLastError();
+    }
+    *tab = ws;
+    if (!ws) return PRONY_OK;
+    fill_tables(h, P, ws);
+    return check_launch(h, "spectral_fill_tables");
+}
 
 }  // namespace
+
+prony_status_t spectral_reserve(prony_handle_t h, int d_max, int n_max) {
+    for (int n = 1; n <= n_max; ++n)
+        for (int d = 1; d <= std::min(d_max, 2); ++d) {     // d = 3 has the lines of d = 2
+            SpecPlan P;
+            if (!plan_forward(h, d, n, 1, P)) continue;
+            const double2* tab = nullptr;
+            const prony_status_t st = tables_for(h, P.P, nullptr, true, &tab);
+            if (st != PRONY_OK) return st;
+        }
+    return PRONY_OK;
+}
+
+size_t spectral_table_bytes(const SpecPlan& P) { return align_up(16 * (size_t)table_sizes(P.P).total, 256); }
 
 bool spectral_plan(prony_handle_t h, int d, int n, int m, bool s0, SpecPlan& P, bool batched) {
     if (!plan_forward(h, d, n, m, P)) return false;
@@ -1067,7 +1198,7 @@ bool spectral_plan(prony_handle_t h, int d, int n, int m, bool s0, SpecPlan& P, 
     P.off_f = 2 * x;
     P.off_p = P.off_f + align_up(16 * (size_t)P.F * P.NP1, 256);
     P.off_r = P.off_p + align_up(16 * (size_t)P.groups * m * P.ells * m, 256);
-    P.ws_bytes = P.off_r + align_up(16 * (size_t)P.L, 256);
+    P.ws_bytes = P.off_r + spectral_table_bytes(P);
     return P.ws_bytes <= kMaxWorkspace;
 }
 
@@ -1075,23 +1206,25 @@ bool spectral_product_plan(prony_handle_t h, int d, int n, int r, SpecPlan& P) {
     if (!plan_forward(h, d, n, r, P)) return false;
     P.pmax = n;
     const size_t budget = lds_budget(h);
-    const int KS = (P.P + 3) / 4;
+    const int KS = (P.P + 3) / 4, H = folded_points(P.P, false);
     if (d <= 2) {
-        const int nrb = (P.P + 15) / 16;
-        auto lds = [&](int nb) { return roots_bytes(P.L) + 2 * 16 * kCols * (size_t)nb * line_rows(P.P); };
-        P.nbi = 1;
-        while (P.nbi < 4 && (P.nbi * nrb) % kWaves && nrb < 4 * kWaves) ++P.nbi;
+        const int nrb = (H + 15) / 16;
+        auto lds = [&](int nb) { return 2 * 16 * kCols * (size_t)nb * line_rows(P.P); };
+        P.nbi = nrb == 1 ? 4 : nrb <= 3 ? 2 : 1;
         while (P.nbi > 1 && lds(P.nbi) > budget) --P.nbi;
         P.lds_inv = lds(P.nbi);
         P.wgs_i = ((P.K1 * r + kCols - 1) / kCols + P.nbi - 1) / P.nbi;
     } else {
-        P.isplits = (P.P + 15) / 16;
-        P.irows = (P.P + P.isplits - 1) / P.isplits;
+        // at most 16 folded rows of axis 2 per workgroup, at least 4, about one workgroup per CU
         for (P.nqi = std::min(r, kCols); P.nqi > 0; P.nqi /= 2) {
-            P.lds_inv = roots_bytes(P.L) + 2 * 8 * (size_t)(4 * KS) * inverse_stride(P.irows, P.nqi);
+            const int lines = P.K1 * ((r + P.nqi - 1) / P.nqi);
+            P.isplits = std::max((H + 15) / 16, std::min((H + 3) / 4, h->num_cus / lines));
+            P.irows = (H + P.isplits - 1) / P.isplits;
+            P.lds_inv = 2 * 8 * (size_t)(4 * KS) * plane_stride(2 * P.irows * P.nqi);
             if (P.lds_inv <= budget) break;
         }
         if (P.nqi == 0) return false;
+        P.isplits = (H + P.irows - 1) / P.irows;
         P.wgs_i = P.K1 * ((r + P.nqi - 1) / P.nqi) * P.isplits;
     }
     if (P.lds_inv > budget) return false;
@@ -1099,7 +1232,7 @@ bool spectral_product_plan(prony_handle_t h, int d, int n, int r, SpecPlan& P) {
     P.off_v = x;
     P.off_f = 2 * x;
     P.off_r = P.off_f + align_up(16 * (size_t)P.F * P.NP1, 256);
-    P.ws_bytes = P.off_r + align_up(16 * (size_t)P.L, 256);
+    P.ws_bytes = P.off_r + spectral_table_bytes(P);
     return P.ws_bytes <= kMaxWorkspace;
 }
 
@@ -1113,9 +1246,9 @@ prony_status_t spectral_product(prony_handle_t h, const SpecPlan& P, unsigned ch
     p.ut = reinterpret_cast<double2*>(ws);
     p.vt = reinterpret_cast<double2*>(ws + P.off_v);
     p.ft = reinterpret_cast<double2*>(ws + P.off_f);
-    p.roots = reinterpret_cast<double2*>(ws + P.off_r);
-    prony_status_t st = allow_lds(h, &spectral_forward_kernel, P.lds_fwd);
+    prony_status_t st = tables_for(h, P.P, reinterpret_cast<double2*>(ws + P.off_r), true, &p.tab);
     if (st != PRONY_OK) return st;
+    if ((st = allow_lds(h, &spectral_forward_kernel, P.lds_fwd)) != PRONY_OK) return st;
     {
         ProfileScope prof(h, "spectral_forward");
         spectral_forward_kernel<<<P.wgs_f + P.wgs_x, kThreads, P.lds_fwd, h->stream>>>(P, p, 0);   // the grid and X
@@ -1239,11 +1372,15 @@ prony_status_t spectral_batch_build(prony_handle_t h, const std::vector<prony_in
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
         return key(a) != key(b) ? key(a) > key(b) : work(a) > work(b);
     });
+    // work table, the tables of every line length, the instances' sections
     size_t off = align_up(sizeof(SpecEntry) * (size_t)count, 256);
+    std::map<int, size_t> tables;
+    for (const SpecPlan& P : plans)
+        if (tables.emplace(P.P, off).second) off += align_up(16 * (size_t)table_sizes(P.P).total, 256);
     std::vector<size_t> base(count);
     for (int pos = 0; pos < count; ++pos) {
         base[pos] = off;
-        off += plans[order[pos]].ws_bytes;
+        off += plans[order[pos]].off_r;
     }
     SpecBatch* S = new (std::nothrow) SpecBatch;
     if (!S) return fail(h, PRONY_ENOMEM, "prony_batch_create: out of host memory");
@@ -1266,8 +1403,8 @@ prony_status_t spectral_batch_build(prony_handle_t h, const std::vector<prony_in
         E.p = SpecPtrs{reinterpret_cast<const double2*>(x.U), reinterpret_cast<const double2*>(x.V), x.m, 1, x.m, 1,
                        reinterpret_cast<const double2*>(x.f), x.sigma, reinterpret_cast<double2*>(w),
                        reinterpret_cast<double2*>(w + P.off_v), reinterpret_cast<double2*>(w + P.off_f),
-                       reinterpret_cast<double2*>(w + P.off_p), reinterpret_cast<double2*>(w + P.off_r),
-                       reinterpret_cast<double2*>(x.S)};
+                       reinterpret_cast<double2*>(w + P.off_p), reinterpret_cast<double2*>(x.S), nullptr,
+                       reinterpret_cast<const double2*>(static_cast<unsigned char*>(S->ws) + tables[P.P])};
         E.fwd_begin = (int)fwd;
         fwd += P.wgs_f + 2 * (int64_t)P.wgs_x;
         if (pos == 0 || key(order[pos - 1]) != key(i)) {
@@ -1289,7 +1426,11 @@ prony_status_t spectral_batch_build(prony_handle_t h, const std::vector<prony_in
         }
     }
     S->fwd_wgs = (int)fwd;
-    e = hipMemcpyAsync(S->ws, host.data(), sizeof(SpecEntry) * (size_t)count, hipMemcpyHostToDevice, h->stream);
+    for (const auto& t : tables)
+        fill_tables(h, t.first, reinterpret_cast<double2*>(static_cast<unsigned char*>(S->ws) + t.second));
+    e = hipGetLastError();
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(S->ws, host.data(), sizeof(SpecEntry) * (size_t)count, hipMemcpyHostToDevice, h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) {
         (void)spectral_batch_free(S);
@@ -1335,9 +1476,11 @@ prony_status_t spectral_batch_launch(prony_handle_t h, const SpecBatch* S) {
 
 // ---- single instances --------------------------------------------------------
 
-prony_status_t spectral_forward(prony_handle_t h, const SpecPlan& P, const SpecPtrs& ptr, bool factors, bool grid) {
-    prony_status_t st = allow_lds(h, &spectral_forward_kernel, P.lds_fwd);
+prony_status_t spectral_forward(prony_handle_t h, const SpecPlan& P, SpecPtrs& ptr, bool factors, bool grid,
+                                bool keep_tables) {
+    prony_status_t st = tables_for(h, P.P, ptr.tables, keep_tables, &ptr.tab);
     if (st != PRONY_OK) return st;
+    if ((st = allow_lds(h, &spectral_forward_kernel, P.lds_fwd)) != PRONY_OK) return st;
     const int first = grid ? 0 : P.wgs_f;
     const int wgs = (grid ? P.wgs_f : 0) + (factors ? 2 * P.wgs_x : 0);
     {
