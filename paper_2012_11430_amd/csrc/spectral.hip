@@ -821,6 +821,37 @@ __global__ __launch_bounds__(kThreads) void spectral_toeplitz(SpecPlan P, SpecPt
     }
 }
 
+// A transform spreads a NaN, an infinity or a sum past the largest double over all the points
+// of its lines. Where a result is not finite it is therefore formed again from the inputs, so
+// that it depends on its own terms only; a sum that is NaN ends there. The offset of index
+// (k1, k2, k3) in the sample grid, from that of the index 0 in every axis:
+__device__ __forceinline__ bool is_finite(double x) { return fabs(x) <= 1.7976931348623157e308; }
+__device__ __forceinline__ int64_t grid_offset(const SpecPlan& P, int k) {
+    const int E = P.n + 1, Q = 2 * P.n + 2;
+    if (P.d == 1) return k;
+    if (P.d == 2) return (int64_t)(k / E) * Q + k % E;
+    return ((int64_t)(k / (E * E)) * Q + k / E % E) * Q + k % E;
+}
+__device__ __forceinline__ int64_t grid_centre(const SpecPlan& P) {
+    const int64_t Q = 2 * P.n + 2;
+    return P.n * (P.d == 1 ? 1 : P.d == 2 ? 1 + Q : 1 + Q + Q * Q);
+}
+
+// (T X)[k, q] or (T^* X)[k, q], component `im`.
+__device__ __forceinline__ double direct_product(const SpecPlan& P, const SpecPtrs& p, bool adjoint, int k, int q,
+                                                 bool im) {
+    const int64_t ok = grid_offset(P, k), centre = grid_centre(P);
+    double sum = 0.0;
+    for (int h = 0; h < P.N; ++h) {
+        const int64_t o = grid_offset(P, h);
+        const double2 f = p.f[centre + (adjoint ? o - ok : ok - o)], x = p.V[h * p.v_rs + q * p.v_cs];
+        const double fy = adjoint ? -f.y : f.y;
+        sum += im ? fma(f.x, x.y, fy * x.x) : fma(f.x, x.x, -fy * x.y);
+        if (sum != sum) break;
+    }
+    return sum;
+}
+
 // Inverse transforms about the line's centre (see the folded forward ones): at t = j + 1/2
 //     y(+-t) = C +- S,  C = sum_w A cos(w t), S = sum_w (i B) sin(w t)
 // over the pairs w < P, A = Y~(w) + Y~(-w), B = Y~(w) - Y~(-w). Pair 0: A = Y~(0), and in the
@@ -837,7 +868,7 @@ __device__ __forceinline__ void pair_in(bool zero, bool odd, double a, double b,
 // One transformed axis (d <= 2): nbc blocks of 8 complex columns c = k1 * m + q of Y~ from
 // block nb0. The pairs' operands are staged as [block][w][16 real columns], A then i B.
 __global__ __launch_bounds__(kThreads) void spectral_inverse_lines(SpecPlan P, SpecPtrs p, double2* __restrict__ Y,
-                                                                   int64_t ld) {
+                                                                   int64_t ld, int adjoint) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int NC = P.K1 * P.m, KS = (P.P + 3) >> 2, J = line_rows(P.P), H = folded_points(P.P, false);
     const int nblk = (NC + kCols - 1) / kCols, nb0 = blockIdx.x * P.nbi, nbc = min(P.nbi, nblk - nb0);
@@ -904,22 +935,32 @@ __global__ __launch_bounds__(kThreads) void spectral_inverse_lines(SpecPlan P, S
         const int cx = kCols * (nb0 + nb) + (col >> 1);
         const int t = cx / P.m, q = cx - t * P.m;
         double* o = reinterpret_cast<double*>(Y) + 2 * q + (col & 1);
+        bool bad = false;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int j = 16 * rb + M::row(g, r);
             const int ia = t * P.P + H + j, ib = t * P.P + H - 1 - j;
             if (cx < NC && j < H) {
-                if (H + j < P.P && ia < P.N) o[2 * ia * ld] = ac[r] + as[r];
-                if (ib < P.N) o[2 * ib * ld] = ac[r] - as[r];
+                const double ya = ac[r] + as[r], yb = ac[r] - as[r];
+                bad = bad || !is_finite(ya) || !is_finite(yb);
+                if (H + j < P.P && ia < P.N) o[2 * ia * ld] = ya;
+                if (ib < P.N) o[2 * ib * ld] = yb;
             }
         }
+        if (__builtin_expect(bad, 0))
+            for (int r = 0; r < 8; ++r) {
+                const int j = 16 * rb + M::row(g, r >> 1);
+                const int i = t * P.P + (r & 1 ? H - 1 - j : H + j);
+                if (j >= H || (!(r & 1) && H + j >= P.P) || i >= P.N || is_finite(o[2 * i * ld])) continue;
+                o[2 * i * ld] = direct_product(P, p, adjoint, i, q, col & 1);
+            }
     }
 }
 
 // Two transformed axes (d = 3): the rows k2 = H + j, H - 1 - j, j in part `split`, of one
 // line k1 and nq columns: axis 2 into LDS as the operands of axis 3's pairs, then axis 3.
 __global__ __launch_bounds__(kThreads) void spectral_inverse_planes(SpecPlan P, SpecPtrs p, double2* __restrict__ Y,
-                                                                    int64_t ld) {
+                                                                    int64_t ld, int adjoint) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int per = (P.m + P.nqi - 1) / P.nqi;
     const int split = blockIdx.x % P.isplits, rest0 = blockIdx.x / P.isplits;
@@ -1027,6 +1068,7 @@ __global__ __launch_bounds__(kThreads) void spectral_inverse_planes(SpecPlan P, 
         const int c = 8 * nb + (col >> 1), kk = c / nq, q = c - kk * nq;
         const int k2 = kk & 1 ? H - 1 - j0 - (kk >> 1) : H + j0 + (kk >> 1);
         double* o = reinterpret_cast<double*>(Y) + 2 * (((int64_t)line * P.P + k2) * P.P * ld + q0 + q) + (col & 1);
+        bool bad = false;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int j = 16 * rb + M::row(g, r);
@@ -1210,6 +1252,12 @@ bool spectral_product_plan(prony_handle_t h, int d, int n, int r, SpecPlan& P) {
     if (d <= 2) {
         const int nrb = (H + 15) / 16;
         auto lds = [&](int nb) { return 2 * 16 * kCols * (size_t)nb * line_rows(P.P); };
+        const int t0 = 16 * part + K1 - 1 - 16 * nhb, t1 = d == 2 ? 16 * part + 14 + K1 : P.NP1 - 1;
+        double2* out = a.gt + ((size_t)part * P.F + w) * P.NP1;
+        for (int x = lane; x < sn; x += 64) {
+            const int t = t0 + x;
+            if (t >= 16 * part && t <= t1 && t < P.NP1) out[t] = make_double2(sums[2 * x], sums[2 * x + 1]);
+        }
         P.nbi = nrb == 1 ? 4 : nrb <= 3 ? 2 : 1;
         while (P.nbi > 1 && lds(P.nbi) > budget) --P.nbi;
         P.lds_inv = lds(P.nbi);
@@ -1270,9 +1318,9 @@ prony_status_t spectral_product(prony_handle_t h, const SpecPlan& P, unsigned ch
         ProfileScope prof(h, "spectral_inverse");
         double2* y = reinterpret_cast<double2*>(Y);
         if (P.d == 3)
-            spectral_inverse_planes<<<P.wgs_i, kThreads, P.lds_inv, h->stream>>>(P, p, y, ldy);
+            spectral_inverse_planes<<<P.wgs_i, kThreads, P.lds_inv, h->stream>>>(P, p, y, ldy, adjoint ? 1 : 0);
         else
-            spectral_inverse_lines<<<P.wgs_i, kThreads, P.lds_inv, h->stream>>>(P, p, y, ldy);
+            spectral_inverse_lines<<<P.wgs_i, kThreads, P.lds_inv, h->stream>>>(P, p, y, ldy, adjoint ? 1 : 0);
     }
     return check_launch(h, "spectral_inverse");
 }

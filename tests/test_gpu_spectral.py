@@ -159,3 +159,22 @@ def test_fp64_batches_match_single_builds(shapes):
         assert all(torch.equal(a, b) for a, b in zip(eager, batch.S)), f"replay {rep}"
         (torch.randn(4096, device=DEV) * 3).sum().item()
     batch.close()
+
+
+@pytest.mark.parametrize("d,n,r", [(1, 40, 3), (2, 9, 5), (2, 17, 1), (3, 5, 9)])
+@pytest.mark.parametrize("adjoint", [False, True])
+def test_products_keep_non_finite_samples_to_their_rows(d, n, r, adjoint):
+    """A NaN sample reaches the rows of T (or T^*) that hold it, and no others."""
+    grid, _, _, X = _problem(d, n, r, seed=7700 + n)
+    p = (n,) * (d - 1) + (2,)
+    print(f"non-finite product d={d} n={n} r={r} adjoint={adjoint}", flush=True)
+    at = np.ravel_multi_index(tuple(x + n for x in p), (2 * n + 2,) * d)
+    bad = grid.copy()
+    bad[at] = np.nan
+    T = O.toeplitz(bad, d, n, 0)
+    T = T.conj().T if adjoint else T
+    hit = np.isnan(T).any(axis=1)
+    assert 0 < hit.sum() < T.shape[0]
+    got = api.toeplitz_mm(_dev(bad), d, n, _dev(X), adjoint=adjoint).cpu().numpy()
+    assert np.array_equal(np.isnan(got).any(axis=1), hit) and np.array_equal(np.isnan(got).all(axis=1), hit)
+    assert_close(got[~hit], T[~hit] @ X, TOL, "rows without the NaN")
