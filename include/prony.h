@@ -309,7 +309,9 @@ prony_status_t prony_coeffs(prony_handle_t handle, int d, int n, int m,
    of S_1..S_d). gf: (2n+2)^d complex128, overwritten. prec selects the MFMA and
    tile-accumulation type (FP32 or FP64); the diagonal bins and the window sums
    added to gf are FP64. Summation order inside a bin is not fixed (LDS atomics),
-   so repeated runs agree to rounding, not bitwise. Requires 1 <= m <= min(N, 32). */
+   so repeated runs agree to rounding, not bitwise; FP64 gradients with d >= 2 in
+   line-spectral form (see prony_build_S) are the same bits each time. A capture for
+   which only the tiles' workspace is there runs the tiles. Requires 1 <= m <= min(N, 32). */
 prony_status_t prony_build_S_adjoint(prony_handle_t handle, int d, int n, int m,
                                      const double* U, int64_t u_rs, int64_t u_cs,
                                      const double* sigma,

@@ -22,10 +22,13 @@
 //                window is then added to the gradient in FP64 (device atomics).
 // The accumulation order inside a bin is not fixed: results agree to rounding,
 // not bitwise, between runs.
+// FP64 gradients of single instances with d >= 2 run in line-spectral form instead
+// (spectral.hip) wherever it applies.
 #include <algorithm>
 
 #include "common.h"
 #include "mfma.h"
+#include "spectral.h"
 
 namespace prony {
 namespace {
@@ -592,6 +595,8 @@ size_t adjoint_workspace_bytes(prony_handle_t h, int d, int n, int m) {
         AdjPlan P;
         if (make_adj_plan(h, d, n, m, ts, P) == PRONY_OK) best = std::max(best, P.ws_bytes);
     }
+    SpecPlan SP;
+    if (spectral_adjoint_plan(h, d, n, m, SP)) best = std::max(best, SP.ws_bytes);
     return best;
 }
 
@@ -624,6 +629,14 @@ extern "C" prony_status_t prony_build_S_adjoint(prony_handle_t h, int d, int n, 
         return launch_adjoint<float>(h, P, U, u_rs, u_cs, sigma, V, v_rs, v_cs, gS, gf);
     }
     if ((st = make_adj_plan(h, d, n, m, sizeof(double), P)) != PRONY_OK) return st;
+    // FP64 in line-spectral form where it applies; a shape the tiles cannot cover is refused
+    // above, and a capture that the tiles' workspace would do for runs them
+    SpecPlan SP;
+    if (spectral_adjoint_plan(h, d, n, m, SP) && workspace_available(h, SP.ws_bytes, P.ws_bytes)) {
+        if ((st = ensure_workspace(h, SP.ws_bytes)) != PRONY_OK) return st;
+        return spectral_adjoint_run(h, SP, static_cast<unsigned char*>(h->ws), U, u_rs, u_cs, sigma, V, v_rs, v_cs,
+                                    gS, gf);
+    }
     return launch_adjoint<double>(h, P, U, u_rs, u_cs, sigma, V, v_rs, v_cs, gS, gf);
 }
 

@@ -86,4 +86,10 @@ bool spectral_product_plan(prony_handle_t h, int d, int n, int r, SpecPlan& P);
 prony_status_t spectral_product(prony_handle_t h, const SpecPlan& P, unsigned char* ws, const double* f,
                                 const double* X, int64_t ldx, bool adjoint, double* Y, int64_t ldy);
 
+// Plan of an FP64 adjoint (d >= 2; the workspace: U~ | V~ | g~ | tables), and the adjoint.
+bool spectral_adjoint_plan(prony_handle_t h, int d, int n, int m, SpecPlan& P);
+prony_status_t spectral_adjoint_run(prony_handle_t h, const SpecPlan& P, unsigned char* ws, const double* U,
+                                    int64_t u_rs, int64_t u_cs, const double* sigma, const double* V, int64_t v_rs,
+                                    int64_t v_cs, const double* gS, double* gf);
+
 }  // namespace prony

@@ -89,7 +89,7 @@ __host__ __device__ inline TableSizes table_sizes(int P) {
     t.ks_g = (P + 4) >> 2;
     t.ks_i = (P + 3) >> 2;
     t.off_g = blocks * t.ks_f * 64;
-    t.off_i = t.off_g + blocks * t.ks_g * 64;
+    t.off_i = t.off_g + ((P + 16) >> 4) * t.ks_g * 64;      // rows 0..P (the adjoint's points)
     t.off_r = t.off_i + ((H + 15) >> 4) * t.ks_i * 64;
     t.total = t.off_r + 2 * P + 8 * 64;      // the K loops load up to 8 steps past a block's end
     return t;
@@ -114,7 +114,7 @@ __global__ __launch_bounds__(kThreads) void spectral_fill_tables(int P, double2*
             const int w = kind == 2 ? k : row, j = kind == 2 ? row : k;
             const int a = kind == 1 ? 2 * w * j : w * (2 * j + 1);
             sincospi((double)(a % (2 * L)) / L, &s, &c);
-            const bool inside = w < P && j < (kind == 1 ? P + 1 : H);
+            const bool inside = kind == 1 ? w <= P && j <= P : w < P && j < H;
             if (inside) v = make_double2(c, kind != 1 && w == 0 ? (j & 1 ? -1.0 : 1.0) : s);
         }
         tab[i] = v;
@@ -1073,11 +1073,431 @@ __global__ __launch_bounds__(kThreads) void spectral_inverse_planes(SpecPlan P, 
         for (int r = 0; r < 4; ++r) {
             const int j = 16 * rb + M::row(g, r);
             if (c < nc2 && k2 < P.P && j < H) {
-                if (H + j < P.P) o[2 * (H + j) * ld] = ac[r] + as[r];
-                o[2 * (H - 1 - j) * ld] = ac[r] - as[r];
+                const double ya = ac[r] + as[r], yb = ac[r] - as[r];
+                bad = bad || !is_finite(ya) || !is_finite(yb);
+                if (H + j < P.P) o[2 * (H + j) * ld] = ya;
+                o[2 * (H - 1 - j) * ld] = yb;
+            }
+        }
+        if (__builtin_expect(bad, 0))
+            for (int r = 0; r < 8; ++r) {
+                const int j = 16 * rb + M::row(g, r >> 1), k3 = r & 1 ? H - 1 - j : H + j;
+                if (j >= H || k3 >= P.P || is_finite(o[2 * k3 * ld])) continue;
+                o[2 * k3 * ld] = direct_product(P, p, adjoint, (line * P.P + k2) * P.P + k3, q0 + q, col & 1);
+            }
+    }
+}
+
+// ---- adjoint -----------------------------------------------------------------
+//
+// grad(p) = sum over k' - h = p of (Z W^T)[k', h], Z[k'] = sum_l (U gS_l Sigma^{-1})[k' - e_l],
+// W = conj(V) (adjoint.hip). Per frequency of the axes 2..d
+//     Z~_w[k1'] = sum_i U~_w[k1' - 1, i] G_1[i] + U~_w[k1', i] sum_{l >= 2} e^{-2 pi i w_l / L} G_l[i],
+//     g~_w(p1)  = sum over k1' - h1 = p1 of Z~_w[k1'] . conj(V~_w[h1]),
+// G_l = gS_l Sigma^{-1}, and grad is the inverse transform of g~. U~ and V~ are those of the
+// S-build: the phase of their lines' centres cancels in U~ conj(V~). d >= 2 only; d = 1 keeps
+// the tiles of adjoint.hip (points of two folded lines would fall on one sample).
+//   8 (n+2)(n+1) m L^(d-1) operations instead of 8 (n+2)^d (n+1)^d m; pack, tiles and sums
+// against the three launches here, in us: d=2 n=15 m=8 17.3 -> 15.9, d=2 n=63 m=20 137 -> 42,
+// d=3 n=12 m=11 63 -> 25, d=3 n=15 m=17 104 -> 38. What is left is latency: the loads of a
+// unit's U~ and V~ (spectral_adjoint 17 us at d=2 n=63, 3 us of it matrix work) and the
+// transforms' short chains.
+
+struct SpecAdjPtrs {
+    SpecPtrs p;          // U, V and their transforms, sigma, tab
+    const double2* gS;
+    double2* gt;         // g~[w][t]; d = 2: by 16-row block of k1', [block][w][t]
+    double2* gf;
+};
+
+// LDS of spectral_adjoint: G [l][i][q] (padded), then per wave a 16 x 17 tile and the
+// diagonal sums of a row block (d = 2) or of all of them.
+__host__ __device__ inline size_t adj_g_bytes(int d, int m) {
+    return 16 * (size_t)d * ((m + 3) & ~3) * (16 * ((m + 15) >> 4));
+}
+__host__ __device__ inline int adj_sums(int d, int K1) {
+    return ((K1 + 15) & ~15) + 16 + (d == 3 ? (K1 + 16) & ~15 : 16);
+}
+__host__ __device__ inline size_t adj_wave_bytes(int d, int K1) { return 16 * (size_t)(16 * 17 + adj_sums(d, K1)); }
+
+// LDS accesses of a wave before and after stay in this order (the hardware keeps it; this
+// is for the compiler).
+__device__ __forceinline__ void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// One unit, a frequency (d = 2: and a 16-row block kb of k1', for there are few frequencies;
+// the blocks' sums are added where they are read), per wave and turn. Z~^T = G^T U~^T
+// (rows q, columns k1') stays in registers: its result layout is the second operand's
+// layout of the products conj(V~) Z~^T (rows h1), whose diagonals are summed through LDS.
+template <int NQB>
+__device__ __forceinline__ void adjoint_body(const SpecPlan& P, const SpecAdjPtrs& a, int wg, int wgs,
+                                             unsigned char* smem) {
+    const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, col = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m = P.m, K1 = P.K1, KM = (m + 3) >> 2, MI = 4 * KM, d = P.d;
+    const int nkb = (K1 + 16) >> 4, nhb = (K1 + 15) >> 4;
+    constexpr int MQ = 16 * NQB;
+    double2* G = reinterpret_cast<double2*>(smem);
+    double2* tile = reinterpret_cast<double2*>(smem + adj_g_bytes(d, m) + adj_wave_bytes(d, K1) * wave);
+    double* sums = reinterpret_cast<double*>(tile + 16 * 17);
+    const double2* roots = a.p.tab + table_sizes(P.P).off_r;
+    for (int e = tid; e < d * MI * MQ; e += kThreads) {
+        const int q = e % MQ, i = e / MQ % MI, l = e / (MQ * MI);
+        double2 v = make_double2(0.0, 0.0);
+        if (q < m && i < m) {
+            v = a.gS[((size_t)l * m + i) * m + q];
+            const double s = a.p.sigma[q];
+            v = make_double2(v.x / s, v.y / s);
+        }
+        G[e] = v;
+    }
+    __syncthreads();
+    const int row_bytes = 16 * m;
+    const int parts = d == 2 ? nkb : 1, sn = adj_sums(d, K1);
+    for (int u = wg * kWaves + wave; u < P.F * parts; u += wgs * kWaves) {
+        const int w = u / parts, part = u - w * parts;
+        const auto ut = buffer_of(a.p.ut + (size_t)w * K1 * m, K1 * row_bytes);
+        const auto vt = buffer_of(a.p.vt + (size_t)w * K1 * m, K1 * row_bytes);
+        wave_order();
+        for (int x = lane; x < 2 * sn; x += 64) sums[x] = 0.0;
+        // phases e^{-2 pi i w_l / L} of the axes 2 (and 3)
+        const double2 r2 = roots[d == 3 ? w / P.L : w], r3 = roots[d == 3 ? w % P.L : 0];
+        for (int kb = part; kb < (d == 2 ? part + 1 : nkb); ++kb) {
+            double2 zs[NQB][4];           // Z~ of column k1' = 16 kb + col, rows q = 16 qb + g + 4 r
+            {
+                acc_t z[NQB][3];
+#pragma unroll
+                for (int b = 0; b < NQB; ++b)
+#pragma unroll
+                    for (int x = 0; x < 3; ++x) z[b][x] = acc_t{0, 0, 0, 0};
+                const int k1 = 16 * kb + col;
+                for (int s0 = 0; s0 < KM; s0 += 4) {
+                    double2 u0[4], u1[4];           // U~[k1'][i], U~[k1' - 1][i], i = 4 s + g
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const int i = 4 * (s0 + k) + g, o = i < m ? k1 * row_bytes + 16 * i : kOutside;
+                        u0[k] = buffer_load(ut, o);
+                        u1[k] = buffer_load(ut, i < m ? o - row_bytes : kOutside);
+                    }
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        if (s0 + k >= KM) break;
+                        const double2* gi = G + (4 * (s0 + k) + g) * MQ + col;
+#pragma unroll
+                        for (int b = 0; b < NQB; ++b) {
+                            const double2 g1 = gi[16 * b], g2 = gi[(size_t)MI * MQ + 16 * b];
+                            double2 gm = make_double2(fma(r2.x, g2.x, r2.y * g2.y), fma(r2.x, g2.y, -r2.y * g2.x));
+                            if (d == 3) {
+                                const double2 g3 = gi[(size_t)2 * MI * MQ + 16 * b];
+                                gm.x = fma(r3.x, g3.x, fma(r3.y, g3.y, gm.x));
+                                gm.y = fma(r3.x, g3.y, fma(-r3.y, g3.x, gm.y));
+                            }
+                            z[b][0] = M::fma(g1.x, u1[k].x, z[b][0]);
+                            z[b][1] = M::fma(g1.y, u1[k].y, z[b][1]);
+                            z[b][2] = M::fma(g1.x + g1.y, u1[k].x + u1[k].y, z[b][2]);
+                            z[b][0] = M::fma(gm.x, u0[k].x, z[b][0]);
+                            z[b][1] = M::fma(gm.y, u0[k].y, z[b][1]);
+                            z[b][2] = M::fma(gm.x + gm.y, u0[k].x + u0[k].y, z[b][2]);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int b = 0; b < NQB; ++b)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        zs[b][r] = make_double2(z[b][0][r] - z[b][1][r], z[b][2][r] - z[b][0][r] - z[b][1][r]);
+            }
+            for (int hb = 0; hb < nhb; ++hb) {
+                double2 v[NQB][4];               // V~[h1][q], h1 = 16 hb + col, q = 16 b + 4 s + g
+#pragma unroll
+                for (int b = 0; b < NQB; ++b)
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) {
+                        const int q = 16 * b + 4 * s + g;
+                        v[b][s] = buffer_load(vt, q < m ? (16 * hb + col) * row_bytes + 16 * q : kOutside);
+                    }
+                acc_t x1 = {0, 0, 0, 0}, x2 = {0, 0, 0, 0}, x3 = {0, 0, 0, 0};
+#pragma unroll
+                for (int b = 0; b < NQB; ++b)
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) {
+                        if (16 * b + 4 * s >= m) break;
+                        x1 = M::fma(v[b][s].x, zs[b][s].x, x1);
+                        x2 = M::fma(v[b][s].y, zs[b][s].y, x2);
+                        x3 = M::fma(v[b][s].x - v[b][s].y, zs[b][s].x + zs[b][s].y, x3);
+                    }
+                // conj(v) z at (h1 = row, k1' = col); rows past K1 are zero rows
+                wave_order();
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    tile[M::row(g, r) * 17 + col] = make_double2(x1[r] + x2[r], x3[r] - x1[r] + x2[r]);
+                wave_order();
+                // lane 2 e + comp sums the diagonal k - h = e - 15
+                const int e = lane >> 1;
+                if (e < 31) {
+                    const double* t = reinterpret_cast<const double*>(tile) + (lane & 1);
+                    const int h0 = max(0, 15 - e), h1 = min(15, 30 - e);
+                    double sum = 0.0;
+#pragma unroll
+                    for (int h = 0; h < 16; ++h) {
+                        const double y = t[2 * (min(max(h, h0), h1) * 17 + e - 15 + min(max(h, h0), h1))];
+                        sum += h >= h0 && h <= h1 ? y : 0.0;
+                    }
+                    // t = k1' - h1 + K1 - 1: place 16 (kb - part + nhb - hb) + e - 15
+                    // holds t = 16 part + K1 - 1 - 16 nhb + place
+                    sums[2 * (16 * (kb - part + nhb - hb) + e - 15) + (lane & 1)] += sum;
+                }
+                wave_order();
+            }
+        }
+        const int t0 = 16 * part + K1 - 1 - 16 * nhb, t1 = d == 2 ? 16 * part + 14 + K1 : P.NP1 - 1;
+        double2* out = a.gt + ((size_t)part * P.F + w) * P.NP1;
+        for (int x = lane; x < sn; x += 64) {
+            const int t = t0 + x;
+            if (t >= 16 * part && t <= t1 && t < P.NP1) out[t] = make_double2(sums[2 * x], sums[2 * x + 1]);
+        }
+    }
+}
+
+// g~ at frequencies w and -w (d = 2), summed over the row blocks that reach t (in order).
+__device__ __forceinline__ void adjoint_pair(const SpecPlan& P, const double2* __restrict__ gt, int w, int t,
+                                             double2& x, double2& y) {
+    const int nkb = (P.K1 + 16) >> 4, hi = min(nkb - 1, t >> 4);
+    const bool two = w > 0 && w < P.P;
+    x = y = make_double2(0.0, 0.0);
+    constexpr int kIn = 4;
+    for (int kb = max(0, (t - P.K1 + 1) >> 4); kb <= hi; kb += kIn) {
+        double2 a[kIn], b[kIn];
+#pragma unroll
+        for (int k = 0; k < kIn; ++k) {
+            const double2* g = gt + (size_t)(kb + k) * P.F * P.NP1 + t;
+            a[k] = kb + k <= hi ? g[(size_t)w * P.NP1] : make_double2(0.0, 0.0);
+            b[k] = kb + k <= hi && two ? g[(size_t)(P.L - w) * P.NP1] : make_double2(0.0, 0.0);
+        }
+#pragma unroll
+        for (int k = 0; k < kIn; ++k) {
+            x = make_double2(x.x + a[k].x, x.y + a[k].y);
+            y = make_double2(y.x + b[k].x, y.y + b[k].y);
+        }
+    }
+}
+
+// grad(p) from the inputs, component `im` (for results that are not finite, see above).
+__device__ __forceinline__ double direct_gradient(const SpecPlan& P, const SpecAdjPtrs& a, const int (&pt)[3],
+                                                  bool im) {
+    const int E = P.n + 1, m = P.m;
+    double sum = 0.0;
+    for (int l = 0; l < P.d; ++l)
+        for (int k = 0; k < P.N; ++k) {
+            // row k + e_l of T_row meets column h = k + e_l - p
+            int h = 0, rest = k;
+            bool inside = true;
+            for (int axis = P.d - 1, s = 1; axis >= 0; --axis, s *= E) {
+                const int x = rest % E + (axis == l ? 1 : 0) - pt[axis];
+                rest /= E;
+                inside = inside && x >= 0 && x < E;
+                h += s * x;
+            }
+            if (!inside) continue;
+            for (int q = 0; q < m; ++q) {
+                double2 z = make_double2(0.0, 0.0);
+                for (int i = 0; i < m; ++i) {
+                    const double2 u = a.p.U[k * a.p.u_rs + i * a.p.u_cs], c = a.gS[((size_t)l * m + i) * m + q];
+                    z.x += u.x * c.x - u.y * c.y;
+                    z.y += u.x * c.y + u.y * c.x;
+                }
+                const double2 v = a.p.V[h * a.p.v_rs + q * a.p.v_cs];
+                sum += (im ? z.y * v.x - z.x * v.y : z.x * v.x + z.y * v.y) / a.p.sigma[q];
+            }
+            if (sum != sum) return sum;
+        }
+    return sum;
+}
+
+// Writes component `im` of grad(p) where it is finite, else returns true. Points with two
+// coordinates n + 1, and the point with all coordinates -n, belong to no T_l.
+__device__ __forceinline__ bool store_gradient(const SpecPlan& P, const SpecAdjPtrs& a, const int (&p)[3], bool im,
+                                               double x) {
+    const int top = P.n + 1, low = -P.n;
+    if ((p[0] == top) + (p[1] == top) + (P.d == 3 && p[2] == top) > 1 ||
+        (p[0] == low && p[1] == low && (P.d == 2 || p[2] == low)))
+        x = 0.0;
+    int64_t at = (int64_t)(p[0] + P.n) * P.L + p[1] + P.n;
+    if (P.d == 3) at = at * P.L + p[2] + P.n;
+    reinterpret_cast<double*>(a.gf + at)[im] = x;
+    return !is_finite(x);
+}
+
+// Inverse transform of g~ at the points +-j, j = 0..P, of a transformed axis: C +- S with
+// A = g~(w) + g~(-w), i B over w = 0..P (w = 0 and P alone, no sine part); the factors are
+// those of the sample grid's forward transform with rows and contraction exchanged.
+// d = 2: 8 sample lines per workgroup.
+__device__ __forceinline__ void adjoint_lines(const SpecPlan& P, const SpecAdjPtrs& a, int blk, unsigned char* smem) {
+    const TableSizes T = table_sizes(P.P);
+    const int K = P.P + 1, KS = T.ks_g, J = line_rows(K);
+    double2* xc = reinterpret_cast<double2*>(smem);
+    double2* xi = xc + (size_t)J * kCols;
+    const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, col = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int e = tid; e < J * kCols; e += kThreads) {
+        const int t = kCols * blk + (e & 7), w = e >> 3;
+        double2 x = make_double2(0.0, 0.0), y = x;
+        if (t < P.NP1 && w < K) adjoint_pair(P, a.gt, w, t, x, y);
+        xc[e] = make_double2(x.x + y.x, x.y + y.y);
+        xi[e] = make_double2(y.y - x.y, x.x - y.x);
+    }
+    __syncthreads();
+    const double scale = 1.0 / P.F;
+    for (int rb = wave; 16 * rb < K; rb += kWaves) {
+        const double2* f = a.p.tab + T.off_g + (size_t)rb * KS * 64 + lane;
+        const double* x1 = reinterpret_cast<const double*>(xc) + 16 * g + col;
+        const double* x2 = reinterpret_cast<const double*>(xi) + 16 * g + col;
+        acc_t ac = {0, 0, 0, 0}, as = {0, 0, 0, 0};
+        for (int s = 0; s < KS; s += 4)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (s + k >= KS) break;
+                const double2 t = f[64 * (s + k)];
+                ac = M::fma(t.x, x1[64 * (s + k)], ac);
+                as = M::fma(t.y, x2[64 * (s + k)], as);
+            }
+        const int t = kCols * blk + (col >> 1);
+        unsigned bad = 0;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const int j = 16 * rb + M::row(g, r >> 1);
+            const double x = (r & 1 ? ac[r >> 1] - as[r >> 1] : ac[r >> 1] + as[r >> 1]) * scale;
+            const int pt[3] = {t - P.n, r & 1 ? -j : j, 0};
+            if (t < P.NP1 && j < K && (!(r & 1) || (j > 0 && j < P.P)))
+                bad |= store_gradient(P, a, pt, col & 1, x) ? 1u << r : 0u;
+        }
+        for (int r = 0; __builtin_expect(bad != 0, 0); ++r, bad >>= 1)
+            if (bad & 1) {
+                const int j = 16 * rb + M::row(g, r >> 1);
+                const int pt[3] = {t - P.n, r & 1 ? -j : j, 0};
+                store_gradient(P, a, pt, col & 1, direct_gradient(P, a, pt, col & 1));
+            }
+    }
+}
+
+// d = 3: the points +-j of axis 2, j in part `split`, of sample line t: axis 2 into LDS
+// as the operands of axis 3's pairs u = 0..P, then axis 3.
+__device__ __forceinline__ void adjoint_planes(const SpecPlan& P, const SpecAdjPtrs& a, int t, int split,
+                                               unsigned char* smem) {
+    const TableSizes T = table_sizes(P.P);
+    const int K = P.P + 1, KS = T.ks_g;
+    const int j0 = split * P.irows, kn = min(P.irows, K - j0);
+    const int ts = plane_stride(2 * P.irows);
+    double* tc = reinterpret_cast<double*>(smem);       // [u][2 j + side], A
+    double* ti = tc + (size_t)4 * KS * ts;              // i B
+    const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, col = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool odd = lane & 1;
+    for (int i = tid; i < (4 * KS - K) * ts; i += kThreads) {
+        tc[(size_t)K * ts + i] = 0.0;
+        ti[(size_t)K * ts + i] = 0.0;
+    }
+    const double2* tab = a.p.tab + T.off_g;
+    const int jr = min(j0 + col, K - 1);
+    const double2* tab2 = tab + (size_t)(jr >> 4) * KS * 64 + 16 * g + (jr & 15);
+    for (int it = wave; 8 * it < K; it += kWaves) {
+        const int u = 8 * it + (col >> 1);
+        acc_t ac[2], as[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) ac[i] = as[i] = acc_t{0, 0, 0, 0};
+        constexpr int kIn = 4;
+        for (int s0 = 0; s0 < KS; s0 += kIn) {
+            double2 f[kIn], x[2][kIn], y[2][kIn];
+#pragma unroll
+            for (int k = 0; k < kIn; ++k) {
+                f[k] = tab2[64 * (s0 + k)];
+                const int w = 4 * (s0 + k) + g;
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const bool in = u < K && w < K && (i == 0 || (u > 0 && u < P.P));
+                    const double2* g3 = a.gt + (size_t)(i == 0 ? u : P.L - u) * P.NP1 + t;
+                    const size_t step = (size_t)P.L * P.NP1;
+                    x[i][k] = in ? g3[w * step] : make_double2(0.0, 0.0);
+                    y[i][k] = in && w > 0 && w < P.P ? g3[(P.L - w) * step] : make_double2(0.0, 0.0);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < kIn; ++k) {
+                if (s0 + k >= KS) break;
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    // A, and i B
+                    const double2 p = x[i][k], q = y[i][k];
+                    ac[i] = M::fma(f[k].x, odd ? p.y + q.y : p.x + q.x, ac[i]);
+                    as[i] = M::fma(f[k].y, odd ? p.x - q.x : q.y - p.y, as[i]);
+                }
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int j = M::row(g, r);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {               // the points +j and -j
+                const double x = h == 0 ? ac[0][r] + as[0][r] : ac[0][r] - as[0][r];
+                const double y = h == 0 ? ac[1][r] + as[1][r] : ac[1][r] - as[1][r];
+                const double b = swap_lane_pair(x - y);
+                if (u < K && j < kn) {
+                    tc[u * ts + 2 * (2 * j + h) + (col & 1)] = x + y;
+                    ti[u * ts + 2 * (2 * j + h) + (col & 1)] = odd ? b : -b;
+                }
             }
         }
     }
+    __syncthreads();
+    const int nc2 = 2 * kn, nb2 = (nc2 + 7) >> 3, nrb = (K + 15) >> 4;
+    const double scale = 1.0 / P.F;
+    for (int it = wave; it < nb2 * nrb; it += kWaves) {
+        const int nb = it / nrb, rb = it - nb * nrb;
+        const double2* f = tab + (size_t)rb * KS * 64 + lane;
+        const double* x1 = tc + g * ts + 16 * nb + col;
+        const double* x2 = ti + g * ts + 16 * nb + col;
+        acc_t ac = {0, 0, 0, 0}, as = {0, 0, 0, 0};
+        for (int s = 0; s < KS; ++s) {
+            const double2 c = f[64 * s];
+            ac = M::fma(c.x, x1[4 * s * ts], ac);
+            as = M::fma(c.y, x2[4 * s * ts], as);
+        }
+        const int c = 8 * nb + (col >> 1), j2 = j0 + (c >> 1);
+        const bool mirror = c & 1;
+        const int p2 = mirror ? -j2 : j2;
+        const bool ok = c < nc2 && (!mirror || (j2 > 0 && j2 < P.P));
+        unsigned bad = 0;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const int j = 16 * rb + M::row(g, r >> 1);
+            const double x = (r & 1 ? ac[r >> 1] - as[r >> 1] : ac[r >> 1] + as[r >> 1]) * scale;
+            const int pt[3] = {t - P.n, p2, r & 1 ? -j : j};
+            if (ok && j < K && (!(r & 1) || (j > 0 && j < P.P)))
+                bad |= store_gradient(P, a, pt, col & 1, x) ? 1u << r : 0u;
+        }
+        for (int r = 0; __builtin_expect(bad != 0, 0); ++r, bad >>= 1)
+            if (bad & 1) {
+                const int j = 16 * rb + M::row(g, r >> 1);
+                const int pt[3] = {t - P.n, p2, r & 1 ? -j : j};
+                store_gradient(P, a, pt, col & 1, direct_gradient(P, a, pt, col & 1));
+            }
+    }
+}
+
+template <int NQB>
+__global__ __launch_bounds__(kThreads) void spectral_adjoint(SpecPlan P, SpecAdjPtrs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    adjoint_body<NQB>(P, a, blockIdx.x, gridDim.x, smem);
+}
+
+__global__ __launch_bounds__(kThreads) void spectral_adjoint_inverse(SpecPlan P, SpecAdjPtrs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    if (P.d == 2)
+        adjoint_lines(P, a, blockIdx.x, smem);
+    else
+        adjoint_planes(P, a, blockIdx.x / P.isplits, blockIdx.x % P.isplits, smem);
 }
 
 template <typename K>
@@ -1252,12 +1672,6 @@ bool spectral_product_plan(prony_handle_t h, int d, int n, int r, SpecPlan& P) {
     if (d <= 2) {
         const int nrb = (H + 15) / 16;
         auto lds = [&](int nb) { return 2 * 16 * kCols * (size_t)nb * line_rows(P.P); };
-        const int t0 = 16 * part + K1 - 1 - 16 * nhb, t1 = d == 2 ? 16 * part + 14 + K1 : P.NP1 - 1;
-        double2* out = a.gt + ((size_t)part * P.F + w) * P.NP1;
-        for (int x = lane; x < sn; x += 64) {
-            const int t = t0 + x;
-            if (t >= 16 * part && t <= t1 && t < P.NP1) out[t] = make_double2(sums[2 * x], sums[2 * x + 1]);
-        }
         P.nbi = nrb == 1 ? 4 : nrb <= 3 ? 2 : 1;
         while (P.nbi > 1 && lds(P.nbi) > budget) --P.nbi;
         P.lds_inv = lds(P.nbi);
@@ -1282,6 +1696,71 @@ bool spectral_product_plan(prony_handle_t h, int d, int n, int r, SpecPlan& P) {
     P.off_r = P.off_f + align_up(16 * (size_t)P.F * P.NP1, 256);
     P.ws_bytes = P.off_r + spectral_table_bytes(P);
     return P.ws_bytes <= kMaxWorkspace;
+}
+
+bool spectral_adjoint_plan(prony_handle_t h, int d, int n, int m, SpecPlan& P) {
+    if (d == 1 || !plan_forward(h, d, n, m, P)) return false;
+    const size_t budget = lds_budget(h);
+    P.lds_gram = adj_g_bytes(d, m) + kWaves * adj_wave_bytes(d, P.K1);
+    const int nkb = d == 2 ? (P.K1 + 16) / 16 : 1;
+    P.groups = (int)std::min<int64_t>(((int64_t)P.F * nkb + kWaves - 1) / kWaves, 4 * (int64_t)h->num_cus);
+    if (d == 2) {
+        P.wgs_i = (P.NP1 + kCols - 1) / kCols;
+        P.lds_inv = 2 * 16 * kCols * (size_t)line_rows(P.P + 1);
+    } else {
+        const int K = P.P + 1;
+        P.isplits = std::max((K + 15) / 16, std::min((K + 3) / 4, h->num_cus / P.NP1));
+        P.irows = (K + P.isplits - 1) / P.isplits;
+        P.isplits = (K + P.irows - 1) / P.irows;
+        P.wgs_i = P.NP1 * P.isplits;
+        P.lds_inv = 2 * 8 * (size_t)(4 * table_sizes(P.P).ks_g) * plane_stride(2 * P.irows);
+    }
+    if (P.lds_gram > budget || P.lds_inv > budget) return false;
+    const size_t x = align_up(16 * (size_t)P.F * P.K1 * m, 256);
+    P.off_v = x;
+    P.off_f = 2 * x;
+    P.off_r = P.off_f + align_up(16 * (size_t)nkb * P.F * P.NP1, 256);
+    P.ws_bytes = P.off_r + spectral_table_bytes(P);
+    return P.ws_bytes <= kMaxWorkspace;
+}
+
+prony_status_t spectral_adjoint_run(prony_handle_t h, const SpecPlan& P, unsigned char* ws, const double* U,
+                                    int64_t u_rs, int64_t u_cs, const double* sigma, const double* V, int64_t v_rs,
+                                    int64_t v_cs, const double* gS, double* gf) {
+    SpecAdjPtrs a{};
+    a.p.U = reinterpret_cast<const double2*>(U);
+    a.p.V = reinterpret_cast<const double2*>(V);
+    a.p.u_rs = u_rs;
+    a.p.u_cs = u_cs;
+    a.p.v_rs = v_rs;
+    a.p.v_cs = v_cs;
+    a.p.sigma = sigma;
+    a.p.ut = reinterpret_cast<double2*>(ws);
+    a.p.vt = reinterpret_cast<double2*>(ws + P.off_v);
+    a.p.tables = reinterpret_cast<double2*>(ws + P.off_r);
+    a.gS = reinterpret_cast<const double2*>(gS);
+    a.gt = reinterpret_cast<double2*>(ws + P.off_f);
+    a.gf = reinterpret_cast<double2*>(gf);
+    prony_status_t st = spectral_forward(h, P, a.p, true, false, true);
+    if (st != PRONY_OK) return st;
+    const bool one = P.nqb == 1;
+    if ((st = one ? allow_lds(h, &spectral_adjoint<1>, P.lds_gram) : allow_lds(h, &spectral_adjoint<2>, P.lds_gram)) !=
+        PRONY_OK)
+        return st;
+    {
+        ProfileScope prof(h, "spectral_adjoint");
+        if (one)
+            spectral_adjoint<1><<<P.groups, kThreads, P.lds_gram, h->stream>>>(P, a);
+        else
+            spectral_adjoint<2><<<P.groups, kThreads, P.lds_gram, h->stream>>>(P, a);
+    }
+    if ((st = check_launch(h, "spectral_adjoint")) != PRONY_OK) return st;
+    if ((st = allow_lds(h, &spectral_adjoint_inverse, P.lds_inv)) != PRONY_OK) return st;
+    {
+        ProfileScope prof(h, "spectral_inverse");
+        spectral_adjoint_inverse<<<P.wgs_i, kThreads, P.lds_inv, h->stream>>>(P, a);
+    }
+    return check_launch(h, "spectral_adjoint_inverse");
 }
 
 prony_status_t spectral_product(prony_handle_t h, const SpecPlan& P, unsigned char* ws, const double* f,

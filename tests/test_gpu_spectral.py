@@ -178,3 +178,36 @@ def test_products_keep_non_finite_samples_to_their_rows(d, n, r, adjoint):
     got = api.toeplitz_mm(_dev(bad), d, n, _dev(X), adjoint=adjoint).cpu().numpy()
     assert np.array_equal(np.isnan(got).any(axis=1), hit) and np.array_equal(np.isnan(got).all(axis=1), hit)
     assert_close(got[~hit], T[~hit] @ X, TOL, "rows without the NaN")
+
+
+@pytest.mark.parametrize("d,n,m", [
+    (2, 1, 1), (2, 6, 4), (2, 7, 15), (2, 14, 16), (2, 15, 17), (2, 16, 32), (2, 31, 3), (2, 33, 20),
+    (3, 1, 2), (3, 3, 16), (3, 6, 7), (3, 7, 17), (3, 8, 32), (3, 14, 9)])
+def test_adjoint_at_tile_edges(d, n, m):
+    """Row blocks of 16 lines (n + 2 rows), one and two column blocks, one to three blocks of
+    the inverse transform's points. The sums hold N m terms on the way to a point of the grid,
+    in line transforms of FP64: the error stays a small multiple of (3 n + m) 2^-53 < 1e-13."""
+    _, U, s, V = _problem(d, n, m, seed=7800 + 100 * d + n + m)
+    rng = np.random.Generator(np.random.PCG64(n))
+    gS = rng.standard_normal((d, m, m)) + 1j * rng.standard_normal((d, m, m))
+    print(f"spectral adjoint d={d} n={n} m={m}", flush=True)
+    ref = O.pencil_adjoint(gS, d, n, U, s, V)
+    got = api.build_S_adjoint(_dev(gS), d, n, _dev(U), _dev(s), _dev(V), prec="fp64")
+    assert_close(got.cpu().numpy(), ref, TOL, f"adjoint d={d} n={n} m={m}")
+    col = api.build_S_adjoint(_dev(gS), d, n, _dev(U.T).T, _dev(s), _dev(V.T).T, prec="fp64")
+    assert torch.equal(col, got)
+    assert np.all(got.cpu().numpy()[ref == 0] == 0)       # points that no T_l holds
+
+
+@pytest.mark.parametrize("d,n,m", [(2, 9, 3), (3, 4, 17)])
+def test_adjoint_keeps_non_finite_rows_to_their_points(d, n, m):
+    _, U, s, V = _problem(d, n, m, seed=7900 + n)
+    rng = np.random.Generator(np.random.PCG64(n))
+    gS = rng.standard_normal((d, m, m)) + 1j * rng.standard_normal((d, m, m))
+    ref = O.pencil_adjoint(gS, d, n, U, s, V)
+    U[1, 0] = np.nan
+    hit = np.isnan(O.pencil_adjoint(gS, d, n, U, s, V))
+    got = api.build_S_adjoint(_dev(gS), d, n, _dev(U), _dev(s), _dev(V), prec="fp64").cpu().numpy()
+    assert 0 < hit.sum() < hit.size
+    assert np.array_equal(np.isnan(got), hit)
+    assert_close(got[~hit], ref[~hit], TOL, "points without the NaN")
