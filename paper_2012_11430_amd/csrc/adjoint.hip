@@ -49,85 +49,136 @@ struct AdjPlan {
     size_t off_z, off_w, off_g, ws_bytes;
 };
 
+// Packing works in blocks, one per workgroup and turn: section 0 (Z) four units of a
+// 16-row tile and 16 columns, one per wave; section 1 (W) four 16 x 16 transposes;
+// section 2 (G(h) and the cleared gradient) kAdjSpan elements.
+constexpr int kAdjSpan = 2048;
+__host__ __device__ inline int adj_col_blocks(const AdjPlan& P) { return (P.cp + 15) >> 4; }
+__host__ __device__ inline int adj_pack_blocks(const AdjPlan& P, int section) {
+    const int kbp = P.sk * P.kc;
+    if (section == 0) return (P.rt * (P.rows / 16) * adj_col_blocks(P) + kWaves - 1) / kWaves;
+    if (section == 1) return ((kbp + 15) / 16 * adj_col_blocks(P) + 3) / 4;
+    return ((kbp > P.gsize ? kbp : P.gsize) + kAdjSpan - 1) / kAdjSpan;
+}
+
+// Z is a contraction over i (K = m per matrix l) and runs on the FP64 matrix cores: each
+// entry on its own lane read m entries of U and of gS per l through the vector caches,
+// 2.5 GB in all for 64 instances of d=2 n=47 m=16 and 112 us; here a wave reads a row tile
+// of U and a block of gS once per K step. W is read in rows of 4 columns by 16 h and
+// written in rows of 16 h (its reads were 16 bytes every row).
 template <typename T>
 __device__ __forceinline__ void adj_pack_body(const AdjPlan& P, const double2* __restrict__ U, int64_t u_rs,
                                               int64_t u_cs, const double* __restrict__ sigma,
                                               const double2* __restrict__ V, int64_t v_rs, int64_t v_cs,
                                               const double2* __restrict__ gS, pair_t<T>* __restrict__ zp,
                                               pair_t<T>* __restrict__ wp, int* __restrict__ gt,
-                                              double2* __restrict__ gf, int section) {
+                                              double2* __restrict__ gf, int section, int block, int nblocks) {
     using T2 = pair_t<T>;
-    const int stride = gridDim.x * blockDim.x;
-    const int first = blockIdx.x * blockDim.x + threadIdx.x;
-    const int kbp = P.sk * P.kc;
+    using M = Mfma<double>;
+    const int kbp = P.sk * P.kc, tid = threadIdx.x, ncb = adj_col_blocks(P);
+    const int total = adj_pack_blocks(P, section);
     if (section == 0) {
         // Z[k'][q] = sum over l (in order) of sum_i U[k'-e_l, i] gS_l[i,q] / sigma_q for
         // the l with k' - e_l in I_n; rows padded to whole tiles and columns to cp with zeros
-        const int nz = P.rt * P.rows * P.cp;
-        const int E = P.n + 2, Pn = P.n + 1;
-        for (int e = first; e < nz; e += stride) {
-            const int kr = e / P.cp, q = e - (e / P.cp) * P.cp;
-            double re = 0.0, im = 0.0;
-            if (kr < P.NR && q < P.m) {
-                int dig[3] = {0, 0, 0};
-                int rem = kr;
-                for (int l = P.d - 1; l >= 0; --l) {
+        const int lane = tid & 63, g = lane >> 4, col = lane & 15;
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int E = P.n + 2, Pn = P.n + 1, units = P.rt * (P.rows / 16) * ncb, KM = (P.m + 3) >> 2;
+        for (int b = block; b < total; b += nblocks) {
+            const int unit = kWaves * b + wave;
+            if (unit >= units) break;
+            const int tile = unit / ncb, q = 16 * (unit - tile * ncb) + col, kr = 16 * tile + col;
+            int dig[3] = {0, 0, 0}, rem = kr, idx = 0;
+#pragma unroll
+            for (int l = 2; l >= 0; --l)
+                if (l < P.d) {
                     dig[l] = rem % E;
                     rem /= E;
                 }
-                for (int ell = 0; ell < P.d; ++ell) {
-                    bool inside = dig[ell] >= 1;
-                    int idx = 0;
-                    for (int l = 0; l < P.d; ++l) {
-                        const int coord = dig[l] - (l == ell ? 1 : 0);
-                        inside = inside && coord <= P.n;
-                        idx = idx * Pn + coord;
+#pragma unroll
+            for (int l = 0; l < 3; ++l)
+                if (l < P.d) idx = idx * Pn + dig[l];
+            double zr[4] = {0.0, 0.0, 0.0, 0.0}, zi[4] = {0.0, 0.0, 0.0, 0.0};
+            int weight = 1;
+            for (int l = 1; l < P.d; ++l) weight *= Pn;
+#pragma unroll
+            for (int ell = 0; ell < 3; ++ell, weight /= Pn) {
+                if (ell >= P.d) break;
+                bool inside = kr < P.NR && dig[ell] >= 1;
+#pragma unroll
+                for (int l = 0; l < 3; ++l) inside = inside && (l >= P.d || l == ell || dig[l] <= P.n);
+                const double2* u0 = U + (int64_t)(idx - weight) * u_rs;
+                const double2* g0 = gS + (size_t)ell * P.m * P.m + q;
+                M::acc_t re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
+                for (int s = 0; s < KM; s += 4) {
+                    double2 u[4], c[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const int i = 4 * (s + k) + g;
+                        u[k] = c[k] = make_double2(0.0, 0.0);
+                        if (inside && i < P.m) u[k] = u0[i * u_cs];
+                        if (q < P.m && i < P.m) c[k] = g0[(size_t)i * P.m];
                     }
-                    if (!inside) continue;
-                    double zr = 0.0, zi = 0.0;
-                    for (int i = 0; i < P.m; ++i) {
-                        const double2 u = U[idx * u_rs + i * u_cs];
-                        const double2 gv = gS[((size_t)ell * P.m + i) * P.m + q];
-                        zr = fma(u.x, gv.x, fma(-u.y, gv.y, zr));
-                        zi = fma(u.x, gv.y, fma(u.y, gv.x, zi));
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        if (s + k >= KM) break;
+                        re = M::fma(u[k].x, c[k].x, re);
+                        im = M::fma(u[k].x, c[k].y, im);
+                        re = M::fma(-u[k].y, c[k].y, re);
+                        im = M::fma(u[k].y, c[k].x, im);
                     }
-                    re += zr;
-                    im += zi;
                 }
-                const double s = sigma[q];
-                re /= s;
-                im /= s;
+                // bit r: row r of the tile holds a term of this l
+                const unsigned rows = (unsigned)__ballot(inside);
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (rows >> M::row(g, r) & 1) {
+                        zr[r] += re[r];
+                        zi[r] += im[r];
+                    }
             }
-            zp[e] = T2{(T)re, (T)im};
+            if (q < P.cp) {
+                const double s = q < P.m ? sigma[q] : 1.0;
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    zp[(size_t)(16 * tile + M::row(g, r)) * P.cp + q] = T2{(T)(zr[r] / s), (T)(zi[r] / s)};
+            }
         }
     } else if (section == 1) {
         // W = conj(V) as (Re, Im) pairs, row q, column h
-        const int nw = P.cp * kbp;
-        for (int e = first; e < nw; e += stride) {
-            const int q = e / kbp, hx = e - (e / kbp) * kbp;
-            double wr = 0.0, wi = 0.0;
-            if (hx < P.kb && q < P.m) {
-                const double2 v = V[hx * v_rs + q * v_cs];
-                wr = v.x;
-                wi = -v.y;   // conj
+        const int tiles = (kbp + 15) / 16 * ncb;
+        for (int b = block; b < total; b += nblocks) {
+            double2 v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int t = 4 * b + k, hx = 16 * (t / ncb) + (tid & 15), q = 16 * (t % ncb) + (tid >> 4);
+                v[k] = make_double2(0.0, 0.0);
+                if (hx < P.kb && q < P.m) v[k] = V[hx * v_rs + q * v_cs];
             }
-            wp[e] = T2{(T)wr, (T)wi};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int t = 4 * b + k, hx = 16 * (t / ncb) + (tid & 15), q = 16 * (t % ncb) + (tid >> 4);
+                // conj; 0 - 0 keeps the padding +0
+                if (t < tiles && hx < kbp && q < P.cp) wp[(size_t)q * kbp + hx] = T2{(T)v[k].x, (T)(0.0 - v[k].y)};
+            }
         }
     } else {
-        for (int hx = first; hx < kbp; hx += stride)
-            gt[hx] = grid_offset_of_index(hx < P.kb ? hx : P.kb - 1, P.d, P.n);
-        for (int p = first; p < P.gsize; p += stride) gf[p] = make_double2(0.0, 0.0);
+        for (int b = block; b < total; b += nblocks)
+            for (int x = b * kAdjSpan + tid; x < (b + 1) * kAdjSpan; x += kThreads) {
+                if (x < kbp) gt[x] = grid_offset_of_index(x < P.kb ? x : P.kb - 1, P.d, P.n);
+                if (x < P.gsize) gf[x] = make_double2(0.0, 0.0);
+            }
     }
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void adjoint_pack(AdjPlan P, const double2* __restrict__ U, int64_t u_rs,
+__global__ __launch_bounds__(kThreads) void adjoint_pack(AdjPlan P, const double2* __restrict__ U, int64_t u_rs,
                                                     int64_t u_cs, const double* __restrict__ sigma,
                                                     const double2* __restrict__ V, int64_t v_rs, int64_t v_cs,
                                                     const double2* __restrict__ gS, pair_t<T>* __restrict__ zp,
                                                     pair_t<T>* __restrict__ wp, int* __restrict__ gt,
                                                     double2* __restrict__ gf) {
-    adj_pack_body<T>(P, U, u_rs, u_cs, sigma, V, v_rs, v_cs, gS, zp, wp, gt, gf, blockIdx.y);
+    adj_pack_body<T>(P, U, u_rs, u_cs, sigma, V, v_rs, v_cs, gS, zp, wp, gt, gf, blockIdx.y, blockIdx.x,
+                     gridDim.x);
 }
 
 // Two 16-row fragments per wave where the rows of Z kept in registers allow it.
@@ -284,13 +335,16 @@ struct AdjEntry {
 };
 
 template <typename T>
-__global__ __launch_bounds__(256) void adjoint_pack_batched(const AdjEntry<T>* __restrict__ entries,
+__global__ __launch_bounds__(kThreads) void adjoint_pack_batched(const AdjEntry<T>* __restrict__ entries,
+                                                            const BatchSlice* __restrict__ slices,
                                                             const double2* __restrict__ gS_all,
                                                             double2* __restrict__ gf_all) {
-    const AdjEntry<T>& e = entries[blockIdx.z];
+    const BatchSlice x = slices[blockIdx.x];
+    const AdjEntry<T>& e = entries[x.entry];
     const int m = e.P.m;
     adj_pack_body<T>(e.P, e.U, m, 1, e.sigma, e.V, m, 1, gS_all + e.gs_off, const_cast<pair_t<T>*>(e.ptr.zp),
-                     const_cast<pair_t<T>*>(e.ptr.wp), const_cast<int*>(e.ptr.gtab), gf_all + e.gf_off, blockIdx.y);
+                     const_cast<pair_t<T>*>(e.ptr.wp), const_cast<int*>(e.ptr.gtab), gf_all + e.gf_off, x.section,
+                     x.block, 1 << 30);
 }
 
 template <typename T, int KS, int RF>
@@ -404,12 +458,11 @@ prony_status_t launch_adjoint(prony_handle_t h, const AdjPlan& P, const double* 
     T2* zp = reinterpret_cast<T2*>(ws + P.off_z);
     T2* wp = reinterpret_cast<T2*>(ws + P.off_w);
     int* gt = reinterpret_cast<int*>(ws + P.off_g);
-    const int64_t largest = std::max<int64_t>({(int64_t)P.rt * P.rows * P.cp, (int64_t)P.cp * P.sk * P.kc,
-                                               (int64_t)P.gsize});
-    const int blocks = (int)std::min<int64_t>((largest + 255) / 256, 2 * (int64_t)h->num_cus);
+    const int blocks = std::min(std::max({adj_pack_blocks(P, 0), adj_pack_blocks(P, 1), adj_pack_blocks(P, 2)}),
+                                2 * h->num_cus);
     {
         ProfileScope prof(h, "adjoint_pack");
-        adjoint_pack<T><<<dim3(blocks, 3), 256, 0, h->stream>>>(
+        adjoint_pack<T><<<dim3(blocks, 3), kThreads, 0, h->stream>>>(
             P, reinterpret_cast<const double2*>(U), u_rs, u_cs, sigma, reinterpret_cast<const double2*>(V), v_rs,
             v_cs, reinterpret_cast<const double2*>(gS), zp, wp, gt, reinterpret_cast<double2*>(gf));
     }
@@ -461,7 +514,8 @@ prony_status_t launch_adj_batched_ks(prony_handle_t h, int rf, const AdjEntry<T>
 struct AdjBatch {
     void* ws = nullptr;           // device AdjEntry<T>[count] (grouped by class), then operands
     int count = 0;
-    int pack_x = 1;
+    const BatchSlice* slices = nullptr;   // device, a packing workgroup each
+    int packs = 0;
     int64_t gs_elems = 0, gf_elems = 0;   // complex elements of the concatenated gS / gf
     struct ClassLaunch {
         int ks, rf, first, count, tiles;
@@ -502,7 +556,14 @@ prony_status_t adj_batch_build(prony_handle_t h, const prony_batch_s* B, AdjBatc
         if (plans[a].rf != plans[b].rf) return plans[a].rf < plans[b].rf;
         return plans[a].nwg > plans[b].nwg;
     });
-    size_t off = align_up(sizeof(AdjEntry<T>) * (size_t)count, 256);
+    std::vector<BatchSlice> packs;
+    for (int pos = 0; pos < count; ++pos)
+        for (int section = 0; section < 3; ++section)
+            for (int b = 0; b < adj_pack_blocks(plans[order[pos]], section); ++b) packs.push_back({pos, section, b});
+    if (packs.size() > (size_t)INT32_MAX / 2)
+        return fail(h, PRONY_ENOTSUP, "prony_build_S_adjoint_batched: too many instances");
+    const size_t off_packs = align_up(sizeof(AdjEntry<T>) * (size_t)count, 256);
+    size_t off = align_up(off_packs + sizeof(BatchSlice) * packs.size(), 256);
     std::vector<size_t> base(count);
     for (int pos = 0; pos < count; ++pos) {
         base[pos] = off;
@@ -517,7 +578,6 @@ prony_status_t adj_batch_build(prony_handle_t h, const prony_batch_s* B, AdjBatc
     unsigned char* w = static_cast<unsigned char*>(A->ws);
     std::vector<AdjEntry<T>> host(count);
     int first = 0;
-    int64_t largest = 1;
     for (int pos = 0; pos < count; ++pos) {
         const int i = order[pos];
         const AdjPlan& P = plans[i];
@@ -545,12 +605,14 @@ prony_status_t adj_batch_build(prony_handle_t h, const prony_batch_s* B, AdjBatc
         cl.count += 1;
         cl.tiles = first;
         cl.lds = std::max(cl.lds, P.lds_bytes);
-        largest = std::max<int64_t>({largest, (int64_t)P.rt * P.rows * P.cp, (int64_t)P.cp * P.sk * P.kc,
-                                     (int64_t)P.gsize});
     }
     A->count = count;
-    A->pack_x = (int)std::min<int64_t>((largest + 255) / 256, 64);
+    A->slices = reinterpret_cast<const BatchSlice*>(w + off_packs);
+    A->packs = (int)packs.size();
     e = hipMemcpyAsync(A->ws, host.data(), sizeof(AdjEntry<T>) * (size_t)count, hipMemcpyHostToDevice, h->stream);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(w + off_packs, packs.data(), sizeof(BatchSlice) * packs.size(), hipMemcpyHostToDevice,
+                           h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) return hip_fail(h, e, "batch adjoint work table upload");
     return PRONY_OK;
@@ -563,7 +625,7 @@ prony_status_t adj_batch_launch(prony_handle_t h, const AdjBatch* A, const doubl
     double2* gf2 = reinterpret_cast<double2*>(gf);
     {
         ProfileScope prof(h, "adjoint_pack");
-        adjoint_pack_batched<T><<<dim3(A->pack_x, 3, A->count), 256, 0, h->stream>>>(entries, gs2, gf2);
+        adjoint_pack_batched<T><<<A->packs, kThreads, 0, h->stream>>>(entries, A->slices, gs2, gf2);
     }
     prony_status_t st = check_launch(h, "adjoint_pack_batched");
     if (st != PRONY_OK) return st;

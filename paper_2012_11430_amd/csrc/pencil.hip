@@ -215,40 +215,54 @@ __device__ __forceinline__ void pack_split(const PencilPlan& P, const double2* _
 // {0..n+1}^d (padded to whole tiles) holding U[k'] where k' lies in I_n and zero
 // elsewhere, columns padded to 16*mbi, so that U_l[k'] = U[k' - e_l] is the packed
 // row ug + k' - shift(e_l); (y = 2) the grid offsets G(h). All index arithmetic
-// fits in 32 bits (checked by the host plan).
+// fits in 32 bits (checked by the host plan). Handles elements first, first + stride, ...
+// below `last` of a section, kPackLoads loads in flight per thread.
+constexpr int kPackLoads = 4;
 template <typename T>
 __device__ __forceinline__ void pack_body(const PencilPlan& P, const double2* __restrict__ U, int64_t u_rs,
                                           int64_t u_cs, const double2* __restrict__ V, int64_t v_rs, int64_t v_cs,
                                           pair_t<T>* __restrict__ vp, pair_t<T>* __restrict__ up,
-                                          int* __restrict__ gt, int section) {
+                                          int* __restrict__ gt, int section, int first, int stride,
+                                          int last) {
     using T2 = pair_t<T>;
     const int kbp = P.sk * P.kc + kPrefetchRows;
-    const int stride = gridDim.x * blockDim.x;
-    const int first = blockIdx.x * blockDim.x + threadIdx.x;
     if (section == 0 && P.split) {
         pack_split(P, V, v_rs, v_cs, reinterpret_cast<u32x4*>(vp), first, stride);
     } else if (section == 0) {
-        const int nv = kbp * P.nrp;
-        for (int i = first; i < nv; i += stride) {
-            const int hx = i / P.nrp;
-            const int j = i - hx * P.nrp;
-            // (Re a) multiplies the first member, (Im a) the second.
-            const double2 pr = pair_of(P, V, v_rs, v_cs, hx, j);
-            vp[i] = T2{(T)pr.x, (T)pr.y};
+        const int nv = min(kbp * P.nrp, last);
+        for (int i0 = first; i0 < nv; i0 += kPackLoads * stride) {
+            double2 pr[kPackLoads];
+#pragma unroll
+            for (int k = 0; k < kPackLoads; ++k) {
+                const int i = i0 + k * stride;
+                const int hx = i / P.nrp;
+                const int j = i - hx * P.nrp;
+                // (Re a) multiplies the first member, (Im a) the second.
+                pr[k] = pair_of(P, V, v_rs, v_cs, i < nv ? hx : P.kb, j);
+            }
+#pragma unroll
+            for (int k = 0; k < kPackLoads; ++k) {
+                const int i = i0 + k * stride;
+                if (i < nv) vp[i] = T2{(T)pr[k].x, (T)pr[k].y};
+            }
         }
     } else if (section == 1) {
         if (P.mode) return;   // the product has no U^* epilogue
         const int mup = P.mbi * 16;
-        const int nu = (P.ug + P.rt * P.rows) * mup;
+        const int nu = min((P.ug + P.rt * P.rows) * mup, last);
         const int E = P.n + 2, Pn = P.n + 1;
-        for (int r = first; r < nu; r += stride) {
-            const int kr = r / mup - P.ug;   // row-extended index k'
-            const int col = r - (r / mup) * mup;
-            double ur = 0.0, ui = 0.0;
-            if (kr >= 0 && kr < P.NR && col < P.m) {
+        for (int r0 = first; r0 < nu; r0 += kPackLoads * stride) {
+            double2 u[kPackLoads];
+#pragma unroll
+            for (int k = 0; k < kPackLoads; ++k) {
+                const int r = r0 + k * stride;
+                const int kr = r / mup - P.ug;   // row-extended index k'
+                const int col = r - (r / mup) * mup;
                 int rem = kr, idx = 0, scale = 1;
-                bool inside = true;
-                for (int l = P.d - 1; l >= 0; --l) {
+                bool inside = r < nu && kr >= 0 && kr < P.NR && col < P.m;
+#pragma unroll
+                for (int l = 0; l < 3; ++l) {
+                    if (l >= P.d) break;
                     const int qq = rem / E;
                     const int coord = rem - qq * E;
                     rem = qq;
@@ -256,16 +270,17 @@ __device__ __forceinline__ void pack_body(const PencilPlan& P, const double2* __
                     idx += coord * scale;
                     scale *= Pn;
                 }
-                if (inside) {
-                    const double2 u = U[idx * u_rs + col * u_cs];
-                    ur = u.x;
-                    ui = u.y;
-                }
+                u[k] = make_double2(0.0, 0.0);
+                if (inside) u[k] = U[idx * u_rs + col * u_cs];
             }
-            up[r] = T2{(T)ur, (T)ui};
+#pragma unroll
+            for (int k = 0; k < kPackLoads; ++k) {
+                const int r = r0 + k * stride;
+                if (r < nu) up[r] = T2{(T)u[k].x, (T)u[k].y};
+            }
         }
     } else {
-        for (int hx = first; hx < kbp; hx += stride) gt[hx] = h_offset(P, hx < P.kb ? hx : P.kb - 1);
+        for (int hx = first; hx < min(kbp, last); hx += stride) gt[hx] = h_offset(P, hx < P.kb ? hx : P.kb - 1);
     }
 }
 
@@ -274,7 +289,8 @@ __global__ __launch_bounds__(256) void pencil_pack(PencilPlan P, const double2* 
                                                    int64_t u_cs, const double2* __restrict__ V, int64_t v_rs,
                                                    int64_t v_cs, pair_t<T>* __restrict__ vp, pair_t<T>* __restrict__ up,
                                                    int* __restrict__ gt) {
-    pack_body<T>(P, U, u_rs, u_cs, V, v_rs, v_cs, vp, up, gt, blockIdx.y);
+    pack_body<T>(P, U, u_rs, u_cs, V, v_rs, v_cs, vp, up, gt, blockIdx.y, blockIdx.x * blockDim.x + threadIdx.x,
+                 gridDim.x * blockDim.x, INT32_MAX);
 }
 
 
@@ -1149,16 +1165,20 @@ struct BatchEntry {
     int tile_begin;
 };
 
-// Packing for every instance of a batch: grid (x, 3, instances). The first
-// thread also resets the work counter of the queue schedule (the tile launch
+// Packing for instances of a batch, one slice of kPackSpan elements per workgroup. The
+// first thread also resets the work counter of the queue schedule (the tile launch
 // follows on the same stream).
+constexpr int kPackSpan = 1024;
 template <typename T>
 __global__ __launch_bounds__(256) void pencil_pack_batched(const BatchEntry<T>* __restrict__ entries,
+                                                           const BatchSlice* __restrict__ slices,
                                                            int* __restrict__ queue_counter) {
-    if (queue_counter && (blockIdx.x | blockIdx.y | blockIdx.z | threadIdx.x) == 0) *queue_counter = 0;
-    const BatchEntry<T>& e = entries[blockIdx.z];
+    if (queue_counter && (blockIdx.x | threadIdx.x) == 0) *queue_counter = 0;
+    const BatchSlice x = slices[blockIdx.x];
+    const BatchEntry<T>& e = entries[x.entry];
     pack_body<T>(e.P, e.U, e.P.m, 1, e.V, e.P.m, 1, const_cast<pair_t<T>*>(e.ptr.vp),
-                 const_cast<pair_t<T>*>(e.ptr.up), const_cast<int*>(e.ptr.gtab), blockIdx.y);
+                 const_cast<pair_t<T>*>(e.ptr.up), const_cast<int*>(e.ptr.gtab), x.section,
+                 x.block * kPackSpan + threadIdx.x, 256, (x.block + 1) * kPackSpan);
 }
 
 // Batched launch over the instances of one column-block class, ordered by
@@ -1357,13 +1377,13 @@ __global__ __launch_bounds__(kFinishThreads) void pencil_finish(PencilPlan P, co
                 [&](int o, double re, double im) { store_s(P, sigma, S, o, re, im); });
 }
 
-// Same for every instance of a batch: grid (slices, instances).
+// Same for instances of a batch, a slice of kFinishOuts outputs per workgroup.
 template <typename T>
-__global__ __launch_bounds__(kFinishThreads) void pencil_finish_batched(const BatchEntry<T>* __restrict__ entries) {
-    const BatchEntry<T>& e = entries[blockIdx.y];
-    const int tot = e.P.m * e.P.C;
-    if ((int)blockIdx.x * kFinishOuts >= tot) return;
-    finish_rows(e.ptr.part, e.P.nwg, tot, blockIdx.x * kFinishOuts,
+__global__ __launch_bounds__(kFinishThreads) void pencil_finish_batched(const BatchEntry<T>* __restrict__ entries,
+                                                                        const BatchSlice* __restrict__ slices) {
+    const BatchSlice x = slices[blockIdx.x];
+    const BatchEntry<T>& e = entries[x.entry];
+    finish_rows(e.ptr.part, e.P.nwg, e.P.m * e.P.C, x.block * kFinishOuts,
                 [&](int o, double re, double im) { store_s(e.P, e.ptr.sigma, e.ptr.S, o, re, im); });
 }
 
@@ -2059,7 +2079,26 @@ prony_status_t batch_build(prony_handle_t h, int count, const prony_instance_t* 
     // workspace layout: entries, queue counter, work items, then per instance vp | up | gt | part
     const size_t off_counter = align_up(sizeof(BatchEntry<T>) * (size_t)count, 256);
     const size_t off_items = off_counter + 256;
-    size_t off = align_up(off_items + sizeof(WorkItem) * nitems, 256);
+    // packing and finishing workgroups, instance by instance in the launch order
+    std::vector<BatchSlice> packs, finishes;
+    auto slice = [](std::vector<BatchSlice>& out, int entry, int section, int64_t elements, int span) {
+        for (int64_t b = 0; b * span < elements; ++b) out.push_back({entry, section, (int)b});
+    };
+    std::vector<int> pack_at(count + 1), finish_at(count + 1);
+    for (int pos = 0; pos < count; ++pos) {
+        const PencilPlan& P = plans[order[pos]];
+        const int64_t kbp = (int64_t)P.sk * P.kc + kPrefetchRows;
+        slice(packs, pos, 0, kbp * P.nrp, kPackSpan);
+        slice(packs, pos, 1, ((int64_t)P.ug + (int64_t)P.rt * P.rows) * P.mbi * 16, kPackSpan);
+        slice(packs, pos, 2, kbp, kPackSpan);
+        slice(finishes, pos, 0, (int64_t)P.m * P.C, kFinishOuts);
+        pack_at[pos + 1] = (int)packs.size();
+        finish_at[pos + 1] = (int)finishes.size();
+    }
+    if (packs.size() > (size_t)INT32_MAX / 2) return fail(h, PRONY_ENOTSUP, "prony_batch_create: too many instances");
+    const size_t off_packs = align_up(off_items + sizeof(WorkItem) * nitems, 256);
+    const size_t off_finishes = align_up(off_packs + sizeof(BatchSlice) * packs.size(), 256);
+    size_t off = align_up(off_finishes + sizeof(BatchSlice) * finishes.size(), 256);
     std::vector<BatchEntry<T>> host(count);
     std::vector<size_t> base(count);
     for (int pos = 0; pos < count; ++pos) {
@@ -2076,7 +2115,6 @@ prony_status_t batch_build(prony_handle_t h, int count, const prony_instance_t* 
     B->ws_bytes = off;
     unsigned char* w = static_cast<unsigned char*>(ws);
     int first = 0;
-    int largest = 1;
     for (int pos = 0; pos < count; ++pos) {
         const int i = order[pos];
         const PencilPlan& P = plans[i];
@@ -2096,24 +2134,22 @@ prony_status_t batch_build(prony_handle_t h, int count, const prony_instance_t* 
         const PencilPlan* prev = pos == 0 ? nullptr : &plans[order[pos - 1]];
         const bool new_class = !prev || prev->ng != P.ng || prev->nb != P.nb || prev->rf != P.rf;
         if (new_class) {
-            B->launches.push_back({P.nb, P.rf, P.ng, pos, 0, 0, 0, 0.0});
+            B->launches.push_back({P.nb, P.rf, P.ng, pos, 0, 0, 0, 0.0, pack_at[pos], 0, finish_at[pos], 0});
             first = 0;
         }
         auto& cl = B->launches.back();
+        cl.packs = pack_at[pos + 1] - cl.pack_first;
+        cl.finishes = finish_at[pos + 1] - cl.finish_first;
         E.tile_begin = first;
         first += P.nwg;
         cl.count += 1;
         cl.tiles = first;
         cl.lds = std::max(cl.lds, P.lds_bytes);
         cl.work += (double)P.nwg * P.kc * P.rf * (2 * P.nb + P.ng);   // MFMAs per K step and fragment
-        const int64_t big = std::max<int64_t>(((int64_t)P.sk * P.kc + kPrefetchRows) * P.nrp,
-                                              ((int64_t)P.ug + (int64_t)P.rt * P.rows) * P.mbi * 16);
-        largest = (int)std::max<int64_t>(largest, (big + 255) / 256);
     }
-    B->pack_x = std::min(largest, 64);
-    for (int i = 0; i < count; ++i)
-        B->finish_x = std::max(B->finish_x, (plans[i].m * plans[i].C + kFinishOuts - 1) / kFinishOuts);
     B->entries = ws;
+    B->pack_slices = reinterpret_cast<const BatchSlice*>(w + off_packs);
+    B->finish_slices = reinterpret_cast<const BatchSlice*>(w + off_finishes);
     std::vector<WorkItem> items;
     items.reserve(nitems);
     std::vector<int> by_cost(count);
@@ -2141,6 +2177,12 @@ prony_status_t batch_build(prony_handle_t h, int count, const prony_instance_t* 
     e = hipMemcpyAsync(ws, host.data(), sizeof(BatchEntry<T>) * (size_t)count, hipMemcpyHostToDevice, h->stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(w + off_items, items.data(), sizeof(WorkItem) * nitems, hipMemcpyHostToDevice, h->stream);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(w + off_packs, packs.data(), sizeof(BatchSlice) * packs.size(), hipMemcpyHostToDevice,
+                           h->stream);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(w + off_finishes, finishes.data(), sizeof(BatchSlice) * finishes.size(),
+                           hipMemcpyHostToDevice, h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) return hip_fail(h, e, "batch work table upload");
     return PRONY_OK;
@@ -2149,16 +2191,23 @@ prony_status_t batch_build(prony_handle_t h, int count, const prony_instance_t* 
 template <typename T>
 prony_status_t batch_launch(prony_handle_t h, prony_batch_s* B) {
     const BatchEntry<T>* entries = static_cast<const BatchEntry<T>*>(B->entries);
-    const bool queue = B->schedule == PRONY_SCHEDULE_QUEUE;
-    int* counter = queue ? static_cast<int*>(B->queue_counter) : nullptr;
-    {
-        ProfileScope prof(h, "pencil_pack");
-        pencil_pack_batched<T><<<dim3(B->pack_x, 3, B->count), 256, 0, h->stream>>>(entries, counter);
-    }
-    prony_status_t st = check_launch(h, "pencil_pack_batched");
-    if (st != PRONY_OK) return st;
-    if (queue) {
+    // packing and finishing of a class (or of all instances), in its stream
+    auto pack = [&](int first, int count, int* counter, hipStream_t stream) {
+        ProfileScope prof(h, "pencil_pack", stream);
+        pencil_pack_batched<T><<<count, 256, 0, stream>>>(entries, B->pack_slices + first, counter);
+        return check_launch(h, "pencil_pack_batched");
+    };
+    auto finish = [&](int first, int count, hipStream_t stream) {
+        ProfileScope prof(h, "pencil_finish", stream);
+        pencil_finish_batched<T><<<count, kFinishThreads, 0, stream>>>(entries, B->finish_slices + first);
+        return check_launch(h, "pencil_finish_batched");
+    };
+    if (B->schedule == PRONY_SCHEDULE_QUEUE) {
         if constexpr (sizeof(T) == 4) {
+            int* counter = static_cast<int*>(B->queue_counter);
+            const auto& last = B->launches.back();
+            prony_status_t st = pack(0, last.pack_first + last.packs, counter, h->stream);
+            if (st != PRONY_OK) return st;
             if (B->queue_lds > 65536) {
                 hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&pencil_tiles_queue<T>),
                                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)B->queue_lds);
@@ -2170,27 +2219,23 @@ prony_status_t batch_launch(prony_handle_t h, prony_batch_s* B) {
                     entries, static_cast<const WorkItem*>(B->queue_items), B->queue_n, counter);
             }
             if ((st = check_launch(h, "pencil_tiles_queue")) != PRONY_OK) return st;
-            ProfileScope prof(h, "pencil_finish");
-            pencil_finish_batched<T><<<dim3(B->finish_x, B->count), kFinishThreads, 0, h->stream>>>(entries);
-            return check_launch(h, "pencil_finish_batched");
+            return finish(0, last.finish_first + last.finishes, h->stream);
         } else {
             return fail(h, PRONY_ENOTSUP, "prony_build_S_batched: the queue schedule is FP32 only");
         }
     }
+    // a class's packing and finishing run in its own lane, beside the products of the others
+    // (packing is bound by memory, the products by the matrix cores)
     std::vector<double> work;
     for (const auto& cl : B->launches) work.push_back(cl.work);
-    st = launch_on_lanes(h, work, [&](int c, hipStream_t stream) {
+    return launch_on_lanes(h, work, [&](int c, hipStream_t stream) {
         const auto& cl = B->launches[c];
-        const prony_status_t s =
-            dispatch_batched<T>(h, cl.nb, cl.rf, cl.ng, entries + cl.first, cl.count, cl.tiles, cl.lds, stream);
-        return s == PRONY_OK ? check_launch(h, "pencil_tiles_batched") : s;
+        prony_status_t s = pack(cl.pack_first, cl.packs, nullptr, stream);
+        if (s != PRONY_OK) return s;
+        s = dispatch_batched<T>(h, cl.nb, cl.rf, cl.ng, entries + cl.first, cl.count, cl.tiles, cl.lds, stream);
+        if (s != PRONY_OK || (s = check_launch(h, "pencil_tiles_batched")) != PRONY_OK) return s;
+        return finish(cl.finish_first, cl.finishes, stream);
     });
-    if (st != PRONY_OK) return st;
-    {
-        ProfileScope prof(h, "pencil_finish");
-        pencil_finish_batched<T><<<dim3(B->finish_x, B->count), kFinishThreads, 0, h->stream>>>(entries);
-    }
-    return check_launch(h, "pencil_finish_batched");
 }
 
 }  // namespace
