@@ -210,7 +210,7 @@ __device__ __forceinline__ void adjoint_body(const AdjPlan& P, const AdjPtrs<T>&
     constexpr int kBuf = kPairs + 1;              // staging buffer stride: the block and one spare slot
     constexpr int kStg = (kPairs + kThreads - 1) / kThreads;   // staged pairs per thread and block
     extern __shared__ __align__(16) unsigned char smem[];
-    double* bins = reinterpret_cast<double*>(smem);
+    double* bins = reinterpret_cast<double*>(smem);      // Re of the window, then Im
     int* gt = reinterpret_cast<int*>(smem + adj_bins_bytes(P.win_cap));
     T2* wst = reinterpret_cast<T2*>(smem + adj_bins_bytes(P.win_cap) + adj_gt_bytes(P.kc));
 
@@ -246,24 +246,28 @@ __device__ __forceinline__ void adjoint_body(const AdjPlan& P, const AdjPtrs<T>&
     // two named registers rather than an array, which the compiler kept in scratch
     T2 stg0 = *wsrc(0, 0), stg1{};
     if constexpr (kStg > 1) stg1 = *wsrc(1, 0);
-    for (int i = tid; i < 2 * W; i += kThreads) bins[i] = 0.0;
+    for (int i = tid; i < W; i += kThreads) bins[i] = bins[P.win_cap + i] = 0.0;
     for (int i = tid; i < P.kc; i += kThreads) gt[i] = ptr.gtab[min(h_first + i, h_last)];
 
+    // Element r of lane group g of fragment f is row 4 RF g + 4 f + r of the wave's rows: the
+    // lanes of one atomic add then meet in a bin (rows and columns one apart share their
+    // diagonal) at most 4 / RF at a time.
+    const int krow0 = k_first + 16 * RF * wave;
+    auto row_of = [](int f, int grp, int r) { return 4 * RF * grp + 4 * f + r; };
     // A operand (rows of Z) for all K steps, kept in registers
-    const int krow0 = k_first + 16 * RF * wave + col;
     T2 a[RF][KS];
 #pragma unroll
     for (int f = 0; f < RF; ++f)
 #pragma unroll
-        for (int s = 0; s < KS; ++s) a[f][s] = ptr.zp[(size_t)(krow0 + 16 * f) * cp + 4 * s + g];
+        for (int s = 0; s < KS; ++s)
+            a[f][s] = ptr.zp[(size_t)(krow0 + row_of(f, M::group_of_row(col), M::elem_of_row(col))) * cp + 4 * s + g];
     // diagonal bin base of the rows this lane's accumulator elements hold
     int gk[RF][4];
 #pragma unroll
     for (int f = 0; f < RF; ++f)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-            gk[f][r] = rowext_offset(min(k_first + 16 * RF * wave + 16 * f + M::row(g, r), P.NR - 1), P.d, P.n) +
-                       P.c0 - lo;
+            gk[f][r] = rowext_offset(min(krow0 + row_of(f, g, r), P.NR - 1), P.d, P.n) + P.c0 - lo;
     wst[slot(0)] = stg0;
     if constexpr (kStg > 1) wst[slot(1)] = stg1;
     __syncthreads();
@@ -290,7 +294,7 @@ __device__ __forceinline__ void adjoint_body(const AdjPlan& P, const AdjPtrs<T>&
 #pragma unroll
             for (int f = 0; f < RF; ++f) acc[f][2] = M::fma(a[f][s].x + a[f][s].y, bsum, acc[f][2]);
         }
-        // element r of lane (g, col) of fragment f: row 16 f + row(g,r), column
+        // element r of lane (g, col) of fragment f: row row_of(f, g, r), column
         // h = 16 hb + col (rows past the last row of Z are zero rows: they add zeros)
         const int gh = gt[hb * kHBlock + col];
 #pragma unroll
@@ -298,9 +302,9 @@ __device__ __forceinline__ void adjoint_body(const AdjPlan& P, const AdjPtrs<T>&
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const T p1 = acc[f][0][r], p2 = acc[f][1][r], p3 = acc[f][2][r];
-                double* bin = &bins[2 * (gk[f][r] - gh)];
+                double* bin = &bins[gk[f][r] - gh];
                 atomicAdd(bin, (double)(p1 - p2));
-                atomicAdd(bin + 1, (double)(p3 - p1 - p2));
+                atomicAdd(bin + P.win_cap, (double)(p3 - p1 - p2));
             }
         // the other buffer was last read before the previous barrier
         wst[((hb + 1) & 1) * kBuf + slot(0)] = stg0;
@@ -309,7 +313,7 @@ __device__ __forceinline__ void adjoint_body(const AdjPlan& P, const AdjPtrs<T>&
     }
     double* out = reinterpret_cast<double*>(ptr.gf + lo);
     for (int i = tid; i < 2 * W; i += kThreads) {
-        const double v = bins[i];
+        const double v = bins[i & 1 ? P.win_cap + (i >> 1) : i >> 1];
         if (v != 0.0) unsafeAtomicAdd(&out[i], v);
     }
 }
