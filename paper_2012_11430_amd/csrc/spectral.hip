@@ -1807,13 +1807,16 @@ prony_status_t spectral_product(prony_handle_t h, const SpecPlan& P, unsigned ch
 // ---- batches -----------------------------------------------------------------
 
 struct SpecBatch {
-    void* ws = nullptr;          // SpecEntry[count], then the instances' workspaces
-    int count = 0;
-    int fwd_wgs = 0;
+    void* ws = nullptr;          // entries, maps, tables, then the instances' workspaces
+    // the entry of every workgroup of the forward and of the Gram launches (classes one
+    // after another), a slice per finishing workgroup
+    const int* fwd_map = nullptr;
+    const int* gram_map = nullptr;
+    const BatchSlice* finish = nullptr;
+    int fwd_wgs = 0, finishes = 0;
     size_t lds_fwd = 0;
-    int finish_x = 1;
     struct ClassLaunch {
-        int nmb, nm0, ns, first, count, wgs;
+        int nmb, nm0, ns, first, wgs;   // first workgroup in gram_map
         size_t lds;
         double work;             // products of the class
     };
@@ -1830,49 +1833,39 @@ struct SpecEntry {
     int fwd_begin, gram_begin;
 };
 
-// Last entry whose `begin` is at most id.
-template <typename Begin>
-__device__ __forceinline__ int entry_of(int id, int count, Begin begin) {
-    int lo = 0, hi = count - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (begin(mid) <= id)
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
-    return lo;
-}
-
-__global__ __launch_bounds__(kThreads) void spectral_forward_batched(const SpecEntry* __restrict__ entries, int count) {
+// A workgroup reads its entry from a table: a binary search over the entries was seven
+// loads one after another, 2 us of the 10 to 20 of a workgroup.
+__global__ __launch_bounds__(kThreads) void spectral_forward_batched(const SpecEntry* __restrict__ entries,
+                                                                     const int* __restrict__ map) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int id = blockIdx.x;
-    const SpecEntry& e = entries[entry_of(id, count, [&](int i) { return entries[i].fwd_begin; })];
-    forward_body(e.P, e.p, id - e.fwd_begin, smem);
+    const SpecEntry& e = entries[map[blockIdx.x]];
+    forward_body(e.P, e.p, blockIdx.x - e.fwd_begin, smem);
 }
 
 template <int NMB, int NM0, int NS>
-__global__ __launch_bounds__(kThreads, 2) void spectral_gram_batched(const SpecEntry* __restrict__ entries, int count) {
+__global__ __launch_bounds__(kThreads, 2) void spectral_gram_batched(const SpecEntry* __restrict__ entries,
+                                                                     const int* __restrict__ map, int first) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int id = blockIdx.x;
-    const SpecEntry& e = entries[entry_of(id, count, [&](int i) { return entries[i].gram_begin; })];
+    const int id = first + blockIdx.x;
+    const SpecEntry& e = entries[map[id]];
     const int x = id - e.gram_begin;
     gram_body<NMB, NM0, NS>(e.P, e.p, x / e.P.nqb, x % e.P.nqb, smem);
 }
 
-__global__ __launch_bounds__(kFinishThreads) void spectral_finish_batched(const SpecEntry* __restrict__ entries) {
-    const SpecEntry& e = entries[blockIdx.y];
-    if ((int)blockIdx.x * kFinishOuts >= e.P.m * e.P.ells * e.P.m) return;
-    finish_body(e.P, e.p, blockIdx.x);
+__global__ __launch_bounds__(kFinishThreads) void spectral_finish_batched(const SpecEntry* __restrict__ entries,
+                                                                          const BatchSlice* __restrict__ slices) {
+    const BatchSlice x = slices[blockIdx.x];
+    const SpecEntry& e = entries[x.entry];
+    finish_body(e.P, e.p, x.block);
 }
 
 template <int NMB, int NM0, int NS>
-prony_status_t launch_gram_batched(prony_handle_t h, const SpecEntry* entries, const SpecBatch::ClassLaunch& cl,
-                                   hipStream_t stream) {
+prony_status_t launch_gram_batched(prony_handle_t h, const SpecEntry* entries, const SpecBatch& S,
+                                   const SpecBatch::ClassLaunch& cl, hipStream_t stream) {
     const prony_status_t st = allow_lds(h, &spectral_gram_batched<NMB, NM0, NS>, cl.lds);
     if (st != PRONY_OK) return st;
     ProfileScope prof(h, "spectral_gram", stream);
-    spectral_gram_batched<NMB, NM0, NS><<<cl.wgs, kThreads, cl.lds, stream>>>(entries + cl.first, cl.count);
+    spectral_gram_batched<NMB, NM0, NS><<<cl.wgs, kThreads, cl.lds, stream>>>(entries, S.gram_map, cl.first);
     return PRONY_OK;
 }
 
@@ -1899,8 +1892,27 @@ prony_status_t spectral_batch_build(prony_handle_t h, const std::vector<prony_in
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
         return key(a) != key(b) ? key(a) > key(b) : work(a) > work(b);
     });
-    // work table, the tables of every line length, the instances' sections
-    size_t off = align_up(sizeof(SpecEntry) * (size_t)count, 256);
+    int64_t fwd_wgs = 0, gram_wgs = 0;
+    for (const SpecPlan& P : plans) {
+        fwd_wgs += P.wgs_f + 2 * (int64_t)P.wgs_x;
+        gram_wgs += (int64_t)P.groups * P.nqb;
+    }
+    if (fwd_wgs > INT32_MAX / 4 || gram_wgs > INT32_MAX / 4)
+        return fail(h, PRONY_ENOTSUP, "prony_batch_create: too many workgroups");
+    std::vector<int> maps;                  // forward, then Gram
+    std::vector<BatchSlice> finish;
+    maps.reserve((size_t)(fwd_wgs + gram_wgs));
+    for (int pos = 0; pos < count; ++pos) {
+        const SpecPlan& P = plans[order[pos]];
+        maps.insert(maps.end(), (size_t)P.wgs_f + 2 * (size_t)P.wgs_x, pos);
+        for (int b = 0; b * kFinishOuts < P.m * P.ells * P.m; ++b) finish.push_back({pos, 0, b});
+    }
+    for (int pos = 0; pos < count; ++pos)
+        maps.insert(maps.end(), (size_t)plans[order[pos]].groups * plans[order[pos]].nqb, pos);
+    // work table, maps, the tables of every line length, the instances' sections
+    const size_t off_maps = align_up(sizeof(SpecEntry) * (size_t)count, 256);
+    const size_t off_finish = align_up(off_maps + sizeof(int) * maps.size(), 256);
+    size_t off = align_up(off_finish + sizeof(BatchSlice) * finish.size(), 256);
     std::map<int, size_t> tables;
     for (const SpecPlan& P : plans)
         if (tables.emplace(P.P, off).second) off += align_up(16 * (size_t)table_sizes(P.P).total, 256);
@@ -1917,47 +1929,47 @@ prony_status_t spectral_batch_build(prony_handle_t h, const std::vector<prony_in
         delete S;
         return fail(h, PRONY_ENOMEM, std::string("batch workspace allocation failed: ") + hipGetErrorString(e));
     }
-    S->count = count;
+    unsigned char* const ws = static_cast<unsigned char*>(S->ws);
+    S->fwd_map = reinterpret_cast<const int*>(ws + off_maps);
+    S->gram_map = S->fwd_map + fwd_wgs;
+    S->finish = reinterpret_cast<const BatchSlice*>(ws + off_finish);
+    S->fwd_wgs = (int)fwd_wgs;
+    S->finishes = (int)finish.size();
     std::vector<SpecEntry> host(count);
-    int64_t fwd = 0, wgs = 0;
+    int fwd = 0, wgs = 0;
     for (int pos = 0; pos < count; ++pos) {
         const int i = order[pos];
         const SpecPlan& P = plans[i];
         const prony_instance_t& x = inst[i];
-        unsigned char* w = static_cast<unsigned char*>(S->ws) + base[pos];
+        unsigned char* w = ws + base[pos];
         SpecEntry& E = host[pos];
         E.P = P;
         E.p = SpecPtrs{reinterpret_cast<const double2*>(x.U), reinterpret_cast<const double2*>(x.V), x.m, 1, x.m, 1,
                        reinterpret_cast<const double2*>(x.f), x.sigma, reinterpret_cast<double2*>(w),
                        reinterpret_cast<double2*>(w + P.off_v), reinterpret_cast<double2*>(w + P.off_f),
                        reinterpret_cast<double2*>(w + P.off_p), reinterpret_cast<double2*>(x.S), nullptr,
-                       reinterpret_cast<const double2*>(static_cast<unsigned char*>(S->ws) + tables[P.P])};
-        E.fwd_begin = (int)fwd;
-        fwd += P.wgs_f + 2 * (int64_t)P.wgs_x;
-        if (pos == 0 || key(order[pos - 1]) != key(i)) {
-            S->launches.push_back({P.nmb, P.nm0, P.ns, pos, 0, 0, 0, 0.0});
-            wgs = 0;
-        }
+                       reinterpret_cast<const double2*>(ws + tables[P.P])};
+        E.fwd_begin = fwd;
+        fwd += P.wgs_f + 2 * P.wgs_x;
+        if (pos == 0 || key(order[pos - 1]) != key(i)) S->launches.push_back({P.nmb, P.nm0, P.ns, wgs, 0, 0, 0.0});
         auto& cl = S->launches.back();
-        E.gram_begin = (int)wgs;
-        wgs += (int64_t)P.groups * P.nqb;
-        cl.count += 1;
-        cl.wgs = (int)wgs;
+        E.gram_begin = wgs;
+        wgs += P.groups * P.nqb;
+        cl.wgs = wgs - cl.first;
         cl.lds = std::max(cl.lds, P.lds_gram);
         cl.work += work(i);
         S->lds_fwd = std::max(S->lds_fwd, P.lds_fwd);
-        S->finish_x = std::max(S->finish_x, (P.m * P.ells * P.m + kFinishOuts - 1) / kFinishOuts);
-        if (fwd > INT32_MAX || wgs > INT32_MAX) {
-            (void)spectral_batch_free(S);
-            return fail(h, PRONY_ENOTSUP, "prony_batch_create: too many workgroups");
-        }
     }
-    S->fwd_wgs = (int)fwd;
     for (const auto& t : tables)
-        fill_tables(h, t.first, reinterpret_cast<double2*>(static_cast<unsigned char*>(S->ws) + t.second));
+        fill_tables(h, t.first, reinterpret_cast<double2*>(ws + t.second));
     e = hipGetLastError();
     if (e == hipSuccess)
-        e = hipMemcpyAsync(S->ws, host.data(), sizeof(SpecEntry) * (size_t)count, hipMemcpyHostToDevice, h->stream);
+        e = hipMemcpyAsync(ws, host.data(), sizeof(SpecEntry) * (size_t)count, hipMemcpyHostToDevice, h->stream);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(ws + off_maps, maps.data(), sizeof(int) * maps.size(), hipMemcpyHostToDevice, h->stream);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(ws + off_finish, finish.data(), sizeof(BatchSlice) * finish.size(), hipMemcpyHostToDevice,
+                           h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) {
         (void)spectral_batch_free(S);
@@ -1973,7 +1985,7 @@ prony_status_t spectral_batch_launch(prony_handle_t h, const SpecBatch* S) {
     if (st != PRONY_OK) return st;
     {
         ProfileScope prof(h, "spectral_forward");
-        spectral_forward_batched<<<S->fwd_wgs, kThreads, S->lds_fwd, h->stream>>>(entries, S->count);
+        spectral_forward_batched<<<S->fwd_wgs, kThreads, S->lds_fwd, h->stream>>>(entries, S->fwd_map);
     }
     if ((st = check_launch(h, "spectral_forward_batched")) != PRONY_OK) return st;
     std::vector<double> work;
@@ -1984,7 +1996,7 @@ prony_status_t spectral_batch_launch(prony_handle_t h, const SpecBatch* S) {
         switch (cl.nmb * 16 + cl.nm0 * 4 + cl.ns) {
 #define PRONY_CASE(B, B0, K)                                          \
     case B * 16 + B0 * 4 + K:                                         \
-        s = launch_gram_batched<B, B0, K>(h, entries, cl, stream);    \
+        s = launch_gram_batched<B, B0, K>(h, entries, *S, cl, stream);    \
         break;
             PRONY_GRAM_CASES(PRONY_CASE)
 #undef PRONY_CASE
@@ -1996,7 +2008,7 @@ prony_status_t spectral_batch_launch(prony_handle_t h, const SpecBatch* S) {
     if (st != PRONY_OK) return st;
     {
         ProfileScope prof(h, "pencil_finish");
-        spectral_finish_batched<<<dim3(S->finish_x, S->count), kFinishThreads, 0, h->stream>>>(entries);
+        spectral_finish_batched<<<S->finishes, kFinishThreads, 0, h->stream>>>(entries, S->finish);
     }
     return check_launch(h, "spectral_finish_batched");
 }
