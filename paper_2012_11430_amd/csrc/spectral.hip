@@ -1529,7 +1529,7 @@ namespace {
 size_t lds_budget(prony_handle_t h) { return std::min<size_t>(h->lds_per_block, 80 * 1024); }
 
 // Geometry and forward transforms of a plan with m columns per factor.
-bool plan_forward(prony_handle_t h, int d, int n, int m, SpecPlan& P) {
+bool plan_forward(prony_handle_t h, int d, int n, int m, SpecPlan& P, bool batched = false) {
     P = SpecPlan{};
     P.d = d;
     P.n = n;
@@ -1553,6 +1553,10 @@ bool plan_forward(prony_handle_t h, int d, int n, int m, SpecPlan& P) {
     P.npb = (P.P + 15) / 16;
     P.nqb = (m + 15) / 16;
     const size_t budget = lds_budget(h);
+    // LDS that a block count is chosen for: members of a batch share their launch, whose
+    // workgroups all take the LDS of the largest (96 uneven instances: 56 us with 72 KB,
+    // 47.5 with 54 KB, 48 with 40 KB, 50 with 27 KB)
+    const size_t want = batched ? std::min<size_t>(budget, 40960) : budget;
     if (d <= 2) {
         // column blocks per workgroup so that its items (a block of pairs against up to two
         // column blocks) occupy the four waves
@@ -1560,9 +1564,9 @@ bool plan_forward(prony_handle_t h, int d, int n, int m, SpecPlan& P) {
         auto lds = [&](int nb, bool grid) {
             return 2 * 16 * kCols * (size_t)nb * line_rows(folded_points(P.P, grid));
         };
-        while (P.nbw > 1 && lds(P.nbw, false) > budget) --P.nbw;
+        while (P.nbw > 1 && lds(P.nbw, false) > want) --P.nbw;
         P.nbwf = P.nbw;
-        while (P.nbwf > 1 && lds(P.nbwf, true) > budget) --P.nbwf;
+        while (P.nbwf > 1 && lds(P.nbwf, true) > want) --P.nbwf;
         P.lds_fwd = std::max(lds(P.nbw, false), lds(P.nbwf, true));
         auto wgs = [&](int64_t cols, int nb) { return (int)(((cols + kCols - 1) / kCols + nb - 1) / nb); };
         P.wgs_x = wgs((int64_t)P.K1 * m, P.nbw);
@@ -1572,9 +1576,12 @@ bool plan_forward(prony_handle_t h, int d, int n, int m, SpecPlan& P) {
         auto lds = [&](int nq, int J) { return 8 * (size_t)(J + 1) * plane_stride(2 * std::min(P.P, 16) * nq); };
         for (P.nq = std::min(m, kCols); P.nq > 0; P.nq /= 2) {
             P.lds_fwd = std::max(lds(P.nq, P.P), lds(1, P.L));
-            if (P.lds_fwd <= budget) break;
+            if (P.lds_fwd <= (P.nq > 1 ? want : budget)) break;
         }
         if (P.nq == 0) return false;
+        // a single instance takes narrower workgroups rather than leave half the CUs idle
+        auto count = [&](int nq) { return (2 * P.K1 * ((m + nq - 1) / nq) + P.NP1) * P.npb; };
+        while (!batched && P.nq > 2 && 2 * count(P.nq) <= h->num_cus) P.nq /= 2;
         P.splits = P.npb;
         P.wgs_x = P.K1 * ((m + P.nq - 1) / P.nq) * P.splits;
         P.wgs_f = P.NP1 * P.splits;
@@ -1636,7 +1643,7 @@ prony_status_t spectral_reserve(prony_handle_t h, int d_max, int n_max) {
 size_t spectral_table_bytes(const SpecPlan& P) { return align_up(16 * (size_t)table_sizes(P.P).total, 256); }
 
 bool spectral_plan(prony_handle_t h, int d, int n, int m, bool s0, SpecPlan& P, bool batched) {
-    if (!plan_forward(h, d, n, m, P)) return false;
+    if (!plan_forward(h, d, n, m, P, batched)) return false;
     P.s0 = s0 ? 1 : 0;
     P.ells = d + P.s0;
     P.nmb = ((d >= 2 ? 2 * m : m) + 15) / 16;
