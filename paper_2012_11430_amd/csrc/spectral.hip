@@ -1567,8 +1567,12 @@ bool plan_forward(prony_handle_t h, int d, int n, int m, SpecPlan& P, bool batch
         while (P.nbw > 1 && lds(P.nbw, false) > want) --P.nbw;
         P.nbwf = P.nbw;
         while (P.nbwf > 1 && lds(P.nbwf, true) > want) --P.nbwf;
-        P.lds_fwd = std::max(lds(P.nbw, false), lds(P.nbwf, true));
         auto wgs = [&](int64_t cols, int nb) { return (int)(((cols + kCols - 1) / kCols + nb - 1) / nb); };
+        // a single instance takes narrower workgroups rather than leave half the CUs idle
+        auto count = [&](int nb, int nbf) { return 2 * wgs((int64_t)P.K1 * m, nb) + wgs(P.NP1, nbf); };
+        while (!batched && P.nbw > 1 && 2 * count((P.nbw + 1) / 2, P.nbwf) <= h->num_cus) P.nbw = (P.nbw + 1) / 2;
+        while (!batched && P.nbwf > 1 && 2 * count(P.nbw, (P.nbwf + 1) / 2) <= h->num_cus) P.nbwf = (P.nbwf + 1) / 2;
+        P.lds_fwd = std::max(lds(P.nbw, false), lds(P.nbwf, true));
         P.wgs_x = wgs((int64_t)P.K1 * m, P.nbw);
         P.wgs_f = wgs(P.NP1, P.nbwf);
     } else {
