@@ -1,0 +1,36 @@
+"""Gram matrix and right-hand side in one launch (per-axis sums) at the edges of its range
+and just past them (the tiled launches): one point more than a run of powers, the largest
+line, the largest N, m below and above a workgroup's sums. Against the oracle's dense
+products; tolerance 1e-12 as for the tiled form: the sums hold at most N = 16384 terms of
+modulus about 1, each with a relative error of at most (n + d) 2^-52 from its powers, so the
+error stays below 2048 x 2^-52 x 2 = 9e-13 of the entry's scale even without cancellation
+of signs. With A^T asked for, the tiled launches give the same products."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import prony_oracle as O
+from paper_2012_11430_amd import api
+from tests._close import assert_close
+
+pytestmark = pytest.mark.gpu
+
+DEV = torch.device("cuda:0")
+
+
+@pytest.mark.parametrize("d,n,m", [(1, 7, 2), (1, 8, 9), (1, 2047, 5), (1, 2048, 3), (2, 1, 4), (2, 63, 20), (2, 127, 64),
+                                   (2, 128, 2), (3, 7, 33), (3, 24, 11), (3, 25, 2)])
+def test_box_sums_match_oracle(d, n, m):
+    rng = np.random.Generator(np.random.PCG64(100 * d + n + m))
+    z = np.exp(2j * np.pi * rng.random((m, d))) * (1 + 1e-4 * rng.standard_normal((m, d)))
+    G = (2 * n + 2) ** d
+    grid = rng.standard_normal(G) + 1j * rng.standard_normal(G)
+    print(f"coeffs d={d} n={n} m={m}", flush=True)
+    gram_ref, rhs_ref = O.coefficient_products(z, grid, d, n)
+    zd, fd = (torch.from_numpy(x).to(DEV) for x in (z, grid))
+    gram, rhs = api.coeffs(zd, fd, d, n)
+    assert_close(gram.cpu().numpy(), gram_ref, 1e-12, "Gram")
+    assert_close(rhs.cpu().numpy(), rhs_ref, 1e-12, "rhs")
+    tiled, rhs_tiled, _ = api.coeffs(zd, fd, d, n, want_AT=True)
+    assert_close(gram.cpu().numpy(), tiled.cpu().numpy(), 1e-12, "Gram, tiled")
+    assert_close(rhs.cpu().numpy(), rhs_tiled.cpu().numpy(), 1e-12, "rhs, tiled")
