@@ -526,11 +526,13 @@ struct AdjBatch {
         size_t lds;
     };
     std::vector<ClassLaunch> launches;
+    SpecAdjBatch* spec = nullptr;   // FP64 in line-spectral form: replaces the tiles above
 };
 
 prony_status_t adj_batch_free(AdjBatch* a) {
     prony_status_t st = PRONY_OK;
     if (a->ws && hipFree(a->ws) != hipSuccess) st = PRONY_EHIP;
+    if (a->spec && spectral_adjoint_batch_free(a->spec) != PRONY_OK) st = PRONY_EHIP;
     delete a;
     return st;
 }
@@ -551,6 +553,12 @@ prony_status_t adj_batch_build(prony_handle_t h, const prony_batch_s* B, AdjBatc
         A->gs_elems += (int64_t)x.d * x.m * x.m;
         gf_off[i] = A->gf_elems;
         A->gf_elems += plans[i].gsize;
+    }
+    // FP64 in line-spectral form where every instance fits it and its memory can be had
+    if constexpr (sizeof(T) == 8) {
+        const prony_status_t st = spectral_adjoint_batch_build(h, B->inst, gs_off, gf_off, &A->spec);
+        if (st == PRONY_OK || st == PRONY_EHIP) return st;
+        h->err.clear();
     }
     // classes by (K steps, fragments); inside a class, most workgroups first
     std::vector<int> order(count);
@@ -624,6 +632,7 @@ prony_status_t adj_batch_build(prony_handle_t h, const prony_batch_s* B, AdjBatc
 
 template <typename T>
 prony_status_t adj_batch_launch(prony_handle_t h, const AdjBatch* A, const double* gS, double* gf) {
+    if (A->spec) return spectral_adjoint_batch_launch(h, A->spec, gS, gf);
     const AdjEntry<T>* entries = static_cast<const AdjEntry<T>*>(A->ws);
     const double2* gs2 = reinterpret_cast<const double2*>(gS);
     double2* gf2 = reinterpret_cast<double2*>(gf);

@@ -87,9 +87,17 @@ prony_status_t spectral_product(prony_handle_t h, const SpecPlan& P, unsigned ch
                                 const double* X, int64_t ldx, bool adjoint, double* Y, int64_t ldy);
 
 // Plan of an FP64 adjoint (d >= 2; the workspace: U~ | V~ | g~ | tables), and the adjoint.
-bool spectral_adjoint_plan(prony_handle_t h, int d, int n, int m, SpecPlan& P);
+bool spectral_adjoint_plan(prony_handle_t h, int d, int n, int m, SpecPlan& P, bool batched = false);
 prony_status_t spectral_adjoint_run(prony_handle_t h, const SpecPlan& P, unsigned char* ws, const double* U,
                                     int64_t u_rs, int64_t u_cs, const double* sigma, const double* V, int64_t v_rs,
                                     int64_t v_cs, const double* gS, double* gf);
+
+// FP64 adjoints of a batch (every instance with d >= 2; else as spectral_batch_build).
+struct SpecAdjBatch;
+prony_status_t spectral_adjoint_batch_build(prony_handle_t h, const std::vector<prony_instance_t>& inst,
+                                            const std::vector<int64_t>& gs_off, const std::vector<int64_t>& gf_off,
+                                            SpecAdjBatch** out);
+prony_status_t spectral_adjoint_batch_launch(prony_handle_t h, const SpecAdjBatch* S, const double* gS, double* gf);
+prony_status_t spectral_adjoint_batch_free(SpecAdjBatch* b);
 
 }  // namespace prony

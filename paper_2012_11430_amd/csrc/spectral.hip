@@ -1709,18 +1709,20 @@ bool spectral_product_plan(prony_handle_t h, int d, int n, int r, SpecPlan& P) {
     return P.ws_bytes <= kMaxWorkspace;
 }
 
-bool spectral_adjoint_plan(prony_handle_t h, int d, int n, int m, SpecPlan& P) {
-    if (d == 1 || !plan_forward(h, d, n, m, P)) return false;
+bool spectral_adjoint_plan(prony_handle_t h, int d, int n, int m, SpecPlan& P, bool batched) {
+    if (d == 1 || !plan_forward(h, d, n, m, P, batched)) return false;
     const size_t budget = lds_budget(h);
     P.lds_gram = adj_g_bytes(d, m) + kWaves * adj_wave_bytes(d, P.K1);
     const int nkb = d == 2 ? (P.K1 + 16) / 16 : 1;
-    P.groups = (int)std::min<int64_t>(((int64_t)P.F * nkb + kWaves - 1) / kWaves, 4 * (int64_t)h->num_cus);
+    // a wave of a batch member takes about four units (the staging of G is per workgroup)
+    const int units = kWaves * (batched ? 4 : 1);
+    P.groups = (int)std::min<int64_t>(((int64_t)P.F * nkb + units - 1) / units, 4 * (int64_t)h->num_cus);
     if (d == 2) {
         P.wgs_i = (P.NP1 + kCols - 1) / kCols;
         P.lds_inv = 2 * 16 * kCols * (size_t)line_rows(P.P + 1);
     } else {
         const int K = P.P + 1;
-        P.isplits = std::max((K + 15) / 16, std::min((K + 3) / 4, h->num_cus / P.NP1));
+        P.isplits = std::max((K + 15) / 16, batched ? 1 : std::min((K + 3) / 4, h->num_cus / P.NP1));
         P.irows = (K + P.isplits - 1) / P.isplits;
         P.isplits = (K + P.irows - 1) / P.irows;
         P.wgs_i = P.NP1 * P.isplits;
@@ -2022,6 +2024,205 @@ prony_status_t spectral_batch_launch(prony_handle_t h, const SpecBatch* S) {
         spectral_finish_batched<<<S->finishes, kFinishThreads, 0, h->stream>>>(entries, S->finish);
     }
     return check_launch(h, "spectral_finish_batched");
+}
+
+// ---- batched adjoints --------------------------------------------------------
+
+struct SpecAdjBatch {
+    void* ws = nullptr;          // entries, maps, tables, then the instances' workspaces
+    const int *fwd_map = nullptr, *adj_map = nullptr, *inv_map = nullptr;   // entry of every workgroup
+    int fwd_wgs = 0, inv_wgs = 0;
+    size_t lds_fwd = 0, lds_inv = 0;
+    struct ClassLaunch {
+        int nqb, first, wgs;     // first workgroup in adj_map
+        size_t lds;
+    };
+    std::vector<ClassLaunch> launches;
+};
+
+namespace {
+
+struct SpecAdjEntry {
+    SpecPlan P;
+    SpecAdjPtrs a;               // gS and gf from the call
+    int64_t gs_off, gf_off;
+    int fwd_begin, adj_begin, inv_begin;
+};
+
+__global__ __launch_bounds__(kThreads) void spectral_adjoint_forward_batched(const SpecAdjEntry* __restrict__ entries,
+                                                                             const int* __restrict__ map) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const SpecAdjEntry& e = entries[map[blockIdx.x]];
+    forward_body(e.P, e.a.p, blockIdx.x - e.fwd_begin + e.P.wgs_f, smem);
+}
+
+template <int NQB>
+__global__ __launch_bounds__(kThreads) void spectral_adjoint_batched(const SpecAdjEntry* __restrict__ entries,
+                                                                     const int* __restrict__ map, int first,
+                                                                     const double2* __restrict__ gS) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int id = first + blockIdx.x;
+    const SpecAdjEntry& e = entries[map[id]];
+    SpecAdjPtrs a = e.a;
+    a.gS = gS + e.gs_off;
+    adjoint_body<NQB>(e.P, a, id - e.adj_begin, e.P.groups, smem);
+}
+
+__global__ __launch_bounds__(kThreads) void spectral_adjoint_inverse_batched(const SpecAdjEntry* __restrict__ entries,
+                                                                             const int* __restrict__ map,
+                                                                             const double2* __restrict__ gS,
+                                                                             double2* __restrict__ gf) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const SpecAdjEntry& e = entries[map[blockIdx.x]];
+    SpecAdjPtrs a = e.a;
+    a.gS = gS + e.gs_off;
+    a.gf = gf + e.gf_off;
+    const int x = blockIdx.x - e.inv_begin;
+    if (e.P.d == 2)
+        adjoint_lines(e.P, a, x, smem);
+    else
+        adjoint_planes(e.P, a, x / e.P.isplits, x % e.P.isplits, smem);
+}
+
+}  // namespace
+
+prony_status_t spectral_adjoint_batch_free(SpecAdjBatch* b) {
+    const prony_status_t st = b->ws && hipFree(b->ws) != hipSuccess ? PRONY_EHIP : PRONY_OK;
+    delete b;
+    return st;
+}
+
+prony_status_t spectral_adjoint_batch_build(prony_handle_t h, const std::vector<prony_instance_t>& inst,
+                                            const std::vector<int64_t>& gs_off, const std::vector<int64_t>& gf_off,
+                                            SpecAdjBatch** out) {
+    const int count = (int)inst.size();
+    std::vector<SpecPlan> plans(count);
+    int64_t fwd_wgs = 0, adj_wgs = 0, inv_wgs = 0;
+    for (int i = 0; i < count; ++i) {
+        SpecPlan& P = plans[i];
+        if (!spectral_adjoint_plan(h, inst[i].d, inst[i].n, inst[i].m, P, true))
+            return fail(h, PRONY_ENOTSUP, "an instance does not fit the line-spectral form");
+        fwd_wgs += 2 * (int64_t)P.wgs_x;
+        adj_wgs += P.groups;
+        inv_wgs += P.wgs_i;
+    }
+    if (std::max({fwd_wgs, adj_wgs, inv_wgs}) > INT32_MAX / 4)
+        return fail(h, PRONY_ENOTSUP, "prony_build_S_adjoint_batched: too many workgroups");
+    // classes by column blocks, the largest instances first
+    std::vector<int> order(count);
+    for (int i = 0; i < count; ++i) order[i] = i;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+        return plans[a].nqb != plans[b].nqb ? plans[a].nqb > plans[b].nqb
+                                            : plans[a].groups * plans[a].m > plans[b].groups * plans[b].m;
+    });
+    std::vector<int> maps;
+    maps.reserve((size_t)(fwd_wgs + adj_wgs + inv_wgs));
+    for (int pos = 0; pos < count; ++pos) maps.insert(maps.end(), 2 * (size_t)plans[order[pos]].wgs_x, pos);
+    for (int pos = 0; pos < count; ++pos) maps.insert(maps.end(), (size_t)plans[order[pos]].groups, pos);
+    for (int pos = 0; pos < count; ++pos) maps.insert(maps.end(), (size_t)plans[order[pos]].wgs_i, pos);
+    const size_t off_maps = align_up(sizeof(SpecAdjEntry) * (size_t)count, 256);
+    size_t off = align_up(off_maps + sizeof(int) * maps.size(), 256);
+    std::map<int, size_t> tables;
+    for (const SpecPlan& P : plans)
+        if (tables.emplace(P.P, off).second) off += align_up(16 * (size_t)table_sizes(P.P).total, 256);
+    std::vector<size_t> base(count);
+    for (int pos = 0; pos < count; ++pos) {
+        base[pos] = off;
+        off += plans[order[pos]].off_r;
+    }
+    SpecAdjBatch* S = new (std::nothrow) SpecAdjBatch;
+    if (!S) return fail(h, PRONY_ENOMEM, "prony_build_S_adjoint_batched: out of host memory");
+    hipError_t e = hipMalloc(&S->ws, off);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        delete S;
+        return fail(h, PRONY_ENOMEM, std::string("batch workspace allocation failed: ") + hipGetErrorString(e));
+    }
+    unsigned char* const ws = static_cast<unsigned char*>(S->ws);
+    S->fwd_map = reinterpret_cast<const int*>(ws + off_maps);
+    S->adj_map = S->fwd_map + fwd_wgs;
+    S->inv_map = S->adj_map + adj_wgs;
+    S->fwd_wgs = (int)fwd_wgs;
+    S->inv_wgs = (int)inv_wgs;
+    std::vector<SpecAdjEntry> host(count);
+    int fwd = 0, adj = 0, inv = 0;
+    for (int pos = 0; pos < count; ++pos) {
+        const int i = order[pos];
+        const SpecPlan& P = plans[i];
+        const prony_instance_t& x = inst[i];
+        unsigned char* w = ws + base[pos];
+        SpecAdjEntry& E = host[pos];
+        E.P = P;
+        E.a = SpecAdjPtrs{};
+        E.a.p.U = reinterpret_cast<const double2*>(x.U);
+        E.a.p.V = reinterpret_cast<const double2*>(x.V);
+        E.a.p.u_rs = E.a.p.v_rs = x.m;
+        E.a.p.u_cs = E.a.p.v_cs = 1;
+        E.a.p.sigma = x.sigma;
+        E.a.p.ut = reinterpret_cast<double2*>(w);
+        E.a.p.vt = reinterpret_cast<double2*>(w + P.off_v);
+        E.a.p.tab = reinterpret_cast<const double2*>(ws + tables[P.P]);
+        E.a.gt = reinterpret_cast<double2*>(w + P.off_f);
+        E.gs_off = gs_off[i];
+        E.gf_off = gf_off[i];
+        E.fwd_begin = fwd;
+        E.adj_begin = adj;
+        E.inv_begin = inv;
+        if (pos == 0 || plans[order[pos - 1]].nqb != P.nqb) S->launches.push_back({P.nqb, adj, 0, 0});
+        auto& cl = S->launches.back();
+        fwd += 2 * P.wgs_x;
+        adj += P.groups;
+        inv += P.wgs_i;
+        cl.wgs = adj - cl.first;
+        cl.lds = std::max(cl.lds, P.lds_gram);
+        S->lds_fwd = std::max(S->lds_fwd, P.lds_fwd);
+        S->lds_inv = std::max(S->lds_inv, P.lds_inv);
+    }
+    for (const auto& t : tables) fill_tables(h, t.first, reinterpret_cast<double2*>(ws + t.second));
+    e = hipGetLastError();
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(ws, host.data(), sizeof(SpecAdjEntry) * (size_t)count, hipMemcpyHostToDevice, h->stream);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(ws + off_maps, maps.data(), sizeof(int) * maps.size(), hipMemcpyHostToDevice, h->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+    if (e != hipSuccess) {
+        (void)spectral_adjoint_batch_free(S);
+        return hip_fail(h, e, "batch adjoint work table upload");
+    }
+    *out = S;
+    return PRONY_OK;
+}
+
+prony_status_t spectral_adjoint_batch_launch(prony_handle_t h, const SpecAdjBatch* S, const double* gS, double* gf) {
+    const SpecAdjEntry* entries = static_cast<const SpecAdjEntry*>(S->ws);
+    const double2* gs2 = reinterpret_cast<const double2*>(gS);
+    prony_status_t st = allow_lds(h, &spectral_adjoint_forward_batched, S->lds_fwd);
+    if (st != PRONY_OK) return st;
+    {
+        ProfileScope prof(h, "spectral_forward");
+        spectral_adjoint_forward_batched<<<S->fwd_wgs, kThreads, S->lds_fwd, h->stream>>>(entries, S->fwd_map);
+    }
+    if ((st = check_launch(h, "spectral_adjoint_forward_batched")) != PRONY_OK) return st;
+    for (const auto& cl : S->launches) {
+        st = cl.nqb == 1 ? allow_lds(h, &spectral_adjoint_batched<1>, cl.lds)
+                         : allow_lds(h, &spectral_adjoint_batched<2>, cl.lds);
+        if (st != PRONY_OK) return st;
+        {
+            ProfileScope prof(h, "spectral_adjoint");
+            if (cl.nqb == 1)
+                spectral_adjoint_batched<1><<<cl.wgs, kThreads, cl.lds, h->stream>>>(entries, S->adj_map, cl.first, gs2);
+            else
+                spectral_adjoint_batched<2><<<cl.wgs, kThreads, cl.lds, h->stream>>>(entries, S->adj_map, cl.first, gs2);
+        }
+        if ((st = check_launch(h, "spectral_adjoint_batched")) != PRONY_OK) return st;
+    }
+    if ((st = allow_lds(h, &spectral_adjoint_inverse_batched, S->lds_inv)) != PRONY_OK) return st;
+    {
+        ProfileScope prof(h, "spectral_inverse");
+        spectral_adjoint_inverse_batched<<<S->inv_wgs, kThreads, S->lds_inv, h->stream>>>(
+            entries, S->inv_map, gs2, reinterpret_cast<double2*>(gf));
+    }
+    return check_launch(h, "spectral_adjoint_inverse_batched");
 }
 
 // ---- single instances --------------------------------------------------------

@@ -211,3 +211,21 @@ def test_adjoint_keeps_non_finite_rows_to_their_points(d, n, m):
     assert 0 < hit.sum() < hit.size
     assert np.array_equal(np.isnan(got), hit)
     assert_close(got[~hit], ref[~hit], TOL, "points without the NaN")
+
+
+@pytest.mark.parametrize("shapes", [
+    [(2, 7, 4), (2, 33, 20), (3, 4, 17), (2, 1, 1), (3, 8, 32), (2, 15, 16)],
+    [(2, 9, 5), (1, 60, 7), (3, 3, 3)],       # d = 1: the tile kernels
+])
+def test_fp64_batched_adjoints_match_the_oracle(shapes):
+    probs = [_problem(d, n, m, seed=8100 + 10 * d + n) for d, n, m in shapes]
+    rng = np.random.Generator(np.random.PCG64(3))
+    gS = [rng.standard_normal((d, m, m)) + 1j * rng.standard_normal((d, m, m)) for d, n, m in shapes]
+    batch = api.Batch([(d, n, _dev(f), _dev(U), _dev(s), _dev(V)) for (d, n, m), (f, U, s, V) in zip(shapes, probs)],
+                      prec="fp64")
+    print(f"batched adjoint {shapes}", flush=True)
+    for scale in (1.0, -2.0):                 # the second call reuses the batch's plan
+        got = batch.adjoint(_dev(np.concatenate([scale * g.reshape(-1) for g in gS])))
+        for (d, n, m), (f, U, s, V), g, x in zip(shapes, probs, gS, torch.split(got, batch.gf_sizes)):
+            assert_close(x.cpu().numpy(), scale * O.pencil_adjoint(g, d, n, U, s, V), TOL, f"d={d} n={n} m={m}")
+    batch.close()
