@@ -1369,11 +1369,11 @@ prony_status_t make_plan(prony_handle_t h, int d, int n, int m, bool with_s0, si
 }
 
 // Sum of the workgroup partials (reduce.h) and Sigma^{-1}: S_l(i, q) = sum / sigma_q.
-template <typename T>
-__global__ __launch_bounds__(kFinishThreads) void pencil_finish(PencilPlan P, const pair_t<T>* __restrict__ part,
+template <typename T, int Threads>
+__global__ __launch_bounds__(Threads) void pencil_finish(PencilPlan P, const pair_t<T>* __restrict__ part,
                                                                 const double* __restrict__ sigma,
                                                                 double2* __restrict__ S) {
-    finish_rows(part, P.nwg, P.m * P.C, blockIdx.x * kFinishOuts,
+    finish_rows<Threads>(part, P.nwg, P.m * P.C, blockIdx.x * kFinishOuts,
                 [&](int o, double re, double im) { store_s(P, sigma, S, o, re, im); });
 }
 
@@ -1583,7 +1583,10 @@ prony_status_t launch_tiles_finish(prony_handle_t h, const PencilPlan& P, const 
     {
         ProfileScope prof(h, "pencil_finish");
         const int tot = P.m * P.C;
-        pencil_finish<T><<<(tot + kFinishOuts - 1) / kFinishOuts, kFinishThreads, 0, h->stream>>>(
+        const int wgs = (tot + kFinishOuts - 1) / kFinishOuts;
+        auto* kernel = finish_threads(P.nwg) == kFinishThreads ? &pencil_finish<T, kFinishThreads>
+                                                               : &pencil_finish<T, kFinishThreadsMany>;
+        kernel<<<wgs, finish_threads(P.nwg), 0, h->stream>>>(
             P, part, sigma, reinterpret_cast<double2*>(S));
     }
     return check_launch(h, "pencil_finish");
