@@ -1821,19 +1821,13 @@ prony_status_t spectral_product(prony_handle_t h, const SpecPlan& P, unsigned ch
 
 struct SpecBatch {
     void* ws = nullptr;          // entries, maps, tables, then the instances' workspaces
-    // the entry of every workgroup of the forward and of the Gram launches (classes one
-    // after another), a slice per finishing workgroup
+    // the entry of every workgroup of the forward and of the Gram launch, a slice per
+    // finishing workgroup
     const int* fwd_map = nullptr;
     const int* gram_map = nullptr;
     const BatchSlice* finish = nullptr;
-    int fwd_wgs = 0, finishes = 0;
-    size_t lds_fwd = 0;
-    struct ClassLaunch {
-        int nmb, nm0, ns, first, wgs;   // first workgroup in gram_map
-        size_t lds;
-        double work;             // products of the class
-    };
-    std::vector<ClassLaunch> launches;
+    int fwd_wgs = 0, gram_wgs = 0, finishes = 0;
+    size_t lds_fwd = 0, lds_gram = 0;
 };
 
 namespace {
@@ -1855,14 +1849,23 @@ __global__ __launch_bounds__(kThreads) void spectral_forward_batched(const SpecE
     forward_body(e.P, e.p, blockIdx.x - e.fwd_begin, smem);
 }
 
-template <int NMB, int NM0, int NS>
+// All instances in one launch, each workgroup through its instance's instantiation. A
+// launch per instantiation on four streams held more small workgroups per CU (this one
+// has the registers of the largest), but forking and joining the streams left the GPU idle
+// for longer than the launches ran beside each other.
 __global__ __launch_bounds__(kThreads, 2) void spectral_gram_batched(const SpecEntry* __restrict__ entries,
-                                                                     const int* __restrict__ map, int first) {
+                                                                     const int* __restrict__ map) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int id = first + blockIdx.x;
-    const SpecEntry& e = entries[map[id]];
-    const int x = id - e.gram_begin;
-    gram_body<NMB, NM0, NS>(e.P, e.p, x / e.P.nqb, x % e.P.nqb, smem);
+    const SpecEntry& e = entries[map[blockIdx.x]];
+    const int x = blockIdx.x - e.gram_begin;
+    switch (e.P.nmb * 16 + e.P.nm0 * 4 + e.P.ns) {
+#define PRONY_CASE(B, B0, K)                                                  \
+    case B * 16 + B0 * 4 + K:                                                 \
+        gram_body<B, B0, K>(e.P, e.p, x / e.P.nqb, x % e.P.nqb, smem);        \
+        break;
+        PRONY_GRAM_CASES(PRONY_CASE)
+#undef PRONY_CASE
+    }
 }
 
 __global__ __launch_bounds__(kFinishThreads) void spectral_finish_batched(const SpecEntry* __restrict__ entries,
@@ -1870,16 +1873,6 @@ __global__ __launch_bounds__(kFinishThreads) void spectral_finish_batched(const 
     const BatchSlice x = slices[blockIdx.x];
     const SpecEntry& e = entries[x.entry];
     finish_body(e.P, e.p, x.block);
-}
-
-template <int NMB, int NM0, int NS>
-prony_status_t launch_gram_batched(prony_handle_t h, const SpecEntry* entries, const SpecBatch& S,
-                                   const SpecBatch::ClassLaunch& cl, hipStream_t stream) {
-    const prony_status_t st = allow_lds(h, &spectral_gram_batched<NMB, NM0, NS>, cl.lds);
-    if (st != PRONY_OK) return st;
-    ProfileScope prof(h, "spectral_gram", stream);
-    spectral_gram_batched<NMB, NM0, NS><<<cl.wgs, kThreads, cl.lds, stream>>>(entries, S.gram_map, cl.first);
-    return PRONY_OK;
 }
 
 }  // namespace
@@ -1896,15 +1889,13 @@ prony_status_t spectral_batch_build(prony_handle_t h, const std::vector<prony_in
     for (int i = 0; i < count; ++i)
         if (!spectral_plan(h, inst[i].d, inst[i].n, inst[i].m, false, plans[i], true))
             return fail(h, PRONY_ENOTSUP, "an instance does not fit the line-spectral form");
-    // classes by Gram instantiation; inside a class (and in the forward launch) the
-    // largest instances first
+    // the largest workgroups first
     std::vector<int> order(count);
     for (int i = 0; i < count; ++i) order[i] = i;
-    auto key = [&](int i) { return plans[i].nmb * 16 + plans[i].nm0 * 4 + plans[i].ns; };
-    auto work = [&](int i) { return (double)plans[i].F * plans[i].K1 * plans[i].m * (plans[i].K1 + 2 * plans[i].m); };
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
-        return key(a) != key(b) ? key(a) > key(b) : work(a) > work(b);
-    });
+    auto work = [&](int i) {
+        return (double)plans[i].F * plans[i].K1 * plans[i].m * (plans[i].K1 + 2 * plans[i].m) / plans[i].groups;
+    };
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return work(a) > work(b); });
     int64_t fwd_wgs = 0, gram_wgs = 0;
     for (const SpecPlan& P : plans) {
         fwd_wgs += P.wgs_f + 2 * (int64_t)P.wgs_x;
@@ -1947,6 +1938,7 @@ prony_status_t spectral_batch_build(prony_handle_t h, const std::vector<prony_in
     S->gram_map = S->fwd_map + fwd_wgs;
     S->finish = reinterpret_cast<const BatchSlice*>(ws + off_finish);
     S->fwd_wgs = (int)fwd_wgs;
+    S->gram_wgs = (int)gram_wgs;
     S->finishes = (int)finish.size();
     std::vector<SpecEntry> host(count);
     int fwd = 0, wgs = 0;
@@ -1964,13 +1956,9 @@ prony_status_t spectral_batch_build(prony_handle_t h, const std::vector<prony_in
                        reinterpret_cast<const double2*>(ws + tables[P.P])};
         E.fwd_begin = fwd;
         fwd += P.wgs_f + 2 * P.wgs_x;
-        if (pos == 0 || key(order[pos - 1]) != key(i)) S->launches.push_back({P.nmb, P.nm0, P.ns, wgs, 0, 0, 0.0});
-        auto& cl = S->launches.back();
         E.gram_begin = wgs;
         wgs += P.groups * P.nqb;
-        cl.wgs = wgs - cl.first;
-        cl.lds = std::max(cl.lds, P.lds_gram);
-        cl.work += work(i);
+        S->lds_gram = std::max(S->lds_gram, P.lds_gram);
         S->lds_fwd = std::max(S->lds_fwd, P.lds_fwd);
     }
     for (const auto& t : tables)
@@ -2001,24 +1989,12 @@ prony_status_t spectral_batch_launch(prony_handle_t h, const SpecBatch* S) {
         spectral_forward_batched<<<S->fwd_wgs, kThreads, S->lds_fwd, h->stream>>>(entries, S->fwd_map);
     }
     if ((st = check_launch(h, "spectral_forward_batched")) != PRONY_OK) return st;
-    std::vector<double> work;
-    for (const auto& cl : S->launches) work.push_back(cl.work);
-    st = launch_on_lanes(h, work, [&](int c, hipStream_t stream) {
-        const auto& cl = S->launches[c];
-        prony_status_t s = PRONY_OK;
-        switch (cl.nmb * 16 + cl.nm0 * 4 + cl.ns) {
-#define PRONY_CASE(B, B0, K)                                          \
-    case B * 16 + B0 * 4 + K:                                         \
-        s = launch_gram_batched<B, B0, K>(h, entries, *S, cl, stream);    \
-        break;
-            PRONY_GRAM_CASES(PRONY_CASE)
-#undef PRONY_CASE
-            default:
-                return fail(h, PRONY_ENOTSUP, "prony_build_S_batched: unexpected spectral plan");
-        }
-        return s == PRONY_OK ? check_launch(h, "spectral_gram_batched") : s;
-    });
-    if (st != PRONY_OK) return st;
+    if ((st = allow_lds(h, &spectral_gram_batched, S->lds_gram)) != PRONY_OK) return st;
+    {
+        ProfileScope prof(h, "spectral_gram");
+        spectral_gram_batched<<<S->gram_wgs, kThreads, S->lds_gram, h->stream>>>(entries, S->gram_map);
+    }
+    if ((st = check_launch(h, "spectral_gram_batched")) != PRONY_OK) return st;
     {
         ProfileScope prof(h, "pencil_finish");
         spectral_finish_batched<<<S->finishes, kFinishThreads, 0, h->stream>>>(entries, S->finish);
