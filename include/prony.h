@@ -107,7 +107,10 @@ const char* prony_last_error(prony_handle_t handle);
    S-build is planned for every precision (PRONY_BF16X3 included), with and
    without S_0, at the default split target, at every target the autotuner
    chooses from and at the target registered for the shape, for m = m_max (or
-   N when smaller) and the 16 largest n up to n_max. Register tuning entries
+   N when smaller) and the 16 largest n up to n_max. The tables of the FP64
+   line-spectral form are made for every n up to n_max (64 MiB at most per handle;
+   a line length past that, or first met under capture or by prony_build_S_noalloc,
+   gets its table made in the workspace on every call). Register tuning entries
    before reserving. */
 prony_status_t prony_reserve(prony_handle_t handle, int d_max, int n_max, int m_max);
 
@@ -116,7 +119,9 @@ prony_status_t prony_reserve(prony_handle_t handle, int d_max, int n_max, int m_
    stream; NULL stops recording. Each call discards earlier records.
    Kernel names: "samples", "toeplitz", "pencil_pack", "pencil_tiles",
    "pencil_tiles_batched", "pencil_finish", "spectral_forward", "spectral_gram",
-   "coeffs_tiles", "coeffs_finish", "adjoint_pack", "adjoint_tiles". */
+   "spectral_toeplitz", "spectral_inverse", "spectral_adjoint",
+   "coeffs_tiles" (the one launch of prony_coeffs where there is one),
+   "coeffs_finish", "adjoint_pack", "adjoint_tiles". */
 prony_status_t prony_profile_enable(prony_handle_t handle, const char* kernel);
 
 /* Synchronise the stream and report the recorded launches of the profiled kernel:
@@ -240,7 +245,8 @@ prony_status_t prony_build_S_plan(prony_handle_t handle, int d, int n, int m, pr
    prony_create). Calls no hipMalloc or hipFree. A call whose plan needs more than
    64 MiB of scratch returns PRONY_ENOTSUP with the size in prony_last_error (c1,
    d=2, n=63, m=20, needs about 10 MB in FP32; call prony_build_S for larger
-   plans). Every call on one device shares that device's array, across handles
+   plans). FP64 calls whose line-spectral form needs more run the tile kernels
+   where those fit. Every call on one device shares that device's array, across handles
    and streams: calls that overlap on one GPU race, so keep them in one stream
    order. The array keeps the last call's contents; the kernels overwrite every
    byte they read, so nothing has to start at zero. */
@@ -367,7 +373,9 @@ typedef struct {
    by decreasing work, builds the queue of all
    tiles (longest first), allocates the batch's own device workspace and uploads
    its work tables (synchronously on the handle's stream). Errors name the
-   offending instance. */
+   offending instance. FP64 batches run in line-spectral form (prony_build_S)
+   where every instance fits it and the memory for it can be had, else as tiles;
+   tuning entries and schedules concern the tiles. */
 prony_status_t prony_batch_create(prony_handle_t handle, int count, const prony_instance_t* instances,
                                   prony_prec_t prec, prony_batch_t* batch);
 
@@ -383,8 +391,8 @@ prony_status_t prony_batch_destroy(prony_batch_t batch);
    PRONY_SCHEDULE_CLASSES — one launch per class of instances with the same tile
                             instantiation (three-product blocks, column blocks,
                             row fragments), spread over the
-                            handle's stream and three auxiliary streams (forked after
-                            the packing launch, joined before the finishing launch).
+                            handle's stream and three auxiliary streams; a class is
+                            packed and finished in its own stream.
                             The default: each class's kernel keeps as many workgroups
                             resident as its own registers and LDS allow (measured
                             faster than the merged queue kernel on a 512-instance mix
@@ -399,9 +407,10 @@ prony_status_t prony_batch_destroy(prony_batch_t batch);
 prony_status_t prony_batch_set_schedule(prony_batch_t batch, int schedule);
 
 /* Enqueue the S-build of every instance of the batch on the handle's stream:
-   one packing launch for all instances, the tile launch(es) of the batch's
-   schedule and one finishing launch (fixed-order sums, Sigma^{-1}) for all
-   instances. Allocates nothing and records no memset, so it can be captured.
+   packing, the tile launch(es) of the batch's schedule and the finishing sums
+   (fixed order, Sigma^{-1}); for FP64 batches in line-spectral form one launch of
+   all transforms, one of all Gram products and one of the finishing sums.
+   Allocates nothing and records no memset, so it can be captured.
    The handle must be the one that created the batch. Launches of one batch
    share its workspace and work counter: they must not overlap (stream order,
    as on the handle's stream, keeps them apart). */
@@ -409,7 +418,9 @@ prony_status_t prony_build_S_batched(prony_handle_t handle, prony_batch_t batch)
 
 /* Adjoint of prony_build_S_batched: prony_build_S_adjoint for every instance of
    the batch, with its U, sigma and V held fixed, in one packing launch and one
-   launch per class of instances with the same d*m.
+   launch per class of instances with the same d*m (FP64 batches without a d = 1
+   instance: the transforms, products and inverse transforms of all instances in
+   line-spectral form).
    gS: device buffer of the gradients dL/dS of all instances, concatenated in the
        order given to prony_batch_create; instance i contributes d_i x m_i x m_i
        complex128 values.

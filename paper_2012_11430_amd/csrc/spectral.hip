@@ -136,6 +136,11 @@ __device__ __forceinline__ double sum_groups(double x) {
     return x + __shfl_xor(x, 32);
 }
 
+// The transforms are bound by latency at the sizes of one instance (a pass of loads, the
+// products of a few items per wave, stores: 9.4 us at d = 2, n = 63, m = 20, 18.4 us at d = 3,
+// n = 20, m = 20, of which 6 us are its 30 MB at the rate of a copy) and by memory in a batch
+// (96 instances: 48 us for 200 MB). Eight waves per workgroup were no faster (19.8 us, batch 68).
+//
 // Forward transform with one transformed axis (d <= 2): nbc blocks of 8 complex
 // columns from block nb0. Columns of a factor: c = line * m + q; of the grid: the
 // sample lines t. out[w * NC + c].
@@ -606,10 +611,14 @@ __device__ __forceinline__ void group_range(const SpecPlan& P, int grp, int& wa,
 // e^{2 pi i w_d / L}; NS = 2: the plain sum and the one with that phase (d = 3: axis 2's
 // phase is the group's, applied to the plain sum at the end). The shifted rows take the
 // plain sum in either case. At most 256 registers, so that two workgroups share a CU and
-// one's loads overlap the other's products. Requesting the next row block's operands
-// before the Gram products, or running the full and partial block of a frequency
-// together on shared V operands, took the kernel past that and lost more to spills
-// (d = 3, n = 20, m = 20: 24 us as it is, 30 and 26; d = 2, n = 63: 9.7, 12.2 and 10.9).
+// one's loads overlap the other's products.
+//   d = 3, n = 20, m = 20 takes 21.7 us (tiles of the row-extended product: 270), the matrix
+// cores busy 45 % of it; the rest is the latency of a block's loads, f~ through LDS, with two
+// waves per SIMD, and eight vector instructions per product. d = 2, n = 63: 10.8 us (tiles:
+// 65). Not faster: requesting the next row block's operands before the Gram products, or the
+// full and partial block of a frequency together on shared V operands (registers spill:
+// 30 and 26 against 24 us at the time); blocks dealt to the waves in turn (24.4 against 21.7
+// us) or to the wave with the least (25.7), so the longest wave is not the bound.
 template <int NMB, int NM0, int NS>
 __device__ __forceinline__ void gram_body(const SpecPlan& P, const SpecPtrs& p, int grp, int qb, unsigned char* smem) {
     const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, col = lane & 15;
@@ -798,6 +807,10 @@ __global__ __launch_bounds__(kFinishThreads) void spectral_finish(SpecPlan P, Sp
 
 // ---- products Y = T X, T^* X -------------------------------------------------
 
+// Three launches per product, each bound by latency: d = 2, n = 63, r = 40 9.4 + 9 + 6 us
+// (tiles of the whole product: 85), d = 3, n = 20, r = 1 10 + 7.5 + 7 us (vector kernel: 47).
+// One column takes the same 16-column blocks: the matrix work is not what it waits for.
+//
 // Y~_w[k1][q] = T_w X~_w (or T_w^* X~_w): one 16-row block of one frequency and one
 // 16-column block per wave and turn.
 __global__ __launch_bounds__(kThreads) void spectral_toeplitz(SpecPlan P, SpecPtrs p, int adjoint) {
@@ -1655,8 +1668,9 @@ bool spectral_plan(prony_handle_t h, int d, int n, int m, bool s0, SpecPlan& P, 
     P.ns = d == 3 || s0 ? 2 : 1;
     const int outer = d == 3 ? P.L : 1;
     // a single instance fills the GPU with two workgroups per CU; a batch member takes
-    // workgroups of about 512 products of 16 x 16 x 4 (several microseconds, so that the
-    // fixed cost of a workgroup and its row of partials stays small)
+    // workgroups of about 512 products of 16 x 16 x 4 whatever else the batch holds (so that
+    // its results do not depend on that): batches of 8 / 30 / 96 / 250 instances take 18 / 25
+    // / 96 / 284 us, with 256 products 13 / 27 / 105 / 336, with 1024 26 / 32 / 92 / 262
     const int R = d >= 2 ? P.K1 + 1 : P.K1, KS = (P.K1 + 3) / 4;
     const int per_w = (R + 15) / 16 * 3 * KS + (R + 3) / 4 * 3 * P.nmb;
     P.gparts = batched ? (int)(((int64_t)P.F / outer * per_w + 511) / 512)
