@@ -391,8 +391,8 @@ prony_status_t prony_batch_destroy(prony_batch_t batch);
    PRONY_SCHEDULE_CLASSES — one launch per class of instances with the same tile
                             instantiation (three-product blocks, column blocks,
                             row fragments), spread over the
-                            handle's stream and three auxiliary streams; a class is
-                            packed and finished in its own stream.
+                            handle's stream and three auxiliary streams (forked after
+                            the packing launch, joined before the finishing launch).
                             The default: each class's kernel keeps as many workgroups
                             resident as its own registers and LDS allow (measured
                             faster than the merged queue kernel on a 512-instance mix
@@ -407,8 +407,8 @@ prony_status_t prony_batch_destroy(prony_batch_t batch);
 prony_status_t prony_batch_set_schedule(prony_batch_t batch, int schedule);
 
 /* Enqueue the S-build of every instance of the batch on the handle's stream:
-   packing, the tile launch(es) of the batch's schedule and the finishing sums
-   (fixed order, Sigma^{-1}); for FP64 batches in line-spectral form one launch of
+   one packing launch for all instances, the tile launch(es) of the batch's
+   schedule and one finishing launch (fixed-order sums, Sigma^{-1}); for FP64 batches in line-spectral form one launch of
    all transforms, one of all Gram products and one of the finishing sums.
    Allocates nothing and records no memset, so it can be captured.
    The handle must be the one that created the batch. Launches of one batch

@@ -220,11 +220,11 @@ struct prony_batch_s {
         int nb, rf, ng, first, count, tiles;
         size_t lds;
         double work;   // sum of nwg * kc over the class (MFMA work, up to a factor)
-        int pack_first, packs, finish_first, finishes;   // its ranges of the slices below
     };
     std::vector<ClassLaunch> launches;
     const prony::BatchSlice* pack_slices = nullptr;     // device, a packing workgroup each
     const prony::BatchSlice* finish_slices = nullptr;   // device, a finishing workgroup each
+    int packs = 0, finishes = 0, pack_span = 0;
     // queue schedule (FP32): one persistent launch over all tiles, longest first
     int schedule = PRONY_SCHEDULE_CLASSES;
     void* queue_counter = nullptr;   // device int, reset by the packing launch

@@ -1165,20 +1165,21 @@ struct BatchEntry {
     int tile_begin;
 };
 
-// Packing for instances of a batch, one slice of kPackSpan elements per workgroup. The
-// first thread also resets the work counter of the queue schedule (the tile launch
-// follows on the same stream).
-constexpr int kPackSpan = 1024;
+// Packing for instances of a batch, one slice of `span` elements per workgroup: one element
+// per thread in small batches, kPackLoads in large ones. The first thread also resets the
+// work counter of the queue schedule (the tile launch follows on the same stream).
+constexpr int kPackSpan = 256 * kPackLoads, kPackSpanSmall = 256;
+constexpr int64_t kPackSmall = 1 << 21;      // elements of a small batch
 template <typename T>
 __global__ __launch_bounds__(256) void pencil_pack_batched(const BatchEntry<T>* __restrict__ entries,
-                                                           const BatchSlice* __restrict__ slices,
+                                                           const BatchSlice* __restrict__ slices, int span,
                                                            int* __restrict__ queue_counter) {
     if (queue_counter && (blockIdx.x | threadIdx.x) == 0) *queue_counter = 0;
     const BatchSlice x = slices[blockIdx.x];
     const BatchEntry<T>& e = entries[x.entry];
     pack_body<T>(e.P, e.U, e.P.m, 1, e.V, e.P.m, 1, const_cast<pair_t<T>*>(e.ptr.vp),
                  const_cast<pair_t<T>*>(e.ptr.up), const_cast<int*>(e.ptr.gtab), x.section,
-                 x.block * kPackSpan + threadIdx.x, 256, (x.block + 1) * kPackSpan);
+                 x.block * span + threadIdx.x, 256, (x.block + 1) * span);
 }
 
 // Batched launch over the instances of one column-block class, ordered by
@@ -2087,16 +2088,19 @@ prony_status_t batch_build(prony_handle_t h, int count, const prony_instance_t* 
     auto slice = [](std::vector<BatchSlice>& out, int entry, int section, int64_t elements, int span) {
         for (int64_t b = 0; b * span < elements; ++b) out.push_back({entry, section, (int)b});
     };
-    std::vector<int> pack_at(count + 1), finish_at(count + 1);
+    auto pack_elements = [](const PencilPlan& P, int section) {
+        const int64_t kbp = (int64_t)P.sk * P.kc + kPrefetchRows;
+        return section == 0 ? kbp * P.nrp
+                            : section == 1 ? ((int64_t)P.ug + (int64_t)P.rt * P.rows) * P.mbi * 16 : kbp;
+    };
+    int64_t elements = 0;
+    for (const PencilPlan& P : plans)
+        for (int section = 0; section < 3; ++section) elements += pack_elements(P, section);
+    B->pack_span = elements <= kPackSmall ? kPackSpanSmall : kPackSpan;
     for (int pos = 0; pos < count; ++pos) {
         const PencilPlan& P = plans[order[pos]];
-        const int64_t kbp = (int64_t)P.sk * P.kc + kPrefetchRows;
-        slice(packs, pos, 0, kbp * P.nrp, kPackSpan);
-        slice(packs, pos, 1, ((int64_t)P.ug + (int64_t)P.rt * P.rows) * P.mbi * 16, kPackSpan);
-        slice(packs, pos, 2, kbp, kPackSpan);
+        for (int section = 0; section < 3; ++section) slice(packs, pos, section, pack_elements(P, section), B->pack_span);
         slice(finishes, pos, 0, (int64_t)P.m * P.C, kFinishOuts);
-        pack_at[pos + 1] = (int)packs.size();
-        finish_at[pos + 1] = (int)finishes.size();
     }
     if (packs.size() > (size_t)INT32_MAX / 2) return fail(h, PRONY_ENOTSUP, "prony_batch_create: too many instances");
     const size_t off_packs = align_up(off_items + sizeof(WorkItem) * nitems, 256);
@@ -2137,12 +2141,10 @@ prony_status_t batch_build(prony_handle_t h, int count, const prony_instance_t* 
         const PencilPlan* prev = pos == 0 ? nullptr : &plans[order[pos - 1]];
         const bool new_class = !prev || prev->ng != P.ng || prev->nb != P.nb || prev->rf != P.rf;
         if (new_class) {
-            B->launches.push_back({P.nb, P.rf, P.ng, pos, 0, 0, 0, 0.0, pack_at[pos], 0, finish_at[pos], 0});
+            B->launches.push_back({P.nb, P.rf, P.ng, pos, 0, 0, 0, 0.0});
             first = 0;
         }
         auto& cl = B->launches.back();
-        cl.packs = pack_at[pos + 1] - cl.pack_first;
-        cl.finishes = finish_at[pos + 1] - cl.finish_first;
         E.tile_begin = first;
         first += P.nwg;
         cl.count += 1;
@@ -2153,6 +2155,8 @@ prony_status_t batch_build(prony_handle_t h, int count, const prony_instance_t* 
     B->entries = ws;
     B->pack_slices = reinterpret_cast<const BatchSlice*>(w + off_packs);
     B->finish_slices = reinterpret_cast<const BatchSlice*>(w + off_finishes);
+    B->packs = (int)packs.size();
+    B->finishes = (int)finishes.size();
     std::vector<WorkItem> items;
     items.reserve(nitems);
     std::vector<int> by_cost(count);
@@ -2194,23 +2198,16 @@ prony_status_t batch_build(prony_handle_t h, int count, const prony_instance_t* 
 template <typename T>
 prony_status_t batch_launch(prony_handle_t h, prony_batch_s* B) {
     const BatchEntry<T>* entries = static_cast<const BatchEntry<T>*>(B->entries);
-    // packing and finishing of a class (or of all instances), in its stream
-    auto pack = [&](int first, int count, int* counter, hipStream_t stream) {
-        ProfileScope prof(h, "pencil_pack", stream);
-        pencil_pack_batched<T><<<count, 256, 0, stream>>>(entries, B->pack_slices + first, counter);
-        return check_launch(h, "pencil_pack_batched");
-    };
-    auto finish = [&](int first, int count, hipStream_t stream) {
-        ProfileScope prof(h, "pencil_finish", stream);
-        pencil_finish_batched<T><<<count, kFinishThreads, 0, stream>>>(entries, B->finish_slices + first);
-        return check_launch(h, "pencil_finish_batched");
-    };
-    if (B->schedule == PRONY_SCHEDULE_QUEUE) {
+    const bool queue = B->schedule == PRONY_SCHEDULE_QUEUE;
+    int* counter = queue ? static_cast<int*>(B->queue_counter) : nullptr;
+    {
+        ProfileScope prof(h, "pencil_pack");
+        pencil_pack_batched<T><<<B->packs, 256, 0, h->stream>>>(entries, B->pack_slices, B->pack_span, counter);
+    }
+    prony_status_t st = check_launch(h, "pencil_pack_batched");
+    if (st != PRONY_OK) return st;
+    if (queue) {
         if constexpr (sizeof(T) == 4) {
-            int* counter = static_cast<int*>(B->queue_counter);
-            const auto& last = B->launches.back();
-            prony_status_t st = pack(0, last.pack_first + last.packs, counter, h->stream);
-            if (st != PRONY_OK) return st;
             if (B->queue_lds > 65536) {
                 hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&pencil_tiles_queue<T>),
                                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)B->queue_lds);
@@ -2221,24 +2218,26 @@ prony_status_t batch_launch(prony_handle_t h, prony_batch_s* B) {
                 pencil_tiles_queue<T><<<B->queue_grid, kThreads, B->queue_lds, h->stream>>>(
                     entries, static_cast<const WorkItem*>(B->queue_items), B->queue_n, counter);
             }
-            if ((st = check_launch(h, "pencil_tiles_queue")) != PRONY_OK) return st;
-            return finish(0, last.finish_first + last.finishes, h->stream);
+            st = check_launch(h, "pencil_tiles_queue");
         } else {
             return fail(h, PRONY_ENOTSUP, "prony_build_S_batched: the queue schedule is FP32 only");
         }
+    } else {
+        std::vector<double> work;
+        for (const auto& cl : B->launches) work.push_back(cl.work);
+        st = launch_on_lanes(h, work, [&](int c, hipStream_t stream) {
+            const auto& cl = B->launches[c];
+            const prony_status_t s =
+                dispatch_batched<T>(h, cl.nb, cl.rf, cl.ng, entries + cl.first, cl.count, cl.tiles, cl.lds, stream);
+            return s == PRONY_OK ? check_launch(h, "pencil_tiles_batched") : s;
+        });
     }
-    // a class's packing and finishing run in its own lane, beside the products of the others
-    // (packing is bound by memory, the products by the matrix cores)
-    std::vector<double> work;
-    for (const auto& cl : B->launches) work.push_back(cl.work);
-    return launch_on_lanes(h, work, [&](int c, hipStream_t stream) {
-        const auto& cl = B->launches[c];
-        prony_status_t s = pack(cl.pack_first, cl.packs, nullptr, stream);
-        if (s != PRONY_OK) return s;
-        s = dispatch_batched<T>(h, cl.nb, cl.rf, cl.ng, entries + cl.first, cl.count, cl.tiles, cl.lds, stream);
-        if (s != PRONY_OK || (s = check_launch(h, "pencil_tiles_batched")) != PRONY_OK) return s;
-        return finish(cl.finish_first, cl.finishes, stream);
-    });
+    if (st != PRONY_OK) return st;
+    {
+        ProfileScope prof(h, "pencil_finish");
+        pencil_finish_batched<T><<<B->finishes, kFinishThreads, 0, h->stream>>>(entries, B->finish_slices);
+    }
+    return check_launch(h, "pencil_finish_batched");
 }
 
 }  // namespace
