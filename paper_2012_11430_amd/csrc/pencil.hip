@@ -229,12 +229,12 @@ __device__ __forceinline__ void pack_body(const PencilPlan& P, const double2* __
     if (section == 0 && P.split) {
         pack_split(P, V, v_rs, v_cs, reinterpret_cast<u32x4*>(vp), first, stride);
     } else if (section == 0) {
-        const int nv = min(kbp * P.nrp, last);
-        for (int i0 = first; i0 < nv; i0 += kPackLoads * stride) {
+        const unsigned nv = min(kbp * P.nrp, last);       // unsigned: i may pass 2^31
+        for (unsigned i0 = first; i0 < nv; i0 += kPackLoads * stride) {
             double2 pr[kPackLoads];
 #pragma unroll
             for (int k = 0; k < kPackLoads; ++k) {
-                const int i = i0 + k * stride;
+                const unsigned i = i0 + k * stride;
                 const int hx = i / P.nrp;
                 const int j = i - hx * P.nrp;
                 // (Re a) multiplies the first member, (Im a) the second.
@@ -242,21 +242,21 @@ __device__ __forceinline__ void pack_body(const PencilPlan& P, const double2* __
             }
 #pragma unroll
             for (int k = 0; k < kPackLoads; ++k) {
-                const int i = i0 + k * stride;
+                const unsigned i = i0 + k * stride;
                 if (i < nv) vp[i] = T2{(T)pr[k].x, (T)pr[k].y};
             }
         }
     } else if (section == 1) {
         if (P.mode) return;   // the product has no U^* epilogue
         const int mup = P.mbi * 16;
-        const int nu = min((P.ug + P.rt * P.rows) * mup, last);
+        const unsigned nu = min((P.ug + P.rt * P.rows) * mup, last);
         const int E = P.n + 2, Pn = P.n + 1;
-        for (int r0 = first; r0 < nu; r0 += kPackLoads * stride) {
+        for (unsigned r0 = first; r0 < nu; r0 += kPackLoads * stride) {
             double2 u[kPackLoads];
 #pragma unroll
             for (int k = 0; k < kPackLoads; ++k) {
-                const int r = r0 + k * stride;
-                const int kr = r / mup - P.ug;   // row-extended index k'
+                const unsigned r = r0 + k * stride;
+                const int kr = (int)(r / mup) - P.ug;   // row-extended index k'
                 const int col = r - (r / mup) * mup;
                 int rem = kr, idx = 0, scale = 1;
                 bool inside = r < nu && kr >= 0 && kr < P.NR && col < P.m;
@@ -275,7 +275,7 @@ __device__ __forceinline__ void pack_body(const PencilPlan& P, const double2* __
             }
 #pragma unroll
             for (int k = 0; k < kPackLoads; ++k) {
-                const int r = r0 + k * stride;
+                const unsigned r = r0 + k * stride;
                 if (r < nu) up[r] = T2{(T)u[k].x, (T)u[k].y};
             }
         }

@@ -615,7 +615,7 @@ __device__ __forceinline__ void group_range(const SpecPlan& P, int grp, int& wa,
 //   d = 3, n = 20, m = 20 takes 21.7 us (tiles of the row-extended product: 270), the matrix
 // cores busy 45 % of it; the rest is the latency of a block's loads, f~ through LDS, with two
 // waves per SIMD, and eight vector instructions per product. d = 2, n = 63: 10.8 us (tiles:
-// 65). Not faster: requesting the next row block's operands before the Gram products, or the
+// 65; one wave per SIMD, matrix cores 30 %). Not faster: requesting the next row block's operands before the Gram products, or the
 // full and partial block of a frequency together on shared V operands (registers spill:
 // 30 and 26 against 24 us at the time); blocks dealt to the waves in turn (24.4 against 21.7
 // us) or to the wave with the least (25.7), so the longest wave is not the bound.
