@@ -216,9 +216,10 @@ __device__ __forceinline__ void pack_split(const PencilPlan& P, const double2* _
 // elsewhere, columns padded to 16*mbi, so that U_l[k'] = U[k' - e_l] is the packed
 // row ug + k' - shift(e_l); (y = 2) the grid offsets G(h). All index arithmetic
 // fits in 32 bits (checked by the host plan). Handles elements first, first + stride, ...
-// below `last` of a section, kPackLoads loads in flight per thread.
+// below `last` of a section, `Loads` loads in flight per thread: kPackLoads in batches; one in
+// single instances, whose threads have one or two elements (5.3 against 5.6 us).
 constexpr int kPackLoads = 4;
-template <typename T>
+template <typename T, int Loads>
 __device__ __forceinline__ void pack_body(const PencilPlan& P, const double2* __restrict__ U, int64_t u_rs,
                                           int64_t u_cs, const double2* __restrict__ V, int64_t v_rs, int64_t v_cs,
                                           pair_t<T>* __restrict__ vp, pair_t<T>* __restrict__ up,
@@ -230,10 +231,10 @@ __device__ __forceinline__ void pack_body(const PencilPlan& P, const double2* __
         pack_split(P, V, v_rs, v_cs, reinterpret_cast<u32x4*>(vp), first, stride);
     } else if (section == 0) {
         const unsigned nv = min(kbp * P.nrp, last);       // unsigned: i may pass 2^31
-        for (unsigned i0 = first; i0 < nv; i0 += kPackLoads * stride) {
-            double2 pr[kPackLoads];
+        for (unsigned i0 = first; i0 < nv; i0 += Loads * stride) {
+            double2 pr[Loads];
 #pragma unroll
-            for (int k = 0; k < kPackLoads; ++k) {
+            for (int k = 0; k < Loads; ++k) {
                 const unsigned i = i0 + k * stride;
                 const int hx = i / P.nrp;
                 const int j = i - hx * P.nrp;
@@ -241,7 +242,7 @@ __device__ __forceinline__ void pack_body(const PencilPlan& P, const double2* __
                 pr[k] = pair_of(P, V, v_rs, v_cs, i < nv ? hx : P.kb, j);
             }
 #pragma unroll
-            for (int k = 0; k < kPackLoads; ++k) {
+            for (int k = 0; k < Loads; ++k) {
                 const unsigned i = i0 + k * stride;
                 if (i < nv) vp[i] = T2{(T)pr[k].x, (T)pr[k].y};
             }
@@ -251,10 +252,10 @@ __device__ __forceinline__ void pack_body(const PencilPlan& P, const double2* __
         const int mup = P.mbi * 16;
         const unsigned nu = min((P.ug + P.rt * P.rows) * mup, last);
         const int E = P.n + 2, Pn = P.n + 1;
-        for (unsigned r0 = first; r0 < nu; r0 += kPackLoads * stride) {
-            double2 u[kPackLoads];
+        for (unsigned r0 = first; r0 < nu; r0 += Loads * stride) {
+            double2 u[Loads];
 #pragma unroll
-            for (int k = 0; k < kPackLoads; ++k) {
+            for (int k = 0; k < Loads; ++k) {
                 const unsigned r = r0 + k * stride;
                 const int kr = (int)(r / mup) - P.ug;   // row-extended index k'
                 const int col = r - (r / mup) * mup;
@@ -274,7 +275,7 @@ __device__ __forceinline__ void pack_body(const PencilPlan& P, const double2* __
                 if (inside) u[k] = U[idx * u_rs + col * u_cs];
             }
 #pragma unroll
-            for (int k = 0; k < kPackLoads; ++k) {
+            for (int k = 0; k < Loads; ++k) {
                 const unsigned r = r0 + k * stride;
                 if (r < nu) up[r] = T2{(T)u[k].x, (T)u[k].y};
             }
@@ -289,7 +290,7 @@ __global__ __launch_bounds__(256) void pencil_pack(PencilPlan P, const double2* 
                                                    int64_t u_cs, const double2* __restrict__ V, int64_t v_rs,
                                                    int64_t v_cs, pair_t<T>* __restrict__ vp, pair_t<T>* __restrict__ up,
                                                    int* __restrict__ gt) {
-    pack_body<T>(P, U, u_rs, u_cs, V, v_rs, v_cs, vp, up, gt, blockIdx.y, blockIdx.x * blockDim.x + threadIdx.x,
+    pack_body<T, 1>(P, U, u_rs, u_cs, V, v_rs, v_cs, vp, up, gt, blockIdx.y, blockIdx.x * blockDim.x + threadIdx.x,
                  gridDim.x * blockDim.x, INT32_MAX);
 }
 
@@ -1177,7 +1178,7 @@ __global__ __launch_bounds__(256) void pencil_pack_batched(const BatchEntry<T>* 
     if (queue_counter && (blockIdx.x | threadIdx.x) == 0) *queue_counter = 0;
     const BatchSlice x = slices[blockIdx.x];
     const BatchEntry<T>& e = entries[x.entry];
-    pack_body<T>(e.P, e.U, e.P.m, 1, e.V, e.P.m, 1, const_cast<pair_t<T>*>(e.ptr.vp),
+    pack_body<T, kPackLoads>(e.P, e.U, e.P.m, 1, e.V, e.P.m, 1, const_cast<pair_t<T>*>(e.ptr.vp),
                  const_cast<pair_t<T>*>(e.ptr.up), const_cast<int*>(e.ptr.gtab), x.section,
                  x.block * span + threadIdx.x, 256, (x.block + 1) * span);
 }
