@@ -335,7 +335,7 @@ struct AdjEntry {
     const double2* V;
     const double* sigma;
     int64_t gs_off, gf_off;   // complex elements
-    int tile_begin;           // first workgroup of this instance within its class launch
+    int tile_begin;           // first tile of this instance in tile_map
 };
 
 template <typename T>
@@ -352,18 +352,11 @@ __global__ __launch_bounds__(kThreads) void adjoint_pack_batched(const AdjEntry<
 }
 
 template <typename T, int KS, int RF>
-__global__ __launch_bounds__(kThreads) void adjoint_tiles_batched(const AdjEntry<T>* __restrict__ entries, int count,
+__global__ __launch_bounds__(kThreads) void adjoint_tiles_batched(const AdjEntry<T>* __restrict__ entries,
+                                                                  const int* __restrict__ map, int first,
                                                                   double2* __restrict__ gf_all) {
-    const int id = blockIdx.x;
-    int lo = 0, hi = count - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (entries[mid].tile_begin <= id)
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
-    const AdjEntry<T>& e = entries[lo];
+    const int id = first + blockIdx.x;
+    const AdjEntry<T>& e = entries[map[id]];
     AdjPtrs<T> ptr = e.ptr;
     ptr.gf = gf_all + e.gf_off;
     adjoint_body<T, KS, RF>(e.P, ptr, id - e.tile_begin);
@@ -490,8 +483,8 @@ prony_status_t launch_adjoint(prony_handle_t h, const AdjPlan& P, const double* 
 }
 
 template <typename T, int KS>
-prony_status_t launch_adj_batched_ks(prony_handle_t h, int rf, const AdjEntry<T>* entries, int count, int tiles,
-                                     size_t lds, double2* gf) {
+prony_status_t launch_adj_batched_ks(prony_handle_t h, int rf, const AdjEntry<T>* entries, const int* map, int first,
+                                     int tiles, size_t lds, double2* gf) {
     if constexpr (adj_rf2_supported(sizeof(T), KS))
         if (rf == 2) {
             if (lds > 65536) {
@@ -500,7 +493,7 @@ prony_status_t launch_adj_batched_ks(prony_handle_t h, int rf, const AdjEntry<T>
                 if (e != hipSuccess) return hip_fail(h, e, "hipFuncSetAttribute");
             }
             ProfileScope prof(h, "adjoint_tiles_batched");
-            adjoint_tiles_batched<T, KS, 2><<<tiles, kThreads, lds, h->stream>>>(entries, count, gf);
+            adjoint_tiles_batched<T, KS, 2><<<tiles, kThreads, lds, h->stream>>>(entries, map, first, gf);
             return PRONY_OK;
         }
     if (lds > 65536) {
@@ -509,7 +502,7 @@ prony_status_t launch_adj_batched_ks(prony_handle_t h, int rf, const AdjEntry<T>
         if (e != hipSuccess) return hip_fail(h, e, "hipFuncSetAttribute");
     }
     ProfileScope prof(h, "adjoint_tiles_batched");
-    adjoint_tiles_batched<T, KS, 1><<<tiles, kThreads, lds, h->stream>>>(entries, count, gf);
+    adjoint_tiles_batched<T, KS, 1><<<tiles, kThreads, lds, h->stream>>>(entries, map, first, gf);
     return PRONY_OK;
 }
 
@@ -519,10 +512,11 @@ struct AdjBatch {
     void* ws = nullptr;           // device AdjEntry<T>[count] (grouped by class), then operands
     int count = 0;
     const BatchSlice* slices = nullptr;   // device, a packing workgroup each
+    const int* tile_map = nullptr;        // device, the entry of every tile
     int packs = 0;
     int64_t gs_elems = 0, gf_elems = 0;   // complex elements of the concatenated gS / gf
     struct ClassLaunch {
-        int ks, rf, first, count, tiles;
+        int ks, rf, first, tiles;         // first tile in tile_map
         size_t lds;
     };
     std::vector<ClassLaunch> launches;
@@ -575,7 +569,12 @@ prony_status_t adj_batch_build(prony_handle_t h, const prony_batch_s* B, AdjBatc
     if (packs.size() > (size_t)INT32_MAX / 2)
         return fail(h, PRONY_ENOTSUP, "prony_build_S_adjoint_batched: too many instances");
     const size_t off_packs = align_up(sizeof(AdjEntry<T>) * (size_t)count, 256);
-    size_t off = align_up(off_packs + sizeof(BatchSlice) * packs.size(), 256);
+    std::vector<int> tile_map;      // class after class
+    for (int pos = 0; pos < count; ++pos) tile_map.insert(tile_map.end(), (size_t)plans[order[pos]].nwg, pos);
+    if (tile_map.size() > (size_t)INT32_MAX)
+        return fail(h, PRONY_ENOTSUP, "prony_build_S_adjoint_batched: too many tiles");
+    const size_t off_map = align_up(off_packs + sizeof(BatchSlice) * packs.size(), 256);
+    size_t off = align_up(off_map + sizeof(int) * tile_map.size(), 256);
     std::vector<size_t> base(count);
     for (int pos = 0; pos < count; ++pos) {
         base[pos] = off;
@@ -607,23 +606,23 @@ prony_status_t adj_batch_build(prony_handle_t h, const prony_batch_s* B, AdjBatc
         E.gf_off = gf_off[i];
         const bool new_class = pos == 0 || plans[order[pos - 1]].ksteps != P.ksteps ||
                                plans[order[pos - 1]].rf != P.rf;
-        if (new_class) {
-            A->launches.push_back({P.ksteps, P.rf, pos, 0, 0, 0});
-            first = 0;
-        }
+        if (new_class) A->launches.push_back({P.ksteps, P.rf, first, 0, 0});
         auto& cl = A->launches.back();
         E.tile_begin = first;
         first += P.nwg;
-        cl.count += 1;
-        cl.tiles = first;
+        cl.tiles = first - cl.first;
         cl.lds = std::max(cl.lds, P.lds_bytes);
     }
     A->count = count;
     A->slices = reinterpret_cast<const BatchSlice*>(w + off_packs);
+    A->tile_map = reinterpret_cast<const int*>(w + off_map);
     A->packs = (int)packs.size();
     e = hipMemcpyAsync(A->ws, host.data(), sizeof(AdjEntry<T>) * (size_t)count, hipMemcpyHostToDevice, h->stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(w + off_packs, packs.data(), sizeof(BatchSlice) * packs.size(), hipMemcpyHostToDevice,
+                           h->stream);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(w + off_map, tile_map.data(), sizeof(int) * tile_map.size(), hipMemcpyHostToDevice,
                            h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) return hip_fail(h, e, "batch adjoint work table upload");
@@ -646,7 +645,7 @@ prony_status_t adj_batch_launch(prony_handle_t h, const AdjBatch* A, const doubl
         switch (cl.ks) {
 #define PRONY_ADJ_BCASE(K)                                                                              \
     case K:                                                                                             \
-        st = launch_adj_batched_ks<T, K>(h, cl.rf, entries + cl.first, cl.count, cl.tiles, cl.lds, gf2); \
+        st = launch_adj_batched_ks<T, K>(h, cl.rf, entries, A->tile_map, cl.first, cl.tiles, cl.lds, gf2);    \
         break;
             PRONY_ADJ_BCASE(2)
             PRONY_ADJ_BCASE(4)

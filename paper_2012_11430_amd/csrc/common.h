@@ -217,13 +217,14 @@ struct prony_batch_s {
     size_t ws_bytes = 0;
     void* entries = nullptr;      // device BatchEntry<T>[count], grouped by class
     struct ClassLaunch {
-        int nb, rf, ng, first, count, tiles;
+        int nb, rf, ng, first, tiles;   // first tile in tile_map
         size_t lds;
         double work;   // sum of nwg * kc over the class (MFMA work, up to a factor)
     };
     std::vector<ClassLaunch> launches;
     const prony::BatchSlice* pack_slices = nullptr;     // device, a packing workgroup each
     const prony::BatchSlice* finish_slices = nullptr;   // device, a finishing workgroup each
+    const int* tile_map = nullptr;                      // device, the entry of every tile
     int packs = 0, finishes = 0, pack_span = 0;
     // queue schedule (FP32): one persistent launch over all tiles, longest first
     int schedule = PRONY_SCHEDULE_CLASSES;

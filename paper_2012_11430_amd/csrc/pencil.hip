@@ -1167,39 +1167,32 @@ struct BatchEntry {
 };
 
 // Packing for instances of a batch, one slice of `span` elements per workgroup: one element
-// per thread in small batches, kPackLoads in large ones. The first thread also resets the
+// per thread in small batches (`Loads`), kPackLoads in large ones. The first thread also resets the
 // work counter of the queue schedule (the tile launch follows on the same stream).
 constexpr int kPackSpan = 256 * kPackLoads, kPackSpanSmall = 256;
 constexpr int64_t kPackSmall = 1 << 21;      // elements of a small batch
-template <typename T>
+template <typename T, int Loads>
 __global__ __launch_bounds__(256) void pencil_pack_batched(const BatchEntry<T>* __restrict__ entries,
-                                                           const BatchSlice* __restrict__ slices, int span,
+                                                           const BatchSlice* __restrict__ slices,
                                                            int* __restrict__ queue_counter) {
     if (queue_counter && (blockIdx.x | threadIdx.x) == 0) *queue_counter = 0;
+    constexpr int span = 256 * Loads;
     const BatchSlice x = slices[blockIdx.x];
     const BatchEntry<T>& e = entries[x.entry];
-    pack_body<T, kPackLoads>(e.P, e.U, e.P.m, 1, e.V, e.P.m, 1, const_cast<pair_t<T>*>(e.ptr.vp),
+    pack_body<T, Loads>(e.P, e.U, e.P.m, 1, e.V, e.P.m, 1, const_cast<pair_t<T>*>(e.ptr.vp),
                  const_cast<pair_t<T>*>(e.ptr.up), const_cast<int*>(e.ptr.gtab), x.section,
                  x.block * span + threadIdx.x, 256, (x.block + 1) * span);
 }
 
 // Batched launch over the instances of one column-block class, ordered by
-// decreasing work: workgroup `id` finds its instance by binary search over the
-// tile offsets (the hardware dispatches workgroups in id order, so the longest
-// tiles start first).
+// decreasing work (the hardware dispatches workgroups in id order, so the longest
+// tiles start first): workgroup first + blockIdx.x reads its entry from a table (a
+// binary search over the entries was a chain of up to nine loads).
 template <typename T, int NB, int RF, int NG>
 __global__ __launch_bounds__(kThreads) void pencil_tiles_batched(const BatchEntry<T>* __restrict__ entries,
-                                                                 int count) {
-    const int id = blockIdx.x;
-    int lo = 0, hi = count - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (entries[mid].tile_begin <= id)
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
-    const BatchEntry<T>& e = entries[lo];
+                                                                 const int* __restrict__ map, int first) {
+    const int id = first + blockIdx.x;
+    const BatchEntry<T>& e = entries[map[id]];
     tile_body<T, NB, RF, 0, false, NG>(e.P, e.ptr, id - e.tile_begin);
 }
 
@@ -1402,7 +1395,7 @@ prony_status_t launch_tiles(prony_handle_t h, const PencilPlan& P, const TilePtr
 }
 
 template <typename T, int NB, int RF, int NG = 0>
-prony_status_t launch_batched(prony_handle_t h, const BatchEntry<T>* entries, int count, int tiles, size_t lds,
+prony_status_t launch_batched(prony_handle_t h, const BatchEntry<T>* entries, const int* map, int first, int tiles, size_t lds,
                               hipStream_t stream) {
     if (lds > 65536) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&pencil_tiles_batched<T, NB, RF, NG>),
@@ -1410,7 +1403,7 @@ prony_status_t launch_batched(prony_handle_t h, const BatchEntry<T>* entries, in
         if (e != hipSuccess) return hip_fail(h, e, "hipFuncSetAttribute");
     }
     ProfileScope prof(h, "pencil_tiles_batched", stream);
-    pencil_tiles_batched<T, NB, RF, NG><<<tiles, kThreads, lds, stream>>>(entries, count);
+    pencil_tiles_batched<T, NB, RF, NG><<<tiles, kThreads, lds, stream>>>(entries, map, first);
     return PRONY_OK;
 }
 
@@ -1525,15 +1518,15 @@ prony_status_t dispatch_tiles(prony_handle_t h, const PencilPlan& P, const TileP
 }
 
 template <typename T>
-prony_status_t dispatch_batched(prony_handle_t h, int nb, int rf, int ng, const BatchEntry<T>* entries, int count,
+prony_status_t dispatch_batched(prony_handle_t h, int nb, int rf, int ng, const BatchEntry<T>* entries, const int* map, int first,
                                 int tiles, size_t lds, hipStream_t stream) {
     if (ng) {
         switch (ng * 16 + nb) {
 #define PRONY_GCASE(NBV, NGV)                                                                           \
     case NGV * 16 + NBV:                                                                                \
         if constexpr (rf_supported(sizeof(T), NBV, 2, false, NGV))                                      \
-            if (rf == 2) return launch_batched<T, NBV, 2, NGV>(h, entries, count, tiles, lds, stream);  \
-        return launch_batched<T, NBV, 1, NGV>(h, entries, count, tiles, lds, stream);
+            if (rf == 2) return launch_batched<T, NBV, 2, NGV>(h, entries, map, first, tiles, lds, stream);  \
+        return launch_batched<T, NBV, 1, NGV>(h, entries, map, first, tiles, lds, stream);
             PRONY_MIXED_CASES(PRONY_GCASE)
 #undef PRONY_GCASE
             default:
@@ -1542,8 +1535,8 @@ prony_status_t dispatch_batched(prony_handle_t h, int nb, int rf, int ng, const 
     }
     // without three-product blocks: one pair block (m <= 8)
     if (nb != 1) return fail(h, PRONY_ENOTSUP, "prony_build_S_batched: unexpected column blocks");
-    if (rf == 2) return launch_batched<T, 1, 2>(h, entries, count, tiles, lds, stream);
-    return launch_batched<T, 1, 1>(h, entries, count, tiles, lds, stream);
+    if (rf == 2) return launch_batched<T, 1, 2>(h, entries, map, first, tiles, lds, stream);
+    return launch_batched<T, 1, 1>(h, entries, map, first, tiles, lds, stream);
 }
 
 // The three launches of one S-build with the packed operands and partial sums in
@@ -2106,7 +2099,10 @@ prony_status_t batch_build(prony_handle_t h, int count, const prony_instance_t* 
     if (packs.size() > (size_t)INT32_MAX / 2) return fail(h, PRONY_ENOTSUP, "prony_batch_create: too many instances");
     const size_t off_packs = align_up(off_items + sizeof(WorkItem) * nitems, 256);
     const size_t off_finishes = align_up(off_packs + sizeof(BatchSlice) * packs.size(), 256);
-    size_t off = align_up(off_finishes + sizeof(BatchSlice) * finishes.size(), 256);
+    const size_t off_map = align_up(off_finishes + sizeof(BatchSlice) * finishes.size(), 256);
+    size_t off = align_up(off_map + sizeof(int) * nitems, 256);
+    std::vector<int> tile_map;      // entry of every tile, class after class
+    tile_map.reserve(nitems);
     std::vector<BatchEntry<T>> host(count);
     std::vector<size_t> base(count);
     for (int pos = 0; pos < count; ++pos) {
@@ -2142,20 +2138,20 @@ prony_status_t batch_build(prony_handle_t h, int count, const prony_instance_t* 
         const PencilPlan* prev = pos == 0 ? nullptr : &plans[order[pos - 1]];
         const bool new_class = !prev || prev->ng != P.ng || prev->nb != P.nb || prev->rf != P.rf;
         if (new_class) {
-            B->launches.push_back({P.nb, P.rf, P.ng, pos, 0, 0, 0, 0.0});
-            first = 0;
+            B->launches.push_back({P.nb, P.rf, P.ng, first, 0, 0, 0.0});
         }
         auto& cl = B->launches.back();
         E.tile_begin = first;
         first += P.nwg;
-        cl.count += 1;
-        cl.tiles = first;
+        tile_map.insert(tile_map.end(), (size_t)P.nwg, pos);
+        cl.tiles = first - cl.first;
         cl.lds = std::max(cl.lds, P.lds_bytes);
         cl.work += (double)P.nwg * P.kc * P.rf * (2 * P.nb + P.ng);   // MFMAs per K step and fragment
     }
     B->entries = ws;
     B->pack_slices = reinterpret_cast<const BatchSlice*>(w + off_packs);
     B->finish_slices = reinterpret_cast<const BatchSlice*>(w + off_finishes);
+    B->tile_map = reinterpret_cast<const int*>(w + off_map);
     B->packs = (int)packs.size();
     B->finishes = (int)finishes.size();
     std::vector<WorkItem> items;
@@ -2191,6 +2187,8 @@ prony_status_t batch_build(prony_handle_t h, int count, const prony_instance_t* 
     if (e == hipSuccess)
         e = hipMemcpyAsync(w + off_finishes, finishes.data(), sizeof(BatchSlice) * finishes.size(),
                            hipMemcpyHostToDevice, h->stream);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(w + off_map, tile_map.data(), sizeof(int) * nitems, hipMemcpyHostToDevice, h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) return hip_fail(h, e, "batch work table upload");
     return PRONY_OK;
@@ -2203,7 +2201,10 @@ prony_status_t batch_launch(prony_handle_t h, prony_batch_s* B) {
     int* counter = queue ? static_cast<int*>(B->queue_counter) : nullptr;
     {
         ProfileScope prof(h, "pencil_pack");
-        pencil_pack_batched<T><<<B->packs, 256, 0, h->stream>>>(entries, B->pack_slices, B->pack_span, counter);
+        if (B->pack_span == kPackSpanSmall)
+            pencil_pack_batched<T, 1><<<B->packs, 256, 0, h->stream>>>(entries, B->pack_slices, counter);
+        else
+            pencil_pack_batched<T, kPackLoads><<<B->packs, 256, 0, h->stream>>>(entries, B->pack_slices, counter);
     }
     prony_status_t st = check_launch(h, "pencil_pack_batched");
     if (st != PRONY_OK) return st;
@@ -2229,7 +2230,7 @@ prony_status_t batch_launch(prony_handle_t h, prony_batch_s* B) {
         st = launch_on_lanes(h, work, [&](int c, hipStream_t stream) {
             const auto& cl = B->launches[c];
             const prony_status_t s =
-                dispatch_batched<T>(h, cl.nb, cl.rf, cl.ng, entries + cl.first, cl.count, cl.tiles, cl.lds, stream);
+                dispatch_batched<T>(h, cl.nb, cl.rf, cl.ng, entries, B->tile_map, cl.first, cl.tiles, cl.lds, stream);
             return s == PRONY_OK ? check_launch(h, "pencil_tiles_batched") : s;
         });
     }
