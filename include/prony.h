@@ -107,8 +107,9 @@ const char* prony_last_error(prony_handle_t handle);
    S-build is planned for every precision (PRONY_BF16X3 included), with and
    without S_0, at the default split target, at every target the autotuner
    chooses from and at the target registered for the shape, for m = m_max (or
-   N when smaller) and the 16 largest n up to n_max. The tables of the FP64
-   line-spectral form are made for every n up to n_max (64 MiB at most per handle;
+   N when smaller) and the 16 largest n up to n_max; the FP64 line-spectral form
+   (prony_build_S), whose workspace does not grow evenly, for every smaller n and m
+   too. The tables of that form are made for every n up to n_max (64 MiB at most per handle;
    a line length past that, or first met under capture or by prony_build_S_noalloc,
    gets its table made in the workspace on every call). Register tuning entries
    before reserving. */

@@ -669,8 +669,6 @@ size_t adjoint_workspace_bytes(prony_handle_t h, int d, int n, int m) {
         AdjPlan P;
         if (make_adj_plan(h, d, n, m, ts, P) == PRONY_OK) best = std::max(best, P.ws_bytes);
     }
-    SpecPlan SP;
-    if (spectral_adjoint_plan(h, d, n, m, SP)) best = std::max(best, SP.ws_bytes);
     return best;
 }
 

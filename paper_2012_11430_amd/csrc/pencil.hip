@@ -1699,7 +1699,7 @@ prony_status_t launch_toeplitz_mm(prony_handle_t h, const PencilPlan& P, const d
 // handle may choose (used by prony_reserve): every precision (the split-bfloat16
 // plan included), with and without S_0, at the default target, every target the
 // autotuner chooses from (1, 2, 3, 4 and 8 workgroups per compute unit) and the
-// target registered for the shape.
+// target registered for the shape. (The line-spectral form: spectral_reserve_bytes.)
 size_t pencil_workspace_bytes(prony_handle_t h, int d, int n, int m) {
     size_t best = 0;
     const std::string saved = h->err;   // plans that do not fit only fail here
@@ -1714,10 +1714,6 @@ size_t pencil_workspace_bytes(prony_handle_t h, int d, int n, int m) {
                     if (make_plan(h, d, n, m, s0 == 1, ts, P, tg, rf, 0, prec == PRONY_BF16X3, true) == PRONY_OK)
                         best = std::max(best, P.ws_bytes);
                 }
-    }
-    for (int s0 = 0; s0 < 2; ++s0) {
-        SpecPlan SP;
-        if (spectral_plan(h, d, n, m, s0 == 1, SP)) best = std::max(best, SP.ws_bytes);
     }
     h->err = saved;
     return best;
@@ -2002,11 +1998,12 @@ extern "C" prony_status_t prony_reserve(prony_handle_t h, int d_max, int n_max, 
     if (h->device < 0) return fail(h, PRONY_ENODEV, "validation-only handle has no device");
     DeviceGuard g(h->device);
     if (!g.ok) return fail(h, PRONY_EHIP, "hipSetDevice failed");
-    // The plans are sized at the largest m; over n, the largest plans come from the
+    // The tile plans are sized at the largest m; over n, the largest plans come from the
     // top of the range (the operands grow with n, the partial sums with the target),
     // so the last 16 values of n are planned.
     size_t need = 0;
-    for (int d = 1; d <= d_max; ++d)
+    for (int d = 1; d <= d_max; ++d) {
+        need = std::max(need, spectral_reserve_bytes(h, d, n_max, m_max));
         for (int n = std::max(1, n_max - 15); n <= n_max; ++n) {
             const int m = (int)std::min<int64_t>(m_max, ipow(n + 1, d));
             if (m <= 32) {
@@ -2015,6 +2012,7 @@ extern "C" prony_status_t prony_reserve(prony_handle_t h, int d_max, int n_max, 
             }
             need = std::max(need, coeffs_workspace_bytes(d, n, m));
         }
+    }
     if ((st = ensure_workspace(h, need)) != PRONY_OK) return st;
     return spectral_reserve(h, d_max, n_max);
 }

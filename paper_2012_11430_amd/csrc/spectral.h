@@ -75,6 +75,11 @@ prony_status_t spectral_gram_finish(prony_handle_t h, const SpecPlan& P, const S
 size_t spectral_table_bytes(const SpecPlan& P);
 prony_status_t spectral_reserve(prony_handle_t h, int d_max, int n_max);
 
+// Largest workspace of a single S-build or adjoint of dimension d within the bounds. It
+// does not grow with n and m: the groups of frequencies (rows of partials) halve where a
+// second column block starts and step with n, and a larger shape may leave the form.
+size_t spectral_reserve_bytes(prony_handle_t h, int d, int n_max, int m_max);
+
 // FP64 batches: the plan of all instances with its own device memory (PRONY_ENOTSUP when
 // one of them does not fit the form, PRONY_ENOMEM), its launches, its release.
 prony_status_t spectral_batch_build(prony_handle_t h, const std::vector<prony_instance_t>& inst, SpecBatch** out);

@@ -1657,6 +1657,22 @@ prony_status_t spectral_reserve(prony_handle_t h, int d_max, int n_max) {
     return PRONY_OK;
 }
 
+size_t spectral_reserve_bytes(prony_handle_t h, int d, int n_max, int m_max) {
+    size_t best = 0;
+    for (int n = 1; n <= std::min(n_max, d == 1 ? kMaxLines * kMaxLines : kMaxLines); ++n) {
+        const int top = (int)std::min<int64_t>(std::min(m_max, 32), ipow(n + 1, d));
+        for (int m = 1; m <= top; ++m) {
+            // (d = 1 stays far below the limit on the workspace: it grows with m between
+            // the steps in the number of column blocks)
+            if (d == 1 && m != top && m % 16) continue;
+            SpecPlan P;
+            if (spectral_plan(h, d, n, m, true, P)) best = std::max(best, P.ws_bytes);
+            if (spectral_adjoint_plan(h, d, n, m, P)) best = std::max(best, P.ws_bytes);
+        }
+    }
+    return best;
+}
+
 size_t spectral_table_bytes(const SpecPlan& P) { return align_up(16 * (size_t)table_sizes(P.P).total, 256); }
 
 bool spectral_plan(prony_handle_t h, int d, int n, int m, bool s0, SpecPlan& P, bool batched) {

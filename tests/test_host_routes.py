@@ -1,0 +1,60 @@
+"""Which kernels a call launches and what it allocates, without a GPU: the library runs
+on a recording stand-in for the HIP runtime (hip_recorder.cpp) that serves allocations
+from host memory and records launches by name."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2012_11430_amd import _lib, build as B
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+FP64, FP32, BF16X3 = _lib.PRONY_FP64, _lib.PRONY_FP32, _lib.PRONY_BF16X3
+
+pytestmark = pytest.mark.skipif(not os.path.exists(B.LIB) or not shutil.which("g++"),
+                                reason="needs the built library and g++")
+
+
+class Result:
+    def __init__(self, line):
+        st, allocations, held, *self.kernels = line.split()
+        self.status, self.allocations, self.held = int(st), int(allocations), int(held)
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("recorder") / "hip_recorder")
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(rocm, "include"),
+                    "-I", os.path.join(ROOT, "include"), os.path.join(ROOT, "tests", "hip_recorder.cpp"), "-o", exe,
+                    "-rdynamic", B.LIB, "-Wl,-rpath," + os.path.dirname(B.LIB), "-Wl,--allow-shlib-undefined"],
+                   check=True)
+
+    def run(commands):
+        out = subprocess.run([exe], input="\n".join(commands) + "\n", capture_output=True, text=True, timeout=300)
+        assert out.returncode == 0, out.stderr
+        lines = out.stdout.splitlines()
+        assert len(lines) == len(commands), out.stdout[-500:]
+        return [Result(x) for x in lines]
+    return run
+
+
+@pytest.mark.parametrize("d_max,n_max,m_max", [(3, 10, 17), (3, 10, 18), (2, 63, 20), (3, 20, 32), (1, 300, 25),
+                                               (1, 1100, 9), (3, 9, 64)])
+def test_calls_within_a_reserve_allocate_nothing(recorder, d_max, n_max, m_max):
+    """prony_reserve covers every single-instance call up to its bounds, not the largest
+    shape alone: a workspace that grows later is freed under graphs captured before."""
+    shapes = [(d, n, m) for d in range(1, d_max + 1)
+              for n in sorted({1, 2, 3, 5, 8, 15, 16, 31, 255, 256, n_max - 9, n_max - 1, n_max} & set(range(1, n_max + 1)))
+              for m in sorted({1, 8, 9, 15, 16, 17, 24, 25, 31, 32, m_max - 1, m_max}
+                              & set(range(1, min(m_max, (n + 1) ** d) + 1)))]
+    calls = [f"reserve {d_max} {n_max} {m_max}"]
+    for d, n, m in shapes:
+        if m <= 32:
+            calls += [f"build {d} {n} {m} {prec} {flags}" for prec in (FP64, FP32, BF16X3) for flags in (0, 1)]
+            calls += [f"adjoint {d} {n} {m} {prec}" for prec in (FP64, FP32)]
+        calls.append(f"coeffs {d} {n} {m} 1")
+    done = recorder(["create"] + calls)
+    grew = [(c, r.status, r.allocations) for c, r in zip(calls[1:], done[2:]) if r.status != 0 or r.allocations]
+    assert not grew, f"{len(grew)} of {len(calls) - 1}: {grew[:5]}"
