@@ -317,8 +317,11 @@ prony_status_t prony_coeffs(prony_handle_t handle, int d, int n, int m,
    tile-accumulation type (FP32 or FP64); the diagonal bins and the window sums
    added to gf are FP64. Summation order inside a bin is not fixed (LDS atomics),
    so repeated runs agree to rounding, not bitwise; FP64 gradients with d >= 2 in
-   line-spectral form (see prony_build_S) are the same bits each time. A capture for
-   which only the tiles' workspace is there runs the tiles. Requires 1 <= m <= min(N, 32). */
+   line-spectral form (see prony_build_S) are the same bits each time. There an input
+   that is not finite reaches the points whose terms hold it and no others; the points
+   of the lines it touched are formed again from their own terms, which takes
+   milliseconds at N = 4096 instead of some ten microseconds. A capture for which only
+   the tiles' workspace is there runs the tiles. Requires 1 <= m <= min(N, 32). */
 prony_status_t prony_build_S_adjoint(prony_handle_t handle, int d, int n, int m,
                                      const double* U, int64_t u_rs, int64_t u_cs,
                                      const double* sigma,

@@ -1297,39 +1297,7 @@ __device__ __forceinline__ void adjoint_pair(const SpecPlan& P, const double2* _
     }
 }
 
-// grad(p) from the inputs, component `im` (for results that are not finite, see above).
-__device__ __forceinline__ double direct_gradient(const SpecPlan& P, const SpecAdjPtrs& a, const int (&pt)[3],
-                                                  bool im) {
-    const int E = P.n + 1, m = P.m;
-    double sum = 0.0;
-    for (int l = 0; l < P.d; ++l)
-        for (int k = 0; k < P.N; ++k) {
-            // row k + e_l of T_row meets column h = k + e_l - p
-            int h = 0, rest = k;
-            bool inside = true;
-            for (int axis = P.d - 1, s = 1; axis >= 0; --axis, s *= E) {
-                const int x = rest % E + (axis == l ? 1 : 0) - pt[axis];
-                rest /= E;
-                inside = inside && x >= 0 && x < E;
-                h += s * x;
-            }
-            if (!inside) continue;
-            for (int q = 0; q < m; ++q) {
-                double2 z = make_double2(0.0, 0.0);
-                for (int i = 0; i < m; ++i) {
-                    const double2 u = a.p.U[k * a.p.u_rs + i * a.p.u_cs], c = a.gS[((size_t)l * m + i) * m + q];
-                    z.x += u.x * c.x - u.y * c.y;
-                    z.y += u.x * c.y + u.y * c.x;
-                }
-                const double2 v = a.p.V[h * a.p.v_rs + q * a.p.v_cs];
-                sum += (im ? z.y * v.x - z.x * v.y : z.x * v.x + z.y * v.y) / a.p.sigma[q];
-            }
-            if (sum != sum) return sum;
-        }
-    return sum;
-}
-
-// Writes component `im` of grad(p) where it is finite, else returns true. Points with two
+// Writes component `im` of grad(p) and returns whether it is not finite. Points with two
 // coordinates n + 1, and the point with all coordinates -n, belong to no T_l.
 __device__ __forceinline__ bool store_gradient(const SpecPlan& P, const SpecAdjPtrs& a, const int (&p)[3], bool im,
                                                double x) {
@@ -1341,6 +1309,120 @@ __device__ __forceinline__ bool store_gradient(const SpecPlan& P, const SpecAdjP
     if (P.d == 3) at = at * P.L + p[2] + P.n;
     reinterpret_cast<double*>(a.gf + at)[im] = x;
     return !is_finite(x);
+}
+
+// Whether any thread's `bad` is set; if so, what the workgroup stored before is visible to
+// all of it.
+__device__ __forceinline__ bool any_bad(bool bad) {
+    if (!__syncthreads_or(bad)) return false;
+    __threadfence_block();
+    __syncthreads();
+    return true;
+}
+
+// The gradient's line (p1[, p2], .) from the inputs, by the whole workgroup, where its values
+// are not finite (see above): per kDirect columns q and pair of lines k_o - h_o = p_o, Z
+// (formed once for all points of the line) and V through LDS, a thread per point. A point
+// costs its n m terms per pair, and Z d m^2 per row and pair: d = 2, n = 63, m = 20 with one
+// entry of U not finite (every line at once) takes 24 ms, d = 3, n = 12, m = 11 11 ms. (A thread
+// per point that forms Z anew for each of its terms takes m^2 steps where this takes about m,
+// up to eight points one after another: 10^9 of them at d = 2, n = 239, m = 32.)
+constexpr int kDirect = 4;
+__host__ __device__ inline size_t direct_bytes(int d, int n, int m) {
+    return sizeof(double2) * kDirect * (2 * (size_t)(n + 2) + d * m);
+}
+__device__ __forceinline__ void direct_line(const SpecPlan& P, const SpecAdjPtrs& a, int p1, int p2,
+                                            unsigned char* smem) {
+    const int n = P.n, m = P.m, d = P.d, E = n + 1, tid = threadIdx.x;
+    double2* zs = reinterpret_cast<double2*>(smem);          // [k][kDirect], k <= n + 1
+    double2* vs = zs + (size_t)(n + 2) * kDirect;            // conj V, [h][kDirect]
+    double2* gs = vs + (size_t)(n + 2) * kDirect;            // gS_l Sigma^{-1}, [l][i][kDirect]
+    double2* g = a.gf + (d == 3 ? (int64_t)(p1 + n) * P.L + p2 + n : p1 + n) * P.L;
+    constexpr int kOwn = 2;                                  // 2 n + 2 <= 480 points
+    double2 sum[kOwn];
+    unsigned bad = 0;                                        // bits 2 x, 2 x + 1: point x's components
+#pragma unroll
+    for (int x = 0; x < kOwn; ++x) {
+        sum[x] = make_double2(0.0, 0.0);
+        const int at = tid + kThreads * x;
+        if (at < P.L) bad |= (is_finite(g[at].x) ? 0u : 1u << 2 * x) | (is_finite(g[at].y) ? 0u : 2u << 2 * x);
+    }
+    const int n2 = d == 3 ? min(n + 1, n + p2) - max(0, p2) + 1 : 1;         // lines of axis 2 that meet
+    const int pairs = (min(n + 1, n + p1) - max(0, p1) + 1) * n2;
+    for (int x = 0; x < pairs * ((m + kDirect - 1) / kDirect); ++x) {
+        // done where every sum wanted is NaN
+        bool open = false;
+#pragma unroll
+        for (int y = 0; y < kOwn; ++y)
+            open |= ((bad >> 2 * y & 1) && sum[y].x == sum[y].x) || ((bad >> 2 * y & 2) && sum[y].y == sum[y].y);
+        if (!__syncthreads_or(open)) break;
+        const int q0 = x / pairs * kDirect, pair = x % pairs;
+        if (pair == 0) {
+            for (int e = tid; e < d * m * kDirect; e += kThreads) {
+                const int q = min(q0 + e % kDirect, m - 1);
+                const double2 w = a.gS[(size_t)(e / kDirect) * m + q];
+                gs[e] = make_double2(w.x / a.p.sigma[q], w.y / a.p.sigma[q]);
+            }
+            __syncthreads();
+        }
+        const int k1 = max(0, p1) + pair / n2, k2 = d == 3 ? max(0, p2) + pair % n2 : 0;
+        if (k1 == n + 1 && k2 == n + 1) continue;            // rows of no T_l
+        // rows that some T_l holds: not the origin, one coordinate n + 1 at most
+        const int lo = k1 + k2 == 0 ? 1 : 0, hi = k1 == n + 1 || k2 == n + 1 ? n : n + 1;
+        const int64_t vrow = (int64_t)(d == 3 ? (k1 - p1) * E + k2 - p2 : k1 - p1) * E;
+        for (int e = tid; e < (n + 2) * kDirect; e += kThreads) {
+            const int k = e / kDirect, q = q0 + e % kDirect;
+            double2 z = make_double2(0.0, 0.0), v = z;
+            if (k >= lo && k <= hi && q < m)
+                for (int l = 0; l < d; ++l) {
+                    const int c[3] = {k1, d == 3 ? k2 : k, k};
+                    bool inside = true;
+                    int row = 0;
+                    for (int axis = 0; axis < d; ++axis) {
+                        const int y = c[axis] - (axis == l ? 1 : 0);
+                        inside = inside && y >= 0 && y <= n;
+                        row = row * E + y;
+                    }
+                    if (!inside) continue;
+#pragma unroll 8
+                    for (int i = 0; i < m; ++i) {
+                        const double2 u = a.p.U[row * a.p.u_rs + i * a.p.u_cs];
+                        const double2 w = gs[(l * m + i) * kDirect + e % kDirect];
+                        z.x = fma(u.x, w.x, fma(-u.y, w.y, z.x));
+                        z.y = fma(u.x, w.y, fma(u.y, w.x, z.y));
+                    }
+                }
+            if (k <= n && q < m) v = a.p.V[(vrow + k) * a.p.v_rs + q * a.p.v_cs];
+            zs[e] = z;
+            vs[e] = make_double2(v.x, -v.y);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int y = 0; y < kOwn; ++y) {
+            const int p = tid + kThreads * y - n;
+            if (!(bad >> 2 * y & 3)) continue;
+            const int h1 = min(n, hi - p);
+#pragma unroll 2
+            for (int h = max(0, lo - p); h <= h1; ++h) {
+                double2 t = make_double2(0.0, 0.0);
+#pragma unroll
+                for (int c = 0; c < kDirect; ++c) {
+                    const double2 z = zs[(h + p) * kDirect + c], v = vs[h * kDirect + c];
+                    t.x = fma(z.x, v.x, fma(-z.y, v.y, t.x));
+                    t.y = fma(z.x, v.y, fma(z.y, v.x, t.y));
+                }
+                sum[y].x += t.x;
+                sum[y].y += t.y;
+            }
+        }
+    }
+#pragma unroll
+    for (int x = 0; x < kOwn; ++x) {
+        const int at = tid + kThreads * x;
+        if (bad >> 2 * x & 1) g[at].x = sum[x].x;
+        if (bad >> 2 * x & 2) g[at].y = sum[x].y;
+    }
+    __syncthreads();
 }
 
 // Inverse transform of g~ at the points +-j, j = 0..P, of a transformed axis: C +- S with
@@ -1363,6 +1445,7 @@ __device__ __forceinline__ void adjoint_lines(const SpecPlan& P, const SpecAdjPt
     }
     __syncthreads();
     const double scale = 1.0 / P.F;
+    bool bad = false;
     for (int rb = wave; 16 * rb < K; rb += kWaves) {
         const double2* f = a.p.tab + T.off_g + (size_t)rb * KS * 64 + lane;
         const double* x1 = reinterpret_cast<const double*>(xc) + 16 * g + col;
@@ -1377,22 +1460,16 @@ __device__ __forceinline__ void adjoint_lines(const SpecPlan& P, const SpecAdjPt
                 as = M::fma(t.y, x2[64 * (s + k)], as);
             }
         const int t = kCols * blk + (col >> 1);
-        unsigned bad = 0;
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
             const int j = 16 * rb + M::row(g, r >> 1);
             const double x = (r & 1 ? ac[r >> 1] - as[r >> 1] : ac[r >> 1] + as[r >> 1]) * scale;
             const int pt[3] = {t - P.n, r & 1 ? -j : j, 0};
-            if (t < P.NP1 && j < K && (!(r & 1) || (j > 0 && j < P.P)))
-                bad |= store_gradient(P, a, pt, col & 1, x) ? 1u << r : 0u;
+            if (t < P.NP1 && j < K && (!(r & 1) || (j > 0 && j < P.P))) bad |= store_gradient(P, a, pt, col & 1, x);
         }
-        for (int r = 0; __builtin_expect(bad != 0, 0); ++r, bad >>= 1)
-            if (bad & 1) {
-                const int j = 16 * rb + M::row(g, r >> 1);
-                const int pt[3] = {t - P.n, r & 1 ? -j : j, 0};
-                store_gradient(P, a, pt, col & 1, direct_gradient(P, a, pt, col & 1));
-            }
     }
+    if (__builtin_expect(any_bad(bad), 0))
+        for (int t = kCols * blk; t < min(kCols * (blk + 1), P.NP1); ++t) direct_line(P, a, t - P.n, 0, smem);
 }
 
 // d = 3: the points +-j of axis 2, j in part `split`, of sample line t: axis 2 into LDS
@@ -1466,6 +1543,7 @@ __device__ __forceinline__ void adjoint_planes(const SpecPlan& P, const SpecAdjP
     __syncthreads();
     const int nc2 = 2 * kn, nb2 = (nc2 + 7) >> 3, nrb = (K + 15) >> 4;
     const double scale = 1.0 / P.F;
+    bool bad = false;
     for (int it = wave; it < nb2 * nrb; it += kWaves) {
         const int nb = it / nrb, rb = it - nb * nrb;
         const double2* f = tab + (size_t)rb * KS * 64 + lane;
@@ -1481,22 +1559,19 @@ __device__ __forceinline__ void adjoint_planes(const SpecPlan& P, const SpecAdjP
         const bool mirror = c & 1;
         const int p2 = mirror ? -j2 : j2;
         const bool ok = c < nc2 && (!mirror || (j2 > 0 && j2 < P.P));
-        unsigned bad = 0;
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
             const int j = 16 * rb + M::row(g, r >> 1);
             const double x = (r & 1 ? ac[r >> 1] - as[r >> 1] : ac[r >> 1] + as[r >> 1]) * scale;
             const int pt[3] = {t - P.n, p2, r & 1 ? -j : j};
-            if (ok && j < K && (!(r & 1) || (j > 0 && j < P.P)))
-                bad |= store_gradient(P, a, pt, col & 1, x) ? 1u << r : 0u;
+            if (ok && j < K && (!(r & 1) || (j > 0 && j < P.P))) bad |= store_gradient(P, a, pt, col & 1, x);
         }
-        for (int r = 0; __builtin_expect(bad != 0, 0); ++r, bad >>= 1)
-            if (bad & 1) {
-                const int j = 16 * rb + M::row(g, r >> 1);
-                const int pt[3] = {t - P.n, p2, r & 1 ? -j : j};
-                store_gradient(P, a, pt, col & 1, direct_gradient(P, a, pt, col & 1));
-            }
     }
+    if (__builtin_expect(any_bad(bad), 0))
+        for (int c = 0; c < 2 * kn; ++c) {
+            const int j2 = j0 + (c >> 1);
+            if (!(c & 1) || (j2 > 0 && j2 < P.P)) direct_line(P, a, t - P.n, c & 1 ? -j2 : j2, smem);
+        }
 }
 
 template <int NQB>
@@ -1758,6 +1833,7 @@ bool spectral_adjoint_plan(prony_handle_t h, int d, int n, int m, SpecPlan& P, b
         P.wgs_i = P.NP1 * P.isplits;
         P.lds_inv = 2 * 8 * (size_t)(4 * table_sizes(P.P).ks_g) * plane_stride(2 * P.irows);
     }
+    P.lds_inv = std::max(P.lds_inv, direct_bytes(d, n, m));
     if (P.lds_gram > budget || P.lds_inv > budget) return false;
     const size_t x = align_up(16 * (size_t)P.F * P.K1 * m, 256);
     P.off_v = x;
