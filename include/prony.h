@@ -341,8 +341,10 @@ prony_status_t prony_build_S_adjoint(prony_handle_t handle, int d, int n, int m,
    prec: arithmetic and tile-accumulation type (FP32 or FP64): MFMA tiles, or vector
          FMAs when r = 1 (one Lanczos step's product); the chunk partials are added
          in FP64 in a fixed order (bitwise reproducible). FP64 runs in line-spectral
-         form where it fits (see prony_build_S; bitwise reproducible too); a
-         non-finite sample then reaches every entry of Y. Requires 1 <= r <= 64.
+         form where it fits (see prony_build_S; bitwise reproducible too). An entry of f or
+         X that is not finite reaches the entries of Y whose terms hold it and no others;
+         there those its transforms touched are summed again one by one (d=2, n=63, r=40
+         with one NaN sample: 1 ms instead of 0.02). Requires 1 <= r <= 64.
    Uses the handle's workspace (grown as needed; PRONY_ECAPTURE if it must grow
    under stream capture). */
 prony_status_t prony_toeplitz_mm(prony_handle_t handle, int d, int n, int adjoint, const double* f, int r,

@@ -850,19 +850,44 @@ __device__ __forceinline__ int64_t grid_centre(const SpecPlan& P) {
     return P.n * (P.d == 1 ? 1 : P.d == 2 ? 1 + Q : 1 + Q + Q * Q);
 }
 
-// (T X)[k, q] or (T^* X)[k, q], component `im`.
-__device__ __forceinline__ double direct_product(const SpecPlan& P, const SpecPtrs& p, bool adjoint, int k, int q,
-                                                 bool im) {
-    const int64_t ok = grid_offset(P, k), centre = grid_centre(P);
-    double sum = 0.0;
-    for (int h = 0; h < P.N; ++h) {
-        const int64_t o = grid_offset(P, h);
-        const double2 f = p.f[centre + (adjoint ? o - ok : ok - o)], x = p.V[h * p.v_rs + q * p.v_cs];
-        const double fy = adjoint ? -f.y : f.y;
-        sum += im ? fma(f.x, x.y, fy * x.x) : fma(f.x, x.x, -fy * x.y);
-        if (sum != sum) break;
+// Whether any thread's `bad` is set (`flag`, in LDS, is zero before); if so, what the
+// workgroup stored before is visible to all of it. Else no wait for the stores: a barrier that
+// waits for them, like __syncthreads_or, took 1 us of a gradient's 16 to 35.
+__device__ __forceinline__ bool any_bad(bool bad, int* flag) {
+    if (bad) *flag = 1;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    if (!*static_cast<volatile int*>(flag)) return false;
+    __threadfence_block();
+    __syncthreads();
+    return true;
+}
+
+// The components of (T X)[k, q] or (T^* X)[k, q] at `y` that are not finite, from the
+// inputs: N terms, loads in flight for several at a time.
+__device__ __forceinline__ void direct_product(const SpecPlan& P, const SpecPtrs& p, bool adjoint, int k, int q,
+                                               double2* y) {
+    const bool fix_x = !is_finite(y->x), fix_y = !is_finite(y->y);
+    if (!fix_x && !fix_y) return;
+    const int64_t row = grid_centre(P) + (adjoint ? -grid_offset(P, k) : grid_offset(P, k));
+    const double2* x = p.V + q * p.v_cs;
+    const int line = P.d == 1 ? P.N : P.n + 1, step = adjoint ? 1 : -1;
+    double re = 0.0, im = 0.0;
+    for (int h0 = 0; h0 < P.N; h0 += line) {
+        const double2* f = p.f + row + step * grid_offset(P, h0);
+        const double2* xl = x + h0 * p.v_rs;
+#pragma unroll 8
+        for (int h = 0; h < line; ++h) {
+            const double2 a = f[(int64_t)step * h], b = xl[h * p.v_rs];
+            const double ay = adjoint ? -a.y : a.y;
+            re = fma(a.x, b.x, fma(-ay, b.y, re));
+            im = fma(a.x, b.y, fma(ay, b.x, im));
+        }
+        if ((!fix_x || re != re) && (!fix_y || im != im)) break;
     }
-    return sum;
+    if (fix_x) y->x = re;
+    if (fix_y) y->y = im;
 }
 
 // Inverse transforms about the line's centre (see the folded forward ones): at t = j + 1/2
@@ -883,6 +908,8 @@ __device__ __forceinline__ void pair_in(bool zero, bool odd, double a, double b,
 __global__ __launch_bounds__(kThreads) void spectral_inverse_lines(SpecPlan P, SpecPtrs p, double2* __restrict__ Y,
                                                                    int64_t ld, int adjoint) {
     extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ int bad_flag;
+    if (threadIdx.x == 0) bad_flag = 0;
     const int NC = P.K1 * P.m, KS = (P.P + 3) >> 2, J = line_rows(P.P), H = folded_points(P.P, false);
     const int nblk = (NC + kCols - 1) / kCols, nb0 = blockIdx.x * P.nbi, nbc = min(P.nbi, nblk - nb0);
     double2* xc = reinterpret_cast<double2*>(smem);
@@ -925,6 +952,7 @@ __global__ __launch_bounds__(kThreads) void spectral_inverse_lines(SpecPlan P, S
         }
     }
     __syncthreads();
+    bool bad = false;
     for (int it = wave; it < nbc * nrb; it += kWaves) {
         const int nb = it / nrb, rb = it - nb * nrb;
         const double* x1 = reinterpret_cast<const double*>(xc + (size_t)nb * J * kCols) + 16 * g + col;
@@ -948,7 +976,6 @@ __global__ __launch_bounds__(kThreads) void spectral_inverse_lines(SpecPlan P, S
         const int cx = kCols * (nb0 + nb) + (col >> 1);
         const int t = cx / P.m, q = cx - t * P.m;
         double* o = reinterpret_cast<double*>(Y) + 2 * q + (col & 1);
-        bool bad = false;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int j = 16 * rb + M::row(g, r);
@@ -960,14 +987,13 @@ __global__ __launch_bounds__(kThreads) void spectral_inverse_lines(SpecPlan P, S
                 if (ib < P.N) o[2 * ib * ld] = yb;
             }
         }
-        if (__builtin_expect(bad, 0))
-            for (int r = 0; r < 8; ++r) {
-                const int j = 16 * rb + M::row(g, r >> 1);
-                const int i = t * P.P + (r & 1 ? H - 1 - j : H + j);
-                if (j >= H || (!(r & 1) && H + j >= P.P) || i >= P.N || is_finite(o[2 * i * ld])) continue;
-                o[2 * i * ld] = direct_product(P, p, adjoint, i, q, col & 1);
-            }
     }
+    // the workgroup's results that are not finite, a thread each
+    if (__builtin_expect(any_bad(bad, &bad_flag), 0))
+        for (int e = tid; e < kCols * nbc * P.P; e += kThreads) {
+            const int c = kCols * nb0 + e / P.P, t = c / P.m, q = c - t * P.m, i = t * P.P + e % P.P;
+            if (c < NC && i < P.N) direct_product(P, p, adjoint, i, q, Y + i * ld + q);
+        }
 }
 
 // Two transformed axes (d = 3): the rows k2 = H + j, H - 1 - j, j in part `split`, of one
@@ -975,6 +1001,8 @@ __global__ __launch_bounds__(kThreads) void spectral_inverse_lines(SpecPlan P, S
 __global__ __launch_bounds__(kThreads) void spectral_inverse_planes(SpecPlan P, SpecPtrs p, double2* __restrict__ Y,
                                                                     int64_t ld, int adjoint) {
     extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ int bad_flag;
+    if (threadIdx.x == 0) bad_flag = 0;
     const int per = (P.m + P.nqi - 1) / P.nqi;
     const int split = blockIdx.x % P.isplits, rest0 = blockIdx.x / P.isplits;
     const int q0 = rest0 % per * P.nqi, line = rest0 / per, nq = min(P.nqi, P.m - q0);
@@ -1054,6 +1082,7 @@ __global__ __launch_bounds__(kThreads) void spectral_inverse_planes(SpecPlan P, 
     __syncthreads();
     // axis 3: columns c = (2 j + side) * nq + q
     const int nc2 = 2 * kn * nq, nb2 = (nc2 + 7) >> 3, nrb = (H + 15) >> 4;
+    bool bad = false;
     for (int it = wave; it < nb2 * nrb; it += kWaves) {
         const int nb = it / nrb, rb = it - nb * nrb;
         const double2* tab3 = tab + (size_t)rb * KS * 64 + lane;
@@ -1081,7 +1110,6 @@ __global__ __launch_bounds__(kThreads) void spectral_inverse_planes(SpecPlan P, 
         const int c = 8 * nb + (col >> 1), kk = c / nq, q = c - kk * nq;
         const int k2 = kk & 1 ? H - 1 - j0 - (kk >> 1) : H + j0 + (kk >> 1);
         double* o = reinterpret_cast<double*>(Y) + 2 * (((int64_t)line * P.P + k2) * P.P * ld + q0 + q) + (col & 1);
-        bool bad = false;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int j = 16 * rb + M::row(g, r);
@@ -1092,13 +1120,14 @@ __global__ __launch_bounds__(kThreads) void spectral_inverse_planes(SpecPlan P, 
                 o[2 * (H - 1 - j) * ld] = yb;
             }
         }
-        if (__builtin_expect(bad, 0))
-            for (int r = 0; r < 8; ++r) {
-                const int j = 16 * rb + M::row(g, r >> 1), k3 = r & 1 ? H - 1 - j : H + j;
-                if (j >= H || k3 >= P.P || is_finite(o[2 * k3 * ld])) continue;
-                o[2 * k3 * ld] = direct_product(P, p, adjoint, (line * P.P + k2) * P.P + k3, q0 + q, col & 1);
-            }
     }
+    if (__builtin_expect(any_bad(bad, &bad_flag), 0))
+        for (int e = tid; e < nc2 * P.P; e += kThreads) {
+            const int c = e / P.P, k3 = e % P.P, kk = c / nq, q = q0 + c - kk * nq;
+            const int k2 = kk & 1 ? H - 1 - j0 - (kk >> 1) : H + j0 + (kk >> 1);
+            const int i = (line * P.P + k2) * P.P + k3;
+            if (k2 < P.P) direct_product(P, p, adjoint, i, q, Y + i * ld + q);
+        }
 }
 
 // ---- adjoint -----------------------------------------------------------------
@@ -1311,15 +1340,6 @@ __device__ __forceinline__ bool store_gradient(const SpecPlan& P, const SpecAdjP
     return !is_finite(x);
 }
 
-// Whether any thread's `bad` is set; if so, what the workgroup stored before is visible to
-// all of it.
-__device__ __forceinline__ bool any_bad(bool bad) {
-    if (!__syncthreads_or(bad)) return false;
-    __threadfence_block();
-    __syncthreads();
-    return true;
-}
-
 // The gradient's line (p1[, p2], .) from the inputs, by the whole workgroup, where its values
 // are not finite (see above): per kDirect columns q and pair of lines k_o - h_o = p_o, Z
 // (formed once for all points of the line) and V through LDS, a thread per point. A point
@@ -1333,7 +1353,10 @@ __host__ __device__ inline size_t direct_bytes(int d, int n, int m) {
 }
 __device__ __forceinline__ void direct_line(const SpecPlan& P, const SpecAdjPtrs& a, int p1, int p2,
                                             unsigned char* smem) {
-    const int n = P.n, m = P.m, d = P.d, E = n + 1, tid = threadIdx.x;
+    // (opaque, so that nothing of this rare path is computed before it is taken)
+    int n = P.n, m = P.m;
+    asm volatile("" : "+s"(n), "+s"(m));
+    const int d = P.d, E = n + 1, tid = threadIdx.x;
     double2* zs = reinterpret_cast<double2*>(smem);          // [k][kDirect], k <= n + 1
     double2* vs = zs + (size_t)(n + 2) * kDirect;            // conj V, [h][kDirect]
     double2* gs = vs + (size_t)(n + 2) * kDirect;            // gS_l Sigma^{-1}, [l][i][kDirect]
@@ -1430,6 +1453,8 @@ __device__ __forceinline__ void direct_line(const SpecPlan& P, const SpecAdjPtrs
 // those of the sample grid's forward transform with rows and contraction exchanged.
 // d = 2: 8 sample lines per workgroup.
 __device__ __forceinline__ void adjoint_lines(const SpecPlan& P, const SpecAdjPtrs& a, int blk, unsigned char* smem) {
+    __shared__ int bad_flag;
+    if (threadIdx.x == 0) bad_flag = 0;
     const TableSizes T = table_sizes(P.P);
     const int K = P.P + 1, KS = T.ks_g, J = line_rows(K);
     double2* xc = reinterpret_cast<double2*>(smem);
@@ -1468,7 +1493,7 @@ __device__ __forceinline__ void adjoint_lines(const SpecPlan& P, const SpecAdjPt
             if (t < P.NP1 && j < K && (!(r & 1) || (j > 0 && j < P.P))) bad |= store_gradient(P, a, pt, col & 1, x);
         }
     }
-    if (__builtin_expect(any_bad(bad), 0))
+    if (__builtin_expect(any_bad(bad, &bad_flag), 0))
         for (int t = kCols * blk; t < min(kCols * (blk + 1), P.NP1); ++t) direct_line(P, a, t - P.n, 0, smem);
 }
 
@@ -1476,6 +1501,8 @@ __device__ __forceinline__ void adjoint_lines(const SpecPlan& P, const SpecAdjPt
 // as the operands of axis 3's pairs u = 0..P, then axis 3.
 __device__ __forceinline__ void adjoint_planes(const SpecPlan& P, const SpecAdjPtrs& a, int t, int split,
                                                unsigned char* smem) {
+    __shared__ int bad_flag;
+    if (threadIdx.x == 0) bad_flag = 0;
     const TableSizes T = table_sizes(P.P);
     const int K = P.P + 1, KS = T.ks_g;
     const int j0 = split * P.irows, kn = min(P.irows, K - j0);
@@ -1567,7 +1594,7 @@ __device__ __forceinline__ void adjoint_planes(const SpecPlan& P, const SpecAdjP
             if (ok && j < K && (!(r & 1) || (j > 0 && j < P.P))) bad |= store_gradient(P, a, pt, col & 1, x);
         }
     }
-    if (__builtin_expect(any_bad(bad), 0))
+    if (__builtin_expect(any_bad(bad, &bad_flag), 0))
         for (int c = 0; c < 2 * kn; ++c) {
             const int j2 = j0 + (c >> 1);
             if (!(c & 1) || (j2 > 0 && j2 < P.P)) direct_line(P, a, t - P.n, c & 1 ? -j2 : j2, smem);

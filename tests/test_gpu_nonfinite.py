@@ -87,3 +87,35 @@ def test_gradients_with_one_entry_not_finite(d, n, m, where, bad):
     if not flat.all():
         assert_close(got[~flat], ref[~flat], 1e-12, "points without the entry")
     assert ms < 100.0
+
+
+@pytest.mark.parametrize("d,n,r", [(1, 40, 3), (1, 1000, 4), (2, 17, 9), (2, 63, 40), (3, 6, 12), (3, 12, 9), (3, 20, 1)])
+@pytest.mark.parametrize("adjoint", [False, True])
+@pytest.mark.parametrize("where", ["f", "X"])
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_products_with_one_entry_not_finite(d, n, r, adjoint, where, bad):
+    from tests.test_gpu_spectral import _fft_product
+    rng = np.random.Generator(np.random.PCG64(8900 + 10 * n + d))
+    N, E = (n + 1) ** d, n + 1
+    grid, X = _cn(rng, (2 * n + 2) ** d), _cn(rng, N, r)
+    ref = _fft_product(grid, d, n, X, adjoint)
+    hit = np.zeros((N, r), dtype=bool)                    # results whose terms hold the entry
+    if where == "X":
+        X[N // 2, r - 1] = bad
+        hit[:, r - 1] = True
+    else:
+        p = np.array([n // 2] + [-(n // 3)] * (d - 1))    # a sample f(p): T[k, k - p]
+        grid[np.ravel_multi_index(tuple(p + n), (2 * n + 2,) * d)] = bad
+        k = np.stack(np.meshgrid(*[np.arange(E)] * d, indexing="ij"), -1).reshape(-1, d)
+        other = k + p if adjoint else k - p
+        hit[np.all((other >= 0) & (other <= n), axis=1)] = True
+    print(f"product d={d} n={n} r={r} adjoint={adjoint} {where} {bad}", flush=True)
+    f, Xd = _dev(grid), _dev(X)
+    api.toeplitz_mm(f, d, n, Xd, adjoint=adjoint)
+    got, ms = _timed(lambda: api.toeplitz_mm(f, d, n, Xd, adjoint=adjoint))
+    print(f"  {ms:.2f} ms", flush=True)
+    got = got.cpu().numpy()
+    assert np.array_equal(~np.isfinite(got), hit)
+    if not hit.all():
+        assert_close(got[~hit], ref[~hit], 1e-12, "results without the entry")
+    assert ms < 100.0
