@@ -219,7 +219,7 @@ prony_status_t prony_build_T(prony_handle_t handle, int d, int n, int which,
            at S + 2*((l*m + i)*m + j), l counted from the first stored matrix.
    Requires 1 <= m <= min(N, 32).
    PRONY_FP64 runs in line-spectral form where it fits (lines of at most 240 points and
-   1 GiB of workspace): DFTs of length 2(n+1) along the axes 2..d (d = 1: along folded
+   1 GiB of workspace that can be had; under capture, that is there): DFTs of length 2(n+1) along the axes 2..d (d = 1: along folded
    lines), then one-dimensional Toeplitz products per frequency, all in FP64. Other
    shapes and precisions run the MFMA tiles on the undivided product. */
 prony_status_t prony_build_S(prony_handle_t handle, int d, int n, int m, const double* f,
@@ -320,8 +320,7 @@ prony_status_t prony_coeffs(prony_handle_t handle, int d, int n, int m,
    line-spectral form (see prony_build_S) are the same bits each time. There an input
    that is not finite reaches the points whose terms hold it and no others; the points
    of the lines it touched are formed again from their own terms, which takes
-   milliseconds at N = 4096 instead of some ten microseconds. A capture for which only
-   the tiles' workspace is there runs the tiles. Requires 1 <= m <= min(N, 32). */
+   milliseconds at N = 4096 instead of some ten microseconds. Requires 1 <= m <= min(N, 32). */
 prony_status_t prony_build_S_adjoint(prony_handle_t handle, int d, int n, int m,
                                      const double* U, int64_t u_rs, int64_t u_cs,
                                      const double* sigma,

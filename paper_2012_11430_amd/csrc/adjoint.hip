@@ -701,14 +701,13 @@ extern "C" prony_status_t prony_build_S_adjoint(prony_handle_t h, int d, int n, 
         return launch_adjoint<float>(h, P, U, u_rs, u_cs, sigma, V, v_rs, v_cs, gS, gf);
     }
     if ((st = make_adj_plan(h, d, n, m, sizeof(double), P)) != PRONY_OK) return st;
-    // FP64 in line-spectral form where it applies; a shape the tiles cannot cover is refused
-    // above, and a capture that the tiles' workspace would do for runs them
+    // in line-spectral form where it applies (a shape the tiles cannot cover is refused above)
     SpecPlan SP;
-    if (spectral_adjoint_plan(h, d, n, m, SP) && workspace_available(h, SP.ws_bytes, P.ws_bytes)) {
-        if ((st = ensure_workspace(h, SP.ws_bytes)) != PRONY_OK) return st;
+    bool spectral = spectral_adjoint_plan(h, d, n, m, SP);
+    if ((st = ensure_form(h, SP.ws_bytes, P.ws_bytes, spectral)) != PRONY_OK) return st;
+    if (spectral)
         return spectral_adjoint_run(h, SP, static_cast<unsigned char*>(h->ws), U, u_rs, u_cs, sigma, V, v_rs, v_cs,
                                     gS, gf);
-    }
     return launch_adjoint<double>(h, P, U, u_rs, u_cs, sigma, V, v_rs, v_cs, gS, gf);
 }
 

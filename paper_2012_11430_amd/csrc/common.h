@@ -76,9 +76,10 @@ struct DeviceGuard {
 // needed while the handle's stream is being captured.
 prony_status_t ensure_workspace(prony_handle_t h, size_t bytes);
 
-// Whether the workspace can hold `bytes`: it does already, or it may grow (the stream
-// is not being captured), or it would have to grow for the `other` form as well.
-bool workspace_available(prony_handle_t h, size_t bytes, size_t other);
+// The workspace of an FP64 call in line-spectral form, or, where that cannot be had (it would
+// have to grow under stream capture, or the memory is not there) and the tiles need less, the
+// tiles' workspace: `spectral` says for which form it is in place.
+prony_status_t ensure_form(prony_handle_t h, size_t spectral_bytes, size_t tiles_bytes, bool& spectral);
 
 // Brackets one kernel launch with profiling events when the handle profiles `name`.
 class ProfileScope {

@@ -56,10 +56,14 @@ prony_status_t ensure_workspace(prony_handle_t h, size_t bytes) {
     return PRONY_OK;
 }
 
-bool workspace_available(prony_handle_t h, size_t bytes, size_t other) {
-    if (bytes <= h->ws_bytes || other > h->ws_bytes) return true;
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(h->stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone;
+prony_status_t ensure_form(prony_handle_t h, size_t spectral_bytes, size_t tiles_bytes, bool& spectral) {
+    if (spectral) {
+        const prony_status_t st = ensure_workspace(h, spectral_bytes);
+        if ((st != PRONY_ECAPTURE && st != PRONY_ENOMEM) || tiles_bytes >= spectral_bytes) return st;
+        h->err.clear();
+        spectral = false;
+    }
+    return ensure_workspace(h, tiles_bytes);
 }
 
 static hipEvent_t next_event(prony_handle_t h) {

@@ -1832,8 +1832,7 @@ extern "C" prony_status_t prony_build_S(prony_handle_t h, int d, int n, int m, c
     if (st != PRONY_OK) return st;
     DeviceGuard g(h->device);
     if (!g.ok) return fail(h, PRONY_EHIP, "hipSetDevice failed");
-    if (B.spectral && !workspace_available(h, B.SP.ws_bytes, B.P.ws_bytes)) B.spectral = false;
-    if ((st = ensure_workspace(h, B.ws_bytes())) != PRONY_OK) return st;
+    if ((st = ensure_form(h, B.SP.ws_bytes, B.P.ws_bytes, B.spectral)) != PRONY_OK) return st;
     return run_build_S(h, B, static_cast<unsigned char*>(h->ws), prec, f, U, u_rs, u_cs, sigma, V, v_rs, v_cs, S);
 }
 
@@ -1910,20 +1909,35 @@ extern "C" prony_status_t prony_factors_create(prony_handle_t h, int d, int n, i
     if (!F) return fail(h, PRONY_ENOMEM, "prony_factors_create: out of host memory");
     F->device = h->device;
     F->prec = prec;
-    F->B = B;
-    F->off_sigma = B.factor_bytes();
-    e = hipMalloc(reinterpret_cast<void**>(&F->mem), F->off_sigma + align_up(sizeof(double) * (size_t)m, 256));
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
+    auto allocate = [&]() -> prony_status_t {
+        F->B = B;
+        F->off_sigma = B.factor_bytes();
+        e = hipMalloc(reinterpret_cast<void**>(&F->mem), F->off_sigma + align_up(sizeof(double) * (size_t)m, 256));
+        if (e != hipSuccess) {
+            F->mem = nullptr;
+            (void)hipGetLastError();
+            return fail(h, PRONY_ENOMEM,
+                        std::string("prony_factors_create: hipMalloc failed: ") + hipGetErrorString(e));
+        }
+        // in line-spectral form also the tables, should the handle not be able to keep them
+        const prony_status_t s = B.spectral ? ensure_workspace(h, spectral_table_bytes(B.SP)) : PRONY_OK;
+        if (s != PRONY_OK) (void)hipFree(F->mem);
+        return s;
+    };
+    st = allocate();
+    if (st == PRONY_ENOMEM && B.spectral && B.P.off_p < B.SP.off_f) {     // the tiles keep less
+        h->err.clear();
+        B.spectral = false;
+        st = allocate();
+    }
+    if (st != PRONY_OK) {
         delete F;
-        return fail(h, PRONY_ENOMEM, std::string("prony_factors_create: hipMalloc failed: ") + hipGetErrorString(e));
+        return st;
     }
     if (B.spectral) {
-        // the tables in the workspace, should the handle not be able to keep them
-        st = ensure_workspace(h, spectral_table_bytes(B.SP));
         SpecPtrs p = spectral_ptrs(B.SP, F->mem, nullptr, nullptr, U, u_rs, u_cs, sigma, V, v_rs, v_cs, nullptr);
         p.tables = static_cast<double2*>(h->ws);
-        if (st == PRONY_OK) st = spectral_forward(h, B.SP, p, true, false, true);
+        st = spectral_forward(h, B.SP, p, true, false, true);
     } else {
         st = prec == PRONY_FP64 ? pack_operands<double>(h, B.P, F->mem, U, u_rs, u_cs, V, v_rs, v_cs)
                                 : pack_operands<float>(h, B.P, F->mem, U, u_rs, u_cs, V, v_rs, v_cs);
@@ -2465,14 +2479,13 @@ extern "C" prony_status_t prony_toeplitz_mm(prony_handle_t h, int d, int n, int 
         st = make_plan(h, d, n, r, false, ts, P, target, 0, 1, false, true);
     if (st != PRONY_OK) return st;
     P.conj_grid = adjoint;
-    // FP64 in line-spectral form where it applies; a shape the tiles cannot cover is
-    // refused above, and a capture that the workspace of the tiles would do for runs them
+    // FP64 in line-spectral form where it applies (a shape the tiles cannot cover is refused
+    // above)
     SpecPlan SP;
-    if (prec == PRONY_FP64 && spectral_product_plan(h, d, n, r, SP) &&
-        workspace_available(h, SP.ws_bytes, P.ws_bytes)) {
-        if ((st = ensure_workspace(h, SP.ws_bytes)) != PRONY_OK) return st;
+    bool spectral = prec == PRONY_FP64 && spectral_product_plan(h, d, n, r, SP);
+    if ((st = ensure_form(h, SP.ws_bytes, P.ws_bytes, spectral)) != PRONY_OK) return st;
+    if (spectral)
         return spectral_product(h, SP, static_cast<unsigned char*>(h->ws), f, X, ldx, adjoint != 0, Y, ldy);
-    }
     return prec == PRONY_FP32 ? launch_toeplitz_mm<float>(h, P, f, X, ldx, Y, ldy)
                               : launch_toeplitz_mm<double>(h, P, f, X, ldx, Y, ldy);
 }

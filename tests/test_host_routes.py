@@ -58,3 +58,27 @@ def test_calls_within_a_reserve_allocate_nothing(recorder, d_max, n_max, m_max):
     done = recorder(["create"] + calls)
     grew = [(c, r.status, r.allocations) for c, r in zip(calls[1:], done[2:]) if r.status != 0 or r.allocations]
     assert not grew, f"{len(grew)} of {len(calls) - 1}: {grew[:5]}"
+
+
+@pytest.mark.parametrize("call,limit,kernel", [
+    (f"adjoint 3 20 20 {FP64}", 11 << 20, "adjoint_tiles<double"),
+    (f"adjoint 2 127 32 {FP64}", 22 << 20, "adjoint_tiles<double"),
+    (f"build 3 12 20 {FP64} 1", 9 << 20, "pencil_tiles<double"),
+    (f"build 3 9 20 {FP64} 0", 3 << 20, "pencil_tiles<double"),
+    (f"factors 3 20 20 {FP64} 0", 11 << 20, "pencil_pack<double>"),
+    (f"factors 2 127 32 {FP64} 1", 17 << 20, "pencil_pack<double>")])
+def test_calls_whose_line_spectral_memory_cannot_be_had_run_the_tiles(recorder, call, limit, kernel):
+    """The limits (bytes that may be held) are enough for the tile kernels and not for the
+    line-spectral form, which runs without a limit."""
+    tune = [f"tune {d} {n} {m} {FP64} 1 64" for d, n, m in ((3, 12, 20), (3, 9, 20))]   # few partial rows
+    few = recorder(["create"] + tune + [f"limit {limit}", call, "destroy"])
+    assert few[-2].status == 0 and few[-2].held <= limit and kernel in " ".join(few[-2].kernels), vars(few[-2])
+    all_of_it = recorder(["create"] + tune + [call])[-1]
+    assert all_of_it.status == 0 and all_of_it.held > limit and "spectral" in " ".join(all_of_it.kernels)
+
+
+def test_factors_packed_for_the_tiles_build_and_are_released(recorder):
+    done = recorder(["create", f"limit {11 << 20}", f"factors 3 20 20 {FP64} 0", "limit 1000000000", "build_factors",
+                     "free_factors", "destroy"])
+    assert [r.status for r in done] == [0] * 7 and done[-1].held == 0
+    assert done[4].kernels[0].startswith("pencil_tiles<double") and done[4].kernels[1].startswith("pencil_finish<double")
