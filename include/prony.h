@@ -219,9 +219,10 @@ prony_status_t prony_build_T(prony_handle_t handle, int d, int n, int which,
            at S + 2*((l*m + i)*m + j), l counted from the first stored matrix.
    Requires 1 <= m <= min(N, 32).
    PRONY_FP64 runs in line-spectral form where it fits (lines of at most 240 points and
-   1 GiB of workspace that can be had; under capture, that is there): DFTs of length 2(n+1) along the axes 2..d (d = 1: along folded
-   lines), then one-dimensional Toeplitz products per frequency, all in FP64. Other
-   shapes and precisions run the MFMA tiles on the undivided product. */
+   1 GiB of workspace that can be had; under capture, that is there): DFTs of length
+   2(n+1) along the axes 2..d (d = 1: along folded lines), then one-dimensional Toeplitz
+   products per frequency, all in FP64. Other shapes and precisions run the MFMA tiles on
+   the undivided product. */
 prony_status_t prony_build_S(prony_handle_t handle, int d, int n, int m, const double* f,
                              const double* U, int64_t u_rs, int64_t u_cs,
                              const double* sigma,
@@ -379,8 +380,9 @@ typedef struct {
    tiles (longest first), allocates the batch's own device workspace and uploads
    its work tables (synchronously on the handle's stream). Errors name the
    offending instance. FP64 batches run in line-spectral form (prony_build_S)
-   where every instance fits it and the memory for it can be had, else as tiles;
-   tuning entries and schedules concern the tiles. */
+   where every instance fits it and the memory for it (at most 64 GiB, the same again
+   for gradients) can be had, else as tiles; tuning entries and schedules concern the
+   tiles. */
 prony_status_t prony_batch_create(prony_handle_t handle, int count, const prony_instance_t* instances,
                                   prony_prec_t prec, prony_batch_t* batch);
 

@@ -1709,6 +1709,10 @@ bool plan_forward(prony_handle_t h, int d, int n, int m, SpecPlan& P, bool batch
 }
 
 constexpr size_t kMaxWorkspace = size_t(1) << 30;
+// A batch's memory, once for S and once for gradients: two to four times what its tiles need
+// (d = 3, n = 15, m = 32: 26 MB an instance against 12), so past about a quarter of the
+// card's memory the rest is left to the caller.
+constexpr size_t kMaxBatch = size_t(64) << 30;
 constexpr size_t kMaxTables = size_t(64) << 20;
 
 void fill_tables(prony_handle_t h, int P, double2* tab) {
@@ -2058,6 +2062,7 @@ prony_status_t spectral_batch_build(prony_handle_t h, const std::vector<prony_in
         base[pos] = off;
         off += plans[order[pos]].off_r;
     }
+    if (off > kMaxBatch) return fail(h, PRONY_ENOMEM, "the line-spectral form of the batch takes too much memory");
     SpecBatch* S = new (std::nothrow) SpecBatch;
     if (!S) return fail(h, PRONY_ENOMEM, "prony_batch_create: out of host memory");
     hipError_t e = hipMalloc(&S->ws, off);
@@ -2239,6 +2244,7 @@ prony_status_t spectral_adjoint_batch_build(prony_handle_t h, const std::vector<
         base[pos] = off;
         off += plans[order[pos]].off_r;
     }
+    if (off > kMaxBatch) return fail(h, PRONY_ENOMEM, "the line-spectral form of the batch takes too much memory");
     SpecAdjBatch* S = new (std::nothrow) SpecAdjBatch;
     if (!S) return fail(h, PRONY_ENOMEM, "prony_build_S_adjoint_batched: out of host memory");
     hipError_t e = hipMalloc(&S->ws, off);

@@ -1,5 +1,5 @@
 // Host-only stand-in for the HIP runtime calls of libprony, and a driver that runs the
-// C ABI on it: allocations come from the host (under a limit that a scenario sets),
+// C ABI on it: allocations are reserved addresses (under a limit that a scenario sets),
 // launches are recorded by kernel name and run nothing. Commands come from stdin, one
 // per line; each prints "<status> <allocations> <bytes held> <kernels launched>".
 // The definitions here take the place of libamdhip64's (the executable comes first in
@@ -8,6 +8,7 @@
 
 #include <cxxabi.h>
 #include <hip/hip_runtime_api.h>
+#include <sys/mman.h>
 
 #include <cstdint>
 #include <cstdlib>
@@ -87,7 +88,9 @@ hipError_t hipMalloc(void** p, size_t n) {
     *p = nullptr;
     if (capturing) return ok(hipErrorStreamCaptureUnsupported);
     if (n > limit - std::min(limit, held_bytes)) return ok(hipErrorOutOfMemory);
-    *p = malloc(n);
+    // addresses only: no kernel runs and no copy is made
+    *p = mmap(nullptr, n, PROT_NONE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+    if (*p == MAP_FAILED) return ok(hipErrorOutOfMemory);
     held[*p] = n;
     held_bytes += n;
     ++allocations;
@@ -95,9 +98,9 @@ hipError_t hipMalloc(void** p, size_t n) {
 }
 hipError_t hipFree(void* p) {
     if (!p) return hipSuccess;
+    munmap(p, held[p]);
     held_bytes -= held[p];
     held.erase(p);
-    free(p);
     return hipSuccess;
 }
 hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t) { return hipSuccess; }

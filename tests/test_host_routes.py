@@ -1,6 +1,6 @@
 """Which kernels a call launches and what it allocates, without a GPU: the library runs
-on a recording stand-in for the HIP runtime (hip_recorder.cpp) that serves allocations
-from host memory and records launches by name."""
+on a recording stand-in for the HIP runtime (hip_recorder.cpp) that counts allocations and
+records launches by name."""
 import os
 import shutil
 import subprocess
@@ -82,3 +82,15 @@ def test_factors_packed_for_the_tiles_build_and_are_released(recorder):
                      "free_factors", "destroy"])
     assert [r.status for r in done] == [0] * 7 and done[-1].held == 0
     assert done[4].kernels[0].startswith("pencil_tiles<double") and done[4].kernels[1].startswith("pencil_finish<double")
+
+
+def test_batches_leave_the_rest_of_the_memory_to_the_caller(recorder):
+    """64 instances run in line-spectral form; 5000, whose transforms would take 134 GB for S
+    and 86 GB for gradients, as tiles, which take 62 and 24 GB."""
+    one = "3 15 32 "
+    few = recorder(["create", f"batch {FP64} " + 64 * one, "run_batch", "adjoint_batch"])
+    assert "spectral" in few[2].kernels[0] and "spectral" in few[3].kernels[-1]
+    many = recorder(["create", f"batch {FP64} " + 5000 * one, "run_batch", "adjoint_batch", "free_batch", "destroy"])
+    assert [r.status for r in many] == [0] * 6 and many[-1].held == 0
+    assert many[1].held < 70e9 and "pencil_tiles_batched" in " ".join(many[2].kernels)
+    assert many[3].held - many[1].held < 30e9 and "adjoint_tiles_batched" in " ".join(many[3].kernels)
