@@ -134,11 +134,9 @@ __global__ __launch_bounds__(kFinishThreads) void coeffs_finish(int m, int rows,
 // Powers are formed as in coeffs_tiles, by binary exponentiation every kStep and by
 // products in between. What is left is latency, one pass of loads, powers and sums:
 // d=2 n=63 m=20 7.2 to 9.6 us against 8.9 + 3.5 us of the two launches above, which stay for
-// A^T itself and where one workgroup would have too many samples to read (kBoxRows).
-// All loads are requested before the powers of z_i.
+// A^T itself and past the sizes of box_fits. All loads are requested before the powers of z_i.
 constexpr int kStep = 8, kLanes = 8;         // powers per run; lanes of one sum
 constexpr int kBoxThreads = 512;
-constexpr int kBoxPowers = 2048, kBoxRows = 16384;
 
 __global__ __launch_bounds__(kBoxThreads) void coeffs_box(int d, int n, int N, int m, const double2* __restrict__ z,
                                                           const double2* __restrict__ f, double2* __restrict__ gram,
@@ -242,6 +240,17 @@ __global__ __launch_bounds__(kBoxThreads) void coeffs_box(int d, int n, int N, i
     }
 }
 
+// The box's time does not depend on m but grows with the line (a lane takes every 8th run of
+// powers one after another: 25.5 us at d = 1, n = 1023) and with the samples that one workgroup
+// reads; the tiles' grows with m past 16. Calls in us, box / tiles: d=1 n=447 m=20 12.2 / 12.3,
+// n=511 13.6 / 12.6, n=511 m=40 13.7 / 14.6, n=767 m=64 19.9 / 24.5; d=2 n=111 m=12 14.7 / 18.0,
+// n=127 18.4 / 18.4; d=3 n=20 m=12 15.6 / 15.6, n=22 19.3 / 15.9, n=24 m=20 24.1 / 27.6.
+bool box_fits(int d, int n, int64_t N, int m) {
+    const int line = m <= 32 ? 448 : m <= 48 ? 544 : 896;
+    const int rows = m > 16 ? 16384 : d == 3 ? 9600 : 14400;
+    return n + 1 <= line && N <= rows;
+}
+
 constexpr int kMaxWorkgroups = 256;   // one 16-row chunk each for N <= 4096
 
 }  // namespace
@@ -269,7 +278,7 @@ extern "C" prony_status_t prony_coeffs(prony_handle_t h, int d, int n, int m, co
     DeviceGuard g(h->device);
     if (!g.ok) return fail(h, PRONY_EHIP, "hipSetDevice failed");
     if ((st = ensure_workspace(h, coeffs_workspace_bytes(d, n, m))) != PRONY_OK) return st;
-    if (!AT_out && N <= kBoxRows && d * (n + 1) <= kBoxPowers) {
+    if (!AT_out && box_fits(d, n, N, m)) {
         {
             ProfileScope prof(h, "coeffs_tiles");
             coeffs_box<<<2 * m, kBoxThreads, 16 * (size_t)d * (n + 1), h->stream>>>(

@@ -34,3 +34,9 @@ def test_box_sums_match_oracle(d, n, m):
     tiled, rhs_tiled, _ = api.coeffs(zd, fd, d, n, want_AT=True)
     assert_close(gram.cpu().numpy(), tiled.cpu().numpy(), 1e-12, "Gram, tiled")
     assert_close(rhs.cpu().numpy(), rhs_tiled.cpu().numpy(), 1e-12, "rhs, tiled")
+
+
+@pytest.mark.parametrize("d,n,m", [(1, 447, 32), (1, 448, 32), (1, 895, 64), (2, 119, 3), (2, 120, 3), (3, 20, 16), (3, 21, 2),
+                                   (3, 24, 17)])
+def test_sums_at_the_ends_of_the_ranges_by_size(d, n, m):
+    test_box_sums_match_oracle(d, n, m)

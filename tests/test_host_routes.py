@@ -94,3 +94,16 @@ def test_batches_leave_the_rest_of_the_memory_to_the_caller(recorder):
     assert [r.status for r in many] == [0] * 6 and many[-1].held == 0
     assert many[1].held < 70e9 and "pencil_tiles_batched" in " ".join(many[2].kernels)
     assert many[3].held - many[1].held < 30e9 and "adjoint_tiles_batched" in " ".join(many[3].kernels)
+
+
+@pytest.mark.parametrize("d,n,m,box", [
+    (1, 447, 20, True), (1, 448, 20, False), (1, 1023, 5, False), (1, 543, 40, True), (1, 895, 64, True), (1, 896, 64, False),
+    (2, 63, 20, True), (2, 119, 16, True), (2, 120, 16, False), (2, 127, 17, True), (2, 128, 17, False),
+    (3, 20, 5, True), (3, 21, 5, False), (3, 24, 20, True), (3, 25, 20, False)])
+def test_vandermonde_products_take_the_form_that_measured_faster(recorder, d, n, m, box):
+    """Sums per axis by one workgroup a row, up to the lines and sample counts where the tiled
+    launches are faster (they took half the time at d = 1, n = 1023)."""
+    one, with_AT = recorder(["create", f"coeffs {d} {n} {m} 0", f"coeffs {d} {n} {m} 1"])[1:]
+    tiled = ["coeffs_tiles", "coeffs_finish"]
+    assert one.status == 0 and one.kernels == (["coeffs_box"] if box else tiled)
+    assert with_AT.status == 0 and with_AT.kernels == tiled
