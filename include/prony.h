@@ -221,8 +221,9 @@ prony_status_t prony_build_T(prony_handle_t handle, int d, int n, int which,
    PRONY_FP64 runs in line-spectral form where it fits (lines of at most 240 points and
    1 GiB of workspace that can be had; under capture, that is there): DFTs of length
    2(n+1) along the axes 2..d (d = 1: along folded lines), then one-dimensional Toeplitz
-   products per frequency, all in FP64. Other shapes and precisions run the MFMA tiles on
-   the undivided product. */
+   products per frequency, all in FP64. Other shapes (the smallest, of up to N = 64,
+   for d = 1 256, among them) and precisions run the MFMA tiles on the
+   undivided product. */
 prony_status_t prony_build_S(prony_handle_t handle, int d, int n, int m, const double* f,
                              const double* U, int64_t u_rs, int64_t u_cs,
                              const double* sigma,

@@ -702,7 +702,7 @@ extern "C" prony_status_t prony_build_S_adjoint(prony_handle_t h, int d, int n, 
     }
     if ((st = make_adj_plan(h, d, n, m, sizeof(double), P)) != PRONY_OK) return st;
     // in line-spectral form where it applies (a shape the tiles cannot cover is refused above)
-    SpecPlan SP;
+    SpecPlan SP{};
     bool spectral = spectral_adjoint_plan(h, d, n, m, SP);
     if ((st = ensure_form(h, SP.ws_bytes, P.ws_bytes, spectral)) != PRONY_OK) return st;
     if (spectral)

@@ -1758,7 +1758,7 @@ namespace {
 struct BuildPlan {
     PencilPlan P;
     bool spectral = false;
-    SpecPlan SP;
+    SpecPlan SP{};
     size_t ws_bytes() const { return spectral ? SP.ws_bytes : P.ws_bytes; }
     // what prepared factors keep: the packed or transformed U and V
     size_t factor_bytes() const { return spectral ? SP.off_f : P.off_p; }
@@ -2481,7 +2481,7 @@ extern "C" prony_status_t prony_toeplitz_mm(prony_handle_t h, int d, int n, int 
     P.conj_grid = adjoint;
     // FP64 in line-spectral form where it applies (a shape the tiles cannot cover is refused
     // above)
-    SpecPlan SP;
+    SpecPlan SP{};
     bool spectral = prec == PRONY_FP64 && spectral_product_plan(h, d, n, r, SP);
     if ((st = ensure_form(h, SP.ws_bytes, P.ws_bytes, spectral)) != PRONY_OK) return st;
     if (spectral)

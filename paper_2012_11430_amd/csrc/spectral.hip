@@ -1781,7 +1781,17 @@ size_t spectral_reserve_bytes(prony_handle_t h, int d, int n_max, int m_max) {
 
 size_t spectral_table_bytes(const SpecPlan& P) { return align_up(16 * (size_t)table_sizes(P.P).total, 256); }
 
+// Single S-builds up to here run the tiles: two launches with prepared factors instead of three
+// (d=1 n=63 m=5 10.4 us against 13.4, n=255 m=8 12.2 against 13.0; d=2 n=7 m=8 11.1 against 13.0, n=15 m=5
+// 13.2 either way; d=3 n=2 m=12 10.5 against 13.0, n=3 m=8 12.6 against 13.0), three without
+// allocation instead of the four that make the tables as well (14.8 against 16.7 to 17.6),
+// three either way in prony_build_S (14.7 to 15.2 both; d=3 n=3 15.5 against 14.7).
+static bool small_build(int d, int n, int m) {
+    return ipow(n + 1, d) <= (m <= 8 ? (d == 1 ? 256 : d == 2 ? 64 : 32) : m > 16 ? 0 : d == 1 ? 64 : 32);
+}
+
 bool spectral_plan(prony_handle_t h, int d, int n, int m, bool s0, SpecPlan& P, bool batched) {
+    if (!batched && small_build(d, n, m)) return false;
     if (!plan_forward(h, d, n, m, P, batched)) return false;
     P.s0 = s0 ? 1 : 0;
     P.ells = d + P.s0;

@@ -107,3 +107,18 @@ def test_vandermonde_products_take_the_form_that_measured_faster(recorder, d, n,
     tiled = ["coeffs_tiles", "coeffs_finish"]
     assert one.status == 0 and one.kernels == (["coeffs_box"] if box else tiled)
     assert with_AT.status == 0 and with_AT.kernels == tiled
+
+
+@pytest.mark.parametrize("d,n,m,tiles", [
+    (1, 255, 8, True), (1, 256, 8, False), (1, 255, 9, False), (1, 63, 16, True), (1, 64, 9, False), (2, 7, 8, True),
+    (2, 8, 2, False), (2, 4, 16, True), (2, 5, 16, False), (3, 2, 8, True), (3, 3, 1, False), (3, 2, 16, True), (3, 2, 17, False)])
+def test_small_fp64_builds_take_the_tiles(recorder, d, n, m, tiles):
+    """Two launches instead of three for prepared factors, three instead of four for the first
+    builds without allocation, and the same kernels in every entry point, so the same bits."""
+    build, factors, prepared, fixed = recorder(
+        ["create", f"build {d} {n} {m} {FP64} 0", f"factors {d} {n} {m} {FP64} 0", "build_factors"])[1:] + recorder(
+        ["create", f"noalloc {d} {n} {m} {FP64} 0"])[1:]
+    for r in (build, factors, prepared, fixed):
+        assert r.status == 0 and any("pencil_tiles" in k or "pencil_pack" in k for k in r.kernels) == tiles, r.kernels
+    assert len(prepared.kernels) == (2 if tiles else 3)
+    assert len(fixed.kernels) == (3 if tiles else 4)
