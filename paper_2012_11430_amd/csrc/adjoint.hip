@@ -22,8 +22,8 @@
 //                window is then added to the gradient in FP64 (device atomics).
 // The accumulation order inside a bin is not fixed: results agree to rounding,
 // not bitwise, between runs.
-// FP64 gradients of single instances with d >= 2 run in line-spectral form instead
-// (spectral.hip) wherever it applies.
+// FP64 gradients with d >= 2, single and batched, run in line-spectral form instead
+// (spectral.hip) wherever it applies, the smallest single ones line by line (adjoint_lines).
 #include <algorithm>
 
 #include "common.h"
@@ -325,6 +325,183 @@ __global__ __launch_bounds__(kThreads) void adjoint_tiles(AdjPlan P, AdjPtrs<T> 
     adjoint_body<T, KS, RF>(P, ptr, L);
 }
 
+// ---- the smallest FP64 gradients, d >= 2 -----------------------------------------
+//
+// For one offset p_o of the outer axes 1..d-1 the gradient's line along the last axis is
+//     grad(p_o, p) = sum_{k - h = p} G[k, h],
+//     G[k, h] = sum over k_o - h_o = p_o and q of Z[(k_o, k), q] conj(V[(h_o, h), q]),
+// with n + 2 <= 16 one 16 x 16 tile whose contraction runs over all pairs of lines at that
+// offset and over q, and whose diagonals are summed once: no bins, no atomics, a fixed order.
+// The offsets x and x - (n + 1), x = 1..n+1, of an outer axis hold n + 2 pairs of lines
+// together: line k meets h = k - x from k = x on, and h = k - x + n + 1 before. So each of
+// the (n+1)^(d-1) tuples of x has (n+2)^(d-1) pairs in 2^(d-1) runs of one offset, dealt out
+// over a workgroup's waves.
+//   Two launches (Z, this) instead of the line-spectral form's three: d=2 n=7 m=8 12.2 us
+// against 15.8 (the tiles: 12.5), d=3 n=3 m=11 15.0 against 16.9; by 150 pairs times K steps
+// the two meet (d=3 n=5 m=11 17.5 against 17.3; at d=3 n=15 m=20 118 against 35), see small_lines.
+constexpr int kLineWaves = 8, kLineThreads = 64 * kLineWaves, kLinePairs = 128;
+
+bool small_lines(int d, int n, int m) {
+    return d >= 2 && n + 2 <= 16 && ipow(n + 2, d - 1) * ((m + 3) / 4) <= kLinePairs;
+}
+size_t lines_lds(int d, int n) { return sizeof(double2) * kLineWaves * (16 * 17 + ((size_t)(2 * n + 2) << (d - 1))); }
+
+// A run of pairs of lines at one offset: sides s1, s2 of the outer axes (d = 2: the first is
+// trivial), the next pair (i1, i2) of its n1 x n2 pairs, how many are left; the rows of Z and
+// of V where the lines of a pair start.
+struct LineRun {
+    int s1, s2, i1, i2, n2, left;
+};
+struct LineAxes {
+    int d, n, x1, x2;
+    __device__ __forceinline__ int n1(int s) const { return d == 2 ? s : s ? n + 2 - x1 : x1; }
+    __device__ __forceinline__ int n2(int s) const { return s ? n + 2 - x2 : x2; }
+    __device__ __forceinline__ LineRun at(int idx) const {
+        int q = d == 2 ? 2 : 0;
+        while (idx >= n1(q >> 1) * n2(q & 1)) idx -= n1(q >> 1) * n2(q & 1), ++q;
+        const int len = n2(q & 1);
+        return LineRun{q >> 1, q & 1, idx / len, idx % len, len, n1(q >> 1) * len - idx};
+    }
+    __device__ __forceinline__ int z_row(const LineRun& r, int i1, int i2) const {
+        const int l1 = r.s1 && d == 3 ? x1 + i1 : i1, l2 = r.s2 ? x2 + i2 : i2;
+        return (l1 * (n + 2) + l2) * (n + 2);
+    }
+    __device__ __forceinline__ int v_row(const LineRun& r, int i1, int i2) const {
+        const int h1 = r.s1 ? i1 : i1 + n + 1 - x1, h2 = r.s2 ? i2 : i2 + n + 1 - x2;
+        return (h1 * (n + 1) + h2) * (n + 1);
+    }
+};
+
+// One point from its own terms (where a zero row of Z, of a k' that no T_l holds, met an
+// entry that is not finite).
+__device__ double2 line_point(const AdjPlan& P, const double2* __restrict__ Z, const double2* __restrict__ V,
+                              int64_t v_rs, int64_t v_cs, const int (&p)[3]) {
+    const int n = P.n, E = n + 1, a0 = P.d == 3 ? 0 : 1;       // axes a0 .. 2 are the gradient's
+    double2 sum = make_double2(0.0, 0.0);
+    for (int h = 0; h < P.N; ++h) {
+        int rest = h, row = 0, top = 0, zero = 1, k[3] = {0, 0, 0};
+        for (int a = 2; a >= a0; --a, rest /= E) k[a] = rest % E + p[a];
+        bool inside = true;
+        for (int a = a0; a < 3; ++a) {
+            inside = inside && k[a] >= 0 && k[a] <= E;
+            row = row * (n + 2) + k[a];
+            top += k[a] == E;
+            zero &= k[a] == 0;
+        }
+        if (!inside || top > 1 || zero) continue;
+        for (int q = 0; q < P.m; ++q) {
+            const double2 z = Z[(int64_t)row * P.cp + q], v = V[h * v_rs + q * v_cs];
+            sum.x = fma(z.x, v.x, fma(z.y, v.y, sum.x));
+            sum.y = fma(z.y, v.x, fma(-z.x, v.y, sum.y));
+        }
+    }
+    return sum;
+}
+
+__global__ __launch_bounds__(kLineThreads) void adjoint_lines(AdjPlan P, const double2* __restrict__ Z,
+                                                              const double2* __restrict__ V, int64_t v_rs,
+                                                              int64_t v_cs, double2* __restrict__ gf) {
+    using M = Mfma<double>;
+    constexpr int CH = 4;                // K steps in flight
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, col = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = P.n, E = n + 1, L = 2 * E, KM = (P.m + 3) >> 2, chunks = (KM + CH - 1) / CH;
+    const int len = L << (P.d - 1), lines = P.d == 3 ? (n + 2) * (n + 2) : n + 2, pair = blockIdx.x;
+    double2* tile = reinterpret_cast<double2*>(smem) + wave * 16 * 17;
+    double2* const all = reinterpret_cast<double2*>(smem) + kLineWaves * 16 * 17;      // [wave][run][place]
+    double2* sums = all + (size_t)wave * len;
+    // (the hardware keeps a wave's LDS accesses in order; this is for the compiler)
+    auto wave_order = [] {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    for (int i = lane; i < len; i += 64) sums[i] = make_double2(0.0, 0.0);
+    const LineAxes X{P.d, n, 1 + pair / E, 1 + pair % E};
+    // rows and columns past the last read the last one again: left out below
+    const double2* za = Z + (int64_t)min(col, E) * P.cp + g;
+    const double2* va = V + (int64_t)min(col, n) * v_rs;
+    const int end = lines * (wave + 1) / kLineWaves;
+    for (int it = lines * wave / kLineWaves; it < end;) {
+        const LineRun run = X.at(it);
+        const int count = min(end - it, run.left), steps = count * chunks;
+        typename M::acc_t re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
+        int i1 = run.i1, i2 = run.i2, c = 0, now = 0;      // step to load next, chunk to multiply next
+        auto load = [&](double2 (&z)[CH], double2 (&v)[CH]) {
+            const double2* zl = za + (int64_t)X.z_row(run, i1, i2) * P.cp;
+            const double2* vl = va + (int64_t)X.v_row(run, i1, i2) * v_rs;
+#pragma unroll
+            for (int k = 0; k < CH; ++k) {
+                const int s = c * CH + k;
+                if (s >= KM) break;
+                z[k] = zl[4 * s];
+                v[k] = vl[(int64_t)min(4 * s + g, P.m - 1) * v_cs];      // Z is zero past m
+            }
+            if (++c == chunks) {
+                c = 0;
+                if (++i2 == run.n2) i2 = 0, ++i1;
+            }
+        };
+        auto mma = [&](const double2 (&z)[CH], const double2 (&v)[CH]) {
+#pragma unroll
+            for (int k = 0; k < CH; ++k) {
+                if (now * CH + k >= KM) break;
+                re = M::fma(z[k].x, v[k].x, re);
+                im = M::fma(z[k].y, v[k].x, im);
+                re = M::fma(z[k].y, v[k].y, re);
+                im = M::fma(-z[k].x, v[k].y, im);
+            }
+            now = now + 1 == chunks ? 0 : now + 1;
+        };
+        double2 z0[CH], z1[CH], v0[CH], v1[CH];
+        load(z0, v0);
+        for (int s = 0; s < steps; s += 2) {
+            if (s + 1 < steps) load(z1, v1);
+            mma(z0, v0);
+            if (s + 1 >= steps) break;
+            if (s + 2 < steps) load(z0, v0);
+            mma(z1, v1);
+        }
+        wave_order();
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = M::row(g, r);
+            tile[col * 17 + row] = row <= E && col <= n ? make_double2(re[r], im[r]) : make_double2(0.0, 0.0);
+        }
+        wave_order();
+        // lane 2 e + comp sums the diagonal k - h = e - 15
+        const int e = lane >> 1, place = e - 15 + n;
+        if (e < 31 && place >= 0 && place < L) {
+            const double* y = reinterpret_cast<const double*>(tile) + (lane & 1);
+            const int h0 = max(0, 15 - e), h1 = min(15, 30 - e);
+            double sum = 0.0;
+#pragma unroll
+            for (int h = 0; h < 16; ++h) {
+                const int hc = min(max(h, h0), h1);
+                const double a = y[2 * (hc * 17 + e - 15 + hc)];
+                sum += h >= h0 && h <= h1 ? a : 0.0;
+            }
+            const int quad = P.d == 2 ? run.s2 : 2 * run.s1 + run.s2;
+            reinterpret_cast<double*>(sums + quad * L + place)[lane & 1] += sum;
+        }
+        it += count;
+    }
+    __syncthreads();
+    for (int e = tid; e < len; e += kLineThreads) {
+        double2 v = all[e];
+#pragma unroll
+        for (int w = 1; w < kLineWaves; ++w) {
+            v.x += all[(size_t)w * len + e].x;
+            v.y += all[(size_t)w * len + e].y;
+        }
+        const int quad = e / L, p2 = quad & 1 ? X.x2 : X.x2 - E, p1 = quad & 2 ? X.x1 : X.x1 - E;
+        const int p[3] = {p1, p2, e % L - n};
+        if (__builtin_expect(!(fabs(v.x) + fabs(v.y) <= 1.7976931348623157e308), 0))
+            v = line_point(P, Z, V, v_rs, v_cs, p);
+        gf[((P.d == 3 ? (int64_t)(p1 + n) * L : 0) + p2 + n) * L + e % L] = v;
+    }
+}
+
 // One instance of a batched adjoint: its plan, packed operands, inputs and the
 // offsets of its gS / gf blocks in the caller's concatenated buffers.
 template <typename T>
@@ -480,6 +657,28 @@ prony_status_t launch_adjoint(prony_handle_t h, const AdjPlan& P, const double* 
     }
     if (st != PRONY_OK) return st;
     return check_launch(h, "adjoint_tiles");
+}
+
+// The two launches of one of the smallest gradients; the workspace holds Z.
+prony_status_t launch_lines(prony_handle_t h, AdjPlan P, const double* U, int64_t u_rs, int64_t u_cs,
+                            const double* sigma, const double* V, int64_t v_rs, int64_t v_cs, const double* gS,
+                            double* gf) {
+    prony_status_t st = ensure_workspace(h, P.ws_bytes);
+    if (st != PRONY_OK) return st;
+    double2* Z = reinterpret_cast<double2*>(static_cast<unsigned char*>(h->ws) + P.off_z);
+    {
+        ProfileScope prof(h, "adjoint_pack");
+        adjoint_pack<double><<<dim3(adj_pack_blocks(P, 0), 1), kThreads, 0, h->stream>>>(
+            P, reinterpret_cast<const double2*>(U), u_rs, u_cs, sigma, reinterpret_cast<const double2*>(V), v_rs,
+            v_cs, reinterpret_cast<const double2*>(gS), Z, nullptr, nullptr, nullptr);
+    }
+    if ((st = check_launch(h, "adjoint_pack")) != PRONY_OK) return st;
+    {
+        ProfileScope prof(h, "adjoint_lines");
+        adjoint_lines<<<(int)ipow(P.n + 1, P.d - 1), kLineThreads, lines_lds(P.d, P.n), h->stream>>>(
+            P, Z, reinterpret_cast<const double2*>(V), v_rs, v_cs, reinterpret_cast<double2*>(gf));
+    }
+    return check_launch(h, "adjoint_lines");
 }
 
 template <typename T, int KS>
@@ -701,6 +900,7 @@ extern "C" prony_status_t prony_build_S_adjoint(prony_handle_t h, int d, int n, 
         return launch_adjoint<float>(h, P, U, u_rs, u_cs, sigma, V, v_rs, v_cs, gS, gf);
     }
     if ((st = make_adj_plan(h, d, n, m, sizeof(double), P)) != PRONY_OK) return st;
+    if (small_lines(d, n, m)) return launch_lines(h, P, U, u_rs, u_cs, sigma, V, v_rs, v_cs, gS, gf);
     // in line-spectral form where it applies (a shape the tiles cannot cover is refused above)
     SpecPlan SP{};
     bool spectral = spectral_adjoint_plan(h, d, n, m, SP);

@@ -122,3 +122,11 @@ def test_small_fp64_builds_take_the_tiles(recorder, d, n, m, tiles):
         assert r.status == 0 and any("pencil_tiles" in k or "pencil_pack" in k for k in r.kernels) == tiles, r.kernels
     assert len(prepared.kernels) == (2 if tiles else 3)
     assert len(fixed.kernels) == (3 if tiles else 4)
+
+
+@pytest.mark.parametrize("d,n,m,kernels", [
+    (2, 1, 4, 2), (2, 7, 32, 2), (2, 14, 32, 2), (2, 15, 2, 3), (3, 3, 20, 2), (3, 3, 21, 3), (3, 9, 4, 2), (3, 10, 1, 3)])
+def test_the_smallest_fp64_gradients_take_two_launches(recorder, d, n, m, kernels):
+    run = recorder(["create", f"reserve {d} {n} {m}", f"adjoint {d} {n} {m} {FP64}"])[-1]
+    assert run.status == 0 and run.allocations == 0 and len(run.kernels) == kernels
+    assert (run.kernels == ["adjoint_pack<double>", "adjoint_lines"]) == (kernels == 2)
