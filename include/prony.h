@@ -221,7 +221,9 @@ prony_status_t prony_build_T(prony_handle_t handle, int d, int n, int which,
    PRONY_FP64 runs in line-spectral form where it fits (lines of at most 240 points and
    1 GiB of workspace that can be had; under capture, that is there): DFTs of length
    2(n+1) along the axes 2..d (d = 1: along folded lines), then one-dimensional Toeplitz
-   products per frequency, all in FP64. Other shapes (the smallest, of up to N = 64,
+   products per frequency, all in FP64. Rounding errors are then relative to the norms
+   of the lines (d = 3: planes) of U, f and V along those axes, about 1e-15 of them at most,
+   not to each entry's own terms. Other shapes (the smallest, of up to N = 64,
    for d = 1 256, among them) and precisions run the MFMA tiles on the
    undivided product. */
 prony_status_t prony_build_S(prony_handle_t handle, int d, int n, int m, const double* f,
@@ -319,7 +321,9 @@ prony_status_t prony_coeffs(prony_handle_t handle, int d, int n, int m,
    tile-accumulation type (FP32 or FP64); the diagonal bins and the window sums
    added to gf are FP64. Summation order inside a bin is not fixed (LDS atomics),
    so repeated runs agree to rounding, not bitwise; FP64 gradients with d >= 2 in
-   line-spectral form (see prony_build_S) are the same bits each time. There an input
+   line-spectral form (see prony_build_S) are the same bits each time, with errors up to
+   about 1e-15 of the norms of the lines that meet in a point (the grid's corners, with few
+   terms each, are ten times less exact than their own terms allow). There an input
    that is not finite reaches the points whose terms hold it and no others; the points
    of the lines it touched are formed again from their own terms, which takes
    milliseconds at N = 4096 instead of some ten microseconds. Requires 1 <= m <= min(N, 32). */
@@ -342,8 +346,11 @@ prony_status_t prony_build_S_adjoint(prony_handle_t handle, int d, int n, int m,
    prec: arithmetic and tile-accumulation type (FP32 or FP64): MFMA tiles, or vector
          FMAs when r = 1 (one Lanczos step's product); the chunk partials are added
          in FP64 in a fixed order (bitwise reproducible). FP64 runs in line-spectral
-         form where it fits (see prony_build_S; bitwise reproducible too). An entry of f or
-         X that is not finite reaches the entries of Y whose terms hold it and no others;
+         form where it fits (see prony_build_S; bitwise reproducible too): an entry's error is
+         up to about 1e-15 of the norms of the lines of f and X that meet in it. Where samples
+         fall off along an axis (damped modes) entries much smaller than their line lose
+         digits that a sum over their own terms would keep. An entry of f or X that is not
+         finite reaches the entries of Y whose terms hold it and no others;
          there those its transforms touched are summed again one by one (d=2, n=63, r=40
          with one NaN sample: 1 ms instead of 0.02). Requires 1 <= r <= 64.
    Uses the handle's workspace (grown as needed; PRONY_ECAPTURE if it must grow

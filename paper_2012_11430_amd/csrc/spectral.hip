@@ -10,9 +10,15 @@
 //     U_l^* T_row V = 1/F sum_w e^{2 pi i w_l / L} sum_k1 U~_w[k1]^* Y_w[k1]   (l >= 2),
 //     U_1^* T_row V = 1/F sum_w sum_k1 U~_w[k1]^* Y_w[k1 + 1].
 // Per instance this takes 8 (n+2)(n+1) m L^(d-1) operations for the products instead
-// of 8 (n+2)^d (n+1)^d m, plus the transforms of U, V and f, for results of the same
-// precision: every sum is FP64, and the lengths of the sums fall from (n+1)^d to
-// (d-1)(n+1) + (n+1). d = 1: k = k1 P + k2 is folded into K1 lines of P points, which
+// of 8 (n+2)^d (n+1)^d m, plus the transforms of U, V and f. Every sum is FP64, but a
+// transform's rounding is relative to its whole line (d = 3: plane), so a result's error is
+// bounded by the norms of the lines that meet in it, not by its own terms. On samples of even
+// size (modes of modulus 1) the errors against extended precision, before (direct sums) and
+// here, normwise: S 1.0 to 1.6e-16 and 1.3 to 3.3e-16, products 4.6 to 6.4e-16 and 3.4 to
+// 5.5e-16, gradients 1.3 to 2.0e-16 and 2.0 to 4.2e-16; of a gradient's corner points, with
+// few terms each, 2e-16 and 1.3 to 3.3e-15 of the value. On damped samples the small entries of
+// a product lose digits: d = 2, n = 31, modulus 0.9 per step 5e-16 of the sum of an entry's
+// |terms|, 0.8 3e-14 (direct sums 1 to 3e-16). d = 1: k = k1 P + k2 is folded into K1 lines of P points, which
 // makes T a two-level Toeplitz matrix with f2(p1, p2) = f(p1 P + p2); S_1 is then the
 // phase form along the second level.
 //
