@@ -162,13 +162,27 @@ def _time(fn, reps):
     return e0.elapsed_time(e1) / reps
 
 
+def _runs_tiles(device, d, n, m, cus) -> bool:
+    """Whether FP64 S-builds of the shape run the tiles: their workspace holds the partial
+    rows of every workgroup, the line-spectral form's does not depend on the entries (which
+    this removes)."""
+    plans = []
+    for target, frag in ((cus, 1), (8 * cus, 2), (0, 0)):
+        register(device, d, n, m, "fp64", False, target, frag)
+        plans.append(plan(device, d, n, m, "fp64"))
+    a, b = plans[:2]
+    return a["workgroups"] == b["workgroups"] or a["workspace"] != b["workspace"]
+
+
 def tune_single(device: torch.device, d: int, n: int, m: int, prec: str, reps: int = 10,
                 path: str | None = None, seed: int = 0, fragments=SINGLE_FRAGMENTS,
                 targets=SINGLE_CANDIDATES, bucket: bool = False) -> dict:
     """Time prony_build_S of shape (d, n, m) for every distinct plan among the
     candidate (fragments, target x CUs) pairs on synthetic inputs; register and
-    cache the fastest (also for the shape's bucket when bucket=True).
-    Returns {(fragments, target): ms} of the plans timed."""
+    cache the fastest (also for the shape's bucket when bucket=True). An FP64 shape that
+    runs in line-spectral form has no plan to choose: it is timed once, its entry is
+    removed and nothing is cached.
+    Returns {(fragments, target): ms} of the plans timed ((0, 0): no entry)."""
     gen = torch.Generator(device="cpu").manual_seed(seed)
     N = (n + 1) ** d
     G = (2 * n + 2) ** d
@@ -177,6 +191,8 @@ def tune_single(device: torch.device, d: int, n: int, m: int, prec: str, reps: i
     V = torch.randn(N, m, dtype=torch.complex128, generator=gen).to(device)
     s = (torch.rand(m, dtype=torch.float64, generator=gen) + 0.5).to(device)
     cus = torch.cuda.get_device_properties(device).multi_processor_count
+    if prec == "fp64" and not _runs_tiles(device, d, n, m, cus):
+        return {(0, 0): _time(lambda: api.build_S(f, d, n, U, s, V, prec=prec), reps)}
     times, seen = {}, set()
     for frag, c in itertools.product(fragments, targets):
         register(device, d, n, m, prec, False, c * cus, frag)

@@ -103,3 +103,18 @@ def test_native_cache_loader_rejects_malformed_entries(tmp_path):
     other.write_text(json.dumps({"devices": {"gfx000:1": {"2,15,5,fp32,single": 3}}, "version": 1}))
     autotune.load_cache_native(DEV, str(other))
     assert autotune.registered(DEV, 2, 15, 5, "fp32", False) == 0
+
+
+def test_tune_single_leaves_the_line_spectral_form_alone(tmp_path):
+    # FP64 shapes that run in line-spectral form have no plan to choose: timed once, no
+    # entry registered or cached; one past the form (N = 64) is tuned as before
+    path = str(tmp_path / "tune.json")
+    d, n, m = 2, 31, 12
+    autotune.register(DEV, d, n, m, "fp64", False, 512, 1)
+    assert list(autotune.tune_single(DEV, d, n, m, "fp64", reps=2, path=path)) == [(0, 0)]
+    assert autotune.registered_tile(DEV, d, n, m, "fp64", False) == (0, 0)
+    assert not (tmp_path / "tune.json").exists()
+    d, n, m = 2, 240, 2
+    times = autotune.tune_single(DEV, d, n, m, "fp64", reps=1, path=path, targets=(1, 8))
+    assert len(times) >= 2 and autotune.registered_tile(DEV, d, n, m, "fp64", False) in times
+    autotune.register(DEV, d, n, m, "fp64", False, 0, 0)
