@@ -72,11 +72,21 @@ def own_flops(prec, d, n, m):
     return gram_flops(d, n, m) if prec == "fp64" else tile_flops(d, n, m)
 
 
+def plan_of(prec, dev, d, n, m):
+    """What an S-build of the shape runs: the tile plan, or in FP64 the line-spectral form's
+    number of frequencies (tuning entries and tile plans do not apply to it)."""
+    from paper_2012_11430_amd import autotune
+    if prec == "fp64":
+        return {"frequencies": (2 * n + 2) ** (d - 1)}
+    p = autotune.plan(dev, d, n, m, prec)
+    return {"fragments_per_wave": p["fragments"], "workgroups": p["workgroups"], "h_per_chunk": p["chunk"]}
+
+
 def source_digest():
     """Digest of the code (comments and whitespace stripped) of the sources the
-    dominant kernel is built from; the stored traffic counters apply while it matches."""
+    dominant kernels are built from; the stored traffic counters apply while it matches."""
     h = hashlib.sha256()
-    for name in ("pencil.hip", "common.h", "mfma.h", "reduce.h"):
+    for name in ("pencil.hip", "spectral.hip", "common.h", "mfma.h", "reduce.h", "spectral.h"):
         with open(os.path.join(ROOT, "paper_2012_11430_amd", "csrc", name)) as fh:
             text = fh.read()
         text = re.sub(r"/\*.*?\*/", " ", text, flags=re.S)
@@ -260,16 +270,17 @@ def main():
     def roofline_of(prec, avg_ms, nlaunch):
         """Roofline of the dominant kernel of one precision: its own MFMA work per launch
         over its average launch time (HIP events); HBM bytes per launch from the stored
-        counters of the same code, workload, precision and split target (the partial
-        rows written depend on the plan), else null."""
-        p = autotune.plan(dev, d, n, m, prec)
-        plan_key = f"{p['fragments']}x{p['workgroups']}"
+        counters of the same code, workload, precision and, for the tiles, plan (which the
+        partial rows written depend on), else null."""
+        plan = plan_of(prec, dev, d, n, m)
+        plan_key = DOMINANT[prec] if prec == "fp64" else f"{plan['fragments_per_wave']}x{plan['workgroups']}"
         traffic = None
-        if prec != "fp64" and traffic_rec.get("source_digest") == source_digest() and traffic_rec.get("workload") == args.workload:
+        if traffic_rec.get("source_digest") == source_digest() and traffic_rec.get("workload") == args.workload:
             traffic = traffic_rec.get("entries", {}).get(prec, {}).get(plan_key, {}).get("hbm_bytes_per_launch")
         achieved = own_flops(prec, d, n, m) / (avg_ms * 1e-3) / 1e12
         return {
-            "bound": "mfma",
+            # spectral_gram: chains of loads, products and stores with one or two waves per SIMD
+            "bound": "latency" if prec == "fp64" else "mfma",
             "kernel": "pencil_tiles_split" if prec == "bf16x3" else DOMINANT[prec],
             "precision": prec,
             "achieved": round(achieved, 3),
@@ -281,8 +292,7 @@ def main():
             "launches_timed": nlaunch,
             "flops_per_launch": own_flops(prec, d, n, m),
             "fs_equivalent_tflops": round(F / (avg_ms * 1e-3) / 1e12, 3),
-            "plan": {"frequencies": (2 * n + 2) ** (d - 1)} if prec == "fp64" else
-                    {"fragments_per_wave": p["fragments"], "workgroups": p["workgroups"], "h_per_chunk": p["chunk"]},
+            "plan": plan,
         }
 
     result = {
@@ -508,7 +518,7 @@ def noise_sweep_c2(dev, args, per_call_ms):
                         "fs_equivalent_tflops": round(s_flops(d, N, m) / (ms * 1e-3) / 1e12, 2),
                         "tiles_ms": round(tiles, 5), "tiles_own_work_tflops": round(own / (tiles * 1e-3) / 1e12, 2),
                         "tiles_frac_of_peak": round(own / (tiles * 1e-3) / 1e12 / PEAK_TFLOPS[prec], 4),
-                        "plan": autotune.plan(dev, d, n, m, prec)}
+                        "plan": plan_of(prec, dev, d, n, m)}
     return {"workload": "c2: d=3, n=19, N=8000, m=30, separation 0.08, |c| log-uniform [1e-2, 1]", "levels": rows,
             "s_build": timing,
             "own_work_flops_per_launch": {p: own_flops(p, d, n, m) for p in ("fp64", "fp32", "bf16x3")}}
