@@ -66,6 +66,10 @@ typedef enum {
                             terms (x = h + m + l, 24 significant bits), the six products
                             above 2^-24 on the bf16 MFMA with FP32 accumulation; then as
                             PRONY_FP32. Same error scale as PRONY_FP32.                   */
+    PRONY_FP64_DIRECT = 4, /* PRONY_FP64 by sums over each entry's own terms (the tile
+                            kernels) in every call, never in line-spectral form (see
+                            prony_build_S): slower, with errors relative to those terms.
+                            Tuning entries are those of PRONY_FP64.                       */
     PRONY_PREC_MAX_ENUM = 0x7FFFFFFF  /* not a precision: makes every value 0..2^31-1 a
                             valid object of this type, so that calls can reject unknown
                             values with PRONY_EINVAL (negative values are not allowed) */
@@ -213,7 +217,7 @@ prony_status_t prony_build_T(prony_handle_t handle, int d, int n, int which,
    U, V:   N x m complex128; entry (k, j) at U + 2*(k*u_rs + j*u_cs) (strides in
            complex elements, both >= 1). V is the right factor itself, not V^*.
    sigma:  m doubles > 0 (device memory).
-   prec:   PRONY_FP64, PRONY_FP32 or PRONY_BF16X3 (see prony_prec_t).
+   prec:   PRONY_FP64, PRONY_FP64_DIRECT, PRONY_FP32 or PRONY_BF16X3 (see prony_prec_t).
    flags:  0 or PRONY_WITH_S0.
    S:      output, (d or d+1) x m x m complex128, row-major per matrix: S_l(i,j)
            at S + 2*((l*m + i)*m + j), l counted from the first stored matrix.
@@ -223,7 +227,7 @@ prony_status_t prony_build_T(prony_handle_t handle, int d, int n, int which,
    2(n+1) along the axes 2..d (d = 1: along folded lines), then one-dimensional Toeplitz
    products per frequency, all in FP64. Rounding errors are then relative to the norms
    of the lines (d = 3: planes) of U, f and V along those axes, about 1e-15 of them at most,
-   not to each entry's own terms. Other shapes (the smallest, of up to N = 64,
+   not to each entry's own terms (PRONY_FP64_DIRECT). Other shapes (the smallest, of up to N = 64,
    for d = 1 256, among them) and precisions run the MFMA tiles on the
    undivided product. */
 prony_status_t prony_build_S(prony_handle_t handle, int d, int n, int m, const double* f,
@@ -323,7 +327,7 @@ prony_status_t prony_coeffs(prony_handle_t handle, int d, int n, int m,
    so repeated runs agree to rounding, not bitwise; FP64 gradients with d >= 2 in
    line-spectral form (see prony_build_S) are the same bits each time, with errors up to
    about 1e-15 of the norms of the lines that meet in a point (the grid's corners, with few
-   terms each, are ten times less exact than their own terms allow). There an input
+   terms each, are ten times less exact than with PRONY_FP64_DIRECT). There an input
    that is not finite reaches the points whose terms hold it and no others; the points
    of the lines it touched are formed again from their own terms, which takes
    milliseconds at N = 4096 instead of some ten microseconds. Requires 1 <= m <= min(N, 32). */
@@ -349,7 +353,7 @@ prony_status_t prony_build_S_adjoint(prony_handle_t handle, int d, int n, int m,
          form where it fits (see prony_build_S; bitwise reproducible too): an entry's error is
          up to about 1e-15 of the norms of the lines of f and X that meet in it. Where samples
          fall off along an axis (damped modes) entries much smaller than their line lose
-         digits that a sum over their own terms would keep. An entry of f or X that is not
+         digits that a sum over their own terms keeps (PRONY_FP64_DIRECT). An entry of f or X that is not
          finite reaches the entries of Y whose terms hold it and no others;
          there those its transforms touched are summed again one by one (d=2, n=63, r=40
          with one NaN sample: 1 ms instead of 0.02). Requires 1 <= r <= 64.

@@ -26,6 +26,7 @@ STATUS_NAMES = {0: "PRONY_OK", 1: "PRONY_EINVAL", 2: "PRONY_ENOTSUP", 3: "PRONY_
 PRONY_FP64 = 0
 PRONY_FP32 = 1
 PRONY_BF16X3 = 2
+PRONY_FP64_DIRECT = 4
 PRONY_WITH_S0 = 1
 PRONY_TUNE_BATCHED = 1
 PRONY_TUNE_BUCKET = 2

@@ -118,7 +118,10 @@ def build_T(f: torch.Tensor, d: int, n: int, which: int = 0, out: torch.Tensor |
     return out
 
 
-_S_PRECS = {"fp64": _lib.PRONY_FP64, "fp32": _lib.PRONY_FP32, "bf16x3": _lib.PRONY_BF16X3}
+# 'fp64_direct': FP64 sums over each entry's own terms in every call (the tile kernels), whose
+# errors are relative to those terms; 'fp64' is faster where its line-spectral form applies
+_PRECS = {"fp64": _lib.PRONY_FP64, "fp64_direct": _lib.PRONY_FP64_DIRECT, "fp32": _lib.PRONY_FP32}
+_S_PRECS = {**_PRECS, "bf16x3": _lib.PRONY_BF16X3}
 
 
 def _build_S(entry: str, f, d, n, U, sigma, V, prec, with_s0, out):
@@ -136,7 +139,7 @@ def _build_S(entry: str, f, d, n, U, sigma, V, prec, with_s0, out):
     if sigma.shape != (m,):
         raise ValueError("sigma must have shape (m,)")
     if prec not in _S_PRECS:
-        raise ValueError("prec must be 'fp64', 'fp32' or 'bf16x3'")
+        raise ValueError("prec must be 'fp64', 'fp64_direct', 'fp32' or 'bf16x3'")
     ells = d + (1 if with_s0 else 0)
     if out is None:
         out = torch.empty((ells, m, m), dtype=torch.complex128, device=dev)
@@ -154,8 +157,8 @@ def build_S(f: torch.Tensor, d: int, n: int, U: torch.Tensor, sigma: torch.Tenso
     """S_l = U^* T_l V Sigma^{-1}, l = 1..d (prony_build_S); shape (d[+1], m, m).
 
     V is the right factor itself (torch.linalg.svd returns V^* as Vh: pass Vh.mH).
-    prec: 'fp64', 'fp32' or 'bf16x3' (three-term bfloat16 splits on the bf16 MFMA,
-    same error scale as 'fp32').
+    prec: 'fp64', 'fp64_direct' (errors relative to each entry's own terms), 'fp32' or
+    'bf16x3' (three-term bfloat16 splits on the bf16 MFMA, same error scale as 'fp32').
     """
     return _build_S("prony_build_S", f, d, n, U, sigma, V, prec, with_s0, out)
 
@@ -189,7 +192,7 @@ class Factors:
         if sigma.shape != (m,):
             raise ValueError("sigma must have shape (m,)")
         if prec not in _S_PRECS:
-            raise ValueError("prec must be 'fp64', 'fp32' or 'bf16x3'")
+            raise ValueError("prec must be 'fp64', 'fp64_direct', 'fp32' or 'bf16x3'")
         self.d, self.n, self.m, self.prec, self.with_s0 = d, n, m, prec, with_s0
         self.device = dev
         self.handle = None
@@ -242,8 +245,8 @@ def build_S_adjoint(gS: torch.Tensor, d: int, n: int, U: torch.Tensor, sigma: to
     m = U.shape[1]
     if gS.shape != (d, m, m) or sigma.shape != (m,):
         raise ValueError("gS must be (d, m, m) and sigma (m,)")
-    if prec not in ("fp64", "fp32"):
-        raise ValueError("prec must be 'fp64' or 'fp32'")
+    if prec not in _PRECS:
+        raise ValueError("prec must be 'fp64', 'fp64_direct' or 'fp32'")
     if out is None:
         out = torch.empty(grid_size(d, n), dtype=torch.complex128, device=dev)
     else:
@@ -251,8 +254,7 @@ def build_S_adjoint(gS: torch.Tensor, d: int, n: int, U: torch.Tensor, sigma: to
         if out.numel() != grid_size(d, n):
             raise ValueError("out must hold (2n+2)^d values")
     _call("prony_build_S_adjoint", dev, d, n, m, _ptr(U), U.stride(0), U.stride(1), _ptr(sigma),
-          _ptr(V), V.stride(0), V.stride(1), _ptr(gS), _lib.PRONY_FP32 if prec == "fp32" else _lib.PRONY_FP64,
-          _ptr(out))
+          _ptr(V), V.stride(0), V.stride(1), _ptr(gS), _PRECS[prec], _ptr(out))
     return out
 
 
@@ -268,8 +270,8 @@ def toeplitz_mm(f: torch.Tensor, d: int, n: int, X: torch.Tensor, adjoint: bool 
         raise ValueError("f must hold the (2n+2)^d sample grid")
     if X.dim() != 2 or X.shape[0] != N or (X.shape[1] > 1 and X.stride(1) != 1):
         raise ValueError("X must be N x r with unit column stride")
-    if prec not in ("fp64", "fp32"):
-        raise ValueError("prec must be 'fp64' or 'fp32'")
+    if prec not in _PRECS:
+        raise ValueError("prec must be 'fp64', 'fp64_direct' or 'fp32'")
     r = X.shape[1]
     if out is None:
         out = torch.empty((N, r), dtype=torch.complex128, device=dev)
@@ -278,7 +280,7 @@ def toeplitz_mm(f: torch.Tensor, d: int, n: int, X: torch.Tensor, adjoint: bool 
         if out.shape != (N, r) or (r > 1 and out.stride(1) != 1):
             raise ValueError("out must be N x r with unit column stride")
     _call("prony_toeplitz_mm", dev, d, n, 1 if adjoint else 0, _ptr(f), r, _ptr(X), X.stride(0),
-          _lib.PRONY_FP32 if prec == "fp32" else _lib.PRONY_FP64, _ptr(out), out.stride(0))
+          _PRECS[prec], _ptr(out), out.stride(0))
     return out
 
 
@@ -331,8 +333,8 @@ class Batch:
     """
 
     def __init__(self, instances, prec: str = "fp32", outputs=None):
-        if prec not in ("fp64", "fp32"):
-            raise ValueError("prec must be 'fp64' or 'fp32'")
+        if prec not in _PRECS:
+            raise ValueError("prec must be 'fp64', 'fp64_direct' or 'fp32'")
         if not instances:
             raise ValueError("empty batch")
         dev = instances[0][2].device
@@ -366,8 +368,7 @@ class Batch:
         self.prec = prec
         self.graph = None
         out = ctypes.c_void_p()
-        _call("prony_batch_create", dev, len(instances), descs,
-              _lib.PRONY_FP32 if prec == "fp32" else _lib.PRONY_FP64, ctypes.byref(out))
+        _call("prony_batch_create", dev, len(instances), descs, _PRECS[prec], ctypes.byref(out))
         self.handle = out
 
     def set_schedule(self, schedule: str) -> None:

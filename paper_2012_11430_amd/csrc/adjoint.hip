@@ -748,7 +748,7 @@ prony_status_t adj_batch_build(prony_handle_t h, const prony_batch_s* B, AdjBatc
         A->gf_elems += plans[i].gsize;
     }
     // FP64 in line-spectral form where every instance fits it and its memory can be had
-    if constexpr (sizeof(T) == 8) {
+    if (sizeof(T) == 8 && !B->direct) {
         const prony_status_t st = spectral_adjoint_batch_build(h, B->inst, gs_off, gf_off, &A->spec);
         if (st == PRONY_OK || st == PRONY_EHIP) return st;
         h->err.clear();
@@ -890,7 +890,8 @@ extern "C" prony_status_t prony_build_S_adjoint(prony_handle_t h, int d, int n, 
         return fail(h, PRONY_EINVAL, "prony_build_S_adjoint: strides must be >= 1");
     if ((N - 1) * u_rs + (m - 1) * u_cs >= (int64_t(1) << 40) || (N - 1) * v_rs + (m - 1) * v_cs >= (int64_t(1) << 40))
         return fail(h, PRONY_EINVAL, "prony_build_S_adjoint: strides out of range");
-    if (prec != PRONY_FP64 && prec != PRONY_FP32) return fail(h, PRONY_EINVAL, "prony_build_S_adjoint: bad precision");
+    if (prec != PRONY_FP64 && prec != PRONY_FP64_DIRECT && prec != PRONY_FP32)
+        return fail(h, PRONY_EINVAL, "prony_build_S_adjoint: bad precision");
     if (h->device < 0) return fail(h, PRONY_ENODEV, "validation-only handle has no device");
     DeviceGuard g(h->device);
     if (!g.ok) return fail(h, PRONY_EHIP, "hipSetDevice failed");
@@ -900,10 +901,12 @@ extern "C" prony_status_t prony_build_S_adjoint(prony_handle_t h, int d, int n, 
         return launch_adjoint<float>(h, P, U, u_rs, u_cs, sigma, V, v_rs, v_cs, gS, gf);
     }
     if ((st = make_adj_plan(h, d, n, m, sizeof(double), P)) != PRONY_OK) return st;
-    if (small_lines(d, n, m)) return launch_lines(h, P, U, u_rs, u_cs, sigma, V, v_rs, v_cs, gS, gf);
+    const bool direct = prec == PRONY_FP64_DIRECT;
+    if (!direct && small_lines(d, n, m))
+        return launch_lines(h, P, U, u_rs, u_cs, sigma, V, v_rs, v_cs, gS, gf);
     // in line-spectral form where it applies (a shape the tiles cannot cover is refused above)
     SpecPlan SP{};
-    bool spectral = spectral_adjoint_plan(h, d, n, m, SP);
+    bool spectral = !direct && spectral_adjoint_plan(h, d, n, m, SP);
     if ((st = ensure_form(h, SP.ws_bytes, P.ws_bytes, spectral)) != PRONY_OK) return st;
     if (spectral)
         return spectral_adjoint_run(h, SP, static_cast<unsigned char*>(h->ws), U, u_rs, u_cs, sigma, V, v_rs, v_cs,

@@ -213,6 +213,7 @@ struct prony_batch_s {
     prony_handle_t owner = nullptr;
     int count = 0;
     prony_prec_t prec = PRONY_FP64;
+    bool direct = false;          // PRONY_FP64_DIRECT (prec is PRONY_FP64): the tiles
     std::vector<prony_instance_t> inst;   // descriptors in the caller's order
     void* ws = nullptr;           // entries + per-instance operands and scratch
     size_t ws_bytes = 0;

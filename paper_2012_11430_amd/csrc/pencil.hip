@@ -1757,6 +1757,7 @@ namespace {
 // where that form applies; the call then runs it instead of the tiles.
 struct BuildPlan {
     PencilPlan P;
+    prony_prec_t prec = PRONY_FP64;      // PRONY_FP64 for PRONY_FP64_DIRECT too
     bool spectral = false;
     SpecPlan SP{};
     size_t ws_bytes() const { return spectral ? SP.ws_bytes : P.ws_bytes; }
@@ -1781,6 +1782,8 @@ prony_status_t plan_build_S(prony_handle_t h, const char* who, int d, int n, int
     if (u_rs < 1 || u_cs < 1 || v_rs < 1 || v_cs < 1) return fail(h, PRONY_EINVAL, w + ": strides must be >= 1");
     if ((N - 1) * u_rs + (m - 1) * u_cs >= (int64_t(1) << 40) || (N - 1) * v_rs + (m - 1) * v_cs >= (int64_t(1) << 40))
         return fail(h, PRONY_EINVAL, w + ": strides out of range");
+    const bool direct = prec == PRONY_FP64_DIRECT;
+    if (direct) prec = PRONY_FP64;
     if (prec != PRONY_FP64 && prec != PRONY_FP32 && prec != PRONY_BF16X3)
         return fail(h, PRONY_EINVAL, w + ": bad precision");
     if (flags & ~PRONY_WITH_S0) return fail(h, PRONY_EINVAL, w + ": unknown flag");
@@ -1789,7 +1792,8 @@ prony_status_t plan_build_S(prony_handle_t h, const char* who, int d, int n, int
     const size_t ts = prec == PRONY_FP64 ? sizeof(double) : sizeof(float);
     st = make_plan(h, d, n, m, s0, ts, B.P, tuned_target(h, d, n, m, prec, 0), tuned_fragments(h, d, n, m, prec, 0),
                    0, prec == PRONY_BF16X3, true);
-    B.spectral = st == PRONY_OK && prec == PRONY_FP64 && spectral_plan(h, d, n, m, s0, B.SP);
+    B.prec = prec;
+    B.spectral = st == PRONY_OK && prec == PRONY_FP64 && !direct && spectral_plan(h, d, n, m, s0, B.SP);
     return st;
 }
 
@@ -1805,15 +1809,15 @@ SpecPtrs spectral_ptrs(const SpecPlan& P, unsigned char* base, unsigned char* re
                     reinterpret_cast<double2*>(S), at(P.off_r), nullptr};
 }
 
-prony_status_t run_build_S(prony_handle_t h, const BuildPlan& B, unsigned char* ws, prony_prec_t prec,
-                           const double* f, const double* U, int64_t u_rs, int64_t u_cs, const double* sigma,
+prony_status_t run_build_S(prony_handle_t h, const BuildPlan& B, unsigned char* ws, const double* f,
+                           const double* U, int64_t u_rs, int64_t u_cs, const double* sigma,
                            const double* V, int64_t v_rs, int64_t v_cs, double* S, bool keep_tables = true) {
     if (B.spectral) {
         SpecPtrs p = spectral_ptrs(B.SP, ws, ws + B.SP.off_f, f, U, u_rs, u_cs, sigma, V, v_rs, v_cs, S);
         const prony_status_t st = spectral_forward(h, B.SP, p, true, true, keep_tables);
         return st == PRONY_OK ? spectral_gram_finish(h, B.SP, p) : st;
     }
-    if (prec == PRONY_FP64) return launch_pencil<double>(h, B.P, ws, f, U, u_rs, u_cs, sigma, V, v_rs, v_cs, S);
+    if (B.prec == PRONY_FP64) return launch_pencil<double>(h, B.P, ws, f, U, u_rs, u_cs, sigma, V, v_rs, v_cs, S);
     return launch_pencil<float>(h, B.P, ws, f, U, u_rs, u_cs, sigma, V, v_rs, v_cs, S);
 }
 
@@ -1833,7 +1837,7 @@ extern "C" prony_status_t prony_build_S(prony_handle_t h, int d, int n, int m, c
     DeviceGuard g(h->device);
     if (!g.ok) return fail(h, PRONY_EHIP, "hipSetDevice failed");
     if ((st = ensure_form(h, B.SP.ws_bytes, B.P.ws_bytes, B.spectral)) != PRONY_OK) return st;
-    return run_build_S(h, B, static_cast<unsigned char*>(h->ws), prec, f, U, u_rs, u_cs, sigma, V, v_rs, v_cs, S);
+    return run_build_S(h, B, static_cast<unsigned char*>(h->ws), f, U, u_rs, u_cs, sigma, V, v_rs, v_cs, S);
 }
 
 extern "C" prony_status_t prony_build_S_plan(prony_handle_t h, int d, int n, int m, prony_prec_t prec, unsigned flags,
@@ -1871,7 +1875,7 @@ extern "C" prony_status_t prony_build_S_noalloc(prony_handle_t h, int d, int n, 
     if (!h->scratch) return fail(h, PRONY_EHIP, "prony_build_S_noalloc: no scratch address for this device");
     DeviceGuard g(h->device);
     if (!g.ok) return fail(h, PRONY_EHIP, "hipSetDevice failed");
-    return run_build_S(h, B, static_cast<unsigned char*>(h->scratch), prec, f, U, u_rs, u_cs, sigma, V, v_rs,
+    return run_build_S(h, B, static_cast<unsigned char*>(h->scratch), f, U, u_rs, u_cs, sigma, V, v_rs,
                        v_cs, S, false);
 }
 
@@ -1939,7 +1943,7 @@ extern "C" prony_status_t prony_factors_create(prony_handle_t h, int d, int n, i
         p.tables = static_cast<double2*>(h->ws);
         st = spectral_forward(h, B.SP, p, true, false, true);
     } else {
-        st = prec == PRONY_FP64 ? pack_operands<double>(h, B.P, F->mem, U, u_rs, u_cs, V, v_rs, v_cs)
+        st = B.prec == PRONY_FP64 ? pack_operands<double>(h, B.P, F->mem, U, u_rs, u_cs, V, v_rs, v_cs)
                                 : pack_operands<float>(h, B.P, F->mem, U, u_rs, u_cs, V, v_rs, v_cs);
     }
     if (st == PRONY_OK) {
@@ -1975,7 +1979,7 @@ extern "C" prony_status_t prony_build_S_factors(prony_handle_t h, prony_factors_
         st = spectral_forward(h, F->B.SP, p, false, true, true);
         return st == PRONY_OK ? spectral_gram_finish(h, F->B.SP, p) : st;
     }
-    if (F->prec == PRONY_FP64) return launch_tiles_finish<double>(h, P, F->mem, part, f, sigma, S);
+    if (F->B.prec == PRONY_FP64) return launch_tiles_finish<double>(h, P, F->mem, part, f, sigma, S);
     return launch_tiles_finish<float>(h, P, F->mem, part, f, sigma, S);
 }
 
@@ -2066,7 +2070,7 @@ prony_status_t batch_build(prony_handle_t h, int count, const prony_instance_t* 
         if (st != PRONY_OK) return fail(h, st, who + h->err);
     }
     // FP64 in line-spectral form where every instance fits it and its memory can be had
-    if constexpr (sizeof(T) == 8) {
+    if (sizeof(T) == 8 && !B->direct) {
         const prony_status_t st = spectral_batch_build(h, B->inst, &B->spec);
         if (st == PRONY_OK || st == PRONY_EHIP) return st;
         h->err.clear();
@@ -2263,6 +2267,8 @@ extern "C" prony_status_t prony_batch_create(prony_handle_t h, int count, const 
     *batch = nullptr;
     if (count < 1 || count > 65535 || !instances)
         return fail(h, PRONY_EINVAL, "prony_batch_create: count must be in 1..65535");
+    const bool direct = prec == PRONY_FP64_DIRECT;
+    if (direct) prec = PRONY_FP64;
     if (prec != PRONY_FP64 && prec != PRONY_FP32) return fail(h, PRONY_EINVAL, "prony_batch_create: bad precision");
     if (h->device < 0) {
         // validate only
@@ -2286,6 +2292,7 @@ extern "C" prony_status_t prony_batch_create(prony_handle_t h, int count, const 
     B->owner = h;
     B->count = count;
     B->prec = prec;
+    B->direct = direct;
     B->inst.assign(instances, instances + count);
     const prony_status_t st = prec == PRONY_FP32 ? batch_build<float>(h, count, instances, B)
                                                  : batch_build<double>(h, count, instances, B);
@@ -2460,7 +2467,8 @@ extern "C" prony_status_t prony_toeplitz_mm(prony_handle_t h, int d, int n, int 
     if (r < 1 || r > 64) return fail(h, PRONY_EINVAL, "prony_toeplitz_mm: r must be in 1..64");
     if (ldx < r || ldy < r) return fail(h, PRONY_EINVAL, "prony_toeplitz_mm: leading dimensions must be >= r");
     if (!f || !X || !Y) return fail(h, PRONY_EINVAL, "prony_toeplitz_mm: null pointer");
-    if (prec != PRONY_FP64 && prec != PRONY_FP32) return fail(h, PRONY_EINVAL, "prony_toeplitz_mm: bad precision");
+    if (prec != PRONY_FP64 && prec != PRONY_FP64_DIRECT && prec != PRONY_FP32)
+        return fail(h, PRONY_EINVAL, "prony_toeplitz_mm: bad precision");
     const int64_t N = ipow(n + 1, d);
     if ((N - 1) * ldx + r >= (int64_t(1) << 40) || (N - 1) * ldy + r >= (int64_t(1) << 40))
         return fail(h, PRONY_EINVAL, "prony_toeplitz_mm: leading dimensions out of range");

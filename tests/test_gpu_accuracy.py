@@ -8,7 +8,10 @@ along the transformed axes that meet in it, not by its own terms alone:
 P' points of x's line. Three transforms round independently, each by about sqrt(P' / 2) 2^-53
 of its line's norm (a random walk of partial sums); 4 covers the largest of many entries.
 S-builds likewise, with the lines of U, f and V that meet: the sum over a line's frequencies
-of the three transforms' products is at most |line of U|_2 |line of f|_1 |line of V|_2."""
+of the three transforms' products is at most |line of U|_2 |line of f|_1 |line of V|_2.
+
+Direct FP64 ('fp64_direct'): |error| <= 4 sqrt(N) 2^-53 sum |terms| for every entry's own terms
+(N of them, two to three roundings each; 4 as above)."""
 import numpy as np
 import pytest
 import torch
@@ -130,3 +133,41 @@ def test_pencil_matrices_hold_the_bound_by_lines(d, n, m, modulus):
         err = np.abs(got[l] - ref).astype(float)
         print(f"  largest error / bound {np.max(err / bound):.2f}", flush=True)
         assert np.all(err <= bound)
+
+
+@pytest.mark.parametrize("d,n,m", [(1, 300, 4), (2, 15, 5), (2, 24, 9), (3, 7, 10)])
+@pytest.mark.parametrize("modulus", [1.0, 0.75])
+def test_direct_results_hold_a_bound_by_their_own_terms(d, n, m, modulus):
+    rng, f, U, s, V = _problem(d, n, m, modulus)
+    print(f"direct d={d} n={n} m={m} modulus={modulus}", flush=True)
+    k, N, L = _box(d, 0, n + 1), (n + 1) ** d, 2 * n + 2
+    limit = 4 * np.sqrt(N) * ROUND
+    block = lambda e: np.stack([f[np.ravel_multi_index(tuple((k[i] - k + e + n).T), (L,) * d)] for i in range(N)])  # noqa: E731
+    X = rng.standard_normal((N, 3)) + 1j * rng.standard_normal((N, 3))
+    T = block(0)
+    for A, adjoint in ((T, False), (T.conj().T, True)):
+        got = api.toeplitz_mm(_dev(f), d, n, _dev(X), adjoint=adjoint, prec="fp64_direct").cpu().numpy()
+        ratio = np.max(np.abs(got - _ext(A, X)).astype(float) / (np.abs(A) @ np.abs(X)))
+        print(f"  product {ratio:.1e}", flush=True)
+        assert ratio <= limit
+    S = api.build_S(_dev(f), d, n, _dev(U), _dev(s), _dev(V), prec="fp64_direct").cpu().numpy()
+    for l in range(d):
+        T = block(np.arange(d) == l)
+        ref = _ext(U.conj().T, _ext(T, V)) / s.astype(np.longdouble)
+        ratio = np.max(np.abs(S[l] - ref).astype(float) / (np.abs(U).T @ (np.abs(T) @ np.abs(V)) / s))
+        print(f"  S_{l + 1} {ratio:.1e}", flush=True)
+        assert ratio <= limit
+    gS = rng.standard_normal((d, m, m)) + 1j * rng.standard_normal((d, m, m))
+    got = api.build_S_adjoint(_dev(gS), d, n, _dev(U), _dev(s), _dev(V), prec="fp64_direct").cpu().numpy()
+    ref, terms = np.zeros(L ** d, dtype=np.clongdouble), np.zeros(L ** d)
+    for l in range(d):
+        Z = _ext(U, gS[l]) / s.astype(np.longdouble)
+        A = np.abs(U) @ np.abs(gS[l]) / s
+        for h in range(N):
+            at = np.ravel_multi_index(tuple((k - k[h] + (np.arange(d) == l) + n).T), (L,) * d)
+            ref[at] += np.dot(Z, np.conj(V[h].astype(np.clongdouble)))
+            terms[at] += A @ np.abs(V[h])
+    held = terms > 0
+    ratio = np.max(np.abs(got - ref).astype(float)[held] / terms[held])
+    print(f"  gradient {ratio:.1e}", flush=True)
+    assert ratio <= limit

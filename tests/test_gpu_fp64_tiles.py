@@ -1,8 +1,7 @@
-"""The FP64 tile kernels, which serve what the line-spectral form does not: lines of more than
-240 points, captures that find only the tiles' workspace, batches with an instance past the
-form. Shapes of those kinds reach every column-block form (pair and three-product blocks, one
-to four fragments, tuned splits), products of one to 64 columns and gradients with d >= 2;
-each test checks through the profiling names that the tiles are what ran. References: padded
+"""The FP64 tile kernels, which serve what the line-spectral form does not: direct FP64, lines
+of more than 240 points, captures that find only the tiles' workspace, batches with an instance
+past the form. They reach every column-block form (pair and three-product blocks, one to four
+fragments, tuned splits), products of one to 64 columns and gradients with d >= 2; each test checks through the profiling names that the tiles are what ran. References: padded
 FFTs. Tolerance: the suite's FP64 bound 1e-12 normwise and entrywise, on data of even size
 (sums of N = 58081 terms: 2^-53 sqrt(N) = 3e-14)."""
 import ctypes
@@ -165,3 +164,81 @@ def test_captures_that_find_only_the_tiles_workspace(d, n, m, fragments):
             torch.cuda.synchronize()
             assert lib.prony_destroy(h) == _lib.PRONY_OK
     raise AssertionError("no capture succeeded")
+
+
+# ---- direct FP64 ------------------------------------------------------------------------
+
+
+def _direct_under_tuned_plans(d, n, m, f, U, s, V, with_s0=False, fragments=(0, 1, 2, 4), targets=(0, 1, 2, 3, 4, 8)):
+    ref = _fft_pencil(f, d, n, U, s, V)[0 if with_s0 else 1:]
+    args = (_dev(f), d, n, _dev(U), _dev(s), _dev(V))
+    cus = torch.cuda.get_device_properties(DEV).multi_processor_count
+    seen = set()
+    try:
+        for frag in fragments:
+            for target in targets:
+                autotune.register(DEV, d, n, m, "fp64", False, target * cus, frag)
+                p = autotune.plan(DEV, d, n, m, "fp64", with_s0=with_s0)
+                if (p["fragments"], p["workgroups"]) in seen:
+                    continue
+                seen.add((p["fragments"], p["workgroups"]))
+                what = f"direct d={d} n={n} m={m} fragments {p['fragments']} workgroups {p['workgroups']}"
+                print(what, flush=True)
+                got = _ran("pencil_tiles", lambda: api.build_S(*args, prec="fp64_direct", with_s0=with_s0))
+                assert_close_per_matrix(got.cpu().numpy(), ref, TOL, what)
+    finally:
+        autotune.register(DEV, d, n, m, "fp64", False, 0, 0)
+    return args, got
+
+
+@pytest.mark.parametrize("d,n,m", [(2, 63, 20), (3, 19, 30), (3, 20, 5), (3, 20, 20)])
+def test_direct_builds_under_every_tuner_target(d, n, m):
+    f, U, s, V, _ = _problem(d, n, m)
+    _direct_under_tuned_plans(d, n, m, f, U, s, V)
+
+
+@pytest.mark.parametrize("d,n,m", [(1, 1, 1), (1, 3, 4), (1, 63, 5), (1, 200, 32), (2, 1, 2), (2, 1, 4), (2, 4, 16), (2, 9, 17),
+                                   (2, 20, 16), (2, 20, 32), (3, 1, 3), (3, 1, 8), (3, 3, 8), (3, 6, 31)])
+def test_direct_builds_ragged_and_the_same_in_every_entry_point(d, n, m):
+    f, U, s, V, _ = _problem(d, n, m)
+    args, last = _direct_under_tuned_plans(d, n, m, f, U, s, V, with_s0=True, targets=(0, 2))
+    out = torch.empty_like(last)
+    one = api.build_S(*args, prec="fp64_direct", with_s0=True)
+    assert torch.equal(api.build_S_noalloc(*args, out=out, prec="fp64_direct", with_s0=True), one)
+    factors = api.Factors(d, n, *args[3:], prec="fp64_direct", with_s0=True)
+    assert torch.equal(factors.build_S(args[0]), one)
+    factors.close()
+
+
+@pytest.mark.parametrize("d,n,r", [(1, 40, 1), (1, 300, 9), (2, 9, 1), (2, 9, 8), (2, 20, 17), (2, 35, 64), (2, 63, 40), (3, 6, 1),
+                                   (3, 9, 16), (3, 12, 33), (3, 20, 1), (3, 20, 2)])
+@pytest.mark.parametrize("adjoint", [False, True])
+def test_direct_products(d, n, r, adjoint):
+    f, X, *_ = _problem(d, n, r)
+    print(f"direct product d={d} n={n} r={r} adjoint={adjoint}", flush=True)
+    got = _ran("toeplitz_mv" if r == 1 else "toeplitz_mm_tiles",
+               lambda: api.toeplitz_mm(_dev(f), d, n, _dev(X), adjoint=adjoint, prec="fp64_direct"))
+    assert_close(got.cpu().numpy(), _fft_product(f, d, n, X, adjoint), TOL, "product")
+
+
+@pytest.mark.parametrize("d,n,m", [(1, 70, 9), (2, 1, 1), (2, 3, 5), (2, 12, 32), (2, 47, 16), (3, 2, 4), (3, 6, 20), (3, 12, 11)])
+def test_direct_gradients(d, n, m):
+    _, U, s, V, gS = _problem(d, n, m)
+    print(f"direct gradient d={d} n={n} m={m}", flush=True)
+    got = _ran("adjoint_tiles",
+               lambda: api.build_S_adjoint(_dev(gS), d, n, _dev(U), _dev(s), _dev(V), prec="fp64_direct"))
+    assert_close(got.cpu().numpy(), _fft_gradient(gS, d, n, U, s, V), TOL, "gradient")
+
+
+def test_direct_batches():
+    shapes = [(2, 47, 16), (1, 70, 9), (2, 3, 5), (2, 12, 32), (3, 2, 4), (3, 6, 20), (1, 300, 32)]
+    probs = [_problem.__wrapped__(d, n, m, 9) for d, n, m in shapes]
+    batch = api.Batch([(d, n, _dev(f), _dev(U), _dev(s), _dev(V)) for (d, n, m), (f, U, s, V, _) in zip(shapes, probs)],
+                      prec="fp64_direct")
+    print("direct batch", flush=True)
+    _ran("pencil_tiles_batched", batch.run)
+    gf = _ran("adjoint_tiles_batched", lambda: batch.adjoint(_dev(np.concatenate([p[4].reshape(-1) for p in probs]))))
+    for S, x, (d, n, m), (f, U, s, V, gS) in zip(batch.S, torch.split(gf, batch.gf_sizes), shapes, probs):
+        assert_close_per_matrix(S.cpu().numpy(), _fft_pencil(f, d, n, U, s, V)[1:], TOL, f"d={d} n={n} m={m}")
+        assert_close(x.cpu().numpy(), _fft_gradient(gS, d, n, U, s, V), TOL, f"gradient d={d} n={n} m={m}")
+    batch.close()

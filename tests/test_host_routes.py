@@ -10,7 +10,7 @@ import pytest
 from paper_2012_11430_amd import _lib, build as B
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-FP64, FP32, BF16X3 = _lib.PRONY_FP64, _lib.PRONY_FP32, _lib.PRONY_BF16X3
+FP64, FP32, BF16X3, DIRECT = _lib.PRONY_FP64, _lib.PRONY_FP32, _lib.PRONY_BF16X3, _lib.PRONY_FP64_DIRECT
 
 pytestmark = pytest.mark.skipif(not os.path.exists(B.LIB) or not shutil.which("g++"),
                                 reason="needs the built library and g++")
@@ -130,3 +130,19 @@ def test_the_smallest_fp64_gradients_take_two_launches(recorder, d, n, m, kernel
     run = recorder(["create", f"reserve {d} {n} {m}", f"adjoint {d} {n} {m} {FP64}"])[-1]
     assert run.status == 0 and run.allocations == 0 and len(run.kernels) == kernels
     assert (run.kernels == ["adjoint_pack<double>", "adjoint_lines"]) == (kernels == 2)
+
+
+def test_direct_fp64_runs_the_tiles_in_every_entry_point(recorder):
+    calls = [f"build 3 9 12 {DIRECT} 1", f"noalloc 2 31 9 {DIRECT} 0", f"factors 2 31 9 {DIRECT} 0", "build_factors",
+             f"adjoint 2 31 9 {DIRECT}", f"adjoint 2 3 2 {DIRECT}", f"product 3 9 4 {DIRECT} 0", f"product 2 31 1 {DIRECT} 1",
+             f"batch {DIRECT} 2 31 9 3 5 4", "run_batch", "adjoint_batch"]
+    done = recorder(["create"] + calls)[1:]
+    assert [r.status for r in done] == [0] * len(done)
+    kernels = [" ".join(r.kernels) for r in done]
+    assert not any("spectral" in k or "adjoint_lines" in k or "float" in k for k in kernels)
+    for k, name in zip(kernels, ["pencil_tiles<double", "pencil_tiles<double", "pencil_pack<double", "pencil_tiles<double",
+                                 "adjoint_tiles<double", "adjoint_tiles<double", "toeplitz_mm_tiles<double",
+                                 "toeplitz_mv<double", "", "pencil_tiles_batched<double", "adjoint_tiles_batched<double"]):
+        assert name in k, (name, k)
+    refused = recorder(["create", "build 2 15 5 3 0", "adjoint 2 15 5 5", f"tune 2 15 5 {DIRECT} 1 64"])[1:]
+    assert [r.status for r in refused] == [_lib.PRONY_EINVAL] * 3
