@@ -224,13 +224,13 @@ __device__ __forceinline__ void pack_body(const PencilPlan& P, const double2* __
                                           int64_t u_cs, const double2* __restrict__ V, int64_t v_rs, int64_t v_cs,
                                           pair_t<T>* __restrict__ vp, pair_t<T>* __restrict__ up,
                                           int* __restrict__ gt, int section, int first, int stride,
-                                          int last) {
+                                          unsigned last) {
     using T2 = pair_t<T>;
     const int kbp = P.sk * P.kc + kPrefetchRows;
     if (section == 0 && P.split) {
         pack_split(P, V, v_rs, v_cs, reinterpret_cast<u32x4*>(vp), first, stride);
     } else if (section == 0) {
-        const unsigned nv = min(kbp * P.nrp, last);       // unsigned: i may pass 2^31
+        const unsigned nv = min((unsigned)(kbp * P.nrp), last);      // i may pass 2^31
         for (unsigned i0 = first; i0 < nv; i0 += Loads * stride) {
             double2 pr[Loads];
 #pragma unroll
@@ -250,7 +250,7 @@ __device__ __forceinline__ void pack_body(const PencilPlan& P, const double2* __
     } else if (section == 1) {
         if (P.mode) return;   // the product has no U^* epilogue
         const int mup = P.mbi * 16;
-        const unsigned nu = min((P.ug + P.rt * P.rows) * mup, last);
+        const unsigned nu = min((unsigned)((P.ug + P.rt * P.rows) * mup), last);
         const int E = P.n + 2, Pn = P.n + 1;
         for (unsigned r0 = first; r0 < nu; r0 += Loads * stride) {
             double2 u[Loads];
@@ -281,7 +281,7 @@ __device__ __forceinline__ void pack_body(const PencilPlan& P, const double2* __
             }
         }
     } else {
-        for (int hx = first; hx < min(kbp, last); hx += stride) gt[hx] = h_offset(P, hx < P.kb ? hx : P.kb - 1);
+        for (int hx = first; hx < (int)min((unsigned)kbp, last); hx += stride) gt[hx] = h_offset(P, hx < P.kb ? hx : P.kb - 1);
     }
 }
 
@@ -291,7 +291,7 @@ __global__ __launch_bounds__(256) void pencil_pack(PencilPlan P, const double2* 
                                                    int64_t v_cs, pair_t<T>* __restrict__ vp, pair_t<T>* __restrict__ up,
                                                    int* __restrict__ gt) {
     pack_body<T, 1>(P, U, u_rs, u_cs, V, v_rs, v_cs, vp, up, gt, blockIdx.y, blockIdx.x * blockDim.x + threadIdx.x,
-                 gridDim.x * blockDim.x, INT32_MAX);
+                 gridDim.x * blockDim.x, UINT32_MAX);
 }
 
 
@@ -1171,6 +1171,10 @@ struct BatchEntry {
 // work counter of the queue schedule (the tile launch follows on the same stream).
 constexpr int kPackSpan = 256 * kPackLoads, kPackSpanSmall = 256;
 constexpr int64_t kPackSmall = 1 << 21;      // elements of a small batch
+// (a section holds up to 2^31 - 1 elements: the end of its last slice may not fit an int)
+__host__ __device__ constexpr unsigned slice_end(int block, int span) { return (unsigned)(block + 1) * (unsigned)span; }
+static_assert(slice_end((INT32_MAX - 1) / kPackSpan, kPackSpan) >= (unsigned)INT32_MAX &&
+              slice_end((INT32_MAX - 1) / kPackSpanSmall, kPackSpanSmall) >= (unsigned)INT32_MAX);
 template <typename T, int Loads>
 __global__ __launch_bounds__(256) void pencil_pack_batched(const BatchEntry<T>* __restrict__ entries,
                                                            const BatchSlice* __restrict__ slices,
@@ -1181,7 +1185,7 @@ __global__ __launch_bounds__(256) void pencil_pack_batched(const BatchEntry<T>* 
     const BatchEntry<T>& e = entries[x.entry];
     pack_body<T, Loads>(e.P, e.U, e.P.m, 1, e.V, e.P.m, 1, const_cast<pair_t<T>*>(e.ptr.vp),
                  const_cast<pair_t<T>*>(e.ptr.up), const_cast<int*>(e.ptr.gtab), x.section,
-                 x.block * span + threadIdx.x, 256, (x.block + 1) * span);
+                 x.block * span + threadIdx.x, 256, slice_end(x.block, span));
 }
 
 // Batched launch over the instances of one column-block class, ordered by
