@@ -126,7 +126,8 @@ prony_status_t prony_reserve(prony_handle_t handle, int d_max, int n_max, int m_
    "pencil_tiles_batched", "pencil_finish", "spectral_forward", "spectral_gram",
    "spectral_toeplitz", "spectral_inverse", "spectral_adjoint",
    "coeffs_tiles" (the one launch of prony_coeffs where there is one),
-   "coeffs_finish", "adjoint_pack", "adjoint_tiles". */
+   "coeffs_finish", "adjoint_pack", "adjoint_tiles", "adjoint_lines" (the second of
+   the two launches of the smallest FP64 gradients). */
 prony_status_t prony_profile_enable(prony_handle_t handle, const char* kernel);
 
 /* Synchronise the stream and report the recorded launches of the profiled kernel:
@@ -248,14 +249,15 @@ prony_status_t prony_build_S_plan(prony_handle_t handle, int d, int n, int m, pr
 
 /* prony_build_S for callers that cannot allocate device memory (code under HIP
    graph capture, serving loops, harnesses that forbid hipMalloc): the same
-   validation, plan, kernels and result as prony_build_S, with the packed operands
+   validation, plan and kernels as prony_build_S (FP64 calls whose line-spectral form
+   does not fit the scratch run the tiles), with the packed operands
    and partial sums in a fixed scratch array of 64 MiB that the library holds on
    every device it runs on until the process ends (looked up once per device by
    prony_create). Calls no hipMalloc or hipFree. A call whose plan needs more than
    64 MiB of scratch returns PRONY_ENOTSUP with the size in prony_last_error (c1,
    d=2, n=63, m=20, needs about 10 MB in FP32; call prony_build_S for larger
-   plans). FP64 calls whose line-spectral form needs more run the tile kernels
-   where those fit. Every call on one device shares that device's array, across handles
+   plans). The result is prony_build_S's, bit for bit where both run the same
+   kernels and to the rounding stated there where not. Every call on one device shares that device's array, across handles
    and streams: calls that overlap on one GPU race, so keep them in one stream
    order. The array keeps the last call's contents; the kernels overwrite every
    byte they read, so nothing has to start at zero. */
@@ -283,8 +285,8 @@ prony_status_t prony_factors_create(prony_handle_t handle, int d, int n, int m,
                                     prony_prec_t prec, unsigned flags, prony_factors_t* factors);
 
 /* S_l = U^* T_l V Sigma^{-1} for the sample grid f with prepared factors: the
-   tile and finishing launches of prony_build_S only (same kernels, plan and
-   fixed-order sums, so the result is bitwise equal to prony_build_S's under that
+   launches of prony_build_S without those that only read U and V (same kernels, plan
+   and fixed-order sums, so the result is bitwise equal to prony_build_S's under that
    plan). f and S as for prony_build_S. The partial rows live in the handle's
    workspace (grown as needed; PRONY_ECAPTURE if it must grow under capture, so
    call once or prony_reserve before capturing). The factors must belong to the
@@ -327,7 +329,9 @@ prony_status_t prony_coeffs(prony_handle_t handle, int d, int n, int m,
    so repeated runs agree to rounding, not bitwise; FP64 gradients with d >= 2 in
    line-spectral form (see prony_build_S) are the same bits each time, with errors up to
    about 1e-15 of the norms of the lines that meet in a point (the grid's corners, with few
-   terms each, are ten times less exact than with PRONY_FP64_DIRECT). There an input
+   terms each, are ten times less exact than with PRONY_FP64_DIRECT); the smallest
+   (n <= 14 and (n + 2)^(d - 1) ceil(m / 4) <= 128) are summed line by line, in a
+   fixed order and without transforms. In line-spectral form an input
    that is not finite reaches the points whose terms hold it and no others; the points
    of the lines it touched are formed again from their own terms, which takes
    milliseconds at N = 4096 instead of some ten microseconds. Requires 1 <= m <= min(N, 32). */
@@ -446,8 +450,9 @@ prony_status_t prony_build_S_batched(prony_handle_t handle, prony_batch_t batch)
    gf: device output, the grid gradients of all instances concatenated in the
        same order; instance i contributes (2n_i+2)^{d_i} complex128 values, all
        overwritten.
-   Computes in the batch's precision (window sums added in FP64; bin order not
-   fixed, as for prony_build_S_adjoint). The first call on a batch plans it and
+   Computes in the batch's precision. Tiles add their window sums in FP64 in an
+   order that is not fixed; the line-spectral form adds in a fixed order (the same
+   bits each time), as for prony_build_S_adjoint. The first call on a batch plans it and
    allocates the batch's adjoint workspace (synchronously on the handle's stream;
    PRONY_ECAPTURE under stream capture); later calls allocate nothing. The handle
    must be the one that created the batch. */

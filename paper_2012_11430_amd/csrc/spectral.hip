@@ -144,8 +144,8 @@ __device__ __forceinline__ double sum_groups(double x) {
 
 // The transforms are bound by latency at the sizes of one instance (a pass of loads, the
 // products of a few items per wave, stores: 9.4 us at d = 2, n = 63, m = 20, 18.4 us at d = 3,
-// n = 20, m = 20, of which 6 us are its 30 MB at the rate of a copy) and by memory in a batch
-// (96 instances: 48 us for 200 MB). Eight waves per workgroup were no faster (19.8 us, batch 68).
+// n = 20, m = 20, of which 10 us are the 50 MB of the counters at the rate of a copy) and by
+// memory in a batch (96 instances: 46 us for 199 MB, 40 at that rate). Eight waves per workgroup were no faster (19.8 us, batch 68).
 //
 // Forward transform with one transformed axis (d <= 2): nbc blocks of 8 complex
 // columns from block nb0. Columns of a factor: c = line * m + q; of the grid: the
