@@ -174,8 +174,8 @@ def build_S_noalloc(f: torch.Tensor, d: int, n: int, U: torch.Tensor, sigma: tor
 
 class Factors:
     """Prepared factors (prony_factors_create): U, sigma and V packed once for
-    S-builds with many sample grids; `build_S(f)` runs only the launches that read the
-    samples or what they gave (prony_build_S_factors) and returns what build_S would under the plan
+    S-builds with many sample grids; `build_S(f)` leaves out the launches that only read
+    U and V (prony_build_S_factors) and returns what build_S would under the plan
     current at creation. The packed copy is the factors' own: U, sigma and V may
     be released afterwards."""
 

@@ -281,7 +281,8 @@ __device__ __forceinline__ void pack_body(const PencilPlan& P, const double2* __
             }
         }
     } else {
-        for (int hx = first; hx < (int)min((unsigned)kbp, last); hx += stride) gt[hx] = h_offset(P, hx < P.kb ? hx : P.kb - 1);
+        for (int hx = first; hx < (int)min((unsigned)kbp, last); hx += stride)
+            gt[hx] = h_offset(P, hx < P.kb ? hx : P.kb - 1);
     }
 }
 

@@ -18,9 +18,10 @@
 // 5.5e-16, gradients 1.3 to 2.0e-16 and 2.0 to 4.2e-16; of a gradient's corner points, with
 // few terms each, 2e-16 and 1.3 to 3.3e-15 of the value. On damped samples the small entries of
 // a product lose digits: d = 2, n = 31, modulus 0.9 per step 5e-16 of the sum of an entry's
-// |terms|, 0.8 3e-14 (direct sums 1 to 3e-16). d = 1: k = k1 P + k2 is folded into K1 lines of P points, which
-// makes T a two-level Toeplitz matrix with f2(p1, p2) = f(p1 P + p2); S_1 is then the
-// phase form along the second level.
+// |terms|, 0.8 3e-14 (direct sums 1 to 3e-16).
+// d = 1: k = k1 P + k2 is folded into K1 lines of P points, which makes T a two-level
+// Toeplitz matrix with f2(p1, p2) = f(p1 P + p2); S_1 is then the phase form along the second
+// level.
 //
 //   spectral_forward  DFTs of U, V and f as real contractions with the cosine and sine
 //                     tables on the FP64 matrix cores, folded about the lines' centres:
@@ -145,7 +146,8 @@ __device__ __forceinline__ double sum_groups(double x) {
 // The transforms are bound by latency at the sizes of one instance (a pass of loads, the
 // products of a few items per wave, stores: 9.4 us at d = 2, n = 63, m = 20, 18.4 us at d = 3,
 // n = 20, m = 20, of which 10 us are the 50 MB of the counters at the rate of a copy) and by
-// memory in a batch (96 instances: 46 us for 199 MB, 40 at that rate). Eight waves per workgroup were no faster (19.8 us, batch 68).
+// memory in a batch (96 instances: 46 us for 199 MB, 40 at that rate). Eight waves per
+// workgroup were no faster (19.8 us, batch 68).
 //
 // Forward transform with one transformed axis (d <= 2): nbc blocks of 8 complex
 // columns from block nb0. Columns of a factor: c = line * m + q; of the grid: the
